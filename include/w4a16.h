@@ -86,7 +86,9 @@ typedef enum {
     W4A16_KERNEL_TILE = 4        /* any M, the scheduler's choice otherwise: 64-column tile x 16, 32 or 64 rows of X
                                     per workgroup, its waves (eight; four at 32 and 64 rows, group 128) own contiguous runs of K (LDS
                                     reduction), plain MFMA operand layout; slices of different workgroups meet as
-                                    in STRIPE                                                                         */
+                                    in STRIPE.  The scheduler's own plans beyond 128 rows may have tiles of 128 rows
+                                    x 256 columns instead (tile_n = 256): four waves side by side, the tiles past the
+                                    last whole round of compute units in S slices of K summed by a second launch      */
 } w4a16_kernel;
 
 /* What the scheduler decided for a shape (Algorithm 1 takes S and the block
@@ -100,7 +102,8 @@ typedef struct {
     int waves_k;           /* K slices inside a workgroup (waves whose results meet in LDS)   */
     int workgroups;        /* workgroups of the multiply launch                               */
     int threads;           /* threads per workgroup                                           */
-    size_t workspace_bytes;/* 64-bit sums [M, N] or FP32 partials [S, M, N]; 0 when S == 1       */
+    size_t workspace_bytes;/* 64-bit sums [M, N] or FP32 partials [S, M, N]; 0 when S == 1.  tile_n = 256: FP32
+                              partials of the split tiles, at most one tile (128 KiB) per compute unit            */
 } w4a16_plan;
 
 /*
@@ -115,7 +118,8 @@ typedef struct {
  * memory).  While `stream` is being captured into a graph nothing can be
  * allocated: a call that would have to returns W4A16_ERR_WORKSPACE; run the
  * same shape once outside the capture first, or use w4a16_set_workspace,
- * w4a16_gemm_ws or w4a16_gemm_noalloc.  If a launch fails
+ * w4a16_gemm_ws or w4a16_gemm_noalloc.  (Plans of 256-column tiles never answer so: without room for the
+ * partials of their split tiles they run these unsplit; the same bits on every call that finds the same room.)  If a launch fails
  * (W4A16_ERR_HIP) the library clears its accumulator again before the next use.
  */
 int w4a16_gemm(const void *X, const uint32_t *Wpacked, const void *scales, const uint32_t *zeros,
@@ -151,7 +155,7 @@ int w4a16_gemm_ws(const void *X, const uint32_t *Wpacked, const void *scales, co
  * or NULL).  Algorithm 1 lists A and C as 16-bit floating point; the paper's runs use FP16, this entry covers
  * the other 16-bit format (bf16 MFMA, FP32 sums, one round-to-nearest-even cast at the end).  Arguments, split
  * buffers, stream rules and errors as w4a16_gemm_ex; kernel = W4A16_KERNEL_AUTO and split = 0 give the
- * scheduler's plan (the same plan as for FP16).  Forced plans: W4A16_KERNEL_TILE for any M,
+ * scheduler's plan (up to 128 rows the same as for FP16).  Forced plans: W4A16_KERNEL_TILE for any M,
  * W4A16_KERNEL_STRIPE for M <= 4; the others return W4A16_ERR_UNSUPPORTED.  Results beyond +-2^25 saturate
  * there when K slices meet in the fixed-point accumulator or when the waves of a workgroup share a slice by
  * ticket (M <= 16), as for FP16, where that bound lies beyond the format's range.
@@ -173,11 +177,12 @@ int w4a16_set_workspace(void *workspace, size_t workspace_bytes);
 /*
  * w4a16_gemm_ex for callers that cannot allocate device memory or wait for the device: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and result as w4a16_gemm_ex
- * (kernel = W4A16_KERNEL_AUTO and split = 0 give w4a16_gemm's plan).  The split buffers are a fixed array of
+ * (kernel = W4A16_KERNEL_AUTO and split = 0 give w4a16_gemm's plan; a plan of 256-column tiles that would split
+ * some of them beyond what the array holds runs them unsplit).  The split buffers are a fixed array of
  * W4A16_NOALLOC_SCRATCH_BYTES that the library's code object holds on every GPU it is loaded on until the
  * process ends; the call allocates nothing, frees nothing and waits for nothing.  A plan that needs more returns
  * W4A16_ERR_WORKSPACE and launches nothing (w4a16_query_plan tells what a plan needs; the scheduler's own plans
- * stay below 1.1 MiB on a GPU of 256 compute units).  A plan that uses the array as accumulator clears that part with one small extra launch first (a
+ * up to 128 rows stay below 1.1 MiB on a GPU of 256 compute units).  A plan that uses the array as accumulator clears that part with one small extra launch first (a
  * kernel, so the call can be captured).  All such calls on one GPU share the one array: calls that overlap in
  * time on that GPU (different streams, or graphs replayed concurrently) race on it.
  */

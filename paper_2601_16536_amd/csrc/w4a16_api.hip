@@ -65,6 +65,8 @@ struct Tuning {
     int tile_waves = 0;     // waves per TILE workgroup (4..8)
     int tile_unit = 0;      // 16 rows of X per workgroup, by ticket: blocks of 32 k per unit (1, 2; default: up to 4 within a group)
     int tile_wide = 0;      // TILE at 32 or 64 rows of X per workgroup, FP16, group 128: 2 = the eight-wave form instead of the four-wave one
+    int panel = 0;          // M > 16: 1 = always the four-wave 256-column form, 2 = never
+    int panel_split = 0;    // its split of the tiles past the last whole round of compute units (1 = none)
     int log = 0;            // 1: every call prints its plan on stderr
 };
 
@@ -77,6 +79,7 @@ const Knob kKnobs[] = {
     {"stripe_unit", &Tuning::stripe_unit},     {"stripe_depth", &Tuning::stripe_depth}, {"stripe_dot2", &Tuning::stripe_dot2},
     {"tile_rows", &Tuning::tile_rows},         {"tile_dyn", &Tuning::tile_dyn},         {"tile_depth", &Tuning::tile_depth},
     {"tile_waves", &Tuning::tile_waves},       {"tile_wide", &Tuning::tile_wide},         {"tile_unit", &Tuning::tile_unit},
+    {"panel", &Tuning::panel},                 {"panel_split", &Tuning::panel_split},
     {"log", &Tuning::log},
 };
 
@@ -208,12 +211,12 @@ size_t stripe_lds_max(int M) { return (size_t)(stripe_by_ticket(M) ? stripe_dyn_
 // there as the clock does): a fixed 3 us; rounds of workgroups x blocks of 32 k per wave x the time of a block
 // (four-wave form: 0.24 us at 32 rows, 0.37 at 64; eight-wave form: 0.37, 0.56, 0.94 at 16, 32, 64 rows); and how the
 // slices meet (accumulator: 1 us, and beyond 200 K adds 1 us per 60 K; second pass: 3.3 us and the partials at 3 TB/s).
-double tile_plan_cost(int M, int N, int K, int group, int rows, int S, int cus)
+double tile_plan_cost(int M, int N, int K, int group, int rows, int S, int cus, bool bf16 = false)
 {
     const int G = K / group;
     const int gps = (G + S - 1) / S;
     S = (G + gps - 1) / gps;
-    const bool four = tile_wide(rows, group);
+    const bool four = tile_wide(rows, group) && !bf16;
     const int waves = four ? 4 : 8;
     const double per_block = four ? (rows == 64 ? 0.37 : 0.24) : (rows == 64 ? 0.94 : (rows == 32 ? 0.56 : 0.37));
     const long long tiles = (N + 63) / 64, wgs = tiles * ((M + rows - 1) / rows) * S;
@@ -227,9 +230,94 @@ double tile_plan_cost(int M, int N, int K, int group, int rows, int S, int cus)
     return 3.0 + (double)rounds * (double)blocks * per_block + finish;
 }
 
-int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4a16_plan *p)
+// PANEL form (w4a16_panel.hip), for the scheduler's own plans beyond 128 rows: tiles of 128 x 256, the last row block of
+// 32, 64, 96 or 128 rows, one tile per compute unit at a time.  The tiles past the last whole round of compute units may be
+// cut into S slices of K that fill the units once more; their FP32 partials (at most one tile per unit, 32 MB) are summed
+// by a second launch.  Costs (us), fitted to 26 (shape, format, group) measured with and without the split (M = 129 ... 2048,
+// K = 2048 ... 28672, N = 1024 ... 28672): a stage of 128 k 1.3 at 128 rows, 0.8, 0.6, 0.47 of that at 96, 64, 32 rows
+// (the unpack is the same work at any number of rows), a quarter and a half more with groups of 64 and 32 (more of Eq. 2's
+// steps), a tenth more for BF16; 3 per tile for its first loads and its stores; the second launch 5 and the partials at 3.5 TB/s.
+double panel_cost(int M, int N, int K, int group, bool bf16, int cus, bool may_split, PanelPlan *p)
+{
+    static const double kRel[5] = {0.0, 0.47, 0.6, 0.8, 1.0};
+    const double stage = 1.3 * (group == 32 ? 1.5 : (group == 64 ? 1.25 : 1.0)) * (bf16 ? 1.1 : 1.0);
+    const double kStageUs[5] = {0.0, stage * kRel[1], stage * kRel[2], stage * kRel[3], stage};
+    const double fixed = 3.0;
+    p->tiles_m = (M + kPanelRows - 1) / kPanelRows;
+    p->tiles_n = (N + kPanelCols - 1) / kPanelCols;
+    p->last_rows = (M - (p->tiles_m - 1) * kPanelRows + 31) / 32 * 32;
+    p->split_tiles = 0;
+    p->split = 1;
+    p->slice_k = K;
+    const int unit = group < 128 ? 128 : group;  // slices begin at a group and at a whole stage
+    const int units = (K + unit - 1) / unit, last_rt = p->last_rows / 32;
+    const long long tiles = (long long)p->tiles_m * p->tiles_n, small = last_rt < 4 ? p->tiles_n : 0, large = tiles - small;
+    // time of the first `n` tiles, the large ones first
+    auto whole = [&](long long n, int k) {
+        const double stages = (k + 127) / 128, c4 = stages * kStageUs[4] + fixed, cl = stages * kStageUs[last_rt] + fixed;
+        const long long n4 = n < large ? n : large, nl = n - n4;
+        double t = (double)(n4 / cus) * c4;
+        const long long busy = n4 % cus, idle = cus - busy;
+        if (busy == 0) return t + (double)((nl + cus - 1) / cus) * cl;
+        const long long fit = idle * (c4 >= 2.0 * cl ? (long long)(c4 / cl) : 1);
+        if (nl <= fit) {
+            const double s = (double)((nl + idle - 1) / idle) * cl;
+            return t + (s > c4 ? s : c4);
+        }
+        return t + c4 + (double)((nl - fit + cus - 1) / cus) * cl;
+    };
+    double best = whole(tiles, K);
+    const long long rest = tiles % cus, done = tiles - rest;
+    if (may_split && rest && units > 1 && tuning().panel_split != 1) {
+        const double before = whole(done, K);
+        const int smax = (int)(cus / rest) < units ? (int)(cus / rest) : units;
+        for (int s = 2; s <= smax && s <= 16; ++s) {
+            const int k = (units + s - 1) / s * unit;
+            if ((long long)k * (s - 1) >= K) continue;  // an empty slice
+            const double c = before + (double)((k + 127) / 128) * kStageUs[rest > small ? 4 : last_rt] + fixed + 5.0 +
+                             (double)rest * s * kPanelPartial * 4.0 / 3.5e6 * (rest > small ? 1.0 : last_rt / 4.0);
+            if (c < best || s == tuning().panel_split) {
+                best = s == tuning().panel_split ? 0.0 : c;
+                p->split_tiles = (int)rest;
+                p->split = s;
+                p->slice_k = k;
+            }
+        }
+    }
+    return 3.0 + best;
+}
+
+bool use_panel(int M, int N, int K, int group, bool bf16, int cus, bool may_split, PanelPlan *p)
+{
+    if (tuning().panel == 2 || !panel_takes(group) || !fits_32bit_offsets(M, N, K, group, K / group)) return false;
+    if ((long long)((M + kPanelRows - 1) / kPanelRows) * ((N + kPanelCols - 1) / kPanelCols) > (1 << 24)) return false;  // a launch's blocks
+    if (tuning().panel == 1 && M > 16) {
+        (void)panel_cost(M, N, K, group, bf16, cus, may_split, p);
+        return true;
+    }
+    if (M <= 128) return false;
+    // against the cheapest plan of 64-column tiles; each of their rounds beyond the first costs about 3.5 us more than the
+    // model says (measured: M = 512 ... 2048, two to nine rounds)
+    double other = 1e30;
+    const int G = K / group;
+    for (int r = 16; r <= 64; r *= 2) {
+        const long long wgs = (long long)((N + 63) / 64) * ((M + r - 1) / r);
+        int smax = (int)(cus / wgs);
+        smax = smax < 1 ? 1 : (smax > G ? G : smax);
+        for (int s = 1; s <= smax; ++s) {
+            const double c = tile_plan_cost(M, N, K, group, r, s, cus, bf16) + 3.5 * (double)((wgs * s - 1) / cus);
+            if (c < other) other = c;
+        }
+    }
+    return panel_cost(M, N, K, group, bf16, cus, may_split, p) < other;
+}
+
+// `panel` (may be null) gets the plan's details where it is one of the PANEL form (tile_n = kPanelCols); may_split = false
+// asks for a plan of that form that needs no workspace.
+int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4a16_plan *p, PanelPlan *panel = nullptr, bool bf16 = false, bool may_split = true)
 {
     const int G = K / group;
+    const bool automatic = kernel == W4A16_KERNEL_AUTO && split == 0;
     if (kernel == W4A16_KERNEL_AUTO) {
         // STRIPE streams large weight matrices faster than TILE, but its 256-column stripes need four
         // times the slices, hence four times the atomic adds (S M N), and its work per unit of K grows with M.
@@ -280,6 +368,20 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
         p->workgroups = (int)(tiles * S);
         p->workspace_bytes = workspace_of(kernel, M, N, S);
         return fits_32bit_offsets(M, N, K, group, gps) ? W4A16_OK : W4A16_ERR_UNSUPPORTED;
+    }
+    PanelPlan pp;
+    if (automatic && use_panel(M, N, K, group, bf16, cus, may_split, &pp)) {
+        p->kernel = W4A16_KERNEL_TILE;
+        p->tile_n = kPanelCols;
+        p->tile_m = kPanelRows;
+        p->waves_k = 1;
+        p->threads = 256;
+        p->split = pp.split;
+        p->groups_per_split = pp.slice_k / group;
+        p->workgroups = pp.tiles_m * pp.tiles_n + pp.split_tiles * (pp.split - 1);
+        p->workspace_bytes = (size_t)pp.split_tiles * (pp.split > 1 ? pp.split : 0) * kPanelPartial * sizeof(float);
+        if (panel) *panel = pp;
+        return W4A16_OK;
     }
     if (kernel == W4A16_KERNEL_TILE) {
         p->tile_n = 64;
@@ -490,18 +592,25 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
     const int dev = current_device();
     if (dev < 0) { note_hip_error(hipErrorNoDevice); return W4A16_ERR_HIP; }
     w4a16_plan plan;
-    rc = make_plan(M, N, K, group, kernel, split, compute_units(dev), &plan);
+    PanelPlan panel;
+    rc = make_plan(M, N, K, group, kernel, split, compute_units(dev), &plan, &panel, bf16);
     if (rc) return rc;
     // bfloat16 activations: the forms the scheduler chooses from (STRIPE by ticket for M <= 4, TILE)
     if (bf16 && (plan.kernel == W4A16_KERNEL_WAVE_SPLIT || (plan.kernel == W4A16_KERNEL_STRIPE && !stripe_by_ticket(M))))
         return W4A16_ERR_UNSUPPORTED;
 
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int finish = finish_of(plan.kernel, M, N, plan.split);
-    if (tuning().log) log_plan(entry, M, N, K, group, plan, finish);
+    const bool by_panel = plan.kernel == W4A16_KERNEL_TILE && plan.tile_n == kPanelCols;
+    int finish = by_panel ? (plan.split > 1 ? kFinishSecondPass : kFinishDirect) : finish_of(plan.kernel, M, N, plan.split);
     Buffers b;
     rc = find_buffers(dev, plan, finish, M, N, st, src, call_ws, call_ws_bytes, &b);
+    if (rc == W4A16_ERR_WORKSPACE && by_panel) {  // the split is worth a workspace where there is one; the plan without it needs none
+        t_hip_error[0] = 0;
+        rc = make_plan(M, N, K, group, kernel, split, compute_units(dev), &plan, &panel, bf16, false);
+        finish = kFinishDirect;
+    }
     if (rc) return rc;
+    if (tuning().log) log_plan(entry, M, N, K, group, plan, finish);
 
     GemmArgs a;
     a.X = static_cast<const uint16_t *>(X);
@@ -528,6 +637,8 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
             e = launch_stripe_dyn(a, finish, b.sync, plan.waves_k, unit, depth, tuning().stripe_dot2 == 1, st);
     } else if (plan.kernel == W4A16_KERNEL_STRIPE) {
         e = launch_stripe(a, finish, b.sync, plan.waves_k, st);
+    } else if (by_panel) {
+        e = launch_panel(a, panel, st);
     } else if (plan.kernel == W4A16_KERNEL_TILE && tile_by_ticket(M, plan.tile_m)) {
         e = launch_tile_dyn(a, finish, b.sync, plan.waves_k, tuning().tile_depth == 2 && !bf16 && plan.waves_k <= 8 ? 2 : 1, tuning().tile_unit, st);
     } else if (plan.kernel == W4A16_KERNEL_TILE && tile_wide(plan.tile_m, group) && !bf16) {
@@ -538,7 +649,7 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
     } else {
         e = launch_wave_split(a, plan.tile_n, st);
     }
-    if (e == hipSuccess && finish == kFinishSecondPass) e = launch_reduce(a.partials, plan.split, M, N, a.Y, bf16, st);
+    if (e == hipSuccess && finish == kFinishSecondPass && !by_panel) e = launch_reduce(a.partials, plan.split, M, N, a.Y, bf16, st);
     if (e != hipSuccess) {
         note_hip_error(e);
         if (b.library_acc) {  // what the failed launch left in the accumulator is unknown

@@ -65,6 +65,17 @@ int stripe_dyn_lds_limit();                                           // most it
 // workgroup, `waves` (4..8) waves per workgroup that split the K slice; `finish` and `sync` as in the STRIPE
 // family.
 hipError_t launch_tile(const GemmArgs &a, int finish, unsigned long long *sync, int rows_x, int waves, hipStream_t stream);
+// PANEL form of the TILE family (many rows): tiles of 128 rows x 256 columns (w4a16_panel.hip).
+constexpr int kPanelRows = 128, kPanelCols = 256;
+constexpr size_t kPanelPartial = (size_t)kPanelRows * kPanelCols;  // floats of one tile's slice in the workspace
+struct PanelPlan {
+    int tiles_m, tiles_n;
+    int last_rows;    // rows of the last row block's tiles: 32, 64, 96 or 128
+    int split_tiles;  // the last so many tiles are cut into `split` slices of slice_k each, summed by a second launch
+    int split, slice_k;
+};
+inline bool panel_takes(int group) { return group % 128 == 0 || group == 64 || group == 32; }
+hipError_t launch_panel(const GemmArgs &a, const PanelPlan &p, hipStream_t stream);
 // TILE family at 64 or 32 rows of X per workgroup, FP16, group = 128: four waves per workgroup (w4a16_tile_wide.hip).
 hipError_t launch_tile_wide(const GemmArgs &a, int finish, unsigned long long *sync, int rows_x, hipStream_t stream);
 // TILE family, 16 rows of X per workgroup, the slice handed out to the waves by ticket (w4a16_tile_dyn.hip); `depth` (1, 2)

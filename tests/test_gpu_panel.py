@@ -1,0 +1,163 @@
+"""The form for many rows (tiles of 128 rows x 256 columns, w4a16_panel.hip) against the oracle at the edges of its tiles,
+stages (128 k), slices and row blocks, in both formats and at every length of scale segment it has."""
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import w4a16_oracle as orc
+from paper_2601_16536_amd import workloads as wl
+
+TOL = 1e-2
+
+
+def say(*a):
+    print("[case]", *a, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    from paper_2601_16536_amd import binding
+    assert torch.cuda.is_available()
+    binding.lib()
+    return torch, binding
+
+
+def err_ratio(Y, ref):
+    return float(np.max(np.abs(Y - ref) / (TOL * (1.0 + np.abs(ref)))))
+
+
+def test_plans_beyond_128_rows_cover_the_problem():
+    """Whatever the shape: slices cover K and none is empty, the workspace is at most one FP32 tile per compute unit, and
+    the grid is the tiles plus the extra slices."""
+    from paper_2601_16536_amd import binding
+    rng = np.random.default_rng(7)
+    seen = set()
+    for _ in range(3000):
+        group = int(rng.choice([32, 64, 96, 128, 256, 384]))
+        G = int(rng.integers(1, 200))
+        K, N, M = G * group, 8 * int(rng.integers(1, 3600)), int(rng.integers(129, 2500))
+        p = binding.query_plan(M, N, K, group)
+        assert p["kernel"] == binding.KERNEL_TILE
+        if p["tile_n"] != 256:
+            continue
+        assert group != 96
+        tiles = -(-M // 128) * -(-N // 256)
+        S, gps = p["split"], p["groups_per_split"]
+        assert S * gps >= G > (S - 1) * gps
+        rest = (p["workgroups"] - tiles) // (S - 1) if S > 1 else 0
+        assert p["workgroups"] == tiles + rest * (S - 1)
+        assert p["workspace_bytes"] == rest * S * 128 * 256 * 4 <= 256 * 128 * 256 * 4
+        assert S == 1 or (gps * group) % 128 == 0
+        seen.add((S > 1, rest == tiles))
+    assert seen == {(False, False), (True, False), (True, True)}
+
+
+# M: last row blocks of 1, 32, 33, 64, 65, 96, 97, 128 rows; N: one column group, a tile less and more than one piece, several
+# tiles; K: one stage, a slice that ends inside a stage (groups of 32 and 64), groups longer than a stage
+CASES = [(129, 128, 8, 128), (160, 640, 248, 128), (161, 1024, 256, 64), (192, 832, 264, 64), (193, 64, 520, 64), (224, 96, 72, 32),
+         (225, 1056, 512, 32), (256, 1280, 1032, 256), (385, 1152, 264, 384), (130, 2048, 768, 128), (65, 256, 520, 128), (17, 384, 264, 128)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N,group", CASES)
+def test_panel_against_the_oracle(gpu, M, K, N, group):
+    torch, binding = gpu
+    index = 9100 + M + K + N
+    X, Wp, s, Zp = wl.make(M, K, N, index=index, group=group, outliers=K >= 128)
+    Xb = wl.make_x_bf16(M, K, index=index)
+    eights = wl.pack_along_n(np.full((K // group, N), 8, np.uint8))
+    dX, dW, dS, dZ = binding.to_device(X, Wp, s, Zp)
+    dXb = torch.from_numpy(Xb.view(np.int16)).cuda().view(torch.bfloat16)
+    refs = {(False, False): orc.gemm(X, Wp, s, Zp, group), (False, True): orc.gemm(X, Wp, s, eights, group),
+            (True, False): orc.gemm_bf16(Xb, Wp, s, Zp, group), (True, True): orc.gemm_bf16(Xb, Wp, s, eights, group)}
+    binding.tune("panel", 1)
+    try:
+        for split in (1, 2, 5, 0):  # of the tiles, where K has as many stages; 0: the planner's
+            binding.tune("panel_split", split)
+            for (bf16, symmetric), ref in refs.items():
+                say("panel", (M, K, N, group), "split", split, "bf16" if bf16 else "fp16", "symmetric" if symmetric else "")
+                Y = torch.full((M, N), float("nan"), dtype=torch.bfloat16 if bf16 else torch.float16, device="cuda")
+                (binding.gemm_bf16 if bf16 else binding.gemm)(dXb if bf16 else dX, dW, dS, None if symmetric else dZ, group, out=Y)
+                first = Y.clone()
+                Y.fill_(float("nan"))
+                (binding.gemm_bf16 if bf16 else binding.gemm)(dXb if bf16 else dX, dW, dS, None if symmetric else dZ, group, out=Y)
+                torch.cuda.synchronize()
+                assert torch.equal(first, Y)
+                assert err_ratio(Y.double().cpu().numpy(), ref) <= 1.0
+    finally:
+        binding.tune("panel", 0)
+        binding.tune("panel_split", 0)
+
+
+@pytest.mark.gpu
+def test_panel_whole_numbers_and_rows_that_are_not_finite(gpu):
+    """Scales that are powers of two and small whole X: every output is exact.  A row of NaN or infinities stays in its own
+    row, also where a slice's last stage reaches beyond K (K = 832, groups of 64: half a stage)."""
+    torch, binding = gpu
+    M, K, N, group = 257, 832, 264, 64
+    rng = np.random.default_rng(5)
+    _, Wp, _, Zp = wl.make(1, K, N, index=9300, group=group)
+    s = (2.0 ** rng.integers(-8, -3, (K // group, N))).astype(np.float16)
+    X = rng.integers(-3, 4, (M, K)).astype(np.float16)
+    want = orc.to_fp16(orc.gemm(X, Wp, s, Zp, group))
+    X[100], X[256] = np.nan, np.inf
+    _, dW, dS, dZ = binding.to_device(X, Wp, s, Zp)
+    binding.tune("panel", 1)
+    try:
+        for split in (1, 3):
+            for dtype in (torch.float16, torch.bfloat16):
+                say("panel whole numbers", split, dtype)
+                binding.tune("panel_split", split)
+                dX = torch.from_numpy(X).cuda().to(dtype)
+                Y = torch.full((M, N), 7.0, dtype=dtype, device="cuda")
+                (binding.gemm if dtype == torch.float16 else binding.gemm_bf16)(dX, dW, dS, dZ, group, out=Y)
+                out = Y.float().cpu().numpy()
+                assert np.isnan(out[100]).all() and not np.isfinite(out[256]).any()
+                keep = [m for m in range(M) if m not in (100, 256)]
+                ref = want.astype(np.float32) if dtype == torch.float16 else torch.from_numpy(want).to(torch.float32).to(dtype).float().numpy()
+                if dtype == torch.bfloat16:  # the sums are exact in FP32 and have more bits than the format: one rounding
+                    exact = orc.gemm(np.nan_to_num(X, nan=0, posinf=0), Wp, s, Zp, group)
+                    ref = torch.from_numpy(exact).to(torch.float32).to(dtype).float().numpy()
+                assert np.array_equal(out[keep], ref[keep])
+    finally:
+        binding.tune("panel", 0)
+        binding.tune("panel_split", 0)
+
+
+@pytest.mark.gpu
+def test_panel_without_room_for_its_partials(gpu):
+    """A plan that would split runs without the split where its workspace is not to be had: a registered workspace too small
+    for it, the array of the entry point that allocates nothing, and a capture with either."""
+    torch, binding = gpu
+    M, K, N = 400, 4096, 7168
+    plan = binding.query_plan(M, N, K, 128)
+    assert plan["tile_n"] == 256 and plan["split"] > 1 and plan["workspace_bytes"] > 4 << 20, plan
+    X, Wp, s, Zp = wl.make(M, K, N, index=9400)
+    ref = orc.gemm(X, Wp, s, Zp, 128)
+    args = binding.to_device(X, Wp, s, Zp)
+    Y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+    ws = torch.empty(1 << 16, dtype=torch.uint8, device="cuda")
+    binding.set_workspace(ws)
+    try:
+        for name, call in (("registered", lambda: binding.gemm(*args, 128, out=Y)), ("noalloc", lambda: binding.gemm_noalloc(*args, 128, out=Y))):
+            say("panel without room", name)
+            Y.fill_(float("nan"))
+            call()
+            torch.cuda.synchronize()
+            assert err_ratio(Y.double().cpu().numpy(), ref) <= 1.0
+            eager = Y.clone()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                call()
+            for _ in range(3):
+                Y.fill_(float("nan"))
+                graph.replay()
+                torch.cuda.synchronize()
+                assert torch.equal(Y, eager)
+    finally:
+        binding.set_workspace(None)
+    binding.gemm(*args, 128, out=Y)
+    assert err_ratio(Y.double().cpu().numpy(), ref) <= 1.0
