@@ -13,7 +13,9 @@ typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 
 // One thread owns one packed row (eight k) of four consecutive columns: a 16-byte
 // load of codes, eight 8-byte stores.  A wave covers 256 columns, so every store
-// instruction writes 512 contiguous bytes of one row of W16.
+// instruction writes 512 contiguous bytes of one row of W16.  Bound by the writes: they are
+// nontemporal (K = 4096, N = 11008: 18.3 us = 6.2 TB/s, 24.0 with ordinary stores; nontemporal
+// loads of the codes as well: 21.0).
 __global__ __launch_bounds__(256) void dequant_kernel(const uint32_t *__restrict__ Wp, const uint16_t *__restrict__ scales,
                                                      const uint32_t *__restrict__ Zp, int group, int N, int rows,
                                                      uint16_t *__restrict__ W16)
@@ -41,7 +43,7 @@ __global__ __launch_bounds__(256) void dequant_kernel(const uint32_t *__restrict
             const int q = (int)((w[c] >> (4 * i)) & 15u);
             h[c] = (_Float16)(s[c] * (float)(q - z[c]));  // the FP32 product is exact; one rounding, to nearest even
         }
-        *reinterpret_cast<half4_t *>(W16 + (size_t)(r * 8 + i) * N + c4) = h;
+        __builtin_nontemporal_store(h, reinterpret_cast<half4_t *>(W16 + (size_t)(r * 8 + i) * N + c4));
     }
 }
 

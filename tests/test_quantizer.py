@@ -175,3 +175,34 @@ def test_hip_quantizer_bit_exact(gpu):
         torch.cuda.synchronize()
         step = want[1].astype(np.float64).repeat(group, axis=0)
         assert np.all(np.abs(back.cpu().numpy().astype(np.float64) - W.astype(np.float64)) <= step * 0.52)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("K,N,group", [(128, 8, 32), (160, 40, 32), (192, 264, 64), (384, 256, 128), (480, 72, 96), (320, 520, 160),
+                                       (768, 248, 256), (1024, 16, 1024)])
+def test_kernel_at_the_edges_of_its_tiles(K, N, group):
+    """The kernel's tiles are 128 rows x 256 columns (whole groups of 32, 64, 128 rows; longer and odd groups in chunks of
+    128 rows).  Codes at ties (weights on a grid of half steps), on FP16 subnormals, and in groups whose scale is rounded
+    far off: bit for bit the oracle's, which divides."""
+    import torch
+    from paper_2601_16536_amd import binding
+    rng = np.random.default_rng([9500, K, N, group])
+    for kind in range(5):
+        W = rng.standard_normal((K, N))
+        if kind == 0:
+            W *= 0.02
+        elif kind == 1:  # range 15, steps of a half: every other weight is a tie
+            W = rng.integers(-14, 17, (K, N)) * 0.5
+        elif kind == 2:  # subnormals: scales of a few units of 2^-24
+            W = rng.integers(-40, 41, (K, N)) * 2.0 ** -24
+        elif kind == 3:  # magnitudes over 25 octaves, one sign
+            W = np.abs(W) * 2.0 ** rng.integers(-20, 5, (K, N))
+        else:
+            W = W * 9000.0
+        W = W.astype(np.float16)
+        print("[case] quantize", (K, N, group), "kind", kind, flush=True)
+        got = [t.cpu().numpy() for t in binding.quantize(torch.from_numpy(W).cuda(), group)]
+        want = qo.quantize(W, group)
+        assert np.array_equal(got[0].view(np.uint32), want[0])
+        assert np.array_equal(got[1].view(np.uint16), want[1].view(np.uint16))
+        assert np.array_equal(got[2].view(np.uint32), want[2])
