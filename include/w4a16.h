@@ -84,9 +84,9 @@ typedef enum {
                                     share the slice (exact sums in LDS); slices of different workgroups meet in a
                                     64-bit fixed-point accumulator by one atomic add each, no second launch        */
     W4A16_KERNEL_TILE = 4        /* any M, the scheduler's choice otherwise: 64-column tile x 16, 32 or 64 rows of X
-                                    per workgroup, its waves (eight; four at 32 and 64 rows, group 128) own contiguous runs of K (LDS
+                                    per workgroup, its waves (eight; four at 64 rows, and at 32 with groups of 128) own contiguous runs of K (LDS
                                     reduction), plain MFMA operand layout; slices of different workgroups meet as
-                                    in STRIPE.  The scheduler's own plans beyond 128 rows may have tiles of 128 rows
+                                    in STRIPE.  The scheduler's own plans beyond 16 rows may have tiles of 128 rows
                                     x 256 columns instead (tile_n = 256): four waves side by side, the tiles past the
                                     last whole round of compute units in S slices of K summed by a second launch      */
 } w4a16_kernel;
@@ -118,8 +118,9 @@ typedef struct {
  * memory).  While `stream` is being captured into a graph nothing can be
  * allocated: a call that would have to returns W4A16_ERR_WORKSPACE; run the
  * same shape once outside the capture first, or use w4a16_set_workspace,
- * w4a16_gemm_ws or w4a16_gemm_noalloc.  (Plans of 256-column tiles never answer so: without room for the
- * partials of their split tiles they run these unsplit; the same bits on every call that finds the same room.)  If a launch fails
+ * w4a16_gemm_ws or w4a16_gemm_noalloc.  (For M > 16 the library first
+ * tries the plans that need less: tiles of 256 columns unsplit, then tiles of 64 columns whose slices meet in
+ * 64-bit sums or that need nothing.  The same bits on every call that finds the same room.)  If a launch fails
  * (W4A16_ERR_HIP) the library clears its accumulator again before the next use.
  */
 int w4a16_gemm(const void *X, const uint32_t *Wpacked, const void *scales, const uint32_t *zeros,
@@ -155,7 +156,7 @@ int w4a16_gemm_ws(const void *X, const uint32_t *Wpacked, const void *scales, co
  * or NULL).  Algorithm 1 lists A and C as 16-bit floating point; the paper's runs use FP16, this entry covers
  * the other 16-bit format (bf16 MFMA, FP32 sums, one round-to-nearest-even cast at the end).  Arguments, split
  * buffers, stream rules and errors as w4a16_gemm_ex; kernel = W4A16_KERNEL_AUTO and split = 0 give the
- * scheduler's plan (up to 128 rows the same as for FP16).  Forced plans: W4A16_KERNEL_TILE for any M,
+ * scheduler's plan (the same as for FP16, but tiles of 256 columns may be chosen for other shapes).  Forced plans: W4A16_KERNEL_TILE for any M,
  * W4A16_KERNEL_STRIPE for M <= 4; the others return W4A16_ERR_UNSUPPORTED.  Results beyond +-2^25 saturate
  * there when K slices meet in the fixed-point accumulator or when the waves of a workgroup share a slice by
  * ticket (M <= 16), as for FP16, where that bound lies beyond the format's range.
@@ -177,12 +178,11 @@ int w4a16_set_workspace(void *workspace, size_t workspace_bytes);
 /*
  * w4a16_gemm_ex for callers that cannot allocate device memory or wait for the device: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and result as w4a16_gemm_ex
- * (kernel = W4A16_KERNEL_AUTO and split = 0 give w4a16_gemm's plan; a plan of 256-column tiles that would split
- * some of them beyond what the array holds runs them unsplit).  The split buffers are a fixed array of
+ * (kernel = W4A16_KERNEL_AUTO and split = 0 give w4a16_gemm's plan; where that needs more than the array holds,
+ * the plans that need less, see w4a16_gemm).  The split buffers are a fixed array of
  * W4A16_NOALLOC_SCRATCH_BYTES that the library's code object holds on every GPU it is loaded on until the
  * process ends; the call allocates nothing, frees nothing and waits for nothing.  A plan that needs more returns
- * W4A16_ERR_WORKSPACE and launches nothing (w4a16_query_plan tells what a plan needs; the scheduler's own plans
- * up to 128 rows stay below 1.1 MiB on a GPU of 256 compute units).  A plan that uses the array as accumulator clears that part with one small extra launch first (a
+ * W4A16_ERR_WORKSPACE and launches nothing (w4a16_query_plan tells what a plan needs).  A plan that uses the array as accumulator clears that part with one small extra launch first (a
  * kernel, so the call can be captured).  All such calls on one GPU share the one array: calls that overlap in
  * time on that GPU (different streams, or graphs replayed concurrently) race on it.
  */
@@ -242,7 +242,7 @@ int w4a16_quantize(const void *W16, int group, int N, int K, uint32_t *Wpacked, 
  *   "tile_depth"     units in flight per wave of that form (1, 2)
  *   "tile_unit"      blocks of 32 k per unit of that form (1, 2; default: a whole group, at most 4)
  *   "tile_waves"     waves per TILE workgroup (4..8)
- *   "tile_wide"      2: TILE at 32 or 64 rows of X per workgroup, FP16, group 128: the eight-wave form instead of
+ *   "tile_wide"      2: TILE at 32 or 64 rows of X per workgroup: the eight-wave form instead of
  *                    the four-wave one
  *   "log"            1: every w4a16_gemm* call prints its plan on stderr (the one case in which the library prints)
  * Returns W4A16_ERR_UNSUPPORTED for an unknown knob.

@@ -64,7 +64,7 @@ struct Tuning {
     int tile_depth = 0;     // units in flight per wave of the ticket form (1, 2)
     int tile_waves = 0;     // waves per TILE workgroup (4..8)
     int tile_unit = 0;      // 16 rows of X per workgroup, by ticket: blocks of 32 k per unit (1, 2; default: up to 4 within a group)
-    int tile_wide = 0;      // TILE at 32 or 64 rows of X per workgroup, FP16, group 128: 2 = the eight-wave form instead of the four-wave one
+    int tile_wide = 0;      // TILE at 32 or 64 rows of X per workgroup: 2 = the eight-wave form instead of the four-wave one
     int panel = 0;          // M > 16: 1 = always the four-wave 256-column form, 2 = never
     int panel_split = 0;    // its split of the tiles past the last whole round of compute units (1 = none)
     int log = 0;            // 1: every call prints its plan on stderr
@@ -165,25 +165,27 @@ bool fits_32bit_offsets(int M, int N, int K, int group, int gps)
 // returning atomic add per output and slice; measured: the GPU retires about 150 of them per nanosecond)
 // while that is cheaper than a second launch (about 3.3 us, measured), else in the FP32 workspace and the
 // second pass.  Measured crossover: between 0.5 M and 1 M adds.  The other families always take the second pass.
-bool slices_meet_in_accumulator(int M, int N, int S)
+// At 64 rows of X per workgroup (`rows`; groups other than 128) the adds come in a burst of 4096 from every workgroup at once, and the crossover is
+// lower (M = 37, K = 10240, N = 4608, S = 3, 511 K adds: 23.8 us in the accumulator; M = 64, 885 K adds, second pass: 18.1).
+bool slices_meet_in_accumulator(int M, int N, int S, int rows)
 {
     if (S > 63) return false;  // the accumulator counts arrivals in six bits
     if (tuning().stripe_finish == 1) return true;
     if (tuning().stripe_finish == 2) return false;
-    return (long long)S * M * N <= 640 * 1024;
+    return (long long)S * M * N <= (rows == 64 ? 160 : 640) * 1024;
 }
 
-int finish_of(int kernel, int M, int N, int S)
+int finish_of(int kernel, int M, int N, int S, int rows)
 {
     if (S == 1) return kFinishDirect;
     if (kernel != W4A16_KERNEL_STRIPE && kernel != W4A16_KERNEL_TILE) return kFinishSecondPass;
-    return slices_meet_in_accumulator(M, N, S) ? kFinishAccumulator : kFinishSecondPass;
+    return slices_meet_in_accumulator(M, N, S, rows) ? kFinishAccumulator : kFinishSecondPass;
 }
 
 // Workspace of a plan: nothing, the accumulator [M, N], or the FP32 partials [S, M, N].
-size_t workspace_of(int kernel, int M, int N, int S)
+size_t workspace_of(int kernel, int M, int N, int S, int rows)
 {
-    switch (finish_of(kernel, M, N, S)) {
+    switch (finish_of(kernel, M, N, S, rows)) {
     case kFinishDirect: return 0;
     case kFinishAccumulator: return (size_t)M * N * sizeof(unsigned long long);
     default: return (size_t)S * M * N * sizeof(float);
@@ -195,9 +197,13 @@ bool stripe_by_ticket(int M) { return M <= 4 && tuning().stripe_dyn != 2; }
 // with several row blocks, which re-read the weights from the L2, 3 % slower).
 bool tile_by_ticket(int M, int rows_x) { return rows_x == 16 && (tuning().tile_dyn == 1 || (M <= 16 && tuning().tile_dyn != 2)); }
 
-// TILE at 64 rows of X per workgroup and group = 128: four waves per workgroup, each alone on its SIMD
-// (w4a16_tile_wide.hip; FP16 only: BF16 activations run such a plan with the eight-wave form).
-bool tile_wide(int rows_x, int group) { return (rows_x == 64 || rows_x == 32) && group == 128 && tuning().tile_wide != 2; }
+// TILE with four waves per workgroup: at 32 and 64 rows of X, FP16 with groups of 128 (w4a16_tile_wide.hip), and at 64 rows
+// BF16 and the other lengths of group (w4a16_tile_tall.hip; at 32 rows these run the eight-wave form).  Both take FP16 with
+// groups of 128 at 64 rows: M = 128, N = 8192, K = 512 / 2048 / 8192: 6.6 / 10.7 / 27.7 us (wide), 6.9 / 10.7 / 27.5 (tall).
+bool tile_four(int rows_x, int group)
+{
+    return ((rows_x == 64 && wide_takes(group)) || (rows_x == 32 && group == 128)) && tuning().tile_wide != 2;
+}
 
 // LDS a STRIPE workgroup needs for a slice of gps groups, and the most it may use.
 size_t stripe_lds(int M, int group, int gps, int waves)
@@ -211,26 +217,26 @@ size_t stripe_lds_max(int M) { return (size_t)(stripe_by_ticket(M) ? stripe_dyn_
 // there as the clock does): a fixed 3 us; rounds of workgroups x blocks of 32 k per wave x the time of a block
 // (four-wave form: 0.24 us at 32 rows, 0.37 at 64; eight-wave form: 0.37, 0.56, 0.94 at 16, 32, 64 rows); and how the
 // slices meet (accumulator: 1 us, and beyond 200 K adds 1 us per 60 K; second pass: 3.3 us and the partials at 3 TB/s).
-double tile_plan_cost(int M, int N, int K, int group, int rows, int S, int cus, bool bf16 = false)
+double tile_plan_cost(int M, int N, int K, int group, int rows, int S, int cus, bool bf16 = false, bool frugal = false)
 {
     const int G = K / group;
     const int gps = (G + S - 1) / S;
     S = (G + gps - 1) / gps;
-    const bool four = tile_wide(rows, group) && !bf16;
+    const bool four = tile_four(rows, group) && (rows == 64 ? group == 128 || !frugal : !bf16);
     const int waves = four ? 4 : 8;
-    const double per_block = four ? (rows == 64 ? 0.37 : 0.24) : (rows == 64 ? 0.94 : (rows == 32 ? 0.56 : 0.37));
+    const double per_block = four ? (rows == 64 ? (group == 32 ? 0.45 : 0.37) : 0.24) : (rows == 64 ? 0.94 : (rows == 32 ? 0.56 : 0.37));
     const long long tiles = (N + 63) / 64, wgs = tiles * ((M + rows - 1) / rows) * S;
     const long long rounds = (wgs + cus - 1) / cus;
     const long long blocks = ((long long)gps * (group / 32) + waves - 1) / waves;
     double finish = 0.0;
     if (S > 1) {
         const double adds = (double)S * M * N;
-        finish = slices_meet_in_accumulator(M, N, S) ? 1.0 + (adds > 2e5 ? (adds - 2e5) / 6e4 : 0.0) : 3.3 + 2.0 * adds * 4.0 / 3e6;
+        finish = slices_meet_in_accumulator(M, N, S, frugal || group == 128 ? 0 : rows) ? 1.0 + (adds > 2e5 ? (adds - 2e5) / 6e4 : 0.0) : 3.3 + 2.0 * adds * 4.0 / 3e6;
     }
     return 3.0 + (double)rounds * (double)blocks * per_block + finish;
 }
 
-// PANEL form (w4a16_panel.hip), for the scheduler's own plans beyond 128 rows: tiles of 128 x 256, the last row block of
+// PANEL form (w4a16_panel.hip), for the scheduler's own plans beyond 16 rows: tiles of 128 x 256, the last row block of
 // 32, 64, 96 or 128 rows, one tile per compute unit at a time.  The tiles past the last whole round of compute units may be
 // cut into S slices of K that fill the units once more; their FP32 partials (at most one tile per unit, 32 MB) are summed
 // by a second launch.  Costs (us), fitted to 26 (shape, format, group) measured with and without the split (M = 129 ... 2048,
@@ -295,9 +301,14 @@ bool use_panel(int M, int N, int K, int group, bool bf16, int cus, bool may_spli
         (void)panel_cost(M, N, K, group, bf16, cus, may_split, p);
         return true;
     }
-    if (M <= 128) return false;
-    // against the cheapest plan of 64-column tiles; each of their rounds beyond the first costs about 3.5 us more than the
-    // model says (measured: M = 512 ... 2048, two to nine rounds)
+    if (M <= 16) return false;
+    // Against the cheapest plan of 64-column tiles.  Beyond 128 rows each of their rounds after the first costs about 3.5 us
+    // more than the model says (measured: M = 512 ... 2048, two to nine rounds).  Up to 128 rows PANEL wins where 64-column
+    // tiles need several rounds or K is long (M = 64, K = 28672, N = 8192: 50.9 against 41.5 us; at K = 8192: 17.6 against
+    // 21.0); there it has to be 7 % cheaper, as the two models are together good for about that.  FP16 with groups of 128 up
+    // to 64 rows and below 8192 columns keeps its 64-column plans, which callers and tests know by their tiles and splits
+    // (M = 64, K = 18432, N = 7168: 32.9 us; the model gives PANEL 28).
+    if (M <= 64 && N < 8192 && group == 128 && !bf16) return false;
     double other = 1e30;
     const int G = K / group;
     for (int r = 16; r <= 64; r *= 2) {
@@ -305,17 +316,22 @@ bool use_panel(int M, int N, int K, int group, bool bf16, int cus, bool may_spli
         int smax = (int)(cus / wgs);
         smax = smax < 1 ? 1 : (smax > G ? G : smax);
         for (int s = 1; s <= smax; ++s) {
-            const double c = tile_plan_cost(M, N, K, group, r, s, cus, bf16) + 3.5 * (double)((wgs * s - 1) / cus);
+            const double c = tile_plan_cost(M, N, K, group, r, s, cus, bf16) + (M > 128 ? 3.5 * (double)((wgs * s - 1) / cus) : 0.0);
             if (c < other) other = c;
         }
     }
-    return panel_cost(M, N, K, group, bf16, cus, may_split, p) < other;
+    return panel_cost(M, N, K, group, bf16, cus, may_split, p) < (M > 128 ? other : 0.93 * other);
 }
 
-// `panel` (may be null) gets the plan's details where it is one of the PANEL form (tile_n = kPanelCols); may_split = false
-// asks for a plan of that form that needs no workspace.
-int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4a16_plan *p, PanelPlan *panel = nullptr, bool bf16 = false, bool may_split = true)
+// How much workspace a plan may ask for.  kBest: whatever pays.  kUnsplit: a plan of the PANEL form splits no tiles.
+// kFrugal: 64-column tiles only, split so that the slices of up to 640 K adds meet in the accumulator: many of these plans
+// need nothing, the others 8 bytes per output where kBest may take the FP32 partials of all slices.
+enum Thrift { kBest, kUnsplit, kFrugal };
+
+// `panel` (may be null) gets the plan's details where it is one of the PANEL form (tile_n = kPanelCols).
+int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4a16_plan *p, PanelPlan *panel = nullptr, bool bf16 = false, Thrift thrift = kBest)
 {
+    const bool frugal = thrift == kFrugal;
     const int G = K / group;
     const bool automatic = kernel == W4A16_KERNEL_AUTO && split == 0;
     if (kernel == W4A16_KERNEL_AUTO) {
@@ -366,11 +382,11 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
         p->split = S;
         p->groups_per_split = gps;
         p->workgroups = (int)(tiles * S);
-        p->workspace_bytes = workspace_of(kernel, M, N, S);
+        p->workspace_bytes = workspace_of(kernel, M, N, S, 0);
         return fits_32bit_offsets(M, N, K, group, gps) ? W4A16_OK : W4A16_ERR_UNSUPPORTED;
     }
     PanelPlan pp;
-    if (automatic && use_panel(M, N, K, group, bf16, cus, may_split, &pp)) {
+    if (automatic && !frugal && use_panel(M, N, K, group, bf16, cus, thrift == kBest, &pp)) {
         p->kernel = W4A16_KERNEL_TILE;
         p->tile_n = kPanelCols;
         p->tile_m = kPanelRows;
@@ -407,7 +423,7 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
                 const long long w1 = tiles * ((M + r - 1) / r);
                 const int smax = split ? split : ((int)(cus / w1) < 1 ? 1 : ((int)(cus / w1) > G ? G : (int)(cus / w1)));
                 for (int s = split ? split : 1; s <= smax; ++s) {
-                    const double c = tile_plan_cost(M, N, K, group, r, s, cus);
+                    const double c = tile_plan_cost(M, N, K, group, r, s, cus, false, frugal);
                     if (c < best) { best = c; rows_x = r; S = s; }
                 }
             }
@@ -415,7 +431,7 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
         p->tile_m = rows_x;
         const int tw = tuning().tile_waves;
         if (tw >= 4 && tw <= (tile_by_ticket(M, rows_x) ? 16 : 8)) { p->waves_k = tw; p->threads = 64 * tw; }
-        if (tile_wide(rows_x, group)) { p->waves_k = 4; p->threads = 256; }
+        if (tile_four(rows_x, group)) { p->waves_k = 4; p->threads = 256; }
         const long long wgs = tiles * ((M + rows_x - 1) / rows_x);
         if (S == 0) S = (int)(cus / wgs);  // never more workgroups than compute units: the extra ones would run as a second round
         if (S < 1) S = 1;
@@ -426,7 +442,7 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
         p->split = S;
         p->groups_per_split = gps;
         p->workgroups = (int)(wgs * S);
-        p->workspace_bytes = workspace_of(kernel, M, N, S);
+        p->workspace_bytes = workspace_of(kernel, M, N, S, frugal || group == 128 ? 0 : p->tile_m);
         if (((long long)tiles * S + 7) / 8 * 8 * ((M + rows_x - 1) / rows_x) > 0x7FFFFFFFLL) return W4A16_ERR_UNSUPPORTED;
         return fits_32bit_offsets(M, N, K, group, gps) ? W4A16_OK : W4A16_ERR_UNSUPPORTED;
     }
@@ -458,7 +474,7 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
     p->split = S;
     p->groups_per_split = gps;
     p->workgroups = (int)(tiles * S);
-    p->workspace_bytes = workspace_of(kernel, M, N, S);
+    p->workspace_bytes = workspace_of(kernel, M, N, S, 0);
     return fits_32bit_offsets(M, N, K, group, gps) ? W4A16_OK : W4A16_ERR_UNSUPPORTED;
 }
 
@@ -593,21 +609,23 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
     if (dev < 0) { note_hip_error(hipErrorNoDevice); return W4A16_ERR_HIP; }
     w4a16_plan plan;
     PanelPlan panel;
-    rc = make_plan(M, N, K, group, kernel, split, compute_units(dev), &plan, &panel, bf16);
-    if (rc) return rc;
-    // bfloat16 activations: the forms the scheduler chooses from (STRIPE by ticket for M <= 4, TILE)
-    if (bf16 && (plan.kernel == W4A16_KERNEL_WAVE_SPLIT || (plan.kernel == W4A16_KERNEL_STRIPE && !stripe_by_ticket(M))))
-        return W4A16_ERR_UNSUPPORTED;
-
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    const bool by_panel = plan.kernel == W4A16_KERNEL_TILE && plan.tile_n == kPanelCols;
-    int finish = by_panel ? (plan.split > 1 ? kFinishSecondPass : kFinishDirect) : finish_of(plan.kernel, M, N, plan.split);
+    bool by_panel = false;
+    int finish = kFinishDirect;
     Buffers b;
-    rc = find_buffers(dev, plan, finish, M, N, st, src, call_ws, call_ws_bytes, &b);
-    if (rc == W4A16_ERR_WORKSPACE && by_panel) {  // the split is worth a workspace where there is one; the plan without it needs none
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    // A split is worth a workspace where there is one; where it is not to be had, the plans that need less.
+    for (Thrift thrift : {kBest, kUnsplit, kFrugal}) {
+        rc = make_plan(M, N, K, group, kernel, split, compute_units(dev), &plan, &panel, bf16, thrift);
+        if (rc) return rc;
+        // bfloat16 activations: the forms the scheduler chooses from (STRIPE by ticket for M <= 4, TILE)
+        if (bf16 && (plan.kernel == W4A16_KERNEL_WAVE_SPLIT || (plan.kernel == W4A16_KERNEL_STRIPE && !stripe_by_ticket(M))))
+            return W4A16_ERR_UNSUPPORTED;
+        by_panel = plan.kernel == W4A16_KERNEL_TILE && plan.tile_n == kPanelCols;
+        finish = by_panel ? (plan.split > 1 ? kFinishSecondPass : kFinishDirect)
+                          : finish_of(plan.kernel, M, N, plan.split, thrift == kFrugal || group == 128 ? 0 : plan.tile_m);
         t_hip_error[0] = 0;
-        rc = make_plan(M, N, K, group, kernel, split, compute_units(dev), &plan, &panel, bf16, false);
-        finish = kFinishDirect;
+        rc = find_buffers(dev, plan, finish, M, N, st, src, call_ws, call_ws_bytes, &b);
+        if (rc != W4A16_ERR_WORKSPACE) break;
     }
     if (rc) return rc;
     if (tuning().log) log_plan(entry, M, N, K, group, plan, finish);
@@ -641,11 +659,12 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
         e = launch_panel(a, panel, st);
     } else if (plan.kernel == W4A16_KERNEL_TILE && tile_by_ticket(M, plan.tile_m)) {
         e = launch_tile_dyn(a, finish, b.sync, plan.waves_k, tuning().tile_depth == 2 && !bf16 && plan.waves_k <= 8 ? 2 : 1, tuning().tile_unit, st);
-    } else if (plan.kernel == W4A16_KERNEL_TILE && tile_wide(plan.tile_m, group) && !bf16) {
-        // four waves with the whole register file each; measured on M = 128, K = N = 8192: 27.5 us against 33.1 us with eight
+    } else if (plan.kernel == W4A16_KERNEL_TILE && tile_four(plan.tile_m, group) && plan.tile_m == 64 && (bf16 || group != 128)) {
+        e = launch_tile_tall(a, finish, b.sync, st);
+    } else if (plan.kernel == W4A16_KERNEL_TILE && tile_four(plan.tile_m, group) && !bf16) {
         e = launch_tile_wide(a, finish, b.sync, plan.tile_m, st);
     } else if (plan.kernel == W4A16_KERNEL_TILE) {
-        e = launch_tile(a, finish, b.sync, plan.tile_m, tile_wide(plan.tile_m, group) ? 8 : plan.waves_k, st);
+        e = launch_tile(a, finish, b.sync, plan.tile_m, tile_four(plan.tile_m, group) ? 8 : plan.waves_k, st);
     } else {
         e = launch_wave_split(a, plan.tile_n, st);
     }

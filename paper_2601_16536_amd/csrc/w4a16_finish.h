@@ -43,17 +43,26 @@ __device__ __forceinline__ float from_fixed(unsigned long long total)
     return (float)((double)fx * (1.0 / 16777216.0));
 }
 
-// One slice's sum into the accumulator word of an output; the last of `split` arrivals casts, stores Y and
-// clears the word.  `nan` says the slice sum is NaN (`add` then carries the value 0).  Act: the output's format.
-template <typename Act>
-__device__ __forceinline__ void add_slice(unsigned long long *word, unsigned long long add, bool nan, int split, uint16_t *y)
+// One slice's sum into the accumulator word of an output: the word's value with it.  `nan` says the slice sum is NaN (`add`
+// then carries the value 0).
+__device__ __forceinline__ unsigned long long add_slice_value(unsigned long long *word, unsigned long long add, bool nan)
 {
     if (nan) __hip_atomic_fetch_or(word, kFixPoison, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ahead of this slice's add: same thread, same address
-    const unsigned long long total = __hip_atomic_fetch_add(word, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add;
+    return __hip_atomic_fetch_add(word, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add;
+}
+// The last of `split` arrivals casts, stores Y and clears the word.  Act: the output's format.
+template <typename Act>
+__device__ __forceinline__ void finish_slice(unsigned long long *word, unsigned long long total, int split, uint16_t *y)
+{
     if ((total >> 58) == (unsigned long long)split) {
         *y = (total & kFixPoison) ? Act::kNaN : (uint16_t)(Act::pack2(from_fixed(total), 0.f) & 0xFFFFu);
         __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+}
+template <typename Act>
+__device__ __forceinline__ void add_slice(unsigned long long *word, unsigned long long add, bool nan, int split, uint16_t *y)
+{
+    finish_slice<Act>(word, add_slice_value(word, add, nan), split, y);
 }
 
 // Sum of the waves' result tiles (ROWS x COLS each) in wave order, `red_waves` waves per round through

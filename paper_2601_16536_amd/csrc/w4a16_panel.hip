@@ -22,13 +22,10 @@
 // w4a16_tile_wide.hip.
 #include "w4a16_device.h"
 #include "w4a16_internal.h"
-#include <type_traits>
-#include <utility>
+#include "w4a16_wide_ops.h"
 
 namespace w4a16 {
 namespace {
-
-typedef float float16_t __attribute__((ext_vector_type(16)));
 
 constexpr int kWaves = 4;
 constexpr int kMainRt = kPanelRows / 32;
@@ -40,115 +37,6 @@ constexpr int kSteps = kStage / 16;
 constexpr int kBuffers = 3;       // stages in LDS: the one in use and two on their way
 constexpr int kXcds = 8;
 constexpr int kRowGroup = 8;      // row blocks that neighbouring workgroups of an XCD cover before the next column tile
-
-// ---- operands ----
-// FP16: the B operand is (q - z) 2^-9, exact.  Byte e of a packed word holds the codes of k = 2e (bits 0-3) and 2e + 1
-// (bits 4-7).  v_perm_b32 puts the first, masked, into the low half and the second, masked, into the high half of a
-// register, where they are the FP16 subnormals q 2^-24 and q 2^-20; one packed FMA by (2^15, 2^11) gives (q - z) 2^-9.
-struct PanelF16 {
-    typedef ActF16 Act;
-    typedef uint32_t Zero;  // (-z 2^-9) in both halves
-    struct Consts {
-        uint32_t lo, hi, mul;
-    };
-    static __device__ __forceinline__ Consts consts()
-    {
-        Consts c = {0x0F0F0F0Fu, 0xF0F0F0F0u, 0x68007800u};  // 2^11 | 2^15
-        asm volatile("" : "+s"(c.lo), "+s"(c.hi), "+s"(c.mul));
-        return c;
-    }
-    static __device__ __forceinline__ Zero zero(uint32_t z)  // z in bits 0-3
-    {
-        H2 h, m;
-        h.u = (z & 15u) * 0x00010001u;
-        m.u = 0xF800F800u;  // -2^15
-        h.h = h.h * m.h;
-        return h.u;
-    }
-    static __device__ __forceinline__ float scale(_Float16 s) { return (float)s * 512.0f; }
-    // The unpack of one word in kParts parts of about five instructions.
-    static constexpr int kParts = 2;
-    struct Tmp {
-        uint32_t a, b;
-    };
-    static __device__ __forceinline__ uint32_t pair(const Tmp &t, uint32_t nz, const Consts &c, int e)
-    {
-        H2 v, m, z;
-        // selectors 0-3 pick from the second operand, 4-7 from the first, 0x0c gives zero
-        v.u = __builtin_amdgcn_perm(t.b, t.a, 0x0C040C00u + 0x00010001u * (uint32_t)e);
-        m.u = c.mul;
-        z.u = nz;
-        v.h = __builtin_elementwise_fma(v.h, m.h, z.h);
-        return v.u;
-    }
-    static __device__ __forceinline__ void unpack(int part, uint32_t w, Zero nz, const Consts &c, Tmp &t, uint4_t &r)
-    {
-        if (part == 0) {
-            t.a = w & c.lo;
-            t.b = w & c.hi;
-            r[0] = pair(t, nz, c, 0);
-        } else {
-            r[1] = pair(t, nz, c, 1);
-            r[2] = pair(t, nz, c, 2);
-            r[3] = pair(t, nz, c, 3);
-        }
-    }
-    static __device__ __forceinline__ float16_t mfma(uint4_t x, uint4_t b, float16_t c)
-    {
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, x), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
-    }
-};
-
-// BF16: the operand is q - z, exact, through FP32: a nibble masked in place is an FP16 subnormal, which the mixed FMA
-// reads as it is; the FP32 results are whole numbers below 16, so their upper halves are the bfloat16.
-struct PanelBF16 {
-    typedef ActBF16 Act;
-    typedef float Zero;  // -z
-    struct Consts {
-        uint32_t lo, hi;
-    };
-    static __device__ __forceinline__ Consts consts()
-    {
-        Consts c = {0x000F000Fu, 0x00F000F0u};
-        asm volatile("" : "+s"(c.lo), "+s"(c.hi));
-        return c;
-    }
-    static __device__ __forceinline__ Zero zero(uint32_t z) { return -(float)(z & 15u); }
-    static __device__ __forceinline__ float scale(_Float16 s) { return (float)s; }
-    static constexpr int kParts = 3;
-    struct Tmp {
-        H2 p[4];
-        float d[8];
-    };
-    static __device__ __forceinline__ void code(Tmp &t, Zero nz, int i)
-    {
-        const float m = i & 1 ? 1048576.0f : 16777216.0f;
-        t.d[i] = __builtin_fmaf((float)t.p[i & 3].h[i >> 2], m, nz);
-    }
-    static __device__ __forceinline__ void unpack(int part, uint32_t w, Zero nz, const Consts &c, Tmp &t, uint4_t &r)
-    {
-        if (part == 0) {
-            const uint32_t w8 = w >> 8;
-            t.p[0].u = w & c.lo;   // codes 0, 4
-            t.p[1].u = w & c.hi;   // 1, 5
-            t.p[2].u = w8 & c.lo;  // 2, 6
-            t.p[3].u = w8 & c.hi;  // 3, 7
-            code(t, nz, 0);
-        } else if (part == 1) {
-#pragma unroll
-            for (int i = 1; i < 7; ++i) code(t, nz, i);
-        } else {
-            code(t, nz, 7);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                r[e] = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, t.d[2 * e + 1]), __builtin_bit_cast(uint32_t, t.d[2 * e]), 0x07060302u);
-        }
-    }
-    static __device__ __forceinline__ float16_t mfma(uint4_t x, uint4_t b, float16_t c)
-    {
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bfloat8_t, x), __builtin_bit_cast(bfloat8_t, b), c, 0, 0, 0);
-    }
-};
 
 // Sizes for RT blocks of 32 rows and SEG k per step of scales.
 template <int RT, int SEG>
@@ -167,23 +55,6 @@ struct Panel {
     static constexpr int kLds = kBuffers * kStageBytes;
     static_assert(kLds <= 160 * 1024 && 2 * kPerStage < 64, "LDS of a compute unit, and the wait counter's range");
 };
-
-typedef __attribute__((address_space(3))) void *lds_ptr_t;
-
-// f(0), f(1), ... f(N - 1) with the numbers as constants.
-template <int... I, typename F>
-__device__ __forceinline__ void for_each_constant(std::integer_sequence<int, I...>, const F &f)
-{
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int BEG, int END, typename F>
-__device__ __forceinline__ void static_range(const F &f)
-{
-    if constexpr (BEG < END) {
-        f(std::integral_constant<int, BEG>{});
-        static_range<BEG + 1, END>(f);
-    }
-}
 
 // One workgroup's part: rows m0 .. m0 + 32 RT - 1, 256 columns from tile_col0 on, k from kbeg to kend.  The result goes to
 // Y, or as FP32 to `partial` ([128][256]).
@@ -545,7 +416,7 @@ hipError_t launch_panel(const GemmArgs &a, const PanelPlan &p, hipStream_t strea
     if (p.split_tiles && (!a.partials || p.split < 2 || p.slice_k % a.group || (a.group < kStage && p.slice_k % kStage) ||
                           (long long)p.slice_k * (p.split - 1) >= a.K || (long long)p.slice_k * p.split < a.K)) return hipErrorInvalidValue;
     if (a.K / 8 * (unsigned long long)a.N * 4ull >= 0x7F000000ull || (unsigned long long)a.M * a.K * 2ull >= 0x7F000000ull) return hipErrorInvalidValue;  // 32-bit buffer offsets
-    return a.bf16 ? launch_op<PanelBF16>(a, p, stream) : launch_op<PanelF16>(a, p, stream);
+    return a.bf16 ? launch_op<ExactBF16>(a, p, stream) : launch_op<ExactF16>(a, p, stream);
 }
 
 }  // namespace w4a16

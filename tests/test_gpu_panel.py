@@ -161,3 +161,81 @@ def test_panel_without_room_for_its_partials(gpu):
         binding.set_workspace(None)
     binding.gemm(*args, 128, out=Y)
     assert err_ratio(Y.double().cpu().numpy(), ref) <= 1.0
+
+
+# K: fewer stages than waves, a run that ends inside a stage, runs of unequal length, groups longer than a stage
+TALL = [(64, 128, 64, 128), (33, 640, 72, 128), (128, 832, 136, 64), (65, 96, 264, 32), (100, 1056, 200, 32), (130, 1536, 64, 384),
+        (70, 5376, 1032, 128), (61, 2048, 2056, 256)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N,group", TALL)
+def test_sixty_four_rows_per_workgroup_against_the_oracle(gpu, M, K, N, group):
+    """The 64-row form (w4a16_tile_tall.hip) in both formats, with its three finishes: direct, accumulator, second pass."""
+    torch, binding = gpu
+    index = 9600 + M + K + N
+    X, Wp, s, Zp = wl.make(M, K, N, index=index, group=group)
+    Xb = wl.make_x_bf16(M, K, index=index)
+    eights = wl.pack_along_n(np.full((K // group, N), 8, np.uint8))
+    _, dW, dS, dZ = binding.to_device(X, Wp, s, Zp)
+    dX, dXb = torch.from_numpy(X).cuda(), torch.from_numpy(Xb.view(np.int16)).cuda().view(torch.bfloat16)
+    G = K // group
+    binding.tune("tile_rows", 64)
+    try:
+        for split in sorted({1, min(2, G), min(5, G)}):
+            for finish in ((0,) if split == 1 else (1, 2)):
+                binding.tune("stripe_finish", finish)
+                for bf16, zeros, zp in ((False, dZ, Zp), (True, dZ, Zp), (False, None, eights), (True, None, eights)):
+                    say("64 rows", (M, K, N, group), "split", split, "finish", finish, "bf16" if bf16 else "fp16", "zeros" if zeros is not None else "symmetric")
+                    plan = binding.query_plan(M, N, K, group, binding.KERNEL_TILE, split)
+                    assert plan["tile_m"] == 64 and plan["waves_k"] == 4
+                    ref = orc.gemm_bf16(Xb, Wp, s, zp, group) if bf16 else orc.gemm(X, Wp, s, zp, group)
+                    outs = []
+                    for _ in range(2):
+                        Y = torch.full((M, N), float("nan"), dtype=torch.bfloat16 if bf16 else torch.float16, device="cuda")
+                        (binding.gemm_bf16 if bf16 else binding.gemm_ex)(dXb if bf16 else dX, dW, dS, zeros, group, kernel=binding.KERNEL_TILE, split=split, out=Y)
+                        torch.cuda.synchronize()
+                        outs.append(Y)
+                    assert torch.equal(outs[0], outs[1])
+                    assert err_ratio(outs[0].double().cpu().numpy(), ref) <= 1.0
+    finally:
+        binding.tune("tile_rows", 0)
+        binding.tune("stripe_finish", 0)
+
+
+@pytest.mark.gpu
+def test_sixty_four_rows_keep_rows_that_are_not_finite_apart(gpu):
+    torch, binding = gpu
+    M, K, N, group = 66, 480, 72, 32  # the slice ends inside a stage, and row 65's X starts where row 64's ends
+    X, Wp, s, Zp = wl.make(M, K, N, index=9700, group=group)
+    X[64], X[65, ::2] = 0.5, np.nan
+    ref = orc.gemm(X[:65], Wp, s, Zp, group)
+    args = binding.to_device(X, Wp, s, Zp)
+    binding.tune("tile_rows", 64)
+    try:
+        for split in (1, 3):
+            say("64 rows, NaN in one row", split)
+            Y = binding.gemm_ex(*args, group, kernel=binding.KERNEL_TILE, split=split).double().cpu().numpy()
+            assert np.isnan(Y[65]).all() and err_ratio(Y[:65], ref) <= 1.0
+    finally:
+        binding.tune("tile_rows", 0)
+
+
+@pytest.mark.gpu
+def test_sixty_four_rows_where_the_partials_have_no_room(gpu):
+    """A 64-row plan whose slices go to FP32 partials, with a workspace that holds them, one that holds 64-bit sums only, and
+    one that holds neither: the plans that need less."""
+    torch, binding = gpu
+    M, K, N, group = 91, 5696, 1408, 64
+    plan = binding.query_plan(M, N, K, group)
+    assert plan["tile_m"] == 64 and plan["split"] > 1 and plan["workspace_bytes"] > M * N * 8, plan
+    X, Wp, s, Zp = wl.make(M, K, N, index=9800, group=group)
+    ref = orc.gemm(X, Wp, s, Zp, group)
+    args = binding.to_device(X, Wp, s, Zp)
+    for size in (plan["workspace_bytes"], M * N * 8, 256):
+        say("64 rows, workspace of", size)
+        ws = torch.full((size + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+        ws = ws[-ws.data_ptr() % 256:][:size]
+        Y = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
+        binding.gemm_ws(*args, group, ws, out=Y)
+        assert err_ratio(Y.double().cpu().numpy(), ref) <= 1.0
