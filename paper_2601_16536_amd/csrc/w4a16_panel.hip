@@ -368,7 +368,15 @@ __global__ __launch_bounds__(256) void panel_reduce_kernel(const GemmArgs a, con
     if (t.m0 + r >= a.M || t.col0 + c >= a.N) return;
     const float *p = a.partials + (size_t)idx * a.split * kPanelPartial + r * kCols + c;
     float4_t acc = *reinterpret_cast<const float4_t *>(p);
-    for (int s = 1; s < a.split; ++s) acc += *reinterpret_cast<const float4_t *>(p + (size_t)s * kPanelPartial);
+    int s = 1;
+    for (; s + 4 <= a.split; s += 4) {  // four loads in flight, added in slice order
+        float4_t v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = *reinterpret_cast<const float4_t *>(p + (size_t)(s + e) * kPanelPartial);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc += v[e];
+    }
+    for (; s < a.split; ++s) acc += *reinterpret_cast<const float4_t *>(p + (size_t)s * kPanelPartial);
     *reinterpret_cast<uint2_t *>(a.Y + (size_t)(t.m0 + r) * a.N + t.col0 + c) = (uint2_t){Act::pack2(acc[0], acc[1]), Act::pack2(acc[2], acc[3])};
 }
 
