@@ -118,9 +118,9 @@ typedef struct {
  * memory).  While `stream` is being captured into a graph nothing can be
  * allocated: a call that would have to returns W4A16_ERR_WORKSPACE; run the
  * same shape once outside the capture first, or use w4a16_set_workspace,
- * w4a16_gemm_ws or w4a16_gemm_noalloc.  (For M > 16 the library first
- * tries the plans that need less: tiles of 256 columns unsplit, then tiles of 64 columns whose slices meet in
- * 64-bit sums or that need nothing.  The same bits on every call that finds the same room.)  If a launch fails
+ * w4a16_gemm_ws or w4a16_gemm_noalloc.  (For M > 16 the library
+ * takes a plan that needs no buffer where there is one, see w4a16_gemm_scratch, and before it answers so tries the
+ * plans that need less.  The same bits on every call that finds the same room.)  If a launch fails
  * (W4A16_ERR_HIP) the library clears its accumulator again before the next use.
  */
 int w4a16_gemm(const void *X, const uint32_t *Wpacked, const void *scales, const uint32_t *zeros,
@@ -165,6 +165,18 @@ int w4a16_gemm_bf16(const void *X, const uint32_t *Wpacked, const void *scales, 
                     int group, int M, int N, int K, void *Y, void *stream, int kernel, int split);
 
 /*
+ * Scratch memory for one call, from the caller's own allocator.  For M > 16 the fastest plan may need the FP32 partials of
+ * Algorithm 1 (Section 3) where another plan needs nothing; w4a16_gemm and the others that work in shared buffers then
+ * run the one that needs nothing, so that calls on several streams may overlap.  w4a16_scratch_bytes tells what the
+ * faster plan needs (0: call w4a16_gemm or w4a16_gemm_bf16), w4a16_gemm_scratch runs it: `scratch` as the workspace of
+ * w4a16_gemm_ws, used by this call alone until its work on `stream` is done; `bf16` nonzero: X and Y as in
+ * w4a16_gemm_bf16.
+ */
+size_t w4a16_scratch_bytes(int M, int N, int K, int group, int bf16);
+int w4a16_gemm_scratch(const void *X, const uint32_t *Wpacked, const void *scales, const uint32_t *zeros,
+                       int group, int M, int N, int K, void *Y, void *stream, int bf16, void *scratch, size_t scratch_bytes);
+
+/*
  * Registers caller-owned split buffers (Algorithm 1's C_i; Section 3) for the
  * current device: device memory, 256-byte aligned, at least 256 bytes, owned by
  * the caller and kept valid until it is replaced or removed (NULL removes it).
@@ -194,7 +206,8 @@ int w4a16_gemm_noalloc(const void *X, const uint32_t *Wpacked, const void *scale
  * 256); forced plans: w4a16_query_plan. */
 size_t w4a16_workspace_bytes(int M, int N, int K, int group);
 
-/* The plan w4a16_gemm_ex would run for these arguments (no launch, no GPU call
+/* The plan w4a16_gemm_ws, given its workspace, would run for these arguments, and w4a16_gemm_ex too unless M > 16, the
+ * plan needs a workspace and another needs none (no launch, no GPU call
  * beyond reading the current device's properties once). */
 int w4a16_query_plan(int M, int N, int K, int group, int kernel, int split, w4a16_plan *out);
 

@@ -16,7 +16,8 @@ ERR_NULL, ERR_SHAPE, ERR_GROUP, ERR_ALIGN, ERR_WORKSPACE, ERR_HIP, ERR_UNSUPPORT
 KERNEL_AUTO, KERNEL_WAVE_SPLIT, KERNEL_STRIPE, KERNEL_TILE = -1, 0, 3, 4  # 1 and 2: retired families
 
 EXPORTS = (
-    "w4a16_gemm", "w4a16_gemm_ex", "w4a16_gemm_ws", "w4a16_gemm_noalloc", "w4a16_gemm_bf16", "w4a16_set_workspace", "w4a16_tune",
+    "w4a16_gemm", "w4a16_gemm_ex", "w4a16_gemm_ws", "w4a16_gemm_noalloc", "w4a16_gemm_bf16", "w4a16_scratch_bytes", "w4a16_gemm_scratch",
+    "w4a16_set_workspace", "w4a16_tune",
     "w4a16_workspace_bytes", "w4a16_query_plan",
     "w4a16_reduce", "w4a16_dequant", "w4a16_quantize", "w4a16_stream_probe", "w4a16_status_string", "w4a16_last_hip_error", "w4a16_shutdown",
 )
@@ -75,6 +76,9 @@ def lib():
         L.w4a16_gemm_ws.argtypes = gemm_args + [ci, ci, vp, sz]
         L.w4a16_gemm_noalloc.argtypes = gemm_args + [ci, ci]
         L.w4a16_gemm_bf16.argtypes = gemm_args + [ci, ci]
+        L.w4a16_scratch_bytes.argtypes = [ci, ci, ci, ci, ci]
+        L.w4a16_scratch_bytes.restype = sz
+        L.w4a16_gemm_scratch.argtypes = gemm_args + [ci, vp, sz]
         L.w4a16_set_workspace.argtypes = [vp, sz]
         L.w4a16_tune.argtypes = [ctypes.c_char_p, ci]
         L.w4a16_workspace_bytes.argtypes = [ci, ci, ci, ci]
@@ -193,12 +197,32 @@ def tune(knob: str, value: int) -> None:
         raise W4A16Error(rc, "w4a16_tune(%r)" % knob)
 
 
+def _scratch(X, group: int, M: int, N: int, K: int, bf16: int):
+    """Scratch memory for one call on the current stream from torch's allocator, which knows when the stream is done with it;
+    None where the call has no use for it."""
+    n = lib().w4a16_scratch_bytes(M, N, K, group, bf16) if M > 16 else 0
+    if not n:
+        return None
+    import torch
+    return X.new_empty(n + 256, dtype=torch.uint8)
+
+
+def _gemm_scratch(X, Wpacked, scales, zeros, group, M, N, K, Y, bf16, scratch) -> int:
+    base = (scratch.data_ptr() + 255) & ~255  # 256-byte aligned
+    return lib().w4a16_gemm_scratch(X.data_ptr(), Wpacked.data_ptr(), scales.data_ptr(), _ptr(zeros), group, M, N, K, Y.data_ptr(),
+                                    _current_stream(), bf16, base, scratch.numel() - 256)
+
+
 def gemm(X, Wpacked, scales, zeros, group: int, out=None, stream=None):
     """Y = X * s (W - z) (Eq. 2).  uint32 storage travels as torch.int32 tensors."""
     M, N, K = _check_tensors(X, Wpacked, scales, zeros, group)
     Y = out if out is not None else X.new_empty((M, N))
-    rc = raw_gemm(X.data_ptr(), Wpacked.data_ptr(), scales.data_ptr(), _ptr(zeros), group, M, N, K,
-                  Y.data_ptr(), _stream(stream))
+    scratch = _scratch(X, group, M, N, K, 0) if stream is None else None
+    if scratch is not None:
+        rc = _gemm_scratch(X, Wpacked, scales, zeros, group, M, N, K, Y, 0, scratch)
+    else:
+        rc = raw_gemm(X.data_ptr(), Wpacked.data_ptr(), scales.data_ptr(), _ptr(zeros), group, M, N, K,
+                      Y.data_ptr(), _stream(stream))
     if rc:
         raise W4A16Error(rc, "w4a16_gemm")
     return Y
@@ -223,6 +247,12 @@ def gemm_bf16(X, Wpacked, scales, zeros, group: int, kernel: int = KERNEL_AUTO, 
     Y = out if out is not None else X.new_empty((M, N))
     if Y.dtype != torch.bfloat16 or tuple(Y.shape) != (M, N) or not Y.is_contiguous():
         raise ValueError("out must be a contiguous bfloat16 [M, N] tensor")
+    scratch = _scratch(X, group, M, N, K, 1) if stream is None and kernel == KERNEL_AUTO and split == 0 else None
+    if scratch is not None:
+        rc = _gemm_scratch(X, Wpacked, scales, zeros, group, M, N, K, Y, 1, scratch)
+        if rc:
+            raise W4A16Error(rc, "w4a16_gemm_bf16")
+        return Y
     rc = lib().w4a16_gemm_bf16(X.data_ptr(), Wpacked.data_ptr(), scales.data_ptr(), _ptr(zeros), group, M, N, K,
                                Y.data_ptr(), _stream(stream), kernel, split)
     if rc:

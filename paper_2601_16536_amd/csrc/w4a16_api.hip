@@ -613,10 +613,18 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
     int finish = kFinishDirect;
     Buffers b;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // A split is worth a workspace where there is one; where it is not to be had, the plans that need less.
+    // A split is worth a workspace where the call brings one; where it is not to be had, the plans that need less.  Buffers
+    // that calls share (the library's, a registered workspace, the fixed array) are for shapes only whose frugal plan needs
+    // them too: calls that need none may overlap on several streams.
+    bool only_free = false;
+    if (src != kFromCall && M > 16) {
+        w4a16_plan frugal;
+        only_free = make_plan(M, N, K, group, kernel, split, compute_units(dev), &frugal, nullptr, bf16, kFrugal) == W4A16_OK && frugal.workspace_bytes == 0;
+    }
     for (Thrift thrift : {kBest, kUnsplit, kFrugal}) {
         rc = make_plan(M, N, K, group, kernel, split, compute_units(dev), &plan, &panel, bf16, thrift);
         if (rc) return rc;
+        if (only_free && plan.workspace_bytes != 0) continue;  // (never the last one)
         // bfloat16 activations: the forms the scheduler chooses from (STRIPE by ticket for M <= 4, TILE)
         if (bf16 && (plan.kernel == W4A16_KERNEL_WAVE_SPLIT || (plan.kernel == W4A16_KERNEL_STRIPE && !stripe_by_ticket(M))))
             return W4A16_ERR_UNSUPPORTED;
@@ -712,6 +720,22 @@ int w4a16_gemm_bf16(const void *X, const uint32_t *Wpacked, const void *scales, 
                     int N, int K, void *Y, void *stream, int kernel, int split)
 {
     return run("gemm_bf16", X, Wpacked, scales, zeros, group, M, N, K, Y, stream, kernel, split, kFromLibrary, nullptr, 0, true);
+}
+
+size_t w4a16_scratch_bytes(int M, int N, int K, int group, int bf16)
+{
+    w4a16_plan p;
+    if (M <= 16 || check_shape(group, M, N, K)) return 0;
+    if (make_plan(M, N, K, group, W4A16_KERNEL_AUTO, 0, compute_units(current_device()), &p, nullptr, bf16 != 0)) return 0;
+    const bool by_panel = p.kernel == W4A16_KERNEL_TILE && p.tile_n == kPanelCols;
+    if (!by_panel && finish_of(p.kernel, M, N, p.split, group == 128 ? 0 : p.tile_m) != kFinishSecondPass) return 0;
+    return p.workspace_bytes;
+}
+
+int w4a16_gemm_scratch(const void *X, const uint32_t *Wpacked, const void *scales, const uint32_t *zeros, int group, int M,
+                       int N, int K, void *Y, void *stream, int bf16, void *scratch, size_t scratch_bytes)
+{
+    return run("gemm_scratch", X, Wpacked, scales, zeros, group, M, N, K, Y, stream, W4A16_KERNEL_AUTO, 0, kFromCall, scratch, scratch_bytes, bf16 != 0);
 }
 
 int w4a16_set_workspace(void *workspace, size_t workspace_bytes)

@@ -239,3 +239,42 @@ def test_sixty_four_rows_where_the_partials_have_no_room(gpu):
         Y = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
         binding.gemm_ws(*args, group, ws, out=Y)
         assert err_ratio(Y.double().cpu().numpy(), ref) <= 1.0
+
+
+@pytest.mark.gpu
+def test_prompts_on_two_streams_at_once(gpu):
+    """Shapes whose 64-column plan needs no buffer may overlap: calls of different inputs on two streams, through the binding
+    (a scratch of each call's own) and through the C entry (a plan that needs none), give what they give one at a time."""
+    torch, binding = gpu
+    M, K, N = 400, 4096, 7168
+    assert binding.query_plan(M, N, K, 128)["workspace_bytes"] > 0
+    _, Wp, s, Zp = wl.make(1, K, N, index=9900)
+    _, dW, dS, dZ = binding.to_device(np.zeros((1, K), np.float16), Wp, s, Zp)
+    Xs = [torch.from_numpy(wl.make_x(M, K, index=9901 + i)).cuda() for i in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+
+    def through_binding(X, Y, st):
+        with torch.cuda.stream(st):
+            binding.gemm(X, dW, dS, dZ, 128, out=Y)
+
+    def through_c(X, Y, st):
+        assert binding.raw_gemm(X.data_ptr(), dW.data_ptr(), dS.data_ptr(), dZ.data_ptr(), 128, M, N, K, Y.data_ptr(), st.cuda_stream) == binding.OK
+
+    for call in (through_binding, through_c):
+        say("two streams", call.__name__)
+        alone = []
+        for X in Xs:
+            Y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+            torch.cuda.synchronize()
+            call(X, Y, streams[0])
+            torch.cuda.synchronize()
+            alone.append(Y)
+        outs = [[torch.empty((M, N), dtype=torch.float16, device="cuda") for _ in range(6)] for _ in Xs]
+        torch.cuda.synchronize()
+        for r in range(6):
+            for X, Y, st in zip(Xs, outs, streams):
+                call(X, Y[r], st)
+        torch.cuda.synchronize()
+        for want, got in zip(alone, outs):
+            assert all(torch.equal(want, Y) for Y in got)
+    assert err_ratio(alone[0].double().cpu().numpy()[:8], orc.gemm(wl.make_x(M, K, index=9901)[:8], Wp, s, Zp, 128)) <= 1.0
