@@ -152,9 +152,12 @@ bool fits_32bit_offsets(int M, int N, int K, int group, int gps)
 //   x S slices of K with S = compute units / stripes, rounded down: one workgroup per compute unit whose
 //   waves share the slice.
 // TILE (everything else): 64-column tiles x 16, 32 or 64 rows of X per workgroup (as many rows as still
-//   leave a workgroup per compute unit at S = 1), eight waves own contiguous runs of the slice's K;
+//   leave a workgroup per compute unit at S = 1), eight or four waves own contiguous runs of the slice's K;
 //   S = compute units / workgroups, rounded down (a workgroup too many would run as a second round).
 //   Its time does not depend on M up to 16; STRIPE's grows with the S M N atomic adds of its finish.
+//
+// PANEL (a form of TILE, M > 16): tiles of 128 rows x 256 columns for prompts, and for batches whose 64-column tiles would
+//   run in several rounds or over a long K (use_panel).
 //
 // WAVE_SPLIT (M <= 4) is kept as a forced plan (w4a16_gemm_ex), the data-parallel form for comparisons:
 //   one workgroup of sixteen waves per column tile of 32 or 64 columns; the sixteen waves are sixteen K

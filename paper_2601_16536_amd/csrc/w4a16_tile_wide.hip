@@ -110,8 +110,7 @@ struct CodesF16 {
     }
 };
 
-// (BF16 activations stay with the eight-wave form: gfx950 has no packed BF16 add, and q - z through FP32 costs more
-// than that form's sum of x.)
+// (BF16 activations and other lengths of group have w4a16_tile_tall.hip at 64 rows and the eight-wave form at 32.)
 
 // A chunk of X into LDS: each wave-wide load puts lane l's 16 bytes at (base + 16 l), 1 KiB per load.
 template <int LOADS>
