@@ -1,0 +1,146 @@
+"""Where a call's own scratch memory (w4a16_scratch_bytes) comes from, and the calls that do without it."""
+import contextlib
+import ctypes
+
+import numpy as np
+import pytest
+
+from oracle import w4a16_oracle as orc
+from paper_2601_16536_amd import workloads as wl
+
+M, K, N = 400, 4096, 7168  # in tiles of 128 x 256 with a split of the last ones: 29 MB of partials; unsplit it needs nothing
+
+
+class FakeTensor:
+    """What the binding sees of a device tensor, on a machine without a device."""
+
+    class device:
+        index = 0
+
+    def __init__(self, size=0, address=4096):
+        self.size, self.address = size, address
+
+    def new_empty(self, size, dtype=None):
+        return FakeTensor(size, 1 << 20)
+
+    def data_ptr(self):
+        return self.address
+
+
+@pytest.fixture()
+def binding():
+    from paper_2601_16536_amd import binding as b
+    b.lib()
+    assert b.lib().w4a16_scratch_bytes(M, N, K, 128, 0) > 0
+    return b
+
+
+def snapshot_with(pool):
+    return lambda *a, **k: [{"device": 0, "address": 0, "total_size": 1 << 19, "segment_pool_id": (0, 0)},
+                            {"device": 1, "address": 1 << 19, "total_size": 1 << 21, "segment_pool_id": (0, 0)},
+                            {"device": 0, "address": 1 << 19, "total_size": 1 << 21, "segment_pool_id": pool}]
+
+
+def no_snapshot(*a, **k):
+    raise RuntimeError("this allocator keeps no record")
+
+
+@pytest.mark.parametrize("capturing,snapshot,scratch", [
+    (False, no_snapshot, True),             # no capture: the block is the call's until the stream is done with it
+    (True, snapshot_with((3, 0)), True),    # a graph that torch records: a pool of its own
+    (True, snapshot_with((0, 0)), False),   # a capture torch knows nothing of: the common pool
+    (True, no_snapshot, False)])
+def test_scratch_under_a_capture_comes_from_the_graphs_own_pool(binding, monkeypatch, capturing, snapshot, scratch):
+    import torch
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: capturing)
+    monkeypatch.setattr(torch.cuda, "memory_snapshot", snapshot)
+    assert (binding._scratch(FakeTensor(), 128, M, N, K, 0) is not None) == scratch
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    from paper_2601_16536_amd import binding
+    assert torch.cuda.is_available()
+    X, Wp, s, Zp = wl.make(M, K, N, index=9450)
+    rows = [0, 127, 128, 399]
+    return torch, binding, binding.to_device(X, Wp, s, Zp), rows, orc.gemm(np.ascontiguousarray(X[rows]), Wp, s, Zp, 128)
+
+
+def check(Y, rows, ref):
+    got = Y.double().cpu().numpy()[rows]
+    assert np.max(np.abs(got - ref) / (1e-2 * (1.0 + np.abs(ref)))) <= 1.0
+
+
+def hip_runtime():
+    with open("/proc/self/maps") as f:
+        path = next(line.split()[-1] for line in f if "libamdhip64" in line)
+    hip, vp = ctypes.CDLL(path), ctypes.c_void_p
+    hip.hipStreamBeginCapture.argtypes = [vp, ctypes.c_int]
+    hip.hipStreamEndCapture.argtypes = [vp, ctypes.POINTER(vp)]
+    hip.hipGraphInstantiate.argtypes = [ctypes.POINTER(vp), vp, vp, vp, ctypes.c_size_t]
+    hip.hipGraphLaunch.argtypes = [vp, vp]
+    hip.hipGraphExecDestroy.argtypes = [vp]
+    hip.hipGraphDestroy.argtypes = [vp]
+    return hip
+
+
+@contextlib.contextmanager
+def captured_by_hip(torch, stream, launch):
+    """Captures on `stream` through the HIP runtime alone; launch[0] then replays."""
+    hip, graph, run = hip_runtime(), ctypes.c_void_p(), ctypes.c_void_p()
+    assert hip.hipStreamBeginCapture(stream.cuda_stream, 0) == 0
+    try:
+        yield
+    finally:
+        rc = hip.hipStreamEndCapture(stream.cuda_stream, ctypes.byref(graph))
+    assert rc == 0 and hip.hipGraphInstantiate(ctypes.byref(run), graph, None, None, 0) == 0
+    launch.append(lambda: hip.hipGraphLaunch(run, stream.cuda_stream))
+    launch.append(lambda: (hip.hipGraphExecDestroy(run), hip.hipGraphDestroy(graph)))
+
+
+@pytest.mark.gpu
+def test_replays_of_a_capture_begun_through_hip_leave_other_tensors_alone(gpu):
+    """What is allocated after the capture keeps its values through replays, and the replays give the eager result."""
+    torch, binding, args, rows, ref = gpu
+    stream = torch.cuda.Stream()
+    Y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+    with torch.cuda.stream(stream):
+        torch.empty(1, dtype=torch.uint8, device="cuda")
+        kept = torch.empty(32 << 20, dtype=torch.uint8, device="cuda")
+        del kept  # a free block that the allocator would hand out for scratch
+        torch.cuda.synchronize()
+        launch = []
+        print("[case] captured through HIP", flush=True)
+        with captured_by_hip(torch, stream, launch):
+            binding.gemm(*args, 128, out=Y)
+        others = [torch.full((n,), 7, dtype=torch.uint8, device="cuda") for n in (32 << 20, 29 << 20, 1 << 20)]
+        torch.cuda.synchronize()
+        for _ in range(3):
+            Y.fill_(float("nan"))
+            assert launch[0]() == 0
+            torch.cuda.synchronize()
+            check(Y, rows, ref)
+            assert all(bool((t == 7).all()) for t in others)
+        launch[1]()
+
+
+@pytest.mark.gpu
+def test_scratch_of_a_graph_that_torch_records(gpu):
+    torch, binding, args, rows, ref = gpu
+    Y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+    binding.gemm(*args, 128, out=Y)
+    eager = Y.clone()
+    check(eager, rows, ref)
+    graph, seen = torch.cuda.CUDAGraph(), []
+    print("[case] captured by torch", flush=True)
+    with torch.cuda.graph(graph):
+        seen.append(binding._scratch(args[0], 128, M, N, K, 0) is not None)
+        binding.gemm(*args, 128, out=Y)
+    assert seen == [True]
+    others = [torch.full((n,), 7, dtype=torch.uint8, device="cuda") for n in (32 << 20, 29 << 20)]
+    for _ in range(3):
+        Y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Y, eager) and all(bool((t == 7).all()) for t in others)
