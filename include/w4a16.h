@@ -120,7 +120,8 @@ typedef struct {
  * same shape once outside the capture first, or use w4a16_set_workspace,
  * w4a16_gemm_ws or w4a16_gemm_noalloc.  (For M > 16 the library
  * takes a plan that needs no buffer where there is one, see w4a16_gemm_scratch, and before it answers so tries the
- * plans that need less.  The same bits on every call that finds the same room.)  If a launch fails
+ * plans that need less, without a registered workspace down to the slower one that needs nothing.  The same bits on every
+ * call that finds the same room.)  If a launch fails
  * (W4A16_ERR_HIP) the library clears its accumulator again before the next use.
  */
 int w4a16_gemm(const void *X, const uint32_t *Wpacked, const void *scales, const uint32_t *zeros,

@@ -328,8 +328,9 @@ bool use_panel(int M, int N, int K, int group, bool bf16, int cus, bool may_spli
 
 // How much workspace a plan may ask for.  kBest: whatever pays.  kUnsplit: a plan of the PANEL form splits no tiles.
 // kFrugal: 64-column tiles only, split so that the slices of up to 640 K adds meet in the accumulator: many of these plans
-// need nothing, the others 8 bytes per output where kBest may take the FP32 partials of all slices.
-enum Thrift { kBest, kUnsplit, kFrugal };
+// need nothing, the others 8 bytes per output where kBest may take the FP32 partials of all slices.  kBare: 64-column tiles
+// and S = 1, no workspace at all.  The last three differ from kBest for the scheduler's own plans beyond 16 rows only.
+enum Thrift { kBest, kUnsplit, kFrugal, kBare };
 
 // `panel` (may be null) gets the plan's details where it is one of the PANEL form (tile_n = kPanelCols).
 int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4a16_plan *p, PanelPlan *panel = nullptr, bool bf16 = false, Thrift thrift = kBest)
@@ -353,6 +354,7 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
     if (kernel == W4A16_KERNEL_STRIPE && M > 16) return W4A16_ERR_UNSUPPORTED;
     if (split < 0 || split > G) return W4A16_ERR_UNSUPPORTED;
     p->kernel = kernel;
+    if (automatic && thrift == kBare && M > 16) split = 1;
     long long tiles;
     int S = split;
     if (kernel == W4A16_KERNEL_STRIPE) {
@@ -389,7 +391,7 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
         return fits_32bit_offsets(M, N, K, group, gps) ? W4A16_OK : W4A16_ERR_UNSUPPORTED;
     }
     PanelPlan pp;
-    if (automatic && !frugal && use_panel(M, N, K, group, bf16, cus, thrift == kBest, &pp)) {
+    if (automatic && thrift < kFrugal && use_panel(M, N, K, group, bf16, cus, thrift == kBest, &pp)) {
         p->kernel = W4A16_KERNEL_TILE;
         p->tile_n = kPanelCols;
         p->tile_m = kPanelRows;
@@ -619,15 +621,22 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
     // A split is worth a workspace where the call brings one; where it is not to be had, the plans that need less.  Buffers
     // that calls share (the library's, a registered workspace, the fixed array) are for shapes only whose frugal plan needs
     // them too: calls that need none may overlap on several streams.
-    bool only_free = false;
+    // Where the library's own buffers are too small and cannot grow (under a capture), the scheduler's plans end with one that
+    // needs none; a caller whose own memory is too small for kFrugal is told so.
+    bool only_free = false, bare = false;
+    if (src == kFromLibrary && M > 16 && kernel == W4A16_KERNEL_AUTO && split == 0) {
+        std::lock_guard<std::mutex> lock(g_mutex);
+        bare = !g_dev[dev].user_ws;
+    }
     if (src != kFromCall && M > 16) {
         w4a16_plan frugal;
         only_free = make_plan(M, N, K, group, kernel, split, compute_units(dev), &frugal, nullptr, bf16, kFrugal) == W4A16_OK && frugal.workspace_bytes == 0;
     }
-    for (Thrift thrift : {kBest, kUnsplit, kFrugal}) {
+    for (Thrift thrift : {kBest, kUnsplit, kFrugal, kBare}) {
+        if (thrift == kBare && !bare) break;
         rc = make_plan(M, N, K, group, kernel, split, compute_units(dev), &plan, &panel, bf16, thrift);
         if (rc) return rc;
-        if (only_free && plan.workspace_bytes != 0) continue;  // (never the last one)
+        if (only_free && plan.workspace_bytes != 0) continue;  // (never kFrugal's)
         // bfloat16 activations: the forms the scheduler chooses from (STRIPE by ticket for M <= 4, TILE)
         if (bf16 && (plan.kernel == W4A16_KERNEL_WAVE_SPLIT || (plan.kernel == W4A16_KERNEL_STRIPE && !stripe_by_ticket(M))))
             return W4A16_ERR_UNSUPPORTED;

@@ -144,3 +144,30 @@ def test_scratch_of_a_graph_that_torch_records(gpu):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(Y, eager) and all(bool((t == 7).all()) for t in others)
+
+
+@pytest.mark.gpu
+def test_a_capture_after_calls_that_brought_their_scratch(gpu):
+    """M = 64, K = 16384, N = 4096: four slices, every plan of two or more needs a buffer.  A call through the binding brings its
+    own and leaves the library without; the same shape under a capture, which may not allocate, and with an explicit stream,
+    which brings none, then runs unsplit."""
+    torch, binding, _, _, _ = gpu
+    m, k, n = 64, 16384, 4096
+    assert binding.lib().w4a16_scratch_bytes(m, n, k, 128, 0) > 0
+    X, Wp, s, Zp = wl.make(m, k, n, index=9460)
+    rows = [0, 31, 32, 63]
+    ref = orc.gemm(np.ascontiguousarray(X[rows]), Wp, s, Zp, 128)
+    args = binding.to_device(X, Wp, s, Zp)
+    binding.shutdown()  # the library holds no split buffers now
+    Y = torch.empty((m, n), dtype=torch.float16, device="cuda")
+    check(binding.gemm(*args, 128), rows, ref)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    print("[case] explicit stream under capture, no buffers", flush=True)
+    with torch.cuda.graph(graph):
+        binding.gemm(*args, 128, out=Y, stream=torch.cuda.current_stream())
+    for _ in range(3):
+        Y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        check(Y, rows, ref)
