@@ -57,6 +57,17 @@ def test_scratch_under_a_capture_comes_from_the_graphs_own_pool(binding, monkeyp
     assert (binding._scratch(FakeTensor(), 128, M, N, K, 0) is not None) == scratch
 
 
+def test_a_full_device_is_no_error_of_a_call_that_can_do_without(binding, monkeypatch):
+    import torch
+
+    def full(*a, **k):
+        raise torch.OutOfMemoryError("no room")
+
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: False)
+    monkeypatch.setattr(FakeTensor, "new_empty", full)
+    assert binding._scratch(FakeTensor(), 128, M, N, K, 0) is None
+
+
 @pytest.fixture(scope="module")
 def gpu():
     import torch
