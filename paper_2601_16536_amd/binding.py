@@ -197,28 +197,28 @@ def tune(knob: str, value: int) -> None:
         raise W4A16Error(rc, "w4a16_tune(%r)" % knob)
 
 
-def _scratch(X, group: int, M: int, N: int, K: int, bf16: int):
-    """Scratch memory for one call on the current stream from torch's allocator, which knows when the stream is done with it;
-    None where the call has no use for it, or where it would not stay the call's own."""
+def _scratch(group: int, M: int, N: int, K: int, bf16: int):
+    """Scratch memory for one call on the current stream of the current device, whatever device its tensors are on, from
+    torch's allocator, which knows when that stream is done with it; None where the call has no use for it, or where it would not stay the call's own."""
     n = lib().w4a16_scratch_bytes(M, N, K, group, bf16) if M > 16 else 0
     if not n:
         return None
     import torch
-    if torch.cuda.is_current_stream_capturing() and not _capture_owns_allocations(X):
+    if torch.cuda.is_current_stream_capturing() and not _capture_owns_allocations():
         return None
     try:
-        return X.new_empty(n + 256, dtype=torch.uint8)
+        return torch.empty(n + 256, dtype=torch.uint8, device="cuda")
     except torch.OutOfMemoryError:  # up to 32 MB that a plan without them does not need
         return None
 
 
-def _capture_owns_allocations(X) -> bool:
+def _capture_owns_allocations() -> bool:
     """Whether what torch allocates on this stream, which is being captured, stays with the graph: while torch itself records
     a graph its allocator serves the stream from a pool of that graph.  Of a capture begun by other means it knows nothing: the
     block would come from the common pool and go to the next tensor while replays of the graph still write to it."""
     import torch
     try:
-        probe = X.new_empty(1, dtype=torch.uint8)
+        probe = torch.empty(1, dtype=torch.uint8, device="cuda")
         address = probe.data_ptr()
         for segment in torch.cuda.memory_snapshot():  # 0.3 ms with 2000 blocks; once per call that is recorded
             if segment["address"] <= address < segment["address"] + segment["total_size"] and segment["device"] == probe.device.index:
@@ -238,7 +238,7 @@ def gemm(X, Wpacked, scales, zeros, group: int, out=None, stream=None):
     """Y = X * s (W - z) (Eq. 2).  uint32 storage travels as torch.int32 tensors."""
     M, N, K = _check_tensors(X, Wpacked, scales, zeros, group)
     Y = out if out is not None else X.new_empty((M, N))
-    scratch = _scratch(X, group, M, N, K, 0) if stream is None else None
+    scratch = _scratch(group, M, N, K, 0) if stream is None else None
     if scratch is not None:
         rc = _gemm_scratch(X, Wpacked, scales, zeros, group, M, N, K, Y, 0, scratch)
     else:
@@ -268,7 +268,7 @@ def gemm_bf16(X, Wpacked, scales, zeros, group: int, kernel: int = KERNEL_AUTO, 
     Y = out if out is not None else X.new_empty((M, N))
     if Y.dtype != torch.bfloat16 or tuple(Y.shape) != (M, N) or not Y.is_contiguous():
         raise ValueError("out must be a contiguous bfloat16 [M, N] tensor")
-    scratch = _scratch(X, group, M, N, K, 1) if stream is None and kernel == KERNEL_AUTO and split == 0 else None
+    scratch = _scratch(group, M, N, K, 1) if stream is None and kernel == KERNEL_AUTO and split == 0 else None
     if scratch is not None:
         rc = _gemm_scratch(X, Wpacked, scales, zeros, group, M, N, K, Y, 1, scratch)
         if rc:

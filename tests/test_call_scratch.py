@@ -11,20 +11,22 @@ from paper_2601_16536_amd import workloads as wl
 M, K, N = 400, 4096, 7168  # in tiles of 128 x 256 with a split of the last ones: 29 MB of partials; unsplit it needs nothing
 
 
-class FakeTensor:
-    """What the binding sees of a device tensor, on a machine without a device."""
+class Block:
+    """A block of the current device's memory, on a machine without a device."""
 
     class device:
         index = 0
 
-    def __init__(self, size=0, address=4096):
-        self.size, self.address = size, address
-
-    def new_empty(self, size, dtype=None):
-        return FakeTensor(size, 1 << 20)
+    def __init__(self, size):
+        self.size = size
 
     def data_ptr(self):
-        return self.address
+        return 1 << 20
+
+
+def empty(size, dtype=None, device=None):
+    assert device == "cuda"  # the current device, whose current stream the call runs on: not the device of a tensor
+    return Block(size)
 
 
 @pytest.fixture()
@@ -54,7 +56,8 @@ def test_scratch_under_a_capture_comes_from_the_graphs_own_pool(binding, monkeyp
     import torch
     monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: capturing)
     monkeypatch.setattr(torch.cuda, "memory_snapshot", snapshot)
-    assert (binding._scratch(FakeTensor(), 128, M, N, K, 0) is not None) == scratch
+    monkeypatch.setattr(torch, "empty", empty)
+    assert (binding._scratch(128, M, N, K, 0) is not None) == scratch
 
 
 def test_a_full_device_is_no_error_of_a_call_that_can_do_without(binding, monkeypatch):
@@ -64,8 +67,8 @@ def test_a_full_device_is_no_error_of_a_call_that_can_do_without(binding, monkey
         raise torch.OutOfMemoryError("no room")
 
     monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: False)
-    monkeypatch.setattr(FakeTensor, "new_empty", full)
-    assert binding._scratch(FakeTensor(), 128, M, N, K, 0) is None
+    monkeypatch.setattr(torch, "empty", full)
+    assert binding._scratch(128, M, N, K, 0) is None
 
 
 @pytest.fixture(scope="module")
@@ -146,7 +149,7 @@ def test_scratch_of_a_graph_that_torch_records(gpu):
     graph, seen = torch.cuda.CUDAGraph(), []
     print("[case] captured by torch", flush=True)
     with torch.cuda.graph(graph):
-        seen.append(binding._scratch(args[0], 128, M, N, K, 0) is not None)
+        seen.append(binding._scratch(128, M, N, K, 0) is not None)
         binding.gemm(*args, 128, out=Y)
     assert seen == [True]
     others = [torch.full((n,), 7, dtype=torch.uint8, device="cuda") for n in (32 << 20, 29 << 20)]
