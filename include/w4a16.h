@@ -169,7 +169,8 @@ int w4a16_gemm_bf16(const void *X, const uint32_t *Wpacked, const void *scales, 
  * Scratch memory for one call, from the caller's own allocator.  For M > 16 the fastest plan may need the FP32 partials of
  * Algorithm 1 (Section 3) where another plan needs nothing; w4a16_gemm and the others that work in shared buffers then
  * run the one that needs nothing, so that calls on several streams may overlap.  w4a16_scratch_bytes tells what the
- * faster plan needs (0: call w4a16_gemm or w4a16_gemm_bf16), w4a16_gemm_scratch runs it: `scratch` as the workspace of
+ * faster plan needs (0: call w4a16_gemm or w4a16_gemm_bf16; always 0 while a workspace is registered for the current
+ * device with w4a16_set_workspace), w4a16_gemm_scratch runs it: `scratch` as the workspace of
  * w4a16_gemm_ws, used by this call alone until its work on `stream` is done; `bf16` nonzero: X and Y as in
  * w4a16_gemm_bf16.
  */
@@ -181,10 +182,11 @@ int w4a16_gemm_scratch(const void *X, const uint32_t *Wpacked, const void *scale
  * Registers caller-owned split buffers (Algorithm 1's C_i; Section 3) for the
  * current device: device memory, 256-byte aligned, at least 256 bytes, owned by
  * the caller and kept valid until it is replaced or removed (NULL removes it).
- * w4a16_gemm and w4a16_gemm_ex then use it instead of library-owned buffers and
- * never allocate; a plan that needs more than `workspace_bytes` returns
- * W4A16_ERR_WORKSPACE.  As with w4a16_gemm_ws the contents need no
- * initialisation.  Calls that overlap in time on one device share it and race.
+ * w4a16_gemm, w4a16_gemm_ex and w4a16_gemm_bf16 then use it instead of library-owned buffers and
+ * never allocate; a plan that needs more than `workspace_bytes` gives way to one that needs less where
+ * the scheduler has one (M > 16), else the call returns W4A16_ERR_WORKSPACE.  As with w4a16_gemm_ws the contents need no
+ * initialisation.  Calls that overlap in time on one device share it and race; calls for
+ * which the scheduler has a plan without a buffer (M > 16) run that one and may overlap.
  */
 int w4a16_set_workspace(void *workspace, size_t workspace_bytes);
 

@@ -181,7 +181,8 @@ def gemm_noalloc(X, Wpacked, scales, zeros, group: int, out, kernel: int = KERNE
 
 def set_workspace(workspace) -> None:
     """Registers a caller-owned workspace tensor (uint8, CUDA, 256-byte aligned) for the current device; None removes it.
-    The tensor must stay alive while it is registered."""
+    The tensor must stay alive while it is registered.  gemm, gemm_ex and gemm_bf16 then work in it or need no buffer, and
+    take no memory beside it."""
     if workspace is None:
         rc = lib().w4a16_set_workspace(None, 0)
     else:

@@ -738,7 +738,12 @@ size_t w4a16_scratch_bytes(int M, int N, int K, int group, int bf16)
 {
     w4a16_plan p;
     if (M <= 16 || check_shape(group, M, N, K)) return 0;
-    if (make_plan(M, N, K, group, W4A16_KERNEL_AUTO, 0, compute_units(current_device()), &p, nullptr, bf16 != 0)) return 0;
+    const int dev = current_device();
+    if (dev >= 0) {  // a registered workspace is what the caller wants used, and nothing beside it
+        std::lock_guard<std::mutex> lock(g_mutex);
+        if (g_dev[dev].user_ws) return 0;
+    }
+    if (make_plan(M, N, K, group, W4A16_KERNEL_AUTO, 0, compute_units(dev), &p, nullptr, bf16 != 0)) return 0;
     const bool by_panel = p.kernel == W4A16_KERNEL_TILE && p.tile_n == kPanelCols;
     if (!by_panel && finish_of(p.kernel, M, N, p.split, group == 128 ? 0 : p.tile_m) != kFinishSecondPass) return 0;
     return p.workspace_bytes;

@@ -185,3 +185,37 @@ def test_a_capture_after_calls_that_brought_their_scratch(gpu):
         graph.replay()
         torch.cuda.synchronize()
         check(Y, rows, ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("m,k,n,written", [(64, 16384, 4096, True),   # every split plan needs a buffer: the registered one
+                                           (M, K, N, False)])         # has a plan that needs none: calls may overlap
+def test_calls_take_no_memory_beside_a_registered_workspace(gpu, m, k, n, written, dtype):
+    torch, binding, _, _, _ = gpu
+    X, Wp, s, Zp = wl.make(m, k, n, index=9470)
+    bf16 = dtype == "bf16"
+    if bf16:
+        X = wl.make_x_bf16(m, k, index=9470)
+    rows = [0, m // 2, m - 1]
+    ref = (orc.gemm_bf16 if bf16 else orc.gemm)(np.ascontiguousarray(X[rows]), Wp, s, Zp, 128)
+    _, dW, dS, dZ = binding.to_device(np.zeros((1, k), np.float16), Wp, s, Zp)
+    dX = torch.from_numpy(X.view(np.int16)).cuda().view(torch.bfloat16) if bf16 else torch.from_numpy(X).cuda()
+    gemm = binding.gemm_bf16 if bf16 else binding.gemm
+    Y = torch.empty((m, n), dtype=dX.dtype, device="cuda")
+    binding.shutdown()
+    size = max(binding.workspace_bytes(m, n, k, 128), 4 << 20)
+    ws = torch.full((size + 256,), 0x55, dtype=torch.uint8, device="cuda")
+    ws = ws[-ws.data_ptr() % 256:][:size]
+    torch.cuda.synchronize()
+    binding.set_workspace(ws)
+    try:
+        torch.cuda.reset_peak_memory_stats()
+        before = torch.cuda.memory_allocated()
+        print("[case] registered", (m, k, n), dtype, flush=True)
+        gemm(dX, dW, dS, dZ, 128, out=Y)
+        assert torch.cuda.max_memory_allocated() == before
+        check(Y, rows, ref)
+        assert bool((ws != 0x55).any()) == written
+    finally:
+        binding.set_workspace(None)
