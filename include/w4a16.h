@@ -157,7 +157,7 @@ int w4a16_gemm_ws(const void *X, const uint32_t *Wpacked, const void *scales, co
  * or NULL).  Algorithm 1 lists A and C as 16-bit floating point; the paper's runs use FP16, this entry covers
  * the other 16-bit format (bf16 MFMA, FP32 sums, one round-to-nearest-even cast at the end).  Arguments, split
  * buffers, stream rules and errors as w4a16_gemm_ex; kernel = W4A16_KERNEL_AUTO and split = 0 give the
- * scheduler's plan (the same as for FP16, but tiles of 256 columns may be chosen for other shapes).  Forced plans: W4A16_KERNEL_TILE for any M,
+ * scheduler's plan (w4a16_query_plan_bf16; beyond 16 rows it may differ from FP16's).  Forced plans: W4A16_KERNEL_TILE for any M,
  * W4A16_KERNEL_STRIPE for M <= 4; the others return W4A16_ERR_UNSUPPORTED.  Results beyond +-2^25 saturate
  * there when K slices meet in the fixed-point accumulator or when the waves of a workgroup share a slice by
  * ticket (M <= 16), as for FP16, where that bound lies beyond the format's range.
@@ -213,6 +213,10 @@ size_t w4a16_workspace_bytes(int M, int N, int K, int group);
  * plan needs a workspace and another needs none (no launch, no GPU call
  * beyond reading the current device's properties once). */
 int w4a16_query_plan(int M, int N, int K, int group, int kernel, int split, w4a16_plan *out);
+
+/* The same for w4a16_gemm_bf16 (and w4a16_gemm_scratch with bf16 set).  A registered workspace of w4a16_workspace_bytes
+ * is enough for w4a16_gemm_bf16 of the same shape too: where its best plan needs more, one that needs less runs. */
+int w4a16_query_plan_bf16(int M, int N, int K, int group, int kernel, int split, w4a16_plan *out);
 
 /* Second pass alone (Algorithm 1, Phase 3): Y[m,n] = fp16(sum_{i<S} partials[i,m,n]),
  * i ascending, FP32 adds, round-to-nearest-even cast.  partials: FP32 [S, M, N]. */

@@ -18,7 +18,7 @@ KERNEL_AUTO, KERNEL_WAVE_SPLIT, KERNEL_STRIPE, KERNEL_TILE = -1, 0, 3, 4  # 1 an
 EXPORTS = (
     "w4a16_gemm", "w4a16_gemm_ex", "w4a16_gemm_ws", "w4a16_gemm_noalloc", "w4a16_gemm_bf16", "w4a16_scratch_bytes", "w4a16_gemm_scratch",
     "w4a16_set_workspace", "w4a16_tune",
-    "w4a16_workspace_bytes", "w4a16_query_plan",
+    "w4a16_workspace_bytes", "w4a16_query_plan", "w4a16_query_plan_bf16",
     "w4a16_reduce", "w4a16_dequant", "w4a16_quantize", "w4a16_stream_probe", "w4a16_status_string", "w4a16_last_hip_error", "w4a16_shutdown",
 )
 
@@ -84,6 +84,7 @@ def lib():
         L.w4a16_workspace_bytes.argtypes = [ci, ci, ci, ci]
         L.w4a16_workspace_bytes.restype = sz
         L.w4a16_query_plan.argtypes = [ci, ci, ci, ci, ci, ci, ctypes.POINTER(Plan)]
+        L.w4a16_query_plan_bf16.argtypes = L.w4a16_query_plan.argtypes
         L.w4a16_reduce.argtypes = [vp, ci, ci, ci, vp, vp]
         L.w4a16_dequant.argtypes = [vp, vp, vp, ci, ci, ci, vp, vp]
         L.w4a16_quantize.argtypes = [vp, ci, ci, ci, vp, vp, vp, vp]
@@ -300,9 +301,11 @@ def workspace_bytes(M: int, N: int, K: int, group: int) -> int:
     return int(lib().w4a16_workspace_bytes(M, N, K, group))
 
 
-def query_plan(M: int, N: int, K: int, group: int, kernel: int = KERNEL_AUTO, split: int = 0) -> dict:
+def query_plan(M: int, N: int, K: int, group: int, kernel: int = KERNEL_AUTO, split: int = 0, bf16: bool = False) -> dict:
+    """The plan of gemm and gemm_ex, or with `bf16` of gemm_bf16."""
     p = Plan()
-    rc = lib().w4a16_query_plan(M, N, K, group, kernel, split, ctypes.byref(p))
+    query = lib().w4a16_query_plan_bf16 if bf16 else lib().w4a16_query_plan
+    rc = query(M, N, K, group, kernel, split, ctypes.byref(p))
     if rc:
         raise W4A16Error(rc, "w4a16_query_plan")
     return p.as_dict()

@@ -168,8 +168,9 @@ bool fits_32bit_offsets(int M, int N, int K, int group, int gps)
 // returning atomic add per output and slice; measured: the GPU retires about 150 of them per nanosecond)
 // while that is cheaper than a second launch (about 3.3 us, measured), else in the FP32 workspace and the
 // second pass.  Measured crossover: between 0.5 M and 1 M adds.  The other families always take the second pass.
-// At 64 rows of X per workgroup (`rows`; groups other than 128) the adds come in a burst of 4096 from every workgroup at once, and the crossover is
-// lower (M = 37, K = 10240, N = 4608, S = 3, 511 K adds: 23.8 us in the accumulator; M = 64, 885 K adds, second pass: 18.1).
+// At 64 rows of X per workgroup (`rows`; BF16, and groups other than 128) the adds come in a burst of 4096 from every workgroup at once, and
+// the crossover is lower (M = 37, K = 10240, N = 4608, S = 3, 511 K adds: 23.8 us in the accumulator; M = 64, 885 K adds, second pass: 18.1;
+// BF16, groups of 128, M = 114, K = 1280, N = 1520, S = 3, 520 K adds: 15.8 and 9.9).
 bool slices_meet_in_accumulator(int M, int N, int S, int rows)
 {
     if (S > 63) return false;  // the accumulator counts arrivals in six bits
@@ -184,6 +185,9 @@ int finish_of(int kernel, int M, int N, int S, int rows)
     if (kernel != W4A16_KERNEL_STRIPE && kernel != W4A16_KERNEL_TILE) return kFinishSecondPass;
     return slices_meet_in_accumulator(M, N, S, rows) ? kFinishAccumulator : kFinishSecondPass;
 }
+
+// The rows that decide it for a TILE plan.  kFrugal's plans, and FP16 with groups of 128 (w4a16_tile_wide.hip), keep the higher crossover.
+int burst_rows(int tile_m, int group, bool bf16, bool frugal) { return frugal || (group == 128 && !bf16) ? 0 : tile_m; }
 
 // Workspace of a plan: nothing, the accumulator [M, N], or the FP32 partials [S, M, N].
 size_t workspace_of(int kernel, int M, int N, int S, int rows)
@@ -203,9 +207,9 @@ bool tile_by_ticket(int M, int rows_x) { return rows_x == 16 && (tuning().tile_d
 // TILE with four waves per workgroup: at 32 and 64 rows of X, FP16 with groups of 128 (w4a16_tile_wide.hip), and at 64 rows
 // BF16 and the other lengths of group (w4a16_tile_tall.hip; at 32 rows these run the eight-wave form).  Both take FP16 with
 // groups of 128 at 64 rows: M = 128, N = 8192, K = 512 / 2048 / 8192: 6.6 / 10.7 / 27.7 us (wide), 6.9 / 10.7 / 27.5 (tall).
-bool tile_four(int rows_x, int group)
+bool tile_four(int rows_x, int group, bool bf16)
 {
-    return ((rows_x == 64 && wide_takes(group)) || (rows_x == 32 && group == 128)) && tuning().tile_wide != 2;
+    return ((rows_x == 64 && wide_takes(group)) || (rows_x == 32 && group == 128 && !bf16)) && tuning().tile_wide != 2;
 }
 
 // LDS a STRIPE workgroup needs for a slice of gps groups, and the most it may use.
@@ -220,12 +224,13 @@ size_t stripe_lds_max(int M) { return (size_t)(stripe_by_ticket(M) ? stripe_dyn_
 // there as the clock does): a fixed 3 us; rounds of workgroups x blocks of 32 k per wave x the time of a block
 // (four-wave form: 0.24 us at 32 rows, 0.37 at 64; eight-wave form: 0.37, 0.56, 0.94 at 16, 32, 64 rows); and how the
 // slices meet (accumulator: 1 us, and beyond 200 K adds 1 us per 60 K; second pass: 3.3 us and the partials at 3 TB/s).
-double tile_plan_cost(int M, int N, int K, int group, int rows, int S, int cus, bool bf16 = false, bool frugal = false)
+// `frugal`: the costs by which kFrugal's plans are chosen, the same for both formats.
+double tile_plan_cost(int M, int N, int K, int group, int rows, int S, int cus, bool bf16, bool frugal)
 {
     const int G = K / group;
     const int gps = (G + S - 1) / S;
     S = (G + gps - 1) / gps;
-    const bool four = tile_four(rows, group) && (rows == 64 ? group == 128 || !frugal : !bf16);
+    const bool four = tile_four(rows, group, bf16 && !frugal) && (rows == 32 || group == 128 || !frugal);
     const int waves = four ? 4 : 8;
     const double per_block = four ? (rows == 64 ? (group == 32 ? 0.45 : 0.37) : 0.24) : (rows == 64 ? 0.94 : (rows == 32 ? 0.56 : 0.37));
     const long long tiles = (N + 63) / 64, wgs = tiles * ((M + rows - 1) / rows) * S;
@@ -234,9 +239,43 @@ double tile_plan_cost(int M, int N, int K, int group, int rows, int S, int cus, 
     double finish = 0.0;
     if (S > 1) {
         const double adds = (double)S * M * N;
-        finish = slices_meet_in_accumulator(M, N, S, frugal || group == 128 ? 0 : rows) ? 1.0 + (adds > 2e5 ? (adds - 2e5) / 6e4 : 0.0) : 3.3 + 2.0 * adds * 4.0 / 3e6;
+        finish = slices_meet_in_accumulator(M, N, S, burst_rows(rows, group, bf16, frugal)) ? 1.0 + (adds > 2e5 ? (adds - 2e5) / 6e4 : 0.0) : 3.3 + 2.0 * adds * 4.0 / 3e6;
     }
     return 3.0 + (double)rounds * (double)blocks * per_block + finish;
+}
+
+// Rows of X per workgroup and S (`split` 0: up to one workgroup per compute unit) that the model finds cheapest.
+struct TileChoice {
+    int rows, S;
+    double cost;
+};
+TileChoice cheapest_tiles(int M, int N, int K, int group, int split, int cus, bool bf16, bool frugal)
+{
+    TileChoice best = {16, 1, 1e30};
+    const int G = K / group;
+    for (int r = 16; r <= 64; r *= 2) {
+        if (r > 16 && r / 2 >= M) break;  // more than half of the block's rows would be empty
+        const long long w1 = (long long)((N + 63) / 64) * ((M + r - 1) / r);
+        const int smax = split ? split : ((int)(cus / w1) < 1 ? 1 : ((int)(cus / w1) > G ? G : (int)(cus / w1)));
+        for (int s = split ? split : 1; s <= smax; ++s) {
+            const double c = tile_plan_cost(M, N, K, group, r, s, cus, bf16, frugal);
+            if (c < best.cost) best = {r, s, c};
+        }
+    }
+    return best;
+}
+
+// The choice for one format.  BF16 has costs of its own with groups of 128 (at 32 rows the eight-wave form), which are good for
+// about a tenth: FP16's choice stays where it is no more than that dearer.  On 250 drawn shapes of 17 to 600 rows where the two
+// differ, against FP16's choice: 13 % faster in the mean (M = 272, K = 3200, N = 5400: 39.0 -> 26.7 us), the slowest 2 % slower; whatever
+// is cheapest by BF16's costs: 11 % in the mean, but 7 of 200 shapes 2 to 17 % slower.
+TileChoice choose_tiles(int M, int N, int K, int group, int split, int cus, bool bf16, bool frugal)
+{
+    TileChoice c = cheapest_tiles(M, N, K, group, split, cus, false, frugal);
+    if (!bf16 || frugal || group != 128) return c;
+    const TileChoice own = cheapest_tiles(M, N, K, group, split, cus, true, false);
+    c.cost = tile_plan_cost(M, N, K, group, c.rows, c.S, cus, true, false);
+    return own.cost < 0.9 * c.cost ? own : c;
 }
 
 // PANEL form (w4a16_panel.hip), for the scheduler's own plans beyond 16 rows: tiles of 128 x 256, the last row block of
@@ -319,7 +358,7 @@ bool use_panel(int M, int N, int K, int group, bool bf16, int cus, bool may_spli
         int smax = (int)(cus / wgs);
         smax = smax < 1 ? 1 : (smax > G ? G : smax);
         for (int s = 1; s <= smax; ++s) {
-            const double c = tile_plan_cost(M, N, K, group, r, s, cus, bf16) + (M > 128 ? 3.5 * (double)((wgs * s - 1) / cus) : 0.0);
+            const double c = tile_plan_cost(M, N, K, group, r, s, cus, bf16, false) + (M > 128 ? 3.5 * (double)((wgs * s - 1) / cus) : 0.0);
             if (c < other) other = c;
         }
     }
@@ -352,6 +391,8 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
         return W4A16_ERR_UNSUPPORTED;
     if (kernel == W4A16_KERNEL_WAVE_SPLIT && M > 4) return W4A16_ERR_UNSUPPORTED;
     if (kernel == W4A16_KERNEL_STRIPE && M > 16) return W4A16_ERR_UNSUPPORTED;
+    // bfloat16 activations: the forms the scheduler chooses from (STRIPE by ticket for M <= 4, TILE)
+    if (bf16 && (kernel == W4A16_KERNEL_WAVE_SPLIT || (kernel == W4A16_KERNEL_STRIPE && !stripe_by_ticket(M)))) return W4A16_ERR_UNSUPPORTED;
     if (split < 0 || split > G) return W4A16_ERR_UNSUPPORTED;
     p->kernel = kernel;
     if (automatic && thrift == kBare && M > 16) split = 1;
@@ -422,21 +463,14 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
             // compute units into a second round, or gives up large row blocks that a split of K would have filled
             // (measured, N = 7168, K = 18432, M = 64: 49.7 us at 16 rows against 33.0 at 64 rows, S = 2): the
             // cheapest of (rows, S) by the model, S up to one workgroup per compute unit (a forced S: the rows for it)
-            double best = 1e30;
-            for (int r = 16; r <= 64; r *= 2) {
-                if (r > 16 && r / 2 >= M) break;  // more than half of the block's rows would be empty
-                const long long w1 = tiles * ((M + r - 1) / r);
-                const int smax = split ? split : ((int)(cus / w1) < 1 ? 1 : ((int)(cus / w1) > G ? G : (int)(cus / w1)));
-                for (int s = split ? split : 1; s <= smax; ++s) {
-                    const double c = tile_plan_cost(M, N, K, group, r, s, cus, false, frugal);
-                    if (c < best) { best = c; rows_x = r; S = s; }
-                }
-            }
+            const TileChoice c = choose_tiles(M, N, K, group, split, cus, bf16, frugal);
+            rows_x = c.rows;
+            S = c.S;
         }
         p->tile_m = rows_x;
         const int tw = tuning().tile_waves;
         if (tw >= 4 && tw <= (tile_by_ticket(M, rows_x) ? 16 : 8)) { p->waves_k = tw; p->threads = 64 * tw; }
-        if (tile_four(rows_x, group)) { p->waves_k = 4; p->threads = 256; }
+        if (tile_four(rows_x, group, bf16)) { p->waves_k = 4; p->threads = 256; }
         const long long wgs = tiles * ((M + rows_x - 1) / rows_x);
         if (S == 0) S = (int)(cus / wgs);  // never more workgroups than compute units: the extra ones would run as a second round
         if (S < 1) S = 1;
@@ -447,7 +481,7 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
         p->split = S;
         p->groups_per_split = gps;
         p->workgroups = (int)(wgs * S);
-        p->workspace_bytes = workspace_of(kernel, M, N, S, frugal || group == 128 ? 0 : p->tile_m);
+        p->workspace_bytes = workspace_of(kernel, M, N, S, burst_rows(p->tile_m, group, bf16, frugal));
         if (((long long)tiles * S + 7) / 8 * 8 * ((M + rows_x - 1) / rows_x) > 0x7FFFFFFFLL) return W4A16_ERR_UNSUPPORTED;
         return fits_32bit_offsets(M, N, K, group, gps) ? W4A16_OK : W4A16_ERR_UNSUPPORTED;
     }
@@ -637,12 +671,9 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
         rc = make_plan(M, N, K, group, kernel, split, compute_units(dev), &plan, &panel, bf16, thrift);
         if (rc) return rc;
         if (only_free && plan.workspace_bytes != 0) continue;  // (never kFrugal's)
-        // bfloat16 activations: the forms the scheduler chooses from (STRIPE by ticket for M <= 4, TILE)
-        if (bf16 && (plan.kernel == W4A16_KERNEL_WAVE_SPLIT || (plan.kernel == W4A16_KERNEL_STRIPE && !stripe_by_ticket(M))))
-            return W4A16_ERR_UNSUPPORTED;
         by_panel = plan.kernel == W4A16_KERNEL_TILE && plan.tile_n == kPanelCols;
         finish = by_panel ? (plan.split > 1 ? kFinishSecondPass : kFinishDirect)
-                          : finish_of(plan.kernel, M, N, plan.split, thrift == kFrugal || group == 128 ? 0 : plan.tile_m);
+                          : finish_of(plan.kernel, M, N, plan.split, burst_rows(plan.tile_m, group, bf16, thrift == kFrugal));
         t_hip_error[0] = 0;
         rc = find_buffers(dev, plan, finish, M, N, st, src, call_ws, call_ws_bytes, &b);
         if (rc != W4A16_ERR_WORKSPACE) break;
@@ -679,12 +710,12 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
         e = launch_panel(a, panel, st);
     } else if (plan.kernel == W4A16_KERNEL_TILE && tile_by_ticket(M, plan.tile_m)) {
         e = launch_tile_dyn(a, finish, b.sync, plan.waves_k, tuning().tile_depth == 2 && !bf16 && plan.waves_k <= 8 ? 2 : 1, tuning().tile_unit, st);
-    } else if (plan.kernel == W4A16_KERNEL_TILE && tile_four(plan.tile_m, group) && plan.tile_m == 64 && (bf16 || group != 128)) {
+    } else if (plan.kernel == W4A16_KERNEL_TILE && tile_four(plan.tile_m, group, bf16) && plan.tile_m == 64 && (bf16 || group != 128)) {
         e = launch_tile_tall(a, finish, b.sync, st);
-    } else if (plan.kernel == W4A16_KERNEL_TILE && tile_four(plan.tile_m, group) && !bf16) {
+    } else if (plan.kernel == W4A16_KERNEL_TILE && tile_four(plan.tile_m, group, bf16)) {
         e = launch_tile_wide(a, finish, b.sync, plan.tile_m, st);
     } else if (plan.kernel == W4A16_KERNEL_TILE) {
-        e = launch_tile(a, finish, b.sync, plan.tile_m, tile_four(plan.tile_m, group) ? 8 : plan.waves_k, st);
+        e = launch_tile(a, finish, b.sync, plan.tile_m, plan.waves_k, st);
     } else {
         e = launch_wave_split(a, plan.tile_n, st);
     }
@@ -745,7 +776,7 @@ size_t w4a16_scratch_bytes(int M, int N, int K, int group, int bf16)
     }
     if (make_plan(M, N, K, group, W4A16_KERNEL_AUTO, 0, compute_units(dev), &p, nullptr, bf16 != 0)) return 0;
     const bool by_panel = p.kernel == W4A16_KERNEL_TILE && p.tile_n == kPanelCols;
-    if (!by_panel && finish_of(p.kernel, M, N, p.split, group == 128 ? 0 : p.tile_m) != kFinishSecondPass) return 0;
+    if (!by_panel && finish_of(p.kernel, M, N, p.split, burst_rows(p.tile_m, group, bf16 != 0, false)) != kFinishSecondPass) return 0;
     return p.workspace_bytes;
 }
 
@@ -781,6 +812,14 @@ int w4a16_query_plan(int M, int N, int K, int group, int kernel, int split, w4a1
     int rc = check_shape(group, M, N, K);
     if (rc) return rc;
     return make_plan(M, N, K, group, kernel, split, compute_units(current_device()), out);
+}
+
+int w4a16_query_plan_bf16(int M, int N, int K, int group, int kernel, int split, w4a16_plan *out)
+{
+    if (!out) return W4A16_ERR_NULL;
+    int rc = check_shape(group, M, N, K);
+    if (rc) return rc;
+    return make_plan(M, N, K, group, kernel, split, compute_units(current_device()), out, nullptr, true);
 }
 
 int w4a16_tune(const char *knob, int value)

@@ -219,3 +219,29 @@ def test_calls_take_no_memory_beside_a_registered_workspace(gpu, m, k, n, writte
         assert bool((ws != 0x55).any()) == written
     finally:
         binding.set_workspace(None)
+
+
+@pytest.mark.gpu
+def test_a_workspace_of_the_shapes_size_is_enough_for_both_formats(gpu):
+    """w4a16_workspace_bytes does not ask for the format.  M = 101, K = 12544, N = 3216: FP16's plan needs nothing, BF16's
+    best one the partials of two slices; with a registered workspace of that size the BF16 call runs a plan that fits."""
+    torch, binding, _, _, _ = gpu
+    m, k, n = 101, 12544, 3216
+    size = binding.workspace_bytes(m, n, k, 128)
+    assert binding.query_plan(m, n, k, 128, bf16=True)["workspace_bytes"] > size >= binding.query_plan(m, n, k, 128)["workspace_bytes"]
+    _, Wp, s, Zp = wl.make(1, k, n, index=9480)
+    Xb = wl.make_x_bf16(m, k, index=9480)
+    rows = [0, 31, 63, 64, 100]
+    ref = orc.gemm_bf16(np.ascontiguousarray(Xb[rows]), Wp, s, Zp, 128)
+    _, dW, dS, dZ = binding.to_device(np.zeros((1, k), np.float16), Wp, s, Zp)
+    dX = torch.from_numpy(Xb.view(np.int16)).cuda().view(torch.bfloat16)
+    ws = torch.full((size + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+    ws = ws[-ws.data_ptr() % 256:][:size]
+    binding.set_workspace(ws)
+    try:
+        print("[case] bf16 in a registered workspace", flush=True)
+        check(binding.gemm_bf16(dX, dW, dS, dZ, 128), rows, ref)
+    finally:
+        binding.set_workspace(None)
+    print("[case] bf16 with its own scratch", flush=True)
+    check(binding.gemm_bf16(dX, dW, dS, dZ, 128), rows, ref)

@@ -3,6 +3,7 @@ function include/w4a16.h declares, argument checks answer before any GPU call,
 and the Split-K scheduler's plans are well formed."""
 import ctypes
 import os
+import random
 import re
 
 import pytest
@@ -195,6 +196,50 @@ def test_tile_plans_for_many_rows_follow_the_cost_model(binding):
         assert (p["tile_m"], p["split"]) == (32, 1)
     finally:
         binding.tune("tile_rows", 0)
+
+
+def bf16_cost(M, N, K, rows, S, cus=256):
+    """The scheduler's cost model (us) of a BF16 plan of 64-column tiles with groups of 128: at 16 and 32 rows eight waves, at 64
+    four, whose slices meet in the accumulator up to 160 K adds."""
+    G = K // 128
+    gps = -(-G // S)
+    S = -(-G // gps)
+    waves, block = {16: (8, 0.37), 32: (8, 0.56), 64: (4, 0.37)}[rows]
+    rounds = -(-(-(-N // 64) * -(-M // rows) * S) // cus)
+    adds, finish = S * M * N, 0.0
+    if S > 1:
+        accumulator = S <= 63 and adds <= (160 if rows == 64 else 640) * 1024
+        finish = 1.0 + max(0.0, (adds - 2e5) / 6e4) if accumulator else 3.3 + 2.0 * adds * 4.0 / 3e6
+    return 3.0 + rounds * -(-gps * 4 // waves) * block + finish
+
+
+def test_bf16_plans_are_costed_as_bf16(binding):
+    """Beyond 16 rows a BF16 plan of 64-column tiles is within a tenth of the cheapest by BF16's own costs, and says what runs:
+    eight waves at 32 rows, where FP16 has a form of four.  M = 71, K = 2176, N = 28664 ran at 32 rows by FP16's costs, 33.2
+    against 28.2 us at 64 rows by the model."""
+    rng = random.Random(11)
+    shapes = [(71, 28664, 2176), (88, 1312, 20992), (52, 22664, 4864)]
+    shapes += [(rng.randint(17, 128), 8 * rng.randint(64, 3584), 128 * rng.randint(8, 224)) for _ in range(400)]
+    binding.tune("panel", 2)
+    try:
+        for M, N, K in shapes:
+            p = binding.query_plan(M, N, K, 128, bf16=True)
+            assert p["tile_n"] == 64 and p["waves_k"] == (4 if p["tile_m"] == 64 else 8) and p["threads"] == 64 * p["waves_k"]
+            best = 1e30
+            for rows in (16, 32, 64):
+                if rows > 16 and rows // 2 >= M:
+                    break
+                most = max(1, min(256 // (-(-N // 64) * -(-M // rows)), K // 128))
+                best = min([best] + [bf16_cost(M, N, K, rows, S) for S in range(1, most + 1)])
+            assert bf16_cost(M, N, K, p["tile_m"], p["split"]) <= best / 0.9 + 1e-9, (M, N, K, p)
+        assert [binding.query_plan(*shapes[0], 128, bf16=b)["tile_m"] for b in (False, True)] == [32, 64]
+    finally:
+        binding.tune("panel", 0)
+    for kernel, M in ((binding.KERNEL_WAVE_SPLIT, 1), (binding.KERNEL_STRIPE, 8)):  # families without a BF16 form
+        assert binding.query_plan(M, 1024, 4096, 128, kernel)["kernel"] == kernel
+        with pytest.raises(binding.W4A16Error) as e:
+            binding.query_plan(M, 1024, 4096, 128, kernel, bf16=True)
+        assert e.value.status == binding.ERR_UNSUPPORTED
 
 
 def test_product_does_not_touch_the_oracle():
