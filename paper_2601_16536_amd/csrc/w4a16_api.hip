@@ -212,6 +212,11 @@ bool tile_four(int rows_x, int group, bool bf16)
     return ((rows_x == 64 && wide_takes(group)) || (rows_x == 32 && group == 128 && !bf16)) && tuning().tile_wide != 2;
 }
 
+// Up to 1024 k per slice a wave of the tall form has no more stages than it keeps in flight, and the BF16 eight-wave kernel for
+// groups of 128 is as fast or faster: 64 rows, BF16, K = 1024: M = 48, N = 16384 / 48640: 8.6 / 22.6 us against 8.9 / 23.2; M = 128,
+// N = 8192: 8.7 against 8.8; K = 1536, M = 48, N = 16384: 11.0 against 10.4.  Groups of other lengths have a slower eight-wave kernel.
+bool short_slices(int group, bool bf16, int gps) { return bf16 && group == 128 && gps <= 8; }
+
 // LDS a STRIPE workgroup needs for a slice of gps groups, and the most it may use.
 size_t stripe_lds(int M, int group, int gps, int waves)
 {
@@ -470,7 +475,6 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
         p->tile_m = rows_x;
         const int tw = tuning().tile_waves;
         if (tw >= 4 && tw <= (tile_by_ticket(M, rows_x) ? 16 : 8)) { p->waves_k = tw; p->threads = 64 * tw; }
-        if (tile_four(rows_x, group, bf16)) { p->waves_k = 4; p->threads = 256; }
         const long long wgs = tiles * ((M + rows_x - 1) / rows_x);
         if (S == 0) S = (int)(cus / wgs);  // never more workgroups than compute units: the extra ones would run as a second round
         if (S < 1) S = 1;
@@ -478,6 +482,7 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
         int gps = (G + S - 1) / S;
         while (gps > 1 && !fits_32bit_offsets(1, N, 8, group, gps)) gps = (gps + 1) / 2;
         S = (G + gps - 1) / gps;
+        if (tile_four(rows_x, group, bf16) && !short_slices(group, bf16, gps)) { p->waves_k = 4; p->threads = 256; }
         p->split = S;
         p->groups_per_split = gps;
         p->workgroups = (int)(wgs * S);
@@ -710,10 +715,9 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
         e = launch_panel(a, panel, st);
     } else if (plan.kernel == W4A16_KERNEL_TILE && tile_by_ticket(M, plan.tile_m)) {
         e = launch_tile_dyn(a, finish, b.sync, plan.waves_k, tuning().tile_depth == 2 && !bf16 && plan.waves_k <= 8 ? 2 : 1, tuning().tile_unit, st);
-    } else if (plan.kernel == W4A16_KERNEL_TILE && tile_four(plan.tile_m, group, bf16) && plan.tile_m == 64 && (bf16 || group != 128)) {
-        e = launch_tile_tall(a, finish, b.sync, st);
-    } else if (plan.kernel == W4A16_KERNEL_TILE && tile_four(plan.tile_m, group, bf16)) {
-        e = launch_tile_wide(a, finish, b.sync, plan.tile_m, st);
+    } else if (plan.kernel == W4A16_KERNEL_TILE && tile_four(plan.tile_m, group, bf16) && !short_slices(group, bf16, plan.groups_per_split)) {
+        if (plan.tile_m == 64 && (bf16 || group != 128)) e = launch_tile_tall(a, finish, b.sync, st);
+        else e = launch_tile_wide(a, finish, b.sync, plan.tile_m, st);
     } else if (plan.kernel == W4A16_KERNEL_TILE) {
         e = launch_tile(a, finish, b.sync, plan.tile_m, plan.waves_k, st);
     } else {

@@ -224,7 +224,8 @@ def test_bf16_plans_are_costed_as_bf16(binding):
     try:
         for M, N, K in shapes:
             p = binding.query_plan(M, N, K, 128, bf16=True)
-            assert p["tile_n"] == 64 and p["waves_k"] == (4 if p["tile_m"] == 64 else 8) and p["threads"] == 64 * p["waves_k"]
+            four = p["tile_m"] == 64 and p["groups_per_split"] > 8  # slices of up to 1024 k: the eight-wave form is as fast
+            assert p["tile_n"] == 64 and p["waves_k"] == (4 if four else 8) and p["threads"] == 64 * p["waves_k"]
             best = 1e30
             for rows in (16, 32, 64):
                 if rows > 16 and rows // 2 >= M:
