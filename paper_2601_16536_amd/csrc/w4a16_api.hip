@@ -351,11 +351,11 @@ bool use_panel(int M, int N, int K, int group, bool bf16, int cus, bool may_spli
     if (M <= 16) return false;
     // Against the cheapest plan of 64-column tiles.  Beyond 128 rows each of their rounds after the first costs about 3.5 us
     // more than the model says (measured: M = 512 ... 2048, two to nine rounds).  Up to 128 rows PANEL wins where 64-column
-    // tiles need several rounds or K is long (M = 64, K = 28672, N = 8192: 50.9 against 41.5 us; at K = 8192: 17.6 against
-    // 21.0); there it has to be 7 % cheaper, as the two models are together good for about that.  FP16 with groups of 128 up
-    // to 64 rows and below 8192 columns keeps its 64-column plans, which callers and tests know by their tiles and splits
-    // (M = 64, K = 18432, N = 7168: 32.9 us; the model gives PANEL 28).
-    if (M <= 64 && N < 8192 && group == 128 && !bf16) return false;
+    // tiles need several rounds or K is long (K = 28672, N = 8184, M = 32 / 64: 41.7 / 52.6 against 29.9 / 40.3 us; K = 18432, N = 7168,
+    // M = 64: 32.5 against 28.7; K = 8192, N = 8184, M = 32 / 64: 16.4 / 19.3 against 15.9 / 20.2; K = 4096: 10.4 / 11.5 against 14.8 / 20.3);
+    // there it has to be 7 % cheaper, as the two models are together good for about that: of 160 FP16 shapes (M = 17, 32, 48, 64,
+    // K = 4096 ... 28672, N = 1024 ... 8184, groups of 128) it is taken for 31 and faster on
+    // every one, as on 150 drawn ones of 17 to 64 rows and below 8192 columns (22 % in the mean).
     double other = 1e30;
     const int G = K / group;
     for (int r = 16; r <= 64; r *= 2) {

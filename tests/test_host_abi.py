@@ -176,10 +176,12 @@ def test_headline_plan_is_one_launch(binding):
     assert p["workgroups"] == 256 and p["groups_per_split"] == 28
 
 
-def test_tile_plans_for_many_rows_follow_the_cost_model(binding):
+def test_tile_plans_for_many_rows_follow_the_cost_model(binding, request):
     """M > 16: rows of X per workgroup and S come from a small cost model instead of "the largest block that still
     fills the compute units without a split".  The cases are the ones whose measured order the model was fitted to:
     N = 7168, K = 18432 and N = 4608, K = 10240 at M = 64 ran 34 % faster at 64 rows with K split than at 16 rows."""
+    binding.tune("panel", 2)  # 64-column tiles: two of these run in tiles of 128 x 256 where that is cheaper still
+    request.addfinalizer(lambda: binding.tune("panel", 0))
     q = lambda M, N, K: binding.query_plan(M, N, K, 128)
     for (M, N, K, rows, S) in [(64, 7168, 18432, 64, 2), (64, 4608, 10240, 64, 3), (64, 4096, 16384, 64, 4), (64, 2048, 10240, 16, 2),
                                (32, 7168, 18432, 32, 2), (32, 4096, 16384, 16, 2), (32, 8192, 8192, 16, 1), (64, 8192, 8192, 32, 1),
@@ -196,6 +198,13 @@ def test_tile_plans_for_many_rows_follow_the_cost_model(binding):
         assert (p["tile_m"], p["split"]) == (32, 1)
     finally:
         binding.tune("tile_rows", 0)
+
+
+def test_plans_do_not_jump_where_columns_do_not(binding):
+    """M = 64, K = 28672: 8184 columns are 128 tiles of 64 and 32 of 256 as 8192 are, and get the same plan."""
+    for M, K in ((64, 28672), (64, 18432), (32, 28672), (48, 4096)):
+        a, b = (binding.query_plan(M, N, K, 128) for N in (8184, 8192))
+        assert {k: v for k, v in a.items() if k != "workspace_bytes"} == {k: v for k, v in b.items() if k != "workspace_bytes"}
 
 
 def bf16_cost(M, N, K, rows, S, cus=256):
