@@ -249,6 +249,14 @@ double tile_plan_cost(int M, int N, int K, int group, int rows, int S, int cus, 
     return 3.0 + (double)rounds * (double)blocks * per_block + finish;
 }
 
+// The next S whose slices are shorter: every S up to it is the same plan.  (With many groups and few columns most are: K = 28672,
+// N = 64, groups of 32 had 768 plans to cost, 20 us, longer than the multiply.)
+int next_split(int G, int s)
+{
+    const int gps = (G + s - 1) / s;
+    return gps > 1 ? (G + gps - 2) / (gps - 1) : G + 1;
+}
+
 // Rows of X per workgroup and S (`split` 0: up to one workgroup per compute unit) that the model finds cheapest.
 struct TileChoice {
     int rows, S;
@@ -262,7 +270,7 @@ TileChoice cheapest_tiles(int M, int N, int K, int group, int split, int cus, bo
         if (r > 16 && r / 2 >= M) break;  // more than half of the block's rows would be empty
         const long long w1 = (long long)((N + 63) / 64) * ((M + r - 1) / r);
         const int smax = split ? split : ((int)(cus / w1) < 1 ? 1 : ((int)(cus / w1) > G ? G : (int)(cus / w1)));
-        for (int s = split ? split : 1; s <= smax; ++s) {
+        for (int s = split ? split : 1; s <= smax; s = next_split(G, s)) {
             const double c = tile_plan_cost(M, N, K, group, r, s, cus, bf16, frugal);
             if (c < best.cost) best = {r, s, c};
         }
@@ -356,18 +364,18 @@ bool use_panel(int M, int N, int K, int group, bool bf16, int cus, bool may_spli
     // there it has to be 7 % cheaper, as the two models are together good for about that: of 160 FP16 shapes (M = 17, 32, 48, 64,
     // K = 4096 ... 28672, N = 1024 ... 8184, groups of 128) it is taken for 31 and faster on
     // every one, as on 150 drawn ones of 17 to 64 rows and below 8192 columns (22 % in the mean).
-    double other = 1e30;
+    const double cost = panel_cost(M, N, K, group, bf16, cus, may_split, p), factor = M > 128 ? 1.0 : 0.93;
     const int G = K / group;
-    for (int r = 16; r <= 64; r *= 2) {
+    for (int r = 64; r >= 16; r /= 2) {
         const long long wgs = (long long)((N + 63) / 64) * ((M + r - 1) / r);
         int smax = (int)(cus / wgs);
         smax = smax < 1 ? 1 : (smax > G ? G : smax);
-        for (int s = 1; s <= smax; ++s) {
+        for (int s = 1; s <= smax; s = next_split(G, s)) {
             const double c = tile_plan_cost(M, N, K, group, r, s, cus, bf16, false) + (M > 128 ? 3.5 * (double)((wgs * s - 1) / cus) : 0.0);
-            if (c < other) other = c;
+            if (cost >= factor * c) return false;
         }
     }
-    return panel_cost(M, N, K, group, bf16, cus, may_split, p) < (M > 128 ? other : 0.93 * other);
+    return true;
 }
 
 // How much workspace a plan may ask for.  kBest: whatever pays.  kUnsplit: a plan of the PANEL form splits no tiles.

@@ -5,6 +5,7 @@ import ctypes
 import os
 import random
 import re
+import time
 
 import pytest
 
@@ -205,6 +206,21 @@ def test_plans_do_not_jump_where_columns_do_not(binding):
     for M, K in ((64, 28672), (64, 18432), (32, 28672), (48, 4096)):
         a, b = (binding.query_plan(M, N, K, 128) for N in (8184, 8192))
         assert {k: v for k, v in a.items() if k != "workspace_bytes"} == {k: v for k, v in b.items() if k != "workspace_bytes"}
+
+
+def test_planning_does_not_outlast_a_narrow_multiply(binding):
+    """Few columns and many groups leave hundreds of S to choose from, most of them the same slices: choosing among them may not
+    take an order of magnitude longer than among the few of a wide matrix (fastest of many runs: 3.5 times; 20 with each costed)."""
+    def fastest(M, N, K, group):
+        best = 1.0
+        for _ in range(60):
+            t = time.perf_counter()
+            for _ in range(20):
+                binding.lib().w4a16_scratch_bytes(M, N, K, group, 1)
+            best = min(best, time.perf_counter() - t)
+        return best
+
+    assert fastest(32, 64, 28672, 32) < 10 * fastest(64, 8192, 8192, 128)
 
 
 def bf16_cost(M, N, K, rows, S, cus=256):
