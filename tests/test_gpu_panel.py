@@ -129,8 +129,9 @@ def test_panel_whole_numbers_and_rows_that_are_not_finite(gpu):
 
 @pytest.mark.gpu
 def test_panel_without_room_for_its_partials(gpu):
-    """A plan that would split runs without the split where its workspace is not to be had: a registered workspace too small
-    for it, the array of the entry point that allocates nothing, and a capture with either."""
+    """A plan that would split runs without the split where its workspace is not to be had: brought by the call and too small,
+    registered and too small, the array of the entry point that allocates nothing, and a capture with each.  The same bits as
+    the unsplit plan."""
     torch, binding = gpu
     M, K, N = 400, 4096, 7168
     plan = binding.query_plan(M, N, K, 128)
@@ -139,16 +140,31 @@ def test_panel_without_room_for_its_partials(gpu):
     ref = orc.gemm(X, Wp, s, Zp, 128)
     args = binding.to_device(X, Wp, s, Zp)
     Y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+    binding.gemm(*args, 128, out=Y)  # with scratch of its own: split
+    assert err_ratio(Y.double().cpu().numpy(), ref) <= 1.0
+    binding.tune("panel_split", 1)
+    try:
+        assert binding.query_plan(M, N, K, 128)["tile_n"] == 256
+        unsplit = binding.gemm(*args, 128)
+    finally:
+        binding.tune("panel_split", 0)
+    assert err_ratio(unsplit.double().cpu().numpy(), ref) <= 1.0
     ws = torch.empty(1 << 16, dtype=torch.uint8, device="cuda")
+
+    def through_c():
+        st = torch.cuda.current_stream().cuda_stream
+        assert binding.raw_gemm(*[t.data_ptr() for t in args], 128, M, N, K, Y.data_ptr(), st) == binding.OK
+
     binding.set_workspace(ws)
     try:
-        for name, call in (("registered", lambda: binding.gemm(*args, 128, out=Y)), ("noalloc", lambda: binding.gemm_noalloc(*args, 128, out=Y))):
+        for name, call in (("its own", lambda: binding.gemm_ws(*args, 128, ws, out=Y)), ("registered", through_c),
+                           ("registered, binding", lambda: binding.gemm(*args, 128, out=Y)),
+                           ("noalloc", lambda: binding.gemm_noalloc(*args, 128, out=Y))):
             say("panel without room", name)
             Y.fill_(float("nan"))
             call()
             torch.cuda.synchronize()
-            assert err_ratio(Y.double().cpu().numpy(), ref) <= 1.0
-            eager = Y.clone()
+            assert torch.equal(Y, unsplit)
             graph = torch.cuda.CUDAGraph()
             with torch.cuda.graph(graph):
                 call()
@@ -156,11 +172,39 @@ def test_panel_without_room_for_its_partials(gpu):
                 Y.fill_(float("nan"))
                 graph.replay()
                 torch.cuda.synchronize()
-                assert torch.equal(Y, eager)
+                assert torch.equal(Y, unsplit)
     finally:
         binding.set_workspace(None)
-    binding.gemm(*args, 128, out=Y)
-    assert err_ratio(Y.double().cpu().numpy(), ref) <= 1.0
+
+
+@pytest.mark.gpu
+def test_panel_gives_way_to_tiles_that_need_less(gpu):
+    """M = 48, K = 14336, N = 7168: the 256-column plan needs more than the 4 MiB of the entry point that allocates nothing and would
+    be slow unsplit; there, and in a workspace of the 64-column plan's size, the 64-column plan runs, with its own finish."""
+    torch, binding = gpu
+    M, K, N = 48, 14336, 7168
+    plan = binding.query_plan(M, N, K, 128)
+    assert plan["tile_n"] == 256 and plan["workspace_bytes"] > 4 << 20, plan
+    binding.tune("panel", 2)
+    small = binding.query_plan(M, N, K, 128)
+    binding.tune("panel", 0)
+    assert small["split"] > 1 and 0 < small["workspace_bytes"] <= 4 << 20, small
+    X, Wp, s, Zp = wl.make(M, K, N, index=9410)
+    rows = [0, 31, 32, 47]
+    ref = orc.gemm(np.ascontiguousarray(X[rows]), Wp, s, Zp, 128)
+    args = binding.to_device(X, Wp, s, Zp)
+    ws = torch.empty(small["workspace_bytes"], dtype=torch.uint8, device="cuda")
+    Y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+    outs = []
+    for name, call in (("noalloc", lambda: binding.gemm_noalloc(*args, 128, out=Y)), ("workspace", lambda: binding.gemm_ws(*args, 128, ws, out=Y)),
+                       ("256 columns", lambda: binding.gemm(*args, 128, out=Y))):
+        say("less room", name)
+        Y.fill_(float("nan"))
+        call()
+        torch.cuda.synchronize()
+        outs.append(Y.clone())
+        assert err_ratio(Y.double().cpu().numpy()[rows], ref) <= 1.0
+    assert torch.equal(outs[0], outs[1])
 
 
 # K: fewer stages than waves, a run that ends inside a stage, runs of unequal length, groups longer than a stage
