@@ -207,6 +207,36 @@ def test_panel_gives_way_to_tiles_that_need_less(gpu):
     assert torch.equal(outs[0], outs[1])
 
 
+# Beyond eight row blocks of 128 the tiles are numbered in bands of eight: a second band, a shorter last one, a last block of 33 rows,
+# several column tiles, split tiles on both sides of a band's edge
+BANDS = [(1185, 128, 520, 64), (1100, 384, 264, 128), (1281, 256, 776, 32), (2049, 160, 520, 32)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N,group", BANDS)
+def test_panel_bands_of_row_blocks_against_the_oracle(gpu, M, K, N, group):
+    torch, binding = gpu
+    X, Wp, s, Zp = wl.make(M, K, N, index=9500 + M, group=group)
+    Xb = wl.make_x_bf16(M, K, index=9500 + M)
+    _, dW, dS, dZ = binding.to_device(X[:1], Wp, s, Zp)
+    dX, dXb = torch.from_numpy(X).cuda(), torch.from_numpy(Xb.view(np.int16)).cuda().view(torch.bfloat16)
+    refs = orc.gemm(X, Wp, s, Zp, group), orc.gemm_bf16(Xb, Wp, s, Zp, group)
+    binding.tune("panel", 1)
+    try:
+        for split in (1, 2):
+            binding.tune("panel_split", split)
+            plan = binding.query_plan(M, N, K, group)
+            assert plan["tile_n"] == 256 and plan["split"] == (split if K > 128 else 1)
+            for x, gemm, ref in ((dX, binding.gemm, refs[0]), (dXb, binding.gemm_bf16, refs[1])):
+                say("panel bands", (M, K, N, group), "split", split, x.dtype)
+                Y = torch.full((M, N), float("nan"), dtype=x.dtype, device="cuda")
+                gemm(x, dW, dS, dZ, group, out=Y)
+                assert err_ratio(Y.double().cpu().numpy(), ref) <= 1.0
+    finally:
+        binding.tune("panel", 0)
+        binding.tune("panel_split", 0)
+
+
 # K: fewer stages than waves, a run that ends inside a stage, runs of unequal length, groups longer than a stage
 TALL = [(64, 128, 64, 128), (33, 640, 72, 128), (128, 832, 136, 64), (65, 96, 264, 32), (100, 1056, 200, 32), (130, 1536, 64, 384),
         (70, 5376, 1032, 128), (61, 2048, 2056, 256)]
