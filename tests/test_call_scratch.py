@@ -57,7 +57,26 @@ def test_scratch_under_a_capture_comes_from_the_graphs_own_pool(binding, monkeyp
     monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: capturing)
     monkeypatch.setattr(torch.cuda, "memory_snapshot", snapshot)
     monkeypatch.setattr(torch, "empty", empty)
+    monkeypatch.setattr(binding, "_capture_id", lambda: 0)
     assert (binding._scratch(128, M, N, K, 0) is not None) == scratch
+
+
+def test_the_answer_for_one_capture_is_not_the_next_ones(binding, monkeypatch):
+    import torch
+    asked = []
+
+    def snapshot(pool):
+        record = snapshot_with(pool)
+        return lambda: asked.append(pool) or record()
+
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: True)
+    monkeypatch.setattr(torch, "empty", empty)
+    for number, pool in ((11, (3, 0)), (12, (0, 0)), (13, (4, 0))):
+        monkeypatch.setattr(binding, "_capture_id", lambda: number)
+        monkeypatch.setattr(torch.cuda, "memory_snapshot", snapshot(pool))
+        for _ in range(3):
+            assert (binding._scratch(128, M, N, K, 0) is not None) == (pool != (0, 0))
+    assert asked == [(3, 0), (0, 0), (4, 0)]  # once per capture
 
 
 def test_a_full_device_is_no_error_of_a_call_that_can_do_without(binding, monkeypatch):
