@@ -50,6 +50,8 @@ def kernel_name(plan, M, group):
             if plan["waves_k"] == 4 and plan["tile_m"] in (32, 64):
                 return "tile_wide_kernel"
             return "tile_group_kernel"
+        if plan["waves_k"] == 4 and plan["tile_m"] == 64:
+            return "tile_tall_kernel"
     return KERNEL_NAMES.get(plan["kernel"], "?")
 
 

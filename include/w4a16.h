@@ -84,7 +84,7 @@ typedef enum {
                                     share the slice (exact sums in LDS); slices of different workgroups meet in a
                                     64-bit fixed-point accumulator by one atomic add each, no second launch        */
     W4A16_KERNEL_TILE = 4        /* any M, the scheduler's choice otherwise: 64-column tile x 16, 32 or 64 rows of X
-                                    per workgroup, its waves (eight; four at 64 rows, and at 32 with groups of 128) own contiguous runs of K (LDS
+                                    per workgroup, its waves (eight; four at 64 rows, and with FP16 and groups of 128 at 32) own contiguous runs of K (LDS
                                     reduction), plain MFMA operand layout; slices of different workgroups meet as
                                     in STRIPE.  The scheduler's own plans beyond 16 rows may have tiles of 128 rows
                                     x 256 columns instead (tile_n = 256): four waves side by side, the tiles past the
@@ -264,6 +264,9 @@ int w4a16_quantize(const void *W16, int group, int N, int K, uint32_t *Wpacked, 
  *   "tile_waves"     waves per TILE workgroup (4..8)
  *   "tile_wide"      2: TILE at 32 or 64 rows of X per workgroup: the eight-wave form instead of
  *                    the four-wave one
+ *   "panel"          M > 16, the scheduler's own plans: 1 = tiles of 128 rows x 256 columns wherever they can run, 2 = never
+ *   "panel_split"    slices of those of these tiles that go past the last whole round of compute units (1 = none; where K
+ *                    has as many)
  *   "log"            1: every w4a16_gemm* call prints its plan on stderr (the one case in which the library prints)
  * Returns W4A16_ERR_UNSUPPORTED for an unknown knob.
  */

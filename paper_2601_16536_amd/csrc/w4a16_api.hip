@@ -209,7 +209,7 @@ bool tile_by_ticket(int M, int rows_x) { return rows_x == 16 && (tuning().tile_d
 // groups of 128 at 64 rows: M = 128, N = 8192, K = 512 / 2048 / 8192: 6.6 / 10.7 / 27.7 us (wide), 6.9 / 10.7 / 27.5 (tall).
 bool tile_four(int rows_x, int group, bool bf16)
 {
-    return ((rows_x == 64 && wide_takes(group)) || (rows_x == 32 && group == 128 && !bf16)) && tuning().tile_wide != 2;
+    return ((rows_x == 64 && panel_takes(group)) || (rows_x == 32 && group == 128 && !bf16)) && tuning().tile_wide != 2;
 }
 
 // Up to 1024 k per slice a wave of the tall form has no more stages than it keeps in flight, and the BF16 eight-wave kernel for

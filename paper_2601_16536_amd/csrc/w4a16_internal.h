@@ -74,13 +74,13 @@ struct PanelPlan {
     int split_tiles;  // the last so many tiles are cut into `split` slices of slice_k each, summed by a second launch
     int split, slice_k;
 };
-// The lengths of group the PANEL form and the four-wave TILE form take: whole stages of 128 k, or a stage's whole parts.
+// The lengths of group the PANEL form and the tall TILE form take: whole stages of 128 k, or a stage's whole parts.
 inline bool panel_takes(int group) { return group % 128 == 0 || group == 64 || group == 32; }
-inline bool wide_takes(int group) { return panel_takes(group); }
 hipError_t launch_panel(const GemmArgs &a, const PanelPlan &p, hipStream_t stream);
-// TILE family at 64 rows of X per workgroup: four waves per workgroup, each alone on its SIMD (w4a16_tile_tall.hip).
+// TILE family at 64 rows of X per workgroup, BF16 and groups other than 128: four waves per workgroup, each alone on its SIMD
+// (w4a16_tile_tall.hip).
 hipError_t launch_tile_tall(const GemmArgs &a, int finish, unsigned long long *sync, hipStream_t stream);
-// TILE family at 32 rows of X per workgroup, FP16, group = 128: four waves per workgroup (w4a16_tile_wide.hip).
+// TILE family at 32 or 64 rows of X per workgroup, FP16, group = 128: four waves per workgroup (w4a16_tile_wide.hip).
 hipError_t launch_tile_wide(const GemmArgs &a, int finish, unsigned long long *sync, int rows_x, hipStream_t stream);
 // TILE family, 16 rows of X per workgroup, the slice handed out to the waves by ticket (w4a16_tile_dyn.hip); `depth` (1, 2)
 // units in flight per wave.

@@ -1,4 +1,4 @@
-// W4A16 multiply for prompts (the scheduler's choice beyond 128 rows where its tiles fill the chip): one workgroup of four
+// W4A16 multiply for prompts, and from 17 rows on for batches over a long K or many columns: one workgroup of four
 // waves per (32 RT rows of X, 256 columns, K slice), every wave alone on its SIMD with 32 RT x 64 of the result; RT = 4, and
 // 1 to 4 in the last row block.
 //
@@ -16,8 +16,8 @@
 //     tile before it takes its step tot += s part;
 //   - the order of instructions is written down slot by slot, one MFMA each.  Left to the compiler's scheduler the same
 //     loop took 243 us where this one takes 224 (M = 2048, K = N = 8192).
-// M = 2048, K = N = 8192: 224-232 us = 1.2 PFLOP/s (FP16; BF16 229-243), 656 us before; the vendor's FP16 GEMM on dense weights
-// takes 235-265 us on the same card.  M = 777, K = 4096, N = 11008: 80 us (BF16), 162 before.
+// M = 2048, K = N = 8192: 224-232 us = 1.2 PFLOP/s (FP16; BF16 229-243), 656 us before; ten launches one after another under
+// the trace, where the power limit sets in: 231 rising to 266 (BF16 271 to 278, the first two 334 and 319).  The vendor's FP16 GEMM on dense weights takes 235-265.  M = 777, K = 4096, N = 11008: 80 us (BF16), 162 before.
 // Arithmetic: products x (q - z) are exact in FP32, sums over a group in FP32 in the MFMA, times s in FP32: as in
 // w4a16_tile_wide.hip.
 #include "w4a16_device.h"

@@ -1,5 +1,5 @@
 // W4A16 multiply, TILE family at 64 rows of X per workgroup for BF16 and for groups other than 128 (FP16 with groups of 128
-// has w4a16_tile_wide.hip): one workgroup of four waves per (64-column tile, 64 rows of X, K slice), every wave alone on its
+// has w4a16_tile_wide.hip, BF16 with groups of 128 and slices of up to 1024 k the eight-wave w4a16_tile.hip): one workgroup of four waves per (64-column tile, 64 rows of X, K slice), every wave alone on its
 // SIMD with a quarter of the slice's K and the whole 64 x 64 result.
 //
 // What bounds it: a stage (128 k) is 64 MFMAs 32x32x16, 160 vector instructions of unpack (FP16; 272 BF16), 64 of Eq. 2's step
@@ -377,7 +377,7 @@ hipError_t launch_seg(const GemmArgs &a, int finish, unsigned long long *sync, h
 
 hipError_t launch_tile_tall(const GemmArgs &a, int finish, unsigned long long *sync, hipStream_t stream)
 {
-    if (!wide_takes(a.group) || !finish_args_ok(a, finish, sync)) return hipErrorInvalidValue;
+    if (!panel_takes(a.group) || !finish_args_ok(a, finish, sync)) return hipErrorInvalidValue;
     const unsigned long long rows = (unsigned long long)a.groups_per_split * (a.group / 8);
     if (rows * a.N * 4ull >= 0x7F000000ull) return hipErrorInvalidValue;  // slice-relative 32-bit buffer offsets
     if ((unsigned long long)a.M * a.K * 2ull >= 0x7F000000ull) return hipErrorInvalidValue;

@@ -1,4 +1,4 @@
-// Pieces of the kernels that give a wave 32 or more rows of X (w4a16_panel.hip, w4a16_tile_wide.hip): the exact operand
+// Pieces of the kernels that give a wave 64 or more rows of X (w4a16_panel.hip, w4a16_tile_tall.hip): the exact operand
 // q - z in the order of k, and compile-time loops.
 #pragma once
 #include "w4a16_device.h"
