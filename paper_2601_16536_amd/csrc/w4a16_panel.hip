@@ -32,8 +32,6 @@ constexpr int kMainRt = kPanelRows / 32;
 constexpr int kWaveCols = 64;
 constexpr int kCols = kWaves * kWaveCols;
 static_assert(kCols == kPanelCols, "the planner's tile");
-constexpr int kStage = 128;       // k per stage
-constexpr int kSteps = kStage / 16;
 constexpr int kBuffers = 3;       // stages in LDS: the one in use and two on their way
 constexpr int kXcds = 8;
 constexpr int kRowGroup = 8;      // row blocks that neighbouring workgroups of an XCD cover before the next column tile
@@ -168,10 +166,7 @@ __device__ __forceinline__ void panel(const GemmArgs &a, unsigned char *const sm
     const float16_t zero16 = part[0];
     uint4_t A[RT][kSteps], B[2][kSteps];
 
-    struct Scales {
-        float s[2][Sh::kSegs];
-        typename Op::Zero z[2][Sh::kSegs];
-    };
+    typedef StageScales<Op, Sh::kSegs> Scales;
     uint32_t sraw[Sh::kSegs], zraw[Sh::kSegs];
     auto read_scales_raw = [&](int buf) {
         const unsigned char *const bs = lds_s + buf * (Sh::kSBytes + Sh::kZBytes);
@@ -183,15 +178,7 @@ __device__ __forceinline__ void panel(const GemmArgs &a, unsigned char *const sm
     };
     auto convert_scales = [&](Scales &g) {
 #pragma unroll
-        for (int e = 0; e < Sh::kSegs; ++e) {
-            H2 s;
-            s.u = sraw[e];
-            const uint32_t z = (zraw[e] | zfill) >> zsh;
-            g.s[0][e] = Op::scale(s.h[0]);
-            g.s[1][e] = Op::scale(s.h[1]);
-            g.z[0][e] = Op::zero(z);
-            g.z[1][e] = Op::zero(z >> 4);
-        }
+        for (int e = 0; e < Sh::kSegs; ++e) g.set(e, sraw[e], (zraw[e] | zfill) >> zsh);
     };
 
 #pragma unroll
@@ -228,35 +215,11 @@ __device__ __forceinline__ void panel(const GemmArgs &a, unsigned char *const sm
         // One slot per MFMA.  The compiler may not move anything from slot to slot: each holds what fits beside one MFMA.
         for_each_constant(std::make_integer_sequence<int, kTiles * kSteps>{}, [&](auto slot_) {
             constexpr int slot = decltype(slot_)::value;
-            constexpr int t = slot / kSteps, ct = t / RT, rt = t % RT, ks = slot % kSteps;
-            constexpr int seg = ks / kStepsPerSeg, pp = (t * Sh::kSegs + seg) & 1;
-            part[pp] = Op::mfma(A[rt][ks], B[ct][ks], ks % kStepsPerSeg == 0 ? zero16 : part[pp]);
+            typedef StageSlot<slot, RT, SEG> Slot;
+            constexpr int t = Slot::t, ct = Slot::ct, rt = Slot::rt, ks = Slot::ks, w_end = Slot::w_end;
+            part[Slot::pp] = Op::mfma(A[rt][ks], B[ct][ks], Slot::kFirst ? zero16 : part[Slot::pp]);
             if constexpr (ct == 1) A[rt][ks] = read_a(nbuf, rt, ks);
-
-            // Eq. 2's step of the segment before (the tile before, for one segment per stage), once its last MFMA is
-            // through: beside the fourth to sixth MFMA, or the second half of a shorter segment.
-            constexpr bool kOne = Sh::kSegs == 1;
-            constexpr int kLate = kOne ? 3 : kStepsPerSeg / 2, kStepSlots = kOne ? 3 : kStepsPerSeg / 2;
-            constexpr int es = ks % kStepsPerSeg - kLate;
-            constexpr bool stepping = es >= 0 && es < kStepSlots;
-            if constexpr (stepping) {
-                constexpr int tp = seg ? t : (t + kTiles - 1) % kTiles;
-                static_range<es * 16 / kStepSlots, (es + 1) * 16 / kStepSlots>([&](auto i_) {
-                    constexpr int i = decltype(i_)::value;
-                    tot[tp][i] = __builtin_fmaf(s_prev, part[pp ^ 1][i], tot[tp][i]);
-                });
-                if constexpr (es == kStepSlots - 1) s_prev = cur.s[ct][seg];
-            }
-            // This tile's share of the unpack: the other column half of this stage (ct = 0), the first one of the next (ct = 1).
-            constexpr int w_beg = rt * kSteps / RT, w_end = (rt + 1) * kSteps / RT;
-            if constexpr (!kOne || !stepping) {
-                constexpr int jobs = (w_end - w_beg) * Op::kParts;
-                constexpr int n = kOne ? kSteps - kStepSlots : kSteps, i = kOne && ks > kLate ? ks - kStepSlots : ks;
-                static_range<i * jobs / n, (i + 1) * jobs / n>([&](auto jb_) {
-                    constexpr int jb = decltype(jb_)::value, w = w_beg + jb / Op::kParts;
-                    Op::unpack(jb % Op::kParts, wv[t & 1][w], ct == 0 ? cur.z[1][w / kStepsPerSeg] : nxt.z[0][w / kStepsPerSeg], consts, tmp, B[ct ^ 1][w]);
-                });
-            }
+            step_and_unpack<Op, Slot>(tot, part, s_prev, cur, nxt, consts, tmp, B, [&](auto w) { return wv[t & 1][w]; });
             // the words of the next tile's share
             if constexpr (ks == 2) {
                 if constexpr (rt + 1 < RT) static_range<w_end, (rt + 2) * kSteps / RT>([&](auto w) { wv[(t & 1) ^ 1][w] = read_w(ct == 0 ? buf : nbuf, ct ^ 1, w); });

@@ -27,8 +27,6 @@ namespace {
 constexpr int kTileCols = 64;
 constexpr int kXcds = 8;
 constexpr int kWaves = 4;
-constexpr int kStage = 128;  // k per stage
-constexpr int kSteps = kStage / 16;
 
 // Sizes for RT blocks of 32 rows and SEG k per step of scales.
 template <int RT, int SEG>
@@ -174,21 +172,10 @@ __global__ __launch_bounds__(64 * kWaves) void tile_tall_kernel(const GemmArgs a
             }
         };
 
-        struct Scales {
-            float s[2][kSegs];
-            typename Op::Zero z[2][kSegs];
-        };
+        typedef StageScales<Op, kSegs> Scales;
         auto scales_of = [&](int place, Scales &g) {
 #pragma unroll
-            for (int e = 0; e < kSegs; ++e) {
-                H2 s;
-                s.u = sq[place][e];
-                const uint32_t z = (zq[place][e] | zfill) >> zsh;
-                g.s[0][e] = Op::scale(s.h[0]);
-                g.s[1][e] = Op::scale(s.h[1]);
-                g.z[0][e] = Op::zero(z);
-                g.z[1][e] = Op::zero(z >> 4);
-            }
+            for (int e = 0; e < kSegs; ++e) g.set(e, sq[place][e], (zq[place][e] | zfill) >> zsh);
         };
 
         const typename Op::Consts consts = Op::consts();
@@ -227,42 +214,19 @@ __global__ __launch_bounds__(64 * kWaves) void tile_tall_kernel(const GemmArgs a
             const int nbuf = buf + 1 == Sh::kBuffers ? 0 : buf + 1;
             for_each_constant(std::make_integer_sequence<int, kTiles * kSteps>{}, [&](auto slot_) {
                 constexpr int slot = decltype(slot_)::value;
-                constexpr int t = slot / kSteps, ct = t / RT, rt = t % RT, ks = slot % kSteps;
-                constexpr int seg = ks / kStepsPerSeg, pp = (t * kSegs + seg) & 1;
+                typedef StageSlot<slot, RT, SEG> Slot;
+                constexpr int ct = Slot::ct, rt = Slot::rt, ks = Slot::ks;
                 if constexpr (slot == RT * kSteps) {
                     // The next stage's X has landed when at most the operations asked for after it are on their way: X of
                     // kBuffers - 1 stages, weights of as many.
                     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(Sh::kWait) : "memory");
                 }
-                part[pp] = Op::mfma(A[rt][ks], B[ct][ks], ks % kStepsPerSeg == 0 ? zero16 : part[pp]);
+                part[Slot::pp] = Op::mfma(A[rt][ks], B[ct][ks], Slot::kFirst ? zero16 : part[Slot::pp]);
                 if constexpr (ct == 1) A[rt][ks] = read_a(nbuf, rt, ks);
-
-                // Eq. 2's step of the segment before (the tile before, for one segment per stage), once its last MFMA is
-                // through: beside the fourth to sixth MFMA, or the second half of a shorter segment.
-                constexpr bool kOne = kSegs == 1;
-                constexpr int kLate = kOne ? 3 : kStepsPerSeg / 2, kStepSlots = kOne ? 3 : kStepsPerSeg / 2;
-                constexpr int es = ks % kStepsPerSeg - kLate;
-                constexpr bool stepping = es >= 0 && es < kStepSlots;
-                if constexpr (stepping) {
-                    constexpr int tp = seg ? t : (t + kTiles - 1) % kTiles;
-                    static_range<es * 16 / kStepSlots, (es + 1) * 16 / kStepSlots>([&](auto i_) {
-                        constexpr int i = decltype(i_)::value;
-                        tot[tp][i] = __builtin_fmaf(s_prev, part[pp ^ 1][i], tot[tp][i]);
-                    });
-                    if constexpr (es == kStepSlots - 1) s_prev = cur.s[ct][seg];
-                }
-                // This tile's share of the unpack: the other column half of this stage (ct = 0), the first one of the next.
-                constexpr int w_beg = rt * kSteps / RT, w_end = (rt + 1) * kSteps / RT;
-                if constexpr (!kOne || !stepping) {
-                    constexpr bool all = !kOne;
-                    constexpr int jobs = (w_end - w_beg) * Op::kParts;
-                    constexpr int n = all ? kSteps : kSteps - kStepSlots, i = !all && ks > kLate ? ks - kStepSlots : ks;
-                    static_range<i * jobs / n, (i + 1) * jobs / n>([&](auto jb_) {
-                        constexpr int jb = decltype(jb_)::value, w = w_beg + jb / Op::kParts;
-                        if constexpr (ct == 0) Op::unpack(jb % Op::kParts, wq[R][w][1], cur.z[1][w / kStepsPerSeg], consts, tmp, B[1][w]);
-                        else Op::unpack(jb % Op::kParts, wq[RN][w][0], nxt.z[0][w / kStepsPerSeg], consts, tmp, B[0][w]);
-                    });
-                }
+                step_and_unpack<Op, Slot>(tot, part, s_prev, cur, nxt, consts, tmp, B, [&](auto w) {
+                    if constexpr (ct == 0) return wq[R][w][1];
+                    else return wq[RN][w][0];
+                });
                 if constexpr (slot == RT * kSteps - 1) scales_of(RN, nxt);
                 // X of the stage kBuffers on, into the buffer whose stage is all in registers, beside the first half's MFMAs;
                 // the weights kRing on, into the registers the first half has emptied, beside the first ones of the second.

@@ -1,5 +1,5 @@
 // Pieces of the kernels that give a wave 64 or more rows of X (w4a16_panel.hip, w4a16_tile_tall.hip): the exact operand
-// q - z in the order of k, and compile-time loops.
+// q - z in the order of k, compile-time loops, and what the stages (128 k) of both kernels have in common.
 #pragma once
 #include "w4a16_device.h"
 #include <type_traits>
@@ -137,6 +137,72 @@ __device__ __forceinline__ void static_range(const F &f)
     if constexpr (BEG < END) {
         f(std::integral_constant<int, BEG>{});
         static_range<BEG + 1, END>(f);
+    }
+}
+
+// ---- a stage of kStage k: scales and zero points per segment of SEG k, and the slots ----
+
+constexpr int kStage = 128;
+constexpr int kSteps = kStage / 16;  // MFMAs 32x32x16 of one result tile
+
+// Eq. 2's constants of a stage for a lane's two columns, from a word of two scales and one of zero points (shifted so that
+// the two are in its low byte) per segment.
+template <typename Op, int SEGS>
+struct StageScales {
+    float s[2][SEGS];
+    typename Op::Zero z[2][SEGS];
+    __device__ __forceinline__ void set(int e, uint32_t scales, uint32_t zeros)
+    {
+        H2 h;
+        h.u = scales;
+        s[0][e] = Op::scale(h.h[0]);
+        s[1][e] = Op::scale(h.h[1]);
+        z[0][e] = Op::zero(zeros);
+        z[1][e] = Op::zero(zeros >> 4);
+    }
+};
+
+// One slot of a stage: an MFMA of tile t = (column half, row block) and what fits beside it.  The tiles take their eight MFMAs one
+// after the other.
+template <int SLOT, int RT, int SEG>
+struct StageSlot {
+    static constexpr int kTiles = 2 * RT, kSegs = kStage / SEG, kStepsPerSeg = SEG / 16;
+    static constexpr int t = SLOT / kSteps, ct = t / RT, rt = t % RT, ks = SLOT % kSteps;
+    static constexpr int seg = ks / kStepsPerSeg, pp = (t * kSegs + seg) & 1;  // segment, and which part sums it adds to
+    static constexpr bool kFirst = ks % kStepsPerSeg == 0;                      // of its segment
+    // Eq. 2's step of the segment before (the tile before, for one segment per stage), once its last MFMA is through: beside
+    // the fourth to sixth MFMA, or the second half of a shorter segment.
+    static constexpr bool kOne = kSegs == 1;
+    static constexpr int kLate = kOne ? 3 : kStepsPerSeg / 2, kStepSlots = kOne ? 3 : kStepsPerSeg / 2;
+    static constexpr int es = ks % kStepsPerSeg - kLate;
+    static constexpr bool kStepping = es >= 0 && es < kStepSlots;
+    static constexpr int tp = seg ? t : (t + kTiles - 1) % kTiles;
+    // this tile's share of the words to be unpacked, in slots that take no step where there is one segment
+    static constexpr int w_beg = rt * kSteps / RT, w_end = (rt + 1) * kSteps / RT;
+    static constexpr bool kUnpacking = !kOne || !kStepping;
+    static constexpr int kUnpackSlots = kOne ? kSteps - kStepSlots : kSteps, kUnpackSlot = kOne && ks > kLate ? ks - kStepSlots : ks;
+};
+
+// The slot's vector work.  `word(w)`: the packed word of step w of the half that is unpacked, the second of this stage beside the
+// first one's MFMAs, the first of the next stage beside the second one's.
+template <typename Op, typename Slot, typename Scales, typename Word, int TILES>
+__device__ __forceinline__ void step_and_unpack(float16_t (&tot)[TILES], const float16_t (&part)[2], float &s_prev, const Scales &cur, const Scales &nxt,
+                                                const typename Op::Consts &consts, typename Op::Tmp &tmp, uint4_t (&B)[2][kSteps], const Word &word)
+{
+    if constexpr (Slot::kStepping) {
+        static_range<Slot::es * 16 / Slot::kStepSlots, (Slot::es + 1) * 16 / Slot::kStepSlots>([&](auto i_) {
+            constexpr int i = decltype(i_)::value;
+            tot[Slot::tp][i] = __builtin_fmaf(s_prev, part[Slot::pp ^ 1][i], tot[Slot::tp][i]);
+        });
+        if constexpr (Slot::es == Slot::kStepSlots - 1) s_prev = cur.s[Slot::ct][Slot::seg];
+    }
+    if constexpr (Slot::kUnpacking) {
+        constexpr int jobs = (Slot::w_end - Slot::w_beg) * Op::kParts, n = Slot::kUnpackSlots, i = Slot::kUnpackSlot;
+        static_range<i * jobs / n, (i + 1) * jobs / n>([&](auto jb_) {
+            constexpr int jb = decltype(jb_)::value, w = Slot::w_beg + jb / Op::kParts;
+            Op::unpack(jb % Op::kParts, word(std::integral_constant<int, w>{}), Slot::ct == 0 ? cur.z[1][w / Slot::kStepsPerSeg] : nxt.z[0][w / Slot::kStepsPerSeg],
+                       consts, tmp, B[Slot::ct ^ 1][w]);
+        });
     }
 }
 
