@@ -86,6 +86,17 @@ __device__ __forceinline__ float apply_scale_zero(float tot, float s, float z, f
     return __builtin_fmaf(s * 16777216.0f, P, __builtin_fmaf(-s * z, xsum, tot));
 }
 
+// The ticket kernels' sums inside a workgroup (w4a16_stripe_dyn.hip, w4a16_tile_dyn.hip).  A wave's sum of one output, in units of
+// 2^-24, is an integer-valued double; it is clamped to +-2^49 (2^25 in units of 1; a NaN stays one), so that up to sixteen waves' sums add up
+// exactly below 2^53, in any order, in a double in LDS.  The atomic add of doubles keeps the conversion to 64-bit integers,
+// some twenty instructions, for after the barrier: once per output instead of once per output and wave.
+constexpr double kSumMax = 562949953421312.0;  // 2^49
+__device__ __forceinline__ void add_wave_sum(double *acc, double t)
+{
+    t = t > kSumMax ? kSumMax : (t < -kSumMax ? -kSumMax : t);
+    if (t != 0.0) __builtin_amdgcn_ds_atomic_fadd_f64((__attribute__((address_space(3))) double *)acc, t);  // (a NaN is not 0)
+}
+
 // Symmetric quantisation (Section 2.1: z = 0 on signed codes, i.e. 8 on the stored unsigned codes) comes without a
 // zero-point tensor.  The kernels then read their zero-point words through a buffer of size 0 (every load is out
 // of range: it returns 0 and moves nothing) and OR this word in: eight zero points of 8.

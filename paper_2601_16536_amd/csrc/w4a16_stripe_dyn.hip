@@ -20,7 +20,7 @@
 //     sum_k x_k s (q_k - z)  =  (2^24 s) P - (s z) sum_k x_k        (Eq. 2, fp32)
 // is rounded to a multiple of 2^-24 (and clamped far outside the FP16 range),
 // and from there on everything is added exactly: as integer-valued doubles per
-// wave, as 64-bit integers in LDS and in the cross-workgroup accumulator.
+// wave and in LDS, as 64-bit integers in the cross-workgroup accumulator.
 // Integer adds commute, hence bitwise reproducible results whatever the
 // schedule.
 //
@@ -55,13 +55,11 @@ namespace {
 
 constexpr int kStripe = 256;            // columns per workgroup: 64 lanes x 4 words
 constexpr int kLdsLimit = 144 * 1024;
-constexpr double kSumMax = 562949953421312.0;   // 2^49 = 2^25 in units of 2^-24: the clamp of a wave's and a workgroup's sum
-constexpr long long kNaNMark = 1ll << 58;       // added to the LDS sum of an output by a wave whose sum is NaN
 
 // LDS of a workgroup, in this order (all 16-byte aligned):
 //   zero entry            16 B
 //   tickets               16 B   (one counter)
-//   acc   [MROWS][256]    64-bit sums of the waves, in units of 2^-24
+//   acc   [MROWS][4][64]  sums of the waves, integer-valued doubles in units of 2^-24, by row, column mod 4, lane
 //   xs    [rows][MROWS]   A-operand entries: eight halves of one packed row of X in unpack order
 //   xsum  [MROWS][rows]   fp32 sum of the eight x of each packed row
 //   sc    [groups][256]   FP16 scales of the stripe
@@ -330,17 +328,12 @@ __global__ __launch_bounds__(1024) void stripe_dyn_kernel(const GemmArgs a, cons
 #endif
 
     // ---- Phase 3 inside the workgroup: exact 64-bit sums in LDS ----
-    unsigned long long *acc = reinterpret_cast<unsigned long long *>(smem + L.acc);
+    // The sum of (row i, column 4 lane + c) at 256 i + 64 c + lane: neighbouring lanes on neighbouring banks.
+    double *const acc = reinterpret_cast<double *>(smem + L.acc);
 #pragma unroll
     for (int i = 0; i < MROWS; ++i)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            double t = tot[c][i];
-            const bool nan = t != t;
-            t = t > kSumMax ? kSumMax : (t < -kSumMax ? -kSumMax : t);
-            const long long fx = nan ? kNaNMark : (long long)t;
-            if (fx != 0) __hip_atomic_fetch_add(acc + i * kStripe + 4 * lane + c, (unsigned long long)fx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
+        for (int c = 0; c < 4; ++c) add_wave_sum(acc + i * kStripe + 64 * c + lane, tot[c][i]);
     __syncthreads();
 #ifdef W4A16_TIMELINE
     const unsigned long long TA = __builtin_amdgcn_s_memrealtime();
@@ -350,11 +343,12 @@ __global__ __launch_bounds__(1024) void stripe_dyn_kernel(const GemmArgs a, cons
     for (int o = tid; o < MROWS * kStripe; o += nthreads) {
         const int m = o / kStripe, col = stripe * kStripe + (o % kStripe);
         if (m >= a.M || col >= a.N) continue;
-        const long long fx = (long long)acc[o];
-        const bool nan = fx >= (kNaNMark >> 1);  // sixteen waves' clamped sums stay below 2^53
+        const double t = acc[m * kStripe + 64 * (o & 3) + ((o % kStripe) >> 2)];
+        const bool nan = t != t;
+        const long long fx = nan ? 0ll : (long long)t;
         const size_t out = (size_t)m * a.N + col;
         if (finish == kFinishAccumulator) {
-            add_slice<Act>(sync + out, to_fixed(nan ? 0ll : fx), nan, a.split, a.Y + out);
+            add_slice<Act>(sync + out, to_fixed(fx), nan, a.split, a.Y + out);
 #ifdef W4A16_TIMELINE
             TB = __builtin_amdgcn_s_memrealtime();
 #endif

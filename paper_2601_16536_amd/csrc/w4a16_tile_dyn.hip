@@ -11,7 +11,7 @@
 // How the slice is shared is the decode kernel's way (w4a16_stripe_dyn.hip): a unit is kUnitBlocks blocks of one
 // quantisation group (the whole group for group = 128), a wave draws its next unit from an LDS ticket counter,
 // every unit's contribution (Eq. 2, fp32) is rounded to a multiple of 2^-24, and from there on all sums are exact
-// (integer-valued doubles per wave, 64-bit integers in LDS and across workgroups): Algorithm 1's Phase 3 with
+// (integer-valued doubles per wave and in LDS, 64-bit integers across workgroups): Algorithm 1's Phase 3 with
 // results that do not depend on which wave took which unit.  A wave stages the X of a unit itself, in its own
 // LDS (no barrier in the loop).
 #include "w4a16_device.h"
@@ -28,10 +28,8 @@ constexpr int kBlockRows = 4;                    // packed rows per block: one M
 // over 32 banks; with 18 entries a packed row starts 8 banks after its predecessor and a row of X 4 banks after its own
 // (measured: SQ_LDS_BANK_CONFLICT 2.4 times lower than with 17).
 constexpr int kRowStride = kRowsX + 2;
-constexpr double kSumMax = 562949953421312.0;    // 2^49 = 2^25 in units of 2^-24: the clamp of a wave's sum
-constexpr long long kNaNMark = 1ll << 58;        // added to the LDS sum of an output by a wave whose sum is NaN
 
-// LDS: ticket counter (16 B), the workgroup's sums [16][64] (64-bit), then per wave and ring place one unit of X.
+// LDS: ticket counter (16 B), the workgroup's sums [4 columns][4 rows][64 lanes] (doubles), then per wave and ring place one unit of X.
 constexpr uint32_t kLdsAcc = 16;
 constexpr uint32_t kLdsX = kLdsAcc + kRowsX * kTileCols * 8;
 template <int UB>
@@ -110,9 +108,9 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
     }
 
     uint32_t *const tickets = reinterpret_cast<uint32_t *>(smem);
-    unsigned long long *const acc = reinterpret_cast<unsigned long long *>(smem + kLdsAcc);
+    double *const acc = reinterpret_cast<double *>(smem + kLdsAcc);
     if (tid == 0) tickets[0] = (uint32_t)(waves * D);
-    for (int e = tid; e < kRowsX * kTileCols; e += nthreads) acc[e] = 0ull;
+    for (int e = tid; e < kRowsX * kTileCols; e += nthreads) acc[e] = 0.0;
     __syncthreads();
 
     unsigned char *const myx = smem + kLdsX + (uint32_t)wave * unit_x_bytes<UB>();  // one unit of X, this wave's own
@@ -183,27 +181,27 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
         if (!any) break;
     }
 
-    // ---- Phase 3 inside the workgroup: exact 64-bit sums in LDS (lane (g, j) holds rows 4 g + i, columns 4 j + c) ----
+    // ---- Phase 3 inside the workgroup: exact sums in LDS (lane (g, j) holds rows 4 g + i, columns 4 j + c), the sum of (c, i, lane) at
+    // 64 (4 c + i) + lane: neighbouring lanes on neighbouring banks.  (As [16][64] the sixteen lanes of a group were 32 bytes apart and
+    // the four groups in the same banks; with the conversions to integers per wave 1.7 us from a wave's last unit to the barrier at
+    // M = 16, K = 14336, N = 4096, 1.2 now, and 1.0 and 0.3 at M = 1, K = 4096, N = 1024: 11.9 -> 11.5 and 5.0 -> 4.35 us per multiply.)
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4; ++i) {
+        if (m0 + 4 * g4 + i >= a.M) continue;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            double t = tot[c][i];
-            const bool nan = t != t;
-            t = t > kSumMax ? kSumMax : (t < -kSumMax ? -kSumMax : t);
-            const long long fx = nan ? kNaNMark : (long long)t;
-            if (fx != 0) __hip_atomic_fetch_add(acc + (4 * g4 + i) * kTileCols + 4 * j + c, (unsigned long long)fx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
+        for (int c = 0; c < 4; ++c) add_wave_sum(acc + 64 * (4 * c + i) + lane, tot[c][i]);
+    }
     __syncthreads();
     // ---- and across workgroups ----
     for (int o = tid; o < kRowsX * kTileCols; o += nthreads) {
-        const int m = m0 + o / kTileCols, col = tile * kTileCols + (o % kTileCols);
+        const int r = o / kTileCols, q = o % kTileCols, m = m0 + r, col = tile * kTileCols + q;
         if (m >= a.M || col >= a.N) continue;
-        const long long fx = (long long)acc[o];
-        const bool nan = fx >= (kNaNMark >> 1);  // sixteen waves' clamped sums stay below 2^53
+        const double t = acc[64 * (4 * (q & 3) + (r & 3)) + 16 * (r >> 2) + (q >> 2)];
+        const bool nan = t != t;
+        const long long fx = nan ? 0ll : (long long)t;
         const size_t out = (size_t)m * a.N + col;
         if (finish == kFinishAccumulator) {
-            add_slice<Act>(sync + out, to_fixed(nan ? 0ll : fx), nan, a.split, a.Y + out);
+            add_slice<Act>(sync + out, to_fixed(fx), nan, a.split, a.Y + out);
         } else {
             constexpr long long lim = 1ll << 49;
             const float v = nan ? __builtin_nanf("") : (float)((double)(fx < -lim ? -lim : (fx > lim ? lim : fx)) * (1.0 / 16777216.0));
