@@ -26,16 +26,20 @@ constexpr uint32_t kOutOfRange = 0x80000000u;  // per-lane buffer offset beyond 
 constexpr uint32_t kRawBuffer = 0x00020000u;   // buffer descriptor word 3: raw 32-bit data, no swizzle
 
 // Nibble masks, kept opaque so they stay in scalar registers and each mask is one v_and_b32
-// (as literals they would be re-materialised per use).
+// (as literals they would be re-materialised per use).  BF16's exponent sits in a vector register: v_and_or_b32 reads one
+// scalar only, and with two scalars the unpack is four vector instructions per word longer.
 struct Masks {
     uint32_t lo, hi;  // 0x000F000F, 0x00F000F0
+    uint32_t base;    // 0x43004300: a pair of bfloat16 128.0
 };
 __device__ __forceinline__ Masks make_masks()
 {
     Masks m;
     m.lo = 0x000F000Fu;
     m.hi = 0x00F000F0u;
+    m.base = 0x43004300u;
     asm volatile("" : "+s"(m.lo), "+s"(m.hi));
+    asm("" : "+v"(m.base));  // (gone where nothing reads it)
     return m;
 }
 
@@ -86,13 +90,32 @@ __device__ __forceinline__ float apply_scale_zero(float tot, float s, float z, f
     return __builtin_fmaf(s * 16777216.0f, P, __builtin_fmaf(-s * z, xsum, tot));
 }
 
+// The ticket kernels' exact sums inside a wave.  With P as the MFMA gives it and xs = sum_k x_k / kCodeScale, a unit of k contributes
+//     sum_k x_k s (q_k - z) = (kCodeScale s) (P - (z + kCodeOffset) xs),
+// in units of 2^-24, rounded to a whole number, to a sum that must not depend on the order of the units.  The sum is a double that
+// starts at 1.5 2^52, where a unit in the last place is 1: one FMA multiplies, rounds and adds.  Rounding to the nearest whole number
+// would depend on the sum only where the contribution is a whole number and a half, to which the scale's factor 1 + 2^-40 does
+// not let it come: parenthesis (24 bits) times s (11 bits) is an odd number m times 2^e, the contribution m (2^40 + 1) 2^(e-40), its
+// last bit 1/2 only if e = 39, beyond 2^78.  (Whole numbers up to 2^39, i.e. values below 2^15, stay what they are; the product
+// s (1 + 2^-40) has at most 52 bits and is exact.)  Sums are whole while they stay within 2^51, values of 2^27, four times the clamp.
+// Three vector instructions per output; product, FMA, rounding, conversion and addition as steps of their own were five.
+constexpr double kTotStart = 6755399441055744.0;       // 1.5 2^52
+constexpr double kUntie = 1.0 + 1.0 / 1099511627776.0;  // 1 + 2^-40
+template <typename Act>
+__device__ __forceinline__ double unit_scale(float s) { return (double)s * ((double)Act::kCodeScale * 16777216.0 * kUntie); }
+__device__ __forceinline__ void add_unit(double &tot, double scale, float P, float z, float xs)
+{
+    tot = __builtin_fma((double)__builtin_fmaf(-z, xs, P), scale, tot);
+}
+
 // The ticket kernels' sums inside a workgroup (w4a16_stripe_dyn.hip, w4a16_tile_dyn.hip).  A wave's sum of one output, in units of
 // 2^-24, is an integer-valued double; it is clamped to +-2^49 (2^25 in units of 1; a NaN stays one), so that up to sixteen waves' sums add up
 // exactly below 2^53, in any order, in a double in LDS.  The atomic add of doubles keeps the conversion to 64-bit integers,
 // some twenty instructions, for after the barrier: once per output instead of once per output and wave.
 constexpr double kSumMax = 562949953421312.0;  // 2^49
-__device__ __forceinline__ void add_wave_sum(double *acc, double t)
+__device__ __forceinline__ void add_wave_sum(double *acc, double tot)
 {
+    double t = tot - kTotStart;
     t = t > kSumMax ? kSumMax : (t < -kSumMax ? -kSumMax : t);
     if (t != 0.0) __builtin_amdgcn_ds_atomic_fadd_f64((__attribute__((address_space(3))) double *)acc, t);  // (a NaN is not 0)
 }
@@ -160,9 +183,8 @@ struct ActBF16 {
     // k order 0,4 | 1,5 | 2,6 | 3,7 as in the FP16 form; every code moved to bits 0-3 of its half
     static __device__ __forceinline__ operand_t unpack(uint32_t w, const Masks &k)
     {
-        const uint32_t base = 0x43004300u;
         B8 r;
-        r.u = (uint4_t){(w & k.lo) | base, ((w >> 4) & k.lo) | base, ((w >> 8) & k.lo) | base, ((w >> 12) & k.lo) | base};
+        r.u = (uint4_t){(w & k.lo) | k.base, ((w >> 4) & k.lo) | k.base, ((w >> 8) & k.lo) | k.base, ((w >> 12) & k.lo) | k.base};
         return r.b;
     }
     static __device__ __forceinline__ uint4_t stage_x(uint4_t d)

@@ -121,9 +121,10 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) tot[c][i] = 0.0;
+        for (int i = 0; i < 4; ++i) tot[c][i] = kTotStart;
     const Masks masks = make_masks();
-    // sum_k x_k over a unit comes from the MFMA too: X against ones (FP16: 16 where the staged x was divided by 16)
+    // sum_k x_k over a unit comes from the MFMA too: X against ones (FP16: 16 where the staged x was divided by 16).  (Against
+    // ones times 2^-24, subnormals, the sum comes out with fewer bits: an error of 2.3e-4 instead of 2.1e-4.)
     const typename Act::operand_t ones = Act::ones();
     const float4_t zero4 = {0.f, 0.f, 0.f, 0.f};
 
@@ -158,11 +159,10 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
         const uint32_t zw = r.zw >> zsh;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const float sp = s[c] * (Act::kCodeScale * kFixScale);  // FP16: 2^48 s (P carries 2^-24, the sums are in units of 2^-24)
-            const float sz24 = -s[c] * ((float)((zw >> (4 * c)) & 15u) + Act::kCodeOffset) * kFixScale;  // -2^24 s z
+            const double scale = unit_scale<Act>(s[c]);
+            const float z = ((float)((zw >> (4 * c)) & 15u) + Act::kCodeOffset) * (1.0f / Act::kCodeScale);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)  // exact from here on: integers, the sum below 2^53 (an infinity or a NaN stays one)
-                tot[c][i] += (double)__builtin_rintf(__builtin_fmaf(sp, part[c][i], sz24 * xsum[i]));
+            for (int i = 0; i < 4; ++i) add_unit(tot[c][i], scale, part[c][i], z, xsum[i]);
         }
     };
 
