@@ -29,17 +29,41 @@ constexpr int kBlockRows = 4;                    // packed rows per block: one M
 // (measured: SQ_LDS_BANK_CONFLICT 2.4 times lower than with 17).
 constexpr int kRowStride = kRowsX + 2;
 
-// LDS: ticket counter (16 B), the workgroup's sums [4 columns][4 rows][64 lanes] (doubles), then per wave and ring place one unit of X.
+// LDS: ticket counter (16 B), the workgroup's sums [column slots][rows][64 lanes] (doubles, Share below), then per wave and ring place one unit of X.
 constexpr uint32_t kLdsAcc = 16;
-constexpr uint32_t kLdsX = kLdsAcc + kRowsX * kTileCols * 8;
 template <int UB>
 constexpr uint32_t unit_x_bytes() { return UB * kBlockRows * kRowStride * 16; }
 
+// Which outputs a lane keeps, by MR = rows of X the kernel is compiled for (M rounded up to 1, 2, 4, 8, 16).  The MFMA's result rows
+// 4 g + i of lane group g are rows of X again and again where there are fewer than 16 (the A operand repeats them, free), so that
+// group g has every output of its column slots and takes on some: all four column slots and rows 4 g .. 4 g + 3 (MR = 16), two slots
+// and rows 4 (g mod 2) .. + 3 (8), one slot and rows 0 .. MR - 1 (1, 2, 4).  The unit's last step, which without its memory accesses
+// took a third of the kernel's time, is then done for outputs that exist only: 16, 8, 4, 2 or 1 per lane.
+template <int MR>
+struct Share {
+    static constexpr int kCols = MR == 16 ? 4 : (MR == 8 ? 2 : 1);  // column slots per lane
+    static constexpr int kRows = MR < 4 ? MR : 4;                   // rows per lane
+    static constexpr int kSums = 64 * kCols * kRows;
+    static constexpr int kRowsStaged = MR < 4 ? 4 : MR;             // rows of X in LDS: what the A operand repeats
+    static constexpr int kBlocksPerLoad = 16 / kRowsStaged;         // a wave-wide load of X: 16 rows of one block, 8 of two, 4 of four
+    // where the sum of (row r, column q of the tile) lies in LDS: neighbouring lanes on neighbouring banks
+    static __device__ __forceinline__ int place(int r, int q)
+    {
+        const int j = q >> 2;
+        if constexpr (MR == 16) return 64 * (4 * (q & 3) + (r & 3)) + 16 * (r >> 2) + j;
+        if constexpr (MR == 8) return 64 * (4 * (q & 1) + (r & 3)) + 16 * ((r >> 2) + (q & 2)) + j;
+        return 64 * r + 16 * (q & 3) + j;
+    }
+};
+
 // BOUND: the most threads of a workgroup (the registers a wave may use follow from it: 128 at 1024, 256 at 512).
-template <typename Act, int UB, int D, int BOUND>
+constexpr uint32_t lds_x(int mr) { return kLdsAcc + (uint32_t)(mr * kTileCols * 8); }  // the sums: one per output, whatever the share
+
+template <typename Act, int UB, int D, int BOUND, int MR>
 __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const int finish, unsigned long long *__restrict__ sync)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    typedef Share<MR> Sh;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -75,13 +99,15 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
     const uint32_t vw = ok ? (uint32_t)(g4 * a.N + col0) * 4u : kOutOfRange;
     const uint32_t vs = ok ? (uint32_t)col0 * 2u : kOutOfRange;
     const uint32_t vz = ok ? (uint32_t)(col0 >> 3) * 4u : kOutOfRange;
-    // X: four neighbouring lanes fetch the 64 bytes one block takes of one row of X; load q of a lane is block q
-    const uint32_t xm = (uint32_t)m0 + (uint32_t)(lane >> 2);
-    const uint32_t vx = xm < (uint32_t)a.M ? (xm * (uint32_t)a.K + ((uint32_t)row_base + (uint32_t)(lane & 3)) * 8u) * 2u : kOutOfRange;
-    const uint32_t xl = (uint32_t)(((lane & 3) * kRowStride + (lane >> 2)) * 16);  // where it goes in the unit's LDS
+    // X: four neighbouring lanes fetch the 64 bytes one block takes of one row of X; load l of a lane is block kBlocksPerLoad l + xb
+    constexpr int kLoadsX = (UB + Sh::kBlocksPerLoad - 1) / Sh::kBlocksPerLoad;
+    const uint32_t xr = (uint32_t)(lane >> 2) % Sh::kRowsStaged, xb = (uint32_t)(lane >> 2) / Sh::kRowsStaged, xm = (uint32_t)m0 + xr;
+    const bool has_x = Sh::kBlocksPerLoad <= UB || xb < UB;
+    const uint32_t vx = xm < (uint32_t)a.M && has_x ? (xm * (uint32_t)a.K + ((uint32_t)row_base + kBlockRows * xb + (uint32_t)(lane & 3)) * 8u) * 2u : kOutOfRange;
+    const uint32_t xl = (xb * (kBlockRows * kRowStride) + (uint32_t)(lane & 3) * kRowStride + xr) * 16u;  // where it goes in the unit's LDS
 
     struct Unit {
-        uint4_t w[UB], x[UB];
+        uint4_t w[UB], x[kLoadsX];
         uint2_t sc;
         uint32_t zw;
     };
@@ -92,8 +118,8 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
         const uint32_t uu = valid ? (uint32_t)u : 0u;
         const uint32_t g = uu / (uint32_t)upg, b0 = uu * UB;  // group and first block (of the slice)
 #pragma unroll
-        for (int q = 0; q < UB; ++q)  // X ahead of the weights: loads return in order, and these mostly come from cache
-            r.x[q] = __builtin_amdgcn_raw_buffer_load_b128(rx, valid ? vx : kOutOfRange, (b0 + q) * (kBlockRows * 16u), 0);
+        for (int l = 0; l < kLoadsX; ++l)  // X ahead of the weights: loads return in order, and these mostly come from cache
+            r.x[l] = __builtin_amdgcn_raw_buffer_load_b128(rx, valid ? vx : kOutOfRange, (b0 + l * Sh::kBlocksPerLoad) * (kBlockRows * 16u), 0);
         r.sc = __builtin_amdgcn_raw_buffer_load_b64(rs, valid ? vs : kOutOfRange, g * row_s, 0);
         r.zw = __builtin_amdgcn_raw_buffer_load_b32(rz, valid ? vz : kOutOfRange, g * row_z, 0) | zfill;
 #pragma unroll
@@ -110,18 +136,20 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
     uint32_t *const tickets = reinterpret_cast<uint32_t *>(smem);
     double *const acc = reinterpret_cast<double *>(smem + kLdsAcc);
     if (tid == 0) tickets[0] = (uint32_t)(waves * D);
-    for (int e = tid; e < kRowsX * kTileCols; e += nthreads) acc[e] = 0.0;
+    for (int e = tid; e < Sh::kSums; e += nthreads) acc[e] = 0.0;
     __syncthreads();
 
-    unsigned char *const myx = smem + kLdsX + (uint32_t)wave * unit_x_bytes<UB>();  // one unit of X, this wave's own
-    const uint32_t xa = (uint32_t)((g4 * kRowStride + j) * 16);                      // this lane's A entry of block 0
-    const uint32_t zsh = (uint32_t)(col0 & 4) * 4u;                                   // this lane's four nibbles in its zero-point word
+    unsigned char *const myx = smem + lds_x(MR) + (uint32_t)wave * unit_x_bytes<UB>();  // one unit of X, this wave's own
+    const uint32_t xa = (uint32_t)((g4 * kRowStride + (MR == 16 ? j : j & (MR == 8 ? 7 : 3))) * 16);  // this lane's A entry of block 0
+    const int slot0 = MR == 16 ? 0 : (MR == 8 ? g4 & 2 : g4);                          // the first of this lane's column slots
+    const int row0 = MR == 16 ? 4 * g4 : (MR == 8 ? 4 * (g4 & 1) : 0);                 // the first of its rows
+    const uint32_t zsh = (uint32_t)((col0 & 4) + slot0) * 4u;                         // its nibbles in its zero-point word
 
-    double tot[4][4];
+    double tot[Sh::kCols][Sh::kRows];
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+    for (int c = 0; c < Sh::kCols; ++c)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) tot[c][i] = kTotStart;
+        for (int i = 0; i < Sh::kRows; ++i) tot[c][i] = kTotStart;
     const Masks masks = make_masks();
     // sum_k x_k over a unit comes from the MFMA too: X against ones (FP16: 16 where the staged x was divided by 16).  (Against
     // ones times 2^-24, subnormals, the sum comes out with fewer bits: an error of 2.3e-4 instead of 2.1e-4.)
@@ -140,8 +168,8 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
         // keep the compiler from moving them across the staging
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
-        for (int q = 0; q < UB; ++q)
-            *reinterpret_cast<uint4_t *>(myx + (uint32_t)q * (kBlockRows * kRowStride * 16) + xl) = Act::stage_x(r.x[q]);
+        for (int l = 0; l < kLoadsX; ++l)
+            if (has_x) *reinterpret_cast<uint4_t *>(myx + (uint32_t)(l * Sh::kBlocksPerLoad) * (kBlockRows * kRowStride * 16) + xl) = Act::stage_x(r.x[l]);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         float4_t part[4], xsum;
 #pragma unroll
@@ -152,17 +180,24 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
             xsum = Act::mfma(x, ones, q == 0 ? zero4 : xsum);
         }
         // the unit is done: scale and zero point (Eq. 2), then the exact sums
-        H2 s01, s23;
-        s01.u = r.sc[0];
-        s23.u = r.sc[1];
-        const float s[4] = {(float)s01.h[0], (float)s01.h[1], (float)s23.h[0], (float)s23.h[1]};
+        const unsigned long long scales = (((unsigned long long)r.sc[1] << 32) | r.sc[0]) >> (16 * slot0);
         const uint32_t zw = r.zw >> zsh;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const double scale = unit_scale<Act>(s[c]);
+        for (int c = 0; c < Sh::kCols; ++c) {
+            H2 s;
+            s.u = (uint32_t)(scales >> (16 * c)) & 0xFFFFu;
+            const double scale = unit_scale<Act>((float)s.h[0]);
             const float z = ((float)((zw >> (4 * c)) & 15u) + Act::kCodeOffset) * (1.0f / Act::kCodeScale);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) add_unit(tot[c][i], scale, part[c][i], z, xsum[i]);
+            for (int i = 0; i < Sh::kRows; ++i) {
+                float P = part[c][i];
+                if constexpr (MR == 8) P = g4 & 2 ? part[c + 2][i] : P;
+                if constexpr (MR <= 4) {
+                    const float even = g4 & 2 ? part[2][i] : P, odd = g4 & 2 ? part[3][i] : part[1][i];
+                    P = g4 & 1 ? odd : even;
+                }
+                add_unit(tot[c][i], scale, P, z, xsum[i]);
+            }
         }
     };
 
@@ -181,22 +216,21 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
         if (!any) break;
     }
 
-    // ---- Phase 3 inside the workgroup: exact sums in LDS (lane (g, j) holds rows 4 g + i, columns 4 j + c), the sum of (c, i, lane) at
-    // 64 (4 c + i) + lane: neighbouring lanes on neighbouring banks.  (As [16][64] the sixteen lanes of a group were 32 bytes apart and
-    // the four groups in the same banks; with the conversions to integers per wave 1.7 us from a wave's last unit to the barrier at
-    // M = 16, K = 14336, N = 4096, 1.2 now, and 1.0 and 0.3 at M = 1, K = 4096, N = 1024: 11.9 -> 11.5 and 5.0 -> 4.35 us per multiply.)
+    // ---- Phase 3 inside the workgroup: exact sums in LDS, neighbouring lanes on neighbouring banks.  (As [16][64] the sixteen lanes of a
+    // group were 32 bytes apart and the four groups in the same banks; with the conversions to integers per wave 1.7 us from a wave's
+    // last unit to the barrier at M = 16, K = 14336, N = 4096, 1.2 now, and 1.0 and 0.3 at M = 1, K = 4096, N = 1024.)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (m0 + 4 * g4 + i >= a.M) continue;
+    for (int i = 0; i < Sh::kRows; ++i) {
+        if (m0 + row0 + i >= a.M) continue;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) add_wave_sum(acc + 64 * (4 * c + i) + lane, tot[c][i]);
+        for (int c = 0; c < Sh::kCols; ++c) add_wave_sum(acc + 64 * (Sh::kRows * c + i) + lane, tot[c][i]);
     }
     __syncthreads();
     // ---- and across workgroups ----
-    for (int o = tid; o < kRowsX * kTileCols; o += nthreads) {
+    for (int o = tid; o < MR * kTileCols; o += nthreads) {
         const int r = o / kTileCols, q = o % kTileCols, m = m0 + r, col = tile * kTileCols + q;
         if (m >= a.M || col >= a.N) continue;
-        const double t = acc[64 * (4 * (q & 3) + (r & 3)) + 16 * (r >> 2) + (q >> 2)];
+        const double t = acc[Sh::place(r, q)];
         const bool nan = t != t;
         const long long fx = nan ? 0ll : (long long)t;
         const size_t out = (size_t)m * a.N + col;
@@ -213,29 +247,33 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
     }
 }
 
-template <typename Act, int UB, int D, int BOUND>
-hipError_t launch_udb(const GemmArgs &a, int finish, unsigned long long *sync, int waves, hipStream_t stream)
+template <typename Act, int UB, int D, int BOUND, int MR>
+hipError_t launch_mr(const GemmArgs &a, int finish, unsigned long long *sync, int waves, hipStream_t stream)
 {
-    const size_t lds = kLdsX + (size_t)waves * unit_x_bytes<UB>();
+    const size_t lds = lds_x(MR) + (size_t)waves * unit_x_bytes<UB>();
     const int ntiles = (a.N + kTileCols - 1) / kTileCols, row_blocks = (a.M + kRowsX - 1) / kRowsX;
-    if (ntiles > 65535 || row_blocks > 65535) return hipErrorInvalidValue;
+    if (ntiles > 65535 || row_blocks > 65535 || (MR < 16 && a.M > MR)) return hipErrorInvalidValue;
     if (lds > 48 * 1024) {  // beyond the default dynamic-LDS allowance
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&tile_dyn_kernel<Act, UB, D, BOUND>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&tile_dyn_kernel<Act, UB, D, BOUND, MR>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((tile_dyn_kernel<Act, UB, D, BOUND>), dim3(a.split, ntiles, row_blocks), dim3(waves * 64), lds, stream, a, finish, sync);
+    hipLaunchKernelGGL((tile_dyn_kernel<Act, UB, D, BOUND, MR>), dim3(a.split, ntiles, row_blocks), dim3(waves * 64), lds, stream, a, finish, sync);
     return hipGetLastError();
 }
 
 template <typename Act, int UB, int D>
 hipError_t launch_ud(const GemmArgs &a, int finish, unsigned long long *sync, int waves, hipStream_t stream)
 {
-    // two units in flight need more than 128 registers: up to eight waves per workgroup only
+    // two units in flight need more than 128 registers: up to eight waves per workgroup only (for sweeps: 16 rows only)
     if constexpr (D == 2) {
         if (waves > 8) return hipErrorInvalidValue;
-        return launch_udb<Act, UB, D, 512>(a, finish, sync, waves, stream);
+        return launch_mr<Act, UB, D, 512, 16>(a, finish, sync, waves, stream);
     } else {
-        return launch_udb<Act, UB, D, 1024>(a, finish, sync, waves, stream);
+        if (a.M == 1) return launch_mr<Act, UB, D, 1024, 1>(a, finish, sync, waves, stream);
+        if (a.M == 2) return launch_mr<Act, UB, D, 1024, 2>(a, finish, sync, waves, stream);
+        if (a.M <= 4) return launch_mr<Act, UB, D, 1024, 4>(a, finish, sync, waves, stream);
+        if (a.M <= 8) return launch_mr<Act, UB, D, 1024, 8>(a, finish, sync, waves, stream);
+        return launch_mr<Act, UB, D, 1024, 16>(a, finish, sync, waves, stream);
     }
 }
 
