@@ -63,7 +63,7 @@ struct Tuning {
     int tile_dyn = 0;       // 16 rows of X per workgroup: 1 = units always handed out by ticket, 2 = never (equal runs per wave)
     int tile_depth = 0;     // units in flight per wave of the ticket form (1, 2)
     int tile_waves = 0;     // waves per TILE workgroup (4..8)
-    int tile_unit = 0;      // 16 rows of X per workgroup, by ticket: blocks of 32 k per unit (1, 2; default: up to 4 within a group)
+    int tile_unit = 0;      // 16 rows of X per workgroup, by ticket: blocks of 32 k per unit (1, 2, 4; 4: of several groups where these are short)
     int tile_wide = 0;      // TILE at 32 or 64 rows of X per workgroup: 2 = the eight-wave form instead of the four-wave one
     int panel = 0;          // M > 16: 1 = always the four-wave 256-column form, 2 = never
     int panel_split = 0;    // its split of the tiles past the last whole round of compute units (1 = none)
@@ -148,13 +148,11 @@ bool fits_32bit_offsets(int M, int N, int K, int group, int gps)
 // Algorithm 1 takes the split factor S and the block sizes as inputs.  Here the
 // scheduler (kernel = AUTO, split = 0) chooses them from the shape alone:
 //
-// STRIPE (M = 1 from about 4 MB of packed weights on, M = 2 from about 20 MB, M <= 4 from about 32 MB): 256-column stripes
-//   x S slices of K with S = compute units / stripes, rounded down: one workgroup per compute unit whose
-//   waves share the slice.
+// STRIPE (M = 1 from 4 MB of packed weights on, M = 2 ... 4 on large matrices): 256-column stripes x S slices of K with S = compute
+//   units / stripes, rounded down: one workgroup per compute unit whose waves share the slice.
 // TILE (everything else): 64-column tiles x 16, 32 or 64 rows of X per workgroup (as many rows as still
-//   leave a workgroup per compute unit at S = 1), eight or four waves own contiguous runs of the slice's K;
-//   S = compute units / workgroups, rounded down (a workgroup too many would run as a second round).
-//   Its time does not depend on M up to 16; STRIPE's grows with the S M N atomic adds of its finish.
+//   leave a workgroup per compute unit at S = 1), eight or four waves; up to 16 rows they share the slice by ticket, in a form for
+//   1, 2, 4, 8 or 16 rows; S = compute units / workgroups, rounded down (a workgroup too many would run as a second round).
 //
 // PANEL (a form of TILE, M > 16): tiles of 128 rows x 256 columns for prompts, and for batches whose 64-column tiles would
 //   run in several rounds or over a long K (use_panel).
@@ -216,6 +214,22 @@ bool tile_four(int rows_x, int group, bool bf16)
 // groups of 128 is as fast or faster: 64 rows, BF16, K = 1024: M = 48, N = 16384 / 48640: 8.6 / 22.6 us against 8.9 / 23.2; M = 128,
 // N = 8192: 8.7 against 8.8; K = 1536, M = 48, N = 16384: 11.0 against 10.4.  Groups of other lengths have a slower eight-wave kernel.
 bool short_slices(int group, bool bf16, int gps) { return bf16 && group == 128 && gps <= 8; }
+
+// Blocks of 32 k per unit of the ticket form.  With groups of 64 and 32 a unit may be one group (2 or 1 KiB of weights in flight per wave)
+// or several: four blocks (4 KiB, but more registers: a second workgroup on the compute unit may not fit).  Several groups where the
+// slice has a unit of four blocks for every wave, and: groups of 32, up to 4 rows, or no more workgroups than compute units (us, one group / several,
+// K = 28672, N = 8192: M = 1 39.7 / 25.6, M = 16 45.1 / 37.8; K = 4096, N = 22016, M = 4 16.6 / 16.5, M = 8 18.1 / 19.4, M = 16 20.2 / 23.5); groups of 64, no more
+// workgroups than compute units, and up to 8 rows (K = 28672, N = 8192, M = 1 26.4 / 23.7; K = 4096, N = 22016 12.2 / 13.2) or slices from 5120 k on
+// (M = 16: K = 28672, N = 8192 32.1 / 29.6, K = 5120, N = 13824 12.7 / 12.6, K = 4096, N = 14336 11.1 / 11.2, K = 11008, N = 4096, S = 4 10.3 / 10.6).
+int ticket_unit_blocks(int M, int group, int gps, int workgroups, int cus)
+{
+    if (tuning().tile_unit) return tuning().tile_unit;
+    if (group > 64) return 4;
+    const bool one_round = workgroups <= cus;
+    const int k = gps * group;
+    const bool several = k >= 1024 && (group == 32 ? M <= 4 || one_round : one_round && (M <= 8 || k >= 5120));
+    return several ? 4 : group / 32;
+}
 
 // LDS a STRIPE workgroup needs for a slice of gps groups, and the most it may use.
 size_t stripe_lds(int M, int group, int gps, int waves)
@@ -391,11 +405,8 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
     const int G = K / group;
     const bool automatic = kernel == W4A16_KERNEL_AUTO && split == 0;
     if (kernel == W4A16_KERNEL_AUTO) {
-        // STRIPE streams large weight matrices faster than TILE, but its 256-column stripes need four
-        // times the slices, hence four times the atomic adds (S M N), and its work per unit of K grows with M.
-        // Measured on the five configurations, the six (N, K) pairs of the paper's Fig. 2 and three K << N shapes
-        // (2 MB to 117 MB of packed weights): STRIPE wins at M = 1 from about 4 MB on, at M = 2 from about
-        // 20 MB on, at M = 3, 4 from about 32 MB on; TILE everywhere else.
+        // STRIPE: M = 1 from 4 MB of packed weights on, M = 2 from 20 MB, M = 3 and 4 from 32 MB.  Below
+        // these sizes it is TILE, many of whose plans there need no workspace: they are not to change for ones that share an accumulator.
         const double packed = 0.5 * (double)K * (double)N;
         const bool stripe = (M == 1 && packed >= 4e6) || (M == 2 && packed >= 20e6) || (M <= 4 && packed >= 32e6);
         kernel = stripe ? W4A16_KERNEL_STRIPE : W4A16_KERNEL_TILE;
@@ -722,7 +733,8 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
     } else if (by_panel) {
         e = launch_panel(a, panel, st);
     } else if (plan.kernel == W4A16_KERNEL_TILE && tile_by_ticket(M, plan.tile_m)) {
-        e = launch_tile_dyn(a, finish, b.sync, plan.waves_k, tuning().tile_depth == 2 && !bf16 && plan.waves_k <= 8 ? 2 : 1, tuning().tile_unit, st);
+        e = launch_tile_dyn(a, finish, b.sync, plan.waves_k, tuning().tile_depth == 2 && !bf16 && plan.waves_k <= 8 ? 2 : 1,
+                            ticket_unit_blocks(M, group, plan.groups_per_split, plan.workgroups, compute_units(dev)), st);
     } else if (plan.kernel == W4A16_KERNEL_TILE && tile_four(plan.tile_m, group, bf16) && !short_slices(group, bf16, plan.groups_per_split)) {
         if (plan.tile_m == 64 && (bf16 || group != 128)) e = launch_tile_tall(a, finish, b.sync, st);
         else e = launch_tile_wide(a, finish, b.sync, plan.tile_m, st);

@@ -83,7 +83,7 @@ hipError_t launch_tile_tall(const GemmArgs &a, int finish, unsigned long long *s
 // TILE family at 32 or 64 rows of X per workgroup, FP16, group = 128: four waves per workgroup (w4a16_tile_wide.hip).
 hipError_t launch_tile_wide(const GemmArgs &a, int finish, unsigned long long *sync, int rows_x, hipStream_t stream);
 // TILE family, 16 rows of X per workgroup, the slice handed out to the waves by ticket (w4a16_tile_dyn.hip); `depth` (1, 2)
-// units in flight per wave.
+// units in flight per wave, of up to `unit_blocks` (1, 2, 4) blocks of 32 k; 4: also of two or four groups of 64 or 32.
 hipError_t launch_tile_dyn(const GemmArgs &a, int finish, unsigned long long *sync, int waves, int depth, int unit_blocks, hipStream_t stream);
 // Clears n words of a fixed-point accumulator.
 hipError_t launch_accumulator_clear(unsigned long long *acc, size_t n, hipStream_t stream);

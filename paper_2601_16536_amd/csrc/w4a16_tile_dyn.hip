@@ -17,6 +17,7 @@
 #include "w4a16_device.h"
 #include "w4a16_finish.h"
 #include "w4a16_internal.h"
+#include <type_traits>
 
 namespace w4a16 {
 namespace {
@@ -56,10 +57,11 @@ struct Share {
     }
 };
 
+// UB: blocks of 32 k per unit; BPG: those of one group in it (UB unless a unit holds several groups).
 // BOUND: the most threads of a workgroup (the registers a wave may use follow from it: 128 at 1024, 256 at 512).
 constexpr uint32_t lds_x(int mr) { return kLdsAcc + (uint32_t)(mr * kTileCols * 8); }  // the sums: one per output, whatever the share
 
-template <typename Act, int UB, int D, int BOUND, int MR>
+template <typename Act, int UB, int BPG, int D, int BOUND, int MR>
 __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const int finish, unsigned long long *__restrict__ sync)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -81,9 +83,9 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
     int gend = gbeg + a.groups_per_split;
     if (gend > a.groups) gend = a.groups;
     const int groups = gend - gbeg;
-    const int bpg = a.group >> 5;                    // blocks per group
-    const int upg = bpg / UB;                        // units per group
-    const int units = groups * upg;
+    constexpr int NG = UB / BPG;                     // groups of a unit
+    const int upg = NG == 1 ? (a.group >> 5) / UB : 1;            // units per group (of a unit of one group)
+    const int units = NG == 1 ? groups * upg : (groups + NG - 1) / NG;
     const int row_base = gbeg * (a.group >> 3);      // first packed row of the slice
 
     const uint32_t row_w = (uint32_t)a.N * 4u, row_s = (uint32_t)a.N * 2u, row_z = (uint32_t)(a.N >> 3) * 4u;
@@ -108,20 +110,27 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
 
     struct Unit {
         uint4_t w[UB], x[kLoadsX];
-        uint2_t sc;
-        uint32_t zw;
+        uint2_t sc[NG];
+        uint32_t zw[NG];
     };
     Unit ring[D];
     int uidx[D];  // unit in ring place p, -1 = none
     auto load_unit = [&](Unit &r, int u) {
         const bool valid = u >= 0;
         const uint32_t uu = valid ? (uint32_t)u : 0u;
-        const uint32_t g = uu / (uint32_t)upg, b0 = uu * UB;  // group and first block (of the slice)
+        const uint32_t g = NG == 1 ? uu / (uint32_t)upg : uu * NG, b0 = uu * UB;  // first group and first block (of the slice)
 #pragma unroll
-        for (int l = 0; l < kLoadsX; ++l)  // X ahead of the weights: loads return in order, and these mostly come from cache
-            r.x[l] = __builtin_amdgcn_raw_buffer_load_b128(rx, valid ? vx : kOutOfRange, (b0 + l * Sh::kBlocksPerLoad) * (kBlockRows * 16u), 0);
-        r.sc = __builtin_amdgcn_raw_buffer_load_b64(rs, valid ? vs : kOutOfRange, g * row_s, 0);
-        r.zw = __builtin_amdgcn_raw_buffer_load_b32(rz, valid ? vz : kOutOfRange, g * row_z, 0) | zfill;
+        for (int l = 0; l < kLoadsX; ++l) {  // X ahead of the weights: loads return in order, and these mostly come from cache
+            // of groups past the slice's last one nothing is read: their weights and scales are out of range, and so is their X (zeros
+            // times whatever follows it would not do: that may be an infinity)
+            const bool in = valid && (NG == 1 || b0 + l * Sh::kBlocksPerLoad + xb < (uint32_t)(groups * BPG));
+            r.x[l] = __builtin_amdgcn_raw_buffer_load_b128(rx, in ? vx : kOutOfRange, (b0 + l * Sh::kBlocksPerLoad) * (kBlockRows * 16u), 0);
+        }
+#pragma unroll
+        for (int h = 0; h < NG; ++h) {
+            r.sc[h] = __builtin_amdgcn_raw_buffer_load_b64(rs, valid ? vs : kOutOfRange, (g + h) * row_s, 0);
+            r.zw[h] = __builtin_amdgcn_raw_buffer_load_b32(rz, valid ? vz : kOutOfRange, (g + h) * row_z, 0) | zfill;
+        }
 #pragma unroll
         for (int q = 0; q < UB; ++q)  // read once from DRAM: nontemporal
             r.w[q] = __builtin_amdgcn_raw_buffer_load_b128(rw, valid ? vw : kOutOfRange, (b0 + q) * (kBlockRows * row_w), 2);
@@ -171,33 +180,38 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
         for (int l = 0; l < kLoadsX; ++l)
             if (has_x) *reinterpret_cast<uint4_t *>(myx + (uint32_t)(l * Sh::kBlocksPerLoad) * (kBlockRows * kRowStride * 16) + xl) = Act::stage_x(r.x[l]);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        float4_t part[4], xsum;
 #pragma unroll
-        for (int q = 0; q < UB; ++q) {
-            const typename Act::operand_t x = Act::x_operand(*reinterpret_cast<const uint4_t *>(myx + (uint32_t)q * (kBlockRows * kRowStride * 16) + xa));
+        for (int h = 0; h < NG; ++h) {
+            float4_t part[4], xsum;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) part[c] = Act::mfma(x, Act::unpack(r.w[q][c], masks), q == 0 ? zero4 : part[c]);
-            xsum = Act::mfma(x, ones, q == 0 ? zero4 : xsum);
-        }
-        // the unit is done: scale and zero point (Eq. 2), then the exact sums
-        const unsigned long long scales = (((unsigned long long)r.sc[1] << 32) | r.sc[0]) >> (16 * slot0);
-        const uint32_t zw = r.zw >> zsh;
+            for (int q = 0; q < BPG; ++q) {
+                const int b = h * BPG + q;
+                const typename Act::operand_t x = Act::x_operand(*reinterpret_cast<const uint4_t *>(myx + (uint32_t)b * (kBlockRows * kRowStride * 16) + xa));
 #pragma unroll
-        for (int c = 0; c < Sh::kCols; ++c) {
-            H2 s;
-            s.u = (uint32_t)(scales >> (16 * c)) & 0xFFFFu;
-            const double scale = unit_scale<Act>((float)s.h[0]);
-            const float z = ((float)((zw >> (4 * c)) & 15u) + Act::kCodeOffset) * (1.0f / Act::kCodeScale);
-#pragma unroll
-            for (int i = 0; i < Sh::kRows; ++i) {
-                float P = part[c][i];
-                if constexpr (MR == 8) P = g4 & 2 ? part[c + 2][i] : P;
-                if constexpr (MR <= 4) {
-                    const float even = g4 & 2 ? part[2][i] : P, odd = g4 & 2 ? part[3][i] : part[1][i];
-                    P = g4 & 1 ? odd : even;
-                }
-                add_unit(tot[c][i], scale, P, z, xsum[i]);
+                for (int c = 0; c < 4; ++c) part[c] = Act::mfma(x, Act::unpack(r.w[b][c], masks), q == 0 ? zero4 : part[c]);
+                xsum = Act::mfma(x, ones, q == 0 ? zero4 : xsum);
             }
+            // the group's share is done: scale and zero point (Eq. 2), then the exact sums
+            const unsigned long long scales = (((unsigned long long)r.sc[h][1] << 32) | r.sc[h][0]) >> (16 * slot0);
+            const uint32_t zw = r.zw[h] >> zsh;
+#pragma unroll
+            for (int c = 0; c < Sh::kCols; ++c) {
+                H2 s;
+                s.u = (uint32_t)(scales >> (16 * c)) & 0xFFFFu;
+                const double scale = unit_scale<Act>((float)s.h[0]);
+                const float z = ((float)((zw >> (4 * c)) & 15u) + Act::kCodeOffset) * (1.0f / Act::kCodeScale);
+#pragma unroll
+                for (int i = 0; i < Sh::kRows; ++i) {
+                    float P = part[c][i];
+                    if constexpr (MR == 8) P = g4 & 2 ? part[c + 2][i] : P;
+                    if constexpr (MR <= 4) {
+                        const float even = g4 & 2 ? part[2][i] : P, odd = g4 & 2 ? part[3][i] : part[1][i];
+                        P = g4 & 1 ? odd : even;
+                    }
+                    add_unit(tot[c][i], scale, P, z, xsum[i]);
+                }
+            }
+            if constexpr (NG > 1) __builtin_amdgcn_sched_barrier(0);  // group after group: mixed, their sums do not fit the registers
         }
     };
 
@@ -247,33 +261,35 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
     }
 }
 
-template <typename Act, int UB, int D, int BOUND, int MR>
+template <typename Act, int UB, int BPG, int D, int BOUND, int MR>
 hipError_t launch_mr(const GemmArgs &a, int finish, unsigned long long *sync, int waves, hipStream_t stream)
 {
     const size_t lds = lds_x(MR) + (size_t)waves * unit_x_bytes<UB>();
     const int ntiles = (a.N + kTileCols - 1) / kTileCols, row_blocks = (a.M + kRowsX - 1) / kRowsX;
     if (ntiles > 65535 || row_blocks > 65535 || (MR < 16 && a.M > MR)) return hipErrorInvalidValue;
     if (lds > 48 * 1024) {  // beyond the default dynamic-LDS allowance
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&tile_dyn_kernel<Act, UB, D, BOUND, MR>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&tile_dyn_kernel<Act, UB, BPG, D, BOUND, MR>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((tile_dyn_kernel<Act, UB, D, BOUND, MR>), dim3(a.split, ntiles, row_blocks), dim3(waves * 64), lds, stream, a, finish, sync);
+    hipLaunchKernelGGL((tile_dyn_kernel<Act, UB, BPG, D, BOUND, MR>), dim3(a.split, ntiles, row_blocks), dim3(waves * 64), lds, stream, a, finish, sync);
     return hipGetLastError();
 }
 
-template <typename Act, int UB, int D>
+template <typename Act, int UB, int BPG, int D>
 hipError_t launch_ud(const GemmArgs &a, int finish, unsigned long long *sync, int waves, hipStream_t stream)
 {
-    // two units in flight need more than 128 registers: up to eight waves per workgroup only (for sweeps: 16 rows only)
+    // two units in flight need more than 128 registers: up to eight waves per workgroup only (for sweeps: 16 rows only); units of
+    // several groups may
+    constexpr int BOUND = D == 2 || UB > BPG ? 512 : 1024;
+    if (64 * waves > BOUND) return hipErrorInvalidValue;
     if constexpr (D == 2) {
-        if (waves > 8) return hipErrorInvalidValue;
-        return launch_mr<Act, UB, D, 512, 16>(a, finish, sync, waves, stream);
+        return launch_mr<Act, UB, BPG, D, BOUND, 16>(a, finish, sync, waves, stream);
     } else {
-        if (a.M == 1) return launch_mr<Act, UB, D, 1024, 1>(a, finish, sync, waves, stream);
-        if (a.M == 2) return launch_mr<Act, UB, D, 1024, 2>(a, finish, sync, waves, stream);
-        if (a.M <= 4) return launch_mr<Act, UB, D, 1024, 4>(a, finish, sync, waves, stream);
-        if (a.M <= 8) return launch_mr<Act, UB, D, 1024, 8>(a, finish, sync, waves, stream);
-        return launch_mr<Act, UB, D, 1024, 16>(a, finish, sync, waves, stream);
+        if (a.M == 1) return launch_mr<Act, UB, BPG, D, BOUND, 1>(a, finish, sync, waves, stream);
+        if (a.M == 2) return launch_mr<Act, UB, BPG, D, BOUND, 2>(a, finish, sync, waves, stream);
+        if (a.M <= 4) return launch_mr<Act, UB, BPG, D, BOUND, 4>(a, finish, sync, waves, stream);
+        if (a.M <= 8) return launch_mr<Act, UB, BPG, D, BOUND, 8>(a, finish, sync, waves, stream);
+        return launch_mr<Act, UB, BPG, D, BOUND, 16>(a, finish, sync, waves, stream);
     }
 }
 
@@ -285,26 +301,28 @@ hipError_t launch_tile_dyn(const GemmArgs &a, int finish, unsigned long long *sy
 {
     if (a.group % 32 != 0 || waves < 1 || waves > 16) return hipErrorInvalidValue;
     if (!finish_args_ok(a, finish, sync)) return hipErrorInvalidValue;
-    const unsigned long long rows = (unsigned long long)a.groups_per_split * (a.group / 8);
+    const unsigned long long rows = ((unsigned long long)a.groups_per_split + 3) * (a.group / 8);  // a last unit of several groups may end past the slice
     if (rows * a.N * 4ull >= 0x7F000000ull) return hipErrorInvalidValue;  // slice-relative 32-bit buffer offsets
     if ((unsigned long long)a.M * a.K * 2ull >= 0x7F000000ull) return hipErrorInvalidValue;
+    // Blocks per unit: the most up to unit_blocks that divide a group, or four of two or four whole groups (in the form with eight
+    // waves and one unit in flight).
     const int bpg = a.group / 32;
-    int ub = bpg % 4 == 0 ? 4 : (bpg % 2 == 0 ? 2 : 1);  // blocks per unit: a unit never crosses a quantisation group
-    if ((unit_blocks == 1 || unit_blocks == 2) && unit_blocks < ub) ub = unit_blocks;  // smaller on request (sweeps)
-    if (a.bf16) {  // bfloat16 activations: the scheduler's depth only
-        if (depth != 1) return hipErrorInvalidValue;
-        if (ub == 4) return launch_ud<ActBF16, 4, 1>(a, finish, sync, waves, stream);
-        if (ub == 2) return launch_ud<ActBF16, 2, 1>(a, finish, sync, waves, stream);
-        return launch_ud<ActBF16, 1, 1>(a, finish, sync, waves, stream);
-    }
-    if (depth == 2) {
-        if (ub == 4) return launch_ud<ActF16, 4, 2>(a, finish, sync, waves, stream);
-        if (ub == 2) return launch_ud<ActF16, 2, 2>(a, finish, sync, waves, stream);
-        return launch_ud<ActF16, 1, 2>(a, finish, sync, waves, stream);
-    }
-    if (ub == 4) return launch_ud<ActF16, 4, 1>(a, finish, sync, waves, stream);
-    if (ub == 2) return launch_ud<ActF16, 2, 1>(a, finish, sync, waves, stream);
-    return launch_ud<ActF16, 1, 1>(a, finish, sync, waves, stream);
+    int ub = 1;
+    if (unit_blocks >= 2 && bpg % 2 == 0) ub = 2;
+    if (unit_blocks >= 4 && (bpg % 4 == 0 || (bpg <= 2 && waves <= 8 && depth == 1))) ub = 4;
+    auto launch = [&](auto act, auto in_flight) {
+        typedef decltype(act) Act;
+        constexpr int D = decltype(in_flight)::value;
+        if constexpr (D == 1) {
+            if (ub == 4 && bpg == 1) return launch_ud<Act, 4, 1, D>(a, finish, sync, waves, stream);
+            if (ub == 4 && bpg == 2) return launch_ud<Act, 4, 2, D>(a, finish, sync, waves, stream);
+        }
+        if (ub == 4) return launch_ud<Act, 4, 4, D>(a, finish, sync, waves, stream);
+        if (ub == 2) return launch_ud<Act, 2, 2, D>(a, finish, sync, waves, stream);
+        return launch_ud<Act, 1, 1, D>(a, finish, sync, waves, stream);
+    };
+    if (a.bf16) return depth == 1 ? launch(ActBF16{}, std::integral_constant<int, 1>{}) : hipErrorInvalidValue;  // the scheduler's depth only
+    return depth == 2 ? launch(ActF16{}, std::integral_constant<int, 2>{}) : launch(ActF16{}, std::integral_constant<int, 1>{});
 }
 
 }  // namespace w4a16
