@@ -148,7 +148,7 @@ bool fits_32bit_offsets(int M, int N, int K, int group, int gps)
 // Algorithm 1 takes the split factor S and the block sizes as inputs.  Here the
 // scheduler (kernel = AUTO, split = 0) chooses them from the shape alone:
 //
-// STRIPE (M = 1 from 4 MB of packed weights on, M = 2 ... 4 on large matrices): 256-column stripes x S slices of K with S = compute
+// STRIPE (M = 1 from 4 MB of packed weights on, M = 2 ... 4 on large matrices where tile_beats_stripe does not hold): 256-column stripes x S slices of K with S = compute
 //   units / stripes, rounded down: one workgroup per compute unit whose waves share the slice.
 // TILE (everything else): 64-column tiles x 16, 32 or 64 rows of X per workgroup (as many rows as still
 //   leave a workgroup per compute unit at S = 1), eight or four waves; up to 16 rows they share the slice by ticket, in a form for
@@ -229,6 +229,38 @@ int ticket_unit_blocks(int M, int group, int gps, int workgroups, int cus)
     const int k = gps * group;
     const bool several = k >= 1024 && (group == 32 ? M <= 4 || one_round : one_round && (M <= 8 || k >= 5120));
     return several ? 4 : group / 32;
+}
+
+// Estimated times (us) of the scheduler's TILE and STRIPE plans at 2 to 4 rows, from 17 shapes (K = 2048 ... 28672, N = 4096 ... 28672, 4 to 122 MB
+// of weights) with groups of 32, 64 and 128 timed both ways; where the models are within 3 % so are the clocks, mostly.
+// TILE's vector instructions bound it: 0.16 us per 128 k of a workgroup's slice (more with short groups), and where its workgroups
+// are more than the compute units, 5.3 TB/s; STRIPE streams at 7 TB/s or at 0.126 us per 32 k of a slice, but it starts and ends slower.
+// M = 2, TILE / STRIPE: K = 28672, N = 8192 22.7 / 23.5; K = N = 8192 8.9 / 9.7; K = 5120, N = 13824 9.0 / 10.0; K = 8192, N = 12288 (192 workgroups
+// on 256 compute units) 12.9 / 12.2; K = 8192, N = 28672 24.9 / 22.6.  M = 4: K = 28672, N = 8192 22.4 / 26.0; K = N = 8192 9.1 / 11.0;
+// K = 28672, N = 5120 16.3 / 18.5; K = 8192, N = 28672 25.6 / 24.9.  (M = 1 stays with STRIPE from 4 MB on: TILE is 2 to 4 % faster on half of
+// these shapes and up to 13 % slower on the others; only below 10 MB is it clearly faster, K = 2048, N = 4096 4.1 / 5.6.)
+bool tile_beats_stripe(int M, int N, int K, int group, int cus)
+{
+    const int G = K / group;
+    const double bytes = 0.5 * K * N * (1.0 + 5.0 / group);
+    auto split = [&](long long tiles, int *S) {  // rounded as make_plan does; returns k per slice
+        *S = (int)(cus / tiles) < 1 ? 1 : ((int)(cus / tiles) > G ? G : (int)(cus / tiles));
+        const int gps = (G + *S - 1) / *S;
+        *S = (G + gps - 1) / gps;
+        return (double)gps * group;
+    };
+    int S;
+    const long long tiles = ((long long)N + 63) / 64, stripes = ((long long)N + 255) / 256;
+    const double slice = split(tiles, &S) / 128.0;
+    const long long rounds = (tiles * S + cus - 1) / cus;
+    double tile = (double)rounds * slice * (group == 32 ? 0.185 : (group == 64 ? 0.168 : 0.16));
+    if (rounds > 1 && bytes / 5.3e6 > tile) tile = bytes / 5.3e6;
+    tile += S > 1 ? 3.5 : 2.6;
+    double stripe = split(stripes, &S) / 32.0 * 0.126;
+    const double stream = bytes / (M == 2 ? 7.1e6 : 6.8e6);
+    if (stream > stripe) stripe = stream;
+    stripe += M == 2 ? 4.8 : 6.0;
+    return tile <= stripe;
 }
 
 // LDS a STRIPE workgroup needs for a slice of gps groups, and the most it may use.
@@ -405,10 +437,11 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
     const int G = K / group;
     const bool automatic = kernel == W4A16_KERNEL_AUTO && split == 0;
     if (kernel == W4A16_KERNEL_AUTO) {
-        // STRIPE: M = 1 from 4 MB of packed weights on, M = 2 from 20 MB, M = 3 and 4 from 32 MB.  Below
+        // STRIPE: M = 1 from 4 MB of packed weights on, and at 2 to 4 rows, from 20 and 32 MB on, where the costs say so.  Below
         // these sizes it is TILE, many of whose plans there need no workspace: they are not to change for ones that share an accumulator.
         const double packed = 0.5 * (double)K * (double)N;
-        const bool stripe = (M == 1 && packed >= 4e6) || (M == 2 && packed >= 20e6) || (M <= 4 && packed >= 32e6);
+        bool stripe = (M == 1 && packed >= 4e6) || (M == 2 && packed >= 20e6) || (M <= 4 && packed >= 32e6);
+        if (stripe && automatic && M >= 2 && tile_beats_stripe(M, N, K, group, cus)) stripe = false;
         kernel = stripe ? W4A16_KERNEL_STRIPE : W4A16_KERNEL_TILE;
     }
     if (kernel != W4A16_KERNEL_WAVE_SPLIT && kernel != W4A16_KERNEL_STRIPE && kernel != W4A16_KERNEL_TILE)
