@@ -119,21 +119,28 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
         const bool valid = u >= 0;
         const uint32_t uu = valid ? (uint32_t)u : 0u;
         const uint32_t g = NG == 1 ? uu / (uint32_t)upg : uu * NG, b0 = uu * UB;  // first group and first block (of the slice)
+        // Groups past the slice's last one: every lane's own offset is out of range (the scalar offset is no part of the slice then, and
+        // the range check is not to depend on it).  Their X too: zeros times whatever follows it would not do, that may be an infinity.
 #pragma unroll
         for (int l = 0; l < kLoadsX; ++l) {  // X ahead of the weights: loads return in order, and these mostly come from cache
-            // of groups past the slice's last one nothing is read: their weights and scales are out of range, and so is their X (zeros
-            // times whatever follows it would not do: that may be an infinity)
-            const bool in = valid && (NG == 1 || b0 + l * Sh::kBlocksPerLoad + xb < (uint32_t)(groups * BPG));
-            r.x[l] = __builtin_amdgcn_raw_buffer_load_b128(rx, in ? vx : kOutOfRange, (b0 + l * Sh::kBlocksPerLoad) * (kBlockRows * 16u), 0);
+            const uint32_t b = b0 + l * Sh::kBlocksPerLoad, last = (uint32_t)(groups * BPG);
+            const bool in = valid && (NG == 1 || b + xb < last);
+            r.x[l] = __builtin_amdgcn_raw_buffer_load_b128(rx, in ? vx : kOutOfRange, (NG == 1 || b < last ? b : 0u) * (kBlockRows * 16u), 0);
         }
+        uint32_t gin[NG];  // group h of the unit, or 0 where there is none
+        bool has[NG];
 #pragma unroll
         for (int h = 0; h < NG; ++h) {
-            r.sc[h] = __builtin_amdgcn_raw_buffer_load_b64(rs, valid ? vs : kOutOfRange, (g + h) * row_s, 0);
-            r.zw[h] = __builtin_amdgcn_raw_buffer_load_b32(rz, valid ? vz : kOutOfRange, (g + h) * row_z, 0) | zfill;
+            has[h] = valid && (h == 0 || g + h < (uint32_t)groups);
+            gin[h] = h == 0 || has[h] ? g + h : 0u;
+            r.sc[h] = __builtin_amdgcn_raw_buffer_load_b64(rs, has[h] ? vs : kOutOfRange, gin[h] * row_s, 0);
+            r.zw[h] = __builtin_amdgcn_raw_buffer_load_b32(rz, has[h] ? vz : kOutOfRange, gin[h] * row_z, 0) | zfill;
         }
 #pragma unroll
-        for (int q = 0; q < UB; ++q)  // read once from DRAM: nontemporal
-            r.w[q] = __builtin_amdgcn_raw_buffer_load_b128(rw, valid ? vw : kOutOfRange, (b0 + q) * (kBlockRows * row_w), 2);
+        for (int q = 0; q < UB; ++q) {  // read once from DRAM: nontemporal
+            const uint32_t b = NG == 1 ? b0 + q : gin[q / BPG] * BPG + q % BPG;
+            r.w[q] = __builtin_amdgcn_raw_buffer_load_b128(rw, has[q / BPG] ? vw : kOutOfRange, b * (kBlockRows * row_w), 2);
+        }
     };
 #pragma unroll
     for (int p = 0; p < D; ++p) {
@@ -301,7 +308,7 @@ hipError_t launch_tile_dyn(const GemmArgs &a, int finish, unsigned long long *sy
 {
     if (a.group % 32 != 0 || waves < 1 || waves > 16) return hipErrorInvalidValue;
     if (!finish_args_ok(a, finish, sync)) return hipErrorInvalidValue;
-    const unsigned long long rows = ((unsigned long long)a.groups_per_split + 3) * (a.group / 8);  // a last unit of several groups may end past the slice
+    const unsigned long long rows = (unsigned long long)a.groups_per_split * (a.group / 8);
     if (rows * a.N * 4ull >= 0x7F000000ull) return hipErrorInvalidValue;  // slice-relative 32-bit buffer offsets
     if ((unsigned long long)a.M * a.K * 2ull >= 0x7F000000ull) return hipErrorInvalidValue;
     // Blocks per unit: the most up to unit_blocks that divide a group, or four of two or four whole groups (in the form with eight
