@@ -472,10 +472,12 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
         S = (G + gps - 1) / gps;
         if (stripe_lds(M, group, gps, wmin) > stripe_lds_max(M)) return W4A16_ERR_UNSUPPORTED;
         if (S > 65535) return W4A16_ERR_UNSUPPORTED;  // a grid dimension of the many-row form
-        // waves: each should get at least four blocks of 16 k; eight measured best for the ticket form (M <= 4), which
-        // is also the most the many-row form holds
+        // Waves: the many-row form's should get at least four blocks of 16 k each, eight at most.  The ticket form (M <= 4) has eight
+        // however short its slice: they stage it together and their sums meet cheaply (M = 1, us, two or four waves for a slice of one or two groups
+        // / eight: K = 2048, N = 4096 5.5 / 4.4; K = N = 4096 5.3 / 4.9; K = 6144, N = 1536 5.1 / 4.6; ten or twelve: within 3 % where the slice is long,
+        // slower where it is short).
         const long long nblocks = (long long)gps * (group / 16);
-        int waves = (int)(nblocks / 4);
+        int waves = stripe_by_ticket(M) ? 8 : (int)(nblocks / 4);
         const int wbest = stripe_by_ticket(M) ? 8 : (wmax > 12 ? 12 : wmax);
         waves = waves < wmin ? wmin : (waves > wbest ? wbest : waves);
         if (tuning().stripe_waves >= wmin && tuning().stripe_waves <= wmax) waves = tuning().stripe_waves;
