@@ -1,4 +1,4 @@
-// W4A16 multiply for few rows of X (the scheduler's choice for 2 <= M <= 16 where the stripe family does not
+// W4A16 multiply for few rows of X (the scheduler's choice for M <= 16 where the stripe family does not
 // pay): one workgroup per (64-column tile, K slice, block of 16 rows of X), the slice handed out to the
 // workgroup's waves in units as they become free.
 //
@@ -8,9 +8,9 @@
 // of each of four packed rows); the A operand is row j of the workgroup's rows of X, k-group g, from LDS.
 // sum_k x_k per row comes from one more MFMA per block, X against a constant operand of ones.
 //
-// How the slice is shared is the decode kernel's way (w4a16_stripe_dyn.hip): a unit is kUnitBlocks blocks of one
-// quantisation group (the whole group for group = 128), a wave draws its next unit from an LDS ticket counter,
-// every unit's contribution (Eq. 2, fp32) is rounded to a multiple of 2^-24, and from there on all sums are exact
+// How the slice is shared is the decode kernel's way (w4a16_stripe_dyn.hip): a unit is up to four blocks of one
+// quantisation group (the whole group for group = 128) or two or four short groups, a wave draws its next unit from an LDS ticket counter,
+// every group's share of it (Eq. 2) is rounded to a multiple of 2^-24, and from there on all sums are exact
 // (integer-valued doubles per wave and in LDS, 64-bit integers across workgroups): Algorithm 1's Phase 3 with
 // results that do not depend on which wave took which unit.  A wave stages the X of a unit itself, in its own
 // LDS (no barrier in the loop).
@@ -39,7 +39,10 @@ constexpr uint32_t unit_x_bytes() { return UB * kBlockRows * kRowStride * 16; }
 // 4 g + i of lane group g are rows of X again and again where there are fewer than 16 (the A operand repeats them, free), so that
 // group g has every output of its column slots and takes on some: all four column slots and rows 4 g .. 4 g + 3 (MR = 16), two slots
 // and rows 4 (g mod 2) .. + 3 (8), one slot and rows 0 .. MR - 1 (1, 2, 4).  The unit's last step, which without its memory accesses
-// took a third of the kernel's time, is then done for outputs that exist only: 16, 8, 4, 2 or 1 per lane.
+// took up to a third of the kernel's loop, is then done for outputs that exist only: 16, 8, 4, 2 or 1 per lane; and a load of X
+// takes several blocks.  What bounds the kernel is its vector instructions: with every load out of range (no memory traffic) it takes 80 to 90 %
+// of its time, and more waves or units in flight do not help.  us per multiply, sixteen rows' work / the form for M:
+// M = 4, K = 4096, N = 11008, BF16 9.4 / 7.95; M = 8, K = 28672, N = 8192 25.55 / 24.7; M = 4, K = 28672, N = 8192 26.0 / 22.5; the same bits.
 template <int MR>
 struct Share {
     static constexpr int kCols = MR == 16 ? 4 : (MR == 8 ? 2 : 1);  // column slots per lane
