@@ -705,6 +705,7 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
 
     const int dev = current_device();
     if (dev < 0) { note_hip_error(hipErrorNoDevice); return W4A16_ERR_HIP; }
+    const int cus = compute_units(dev);
     w4a16_plan plan;
     PanelPlan panel;
     bool by_panel = false;
@@ -723,11 +724,11 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
     }
     if (src != kFromCall && M > 16) {
         w4a16_plan frugal;
-        only_free = make_plan(M, N, K, group, kernel, split, compute_units(dev), &frugal, nullptr, bf16, kFrugal) == W4A16_OK && frugal.workspace_bytes == 0;
+        only_free = make_plan(M, N, K, group, kernel, split, cus, &frugal, nullptr, bf16, kFrugal) == W4A16_OK && frugal.workspace_bytes == 0;
     }
     for (Thrift thrift : {kBest, kUnsplit, kFrugal, kBare}) {
         if (thrift == kBare && !bare) break;
-        rc = make_plan(M, N, K, group, kernel, split, compute_units(dev), &plan, &panel, bf16, thrift);
+        rc = make_plan(M, N, K, group, kernel, split, cus, &plan, &panel, bf16, thrift);
         if (rc) return rc;
         if (only_free && plan.workspace_bytes != 0) continue;  // (never kFrugal's)
         by_panel = plan.kernel == W4A16_KERNEL_TILE && plan.tile_n == kPanelCols;
@@ -769,7 +770,7 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
         e = launch_panel(a, panel, st);
     } else if (plan.kernel == W4A16_KERNEL_TILE && tile_by_ticket(M, plan.tile_m)) {
         e = launch_tile_dyn(a, finish, b.sync, plan.waves_k, tuning().tile_depth == 2 && !bf16 && plan.waves_k <= 8 ? 2 : 1,
-                            ticket_unit_blocks(M, group, plan.groups_per_split, plan.workgroups, compute_units(dev)), st);
+                            ticket_unit_blocks(M, group, plan.groups_per_split, plan.workgroups, cus), st);
     } else if (plan.kernel == W4A16_KERNEL_TILE && tile_four(plan.tile_m, group, bf16) && !short_slices(group, bf16, plan.groups_per_split)) {
         if (plan.tile_m == 64 && (bf16 || group != 128)) e = launch_tile_tall(a, finish, b.sync, st);
         else e = launch_tile_wide(a, finish, b.sync, plan.tile_m, st);
