@@ -79,7 +79,7 @@ typedef enum {
     W4A16_KERNEL_AUTO = -1,
     W4A16_KERNEL_WAVE_SPLIT = 0, /* M <= 4: narrow column tile per workgroup, its 16 waves split K, LDS reduction */
     /* 1 and 2 belonged to two earlier families, retired: W4A16_ERR_UNSUPPORTED */
-    W4A16_KERNEL_STRIPE = 3,     /* M <= 16; the scheduler's choice for M = 1 (2; 3, 4) from about 4 MB (20 MB; 32 MB)
+    W4A16_KERNEL_STRIPE = 3,     /* M <= 16; the scheduler's choice for M = 1 from about 4 MB, a candidate for M = 2 (3, 4) from 20 MB (32 MB)
                                     of packed weights on: 256-column stripe x K slice per workgroup, its waves
                                     share the slice (exact sums in LDS); slices of different workgroups meet in a
                                     64-bit fixed-point accumulator by one atomic add each, no second launch        */
@@ -260,7 +260,7 @@ int w4a16_quantize(const void *W16, int group, int N, int K, uint32_t *Wpacked, 
  *   "tile_rows"      rows of X per TILE workgroup (16, 32, 64)
  *   "tile_dyn"       16 rows of X per workgroup: 1 = units of K always handed out by ticket, 2 = never
  *   "tile_depth"     units in flight per wave of that form (1, 2)
- *   "tile_unit"      blocks of 32 k per unit of that form (1, 2; default: a whole group, at most 4)
+ *   "tile_unit"      blocks of 32 k per unit of that form (1, 2, 4; 4: of several groups of 64 or 32)
  *   "tile_waves"     waves per TILE workgroup (4..8)
  *   "tile_wide"      2: TILE at 32 or 64 rows of X per workgroup: the eight-wave form instead of
  *                    the four-wave one
