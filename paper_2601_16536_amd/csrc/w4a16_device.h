@@ -90,24 +90,28 @@ __device__ __forceinline__ float apply_scale_zero(float tot, float s, float z, f
     return __builtin_fmaf(s * 16777216.0f, P, __builtin_fmaf(-s * z, xsum, tot));
 }
 
-// The ticket kernels' exact sums inside a wave.  With P as the MFMA gives it and xs = sum_k x_k / kCodeScale, a unit of k contributes
-//     sum_k x_k s (q_k - z) = (kCodeScale s) (P - (z + kCodeOffset) xs),
-// in units of 2^-24, rounded to a whole number, to a sum that must not depend on the order of the units.  The sum is a double that
-// starts at 1.5 2^52, where a unit in the last place is 1: one FMA multiplies, rounds and adds.  Rounding to the nearest whole number
-// would depend on the sum only where the contribution is a whole number and a half, to which the scale's factor 1 + 2^-40 does
-// not let it come: parenthesis (24 bits) times s (11 bits) is an odd number m times 2^e, the contribution m (2^40 + 1) 2^(e-40), its
-// last bit 1/2 only if e = 39, beyond 2^78.  (Whole numbers up to 2^39, i.e. values below 2^15, stay what they are; the product
-// s (1 + 2^-40) has at most 52 bits and is exact.)  Sums are whole while they stay within 2^51, values of 2^27, four times the clamp;
-// what a sum that was ever beyond that has lost is more than the clamp lets through.
-// Three vector instructions per output; product, FMA, rounding, conversion and addition as steps of their own were five (TILE, M = 16,
-// K = 14336, N = 4096 11.4 -> 11.2 us, M = 8, K = 28672, N = 8192 25.95 -> 25.55; the BF16 unpack beside it, M = 4, K = 4096, N = 11008 10.05 -> 9.4).
-constexpr double kTotStart = 6755399441055744.0;       // 1.5 2^52
-constexpr double kUntie = 1.0 + 1.0 / 1099511627776.0;  // 1 + 2^-40
+// The ticket kernels' exact sums inside a wave.  A unit of k of one group contributes (Eq. 2, FP32)
+//     sum_k x_k s (q_k - z) = (kCodeScale s) P - s (z + kCodeOffset) xsum,
+// in units of 2^-24 and rounded to a whole number by itself, ahead of the sum: which units a wave has differs from run to run, so the
+// rounding must not depend on what was summed before.  The sum is a double, whole and exact below 2^53 (values of 2^29), of which a wave's
+// final sum may have 2^49; an infinity or a NaN stays one.
+// One FP64 FMA into a sum that starts at 1.5 2^52 would multiply, round and add in three vector instructions per output instead of
+// five, but it sends a contribution halfway between two whole numbers to the even SUM (a factor on the scale only moves these
+// halves elsewhere: 1 + 2^-40 to the odd multiples of 2^39, values of 32768) and is whole up to 2^51 only.  It was no faster: us for a step of
+// several layers, FMA / as here: M = 1, K = 28672, N = 8192 47.6 / 47.7; M = 4, K = 4096, N = 11008, BF16 71.9 / 71.5; M = 8, K = 28672, N = 8192
+// 50.1 / 50.2; M = 16, K = 14336, N = 4096 80.0 / 80.0.
+constexpr float kFixScale = 16777216.0f;  // 2^24
+struct UnitScales {
+    float sp, sz;  // 2^24 kCodeScale s (FP16: 2^48 s, P carries 2^-24) and -2^24 s (z + kCodeOffset), exact both
+};
 template <typename Act>
-__device__ __forceinline__ double unit_scale(float s) { return (double)s * ((double)Act::kCodeScale * 16777216.0 * kUntie); }
-__device__ __forceinline__ void add_unit(double &tot, double scale, float P, float z, float xs)
+__device__ __forceinline__ UnitScales unit_scales(float s, uint32_t code)
 {
-    tot = __builtin_fma((double)__builtin_fmaf(-z, xs, P), scale, tot);
+    return {s * (Act::kCodeScale * kFixScale), -s * ((float)code + Act::kCodeOffset) * kFixScale};
+}
+__device__ __forceinline__ void add_unit(double &tot, UnitScales u, float P, float xsum)
+{
+    tot += (double)__builtin_rintf(__builtin_fmaf(u.sp, P, u.sz * xsum));
 }
 
 // The ticket kernels' sums inside a workgroup (w4a16_stripe_dyn.hip, w4a16_tile_dyn.hip).  A wave's sum of one output, in units of
@@ -115,9 +119,8 @@ __device__ __forceinline__ void add_unit(double &tot, double scale, float P, flo
 // exactly below 2^53, in any order, in a double in LDS.  The atomic add of doubles keeps the conversion to 64-bit integers,
 // some twenty instructions, for after the barrier: once per output instead of once per output and wave.
 constexpr double kSumMax = 562949953421312.0;  // 2^49
-__device__ __forceinline__ void add_wave_sum(double *acc, double tot)
+__device__ __forceinline__ void add_wave_sum(double *acc, double t)
 {
-    double t = tot - kTotStart;
     t = t > kSumMax ? kSumMax : (t < -kSumMax ? -kSumMax : t);
     if (t != 0.0) __builtin_amdgcn_ds_atomic_fadd_f64((__attribute__((address_space(3))) double *)acc, t);  // (a NaN is not 0)
 }

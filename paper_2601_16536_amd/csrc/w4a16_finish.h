@@ -13,7 +13,6 @@ namespace w4a16 {
 //               biased by 2^50 to be positive: 63 slices stay below 2^57;
 //   bit   57    set (by an atomic OR that precedes its slice's add) when a slice sum is NaN: the result is NaN;
 //   bits 58-63  arrivals: up to 63 slices.
-constexpr float kFixScale = 16777216.0f;            // 2^24
 constexpr float kFixClamp = 33554432.0f;            // 2^25
 constexpr int kFixMaxSlices = 63;
 constexpr unsigned long long kFixBias = 1ull << 50;

@@ -18,7 +18,7 @@
 // previous one.  Which wave computes which unit now differs from run to run, so
 // the sums must not depend on it: every unit's contribution
 //     sum_k x_k s (q_k - z)  =  (2^24 s) P - (s z) sum_k x_k        (Eq. 2, fp32)
-// is rounded to a multiple of 2^-24,
+// is rounded to a multiple of 2^-24 by itself (add_unit, w4a16_device.h),
 // and from there on everything is added exactly: as integer-valued doubles per
 // wave and in LDS, as 64-bit integers in the cross-workgroup accumulator.
 // Integer adds commute, hence bitwise reproducible results whatever the
@@ -61,7 +61,7 @@ constexpr int kLdsLimit = 144 * 1024;
 //   tickets               16 B   (one counter)
 //   acc   [MROWS][4][64]  sums of the waves, integer-valued doubles in units of 2^-24, by row, column mod 4, lane
 //   xs    [rows][MROWS]   A-operand entries: eight halves of one packed row of X in unpack order
-//   xsum  [MROWS][rows]   fp32 sum of the eight x of each packed row, over kCodeScale
+//   xsum  [MROWS][rows]   fp32 sum of the eight x of each packed row
 //   sc    [groups][256]   FP16 scales of the stripe
 //   zp    [groups][32]    packed zero points of the stripe
 struct Lds {
@@ -153,7 +153,7 @@ __global__ __launch_bounds__(1024) void stripe_dyn_kernel(const GemmArgs a, cons
         if (e >= n_x) return;
         const int row = e / MROWS, m = e % MROWS;
         *reinterpret_cast<uint4_t *>(smem + L.xs + (uint32_t)e * 16u) = Act::stage_x(d);
-        *reinterpret_cast<float *>(smem + L.xsum + ((uint32_t)m * rows + row) * 4u) = Act::sum_x(d) * (1.0f / Act::kCodeScale);
+        *reinterpret_cast<float *>(smem + L.xsum + ((uint32_t)m * rows + row) * 4u) = Act::sum_x(d);
     };
     auto sc_put = [&](int e, uint4_t d) { if (e < n_sc) *reinterpret_cast<uint4_t *>(smem + L.sc + (uint32_t)e * 16u) = d; };
     auto zp_put = [&](int e, uint4_t d) { if (e < n_zp) *reinterpret_cast<uint4_t *>(smem + L.zp + (uint32_t)e * 16u) = d | zfill; };
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(1024) void stripe_dyn_kernel(const GemmArgs a, cons
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
-        for (int i = 0; i < MROWS; ++i) tot[c][i] = kTotStart;
+        for (int i = 0; i < MROWS; ++i) tot[c][i] = 0.0;
     const Masks masks = make_masks();
     const float4_t zero4 = {0.f, 0.f, 0.f, 0.f};
 
@@ -275,10 +275,9 @@ __global__ __launch_bounds__(1024) void stripe_dyn_kernel(const GemmArgs a, cons
         const float s[4] = {(float)s01.h[0], (float)s01.h[1], (float)s23.h[0], (float)s23.h[1]};
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const double scale = unit_scale<Act>(s[c]);
-            const float z = (float)((zw >> (4 * c)) & 15u) + Act::kCodeOffset;
+            const UnitScales u = unit_scales<Act>(s[c], (zw >> (4 * c)) & 15u);
 #pragma unroll
-            for (int i = 0; i < MROWS; ++i) add_unit(tot[c][i], scale, part[c][i], z, xs[i]);
+            for (int i = 0; i < MROWS; ++i) add_unit(tot[c][i], u, part[c][i], xs[i]);
         }
     };
 

@@ -168,7 +168,7 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
 #pragma unroll
     for (int c = 0; c < Sh::kCols; ++c)
 #pragma unroll
-        for (int i = 0; i < Sh::kRows; ++i) tot[c][i] = kTotStart;
+        for (int i = 0; i < Sh::kRows; ++i) tot[c][i] = 0.0;
     const Masks masks = make_masks();
     // sum_k x_k over a unit comes from the MFMA too: X against ones (FP16: 16 where the staged x was divided by 16).  (Against
     // ones times 2^-24, subnormals, the sum comes out with fewer bits: an error of 2.3e-4 instead of 2.1e-4.)
@@ -208,8 +208,7 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
             for (int c = 0; c < Sh::kCols; ++c) {
                 H2 s;
                 s.u = (uint32_t)(scales >> (16 * c)) & 0xFFFFu;
-                const double scale = unit_scale<Act>((float)s.h[0]);
-                const float z = ((float)((zw >> (4 * c)) & 15u) + Act::kCodeOffset) * (1.0f / Act::kCodeScale);
+                const UnitScales u = unit_scales<Act>((float)s.h[0], (zw >> (4 * c)) & 15u);
 #pragma unroll
                 for (int i = 0; i < Sh::kRows; ++i) {
                     float P = part[c][i];
@@ -218,7 +217,7 @@ __global__ __launch_bounds__(BOUND) void tile_dyn_kernel(const GemmArgs a, const
                         const float even = g4 & 2 ? part[2][i] : P, odd = g4 & 2 ? part[3][i] : part[1][i];
                         P = g4 & 1 ? odd : even;
                     }
-                    add_unit(tot[c][i], scale, P, z, xsum[i]);
+                    add_unit(tot[c][i], u, P, xsum[i]);
                 }
             }
             if constexpr (NG > 1) __builtin_amdgcn_sched_barrier(0);  // group after group: mixed, their sums do not fit the registers

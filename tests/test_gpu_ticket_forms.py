@@ -70,15 +70,16 @@ def test_last_unit_of_several_groups_reads_no_other_row(gpu, group):
         assert bool(torch.isnan(y[1::2]).all())
 
 
+@pytest.mark.parametrize("odd,step", [(1, 0), (3, 2), (5, 2)])
 @pytest.mark.parametrize("kernel", ["TILE", "STRIPE"])
-def test_contributions_halfway_between_two_steps(gpu, kernel):
-    """Units that contribute an odd multiple of 2^-25, halfway between two values of the exact sums: they round away from zero, by
+def test_contributions_halfway_between_two_steps(gpu, kernel, odd, step):
+    """Units that contribute an odd multiple of 2^-25, halfway between two values of the exact sums: they round to the even one, by
     themselves, whatever has been summed before.  64 units in one column per sign: the sum is known."""
     torch, binding = gpu
     group, G, N = 128, 64, 16
     K = group * G
-    q = np.full((K, N), 8, np.uint8)
-    q[:, 1::2] = 6  # with z = 7: contributions of +1 and -1 times x s
+    q = np.full((K, N), 7 + odd, np.uint8)
+    q[:, 1::2] = 7 - odd  # with z = 7: contributions of +odd and -odd times x s
     X = np.zeros((4, K), np.float16)
     X[:, ::group] = 2.0 ** -14
     s = np.full((G, N), 2.0 ** -11, np.float16)
@@ -87,5 +88,105 @@ def test_contributions_halfway_between_two_steps(gpu, kernel):
         for split in (1, 2, 8):
             say("halves", kernel, M, split)
             Y = run_gpu(gpu, X[:M], Wp, s, Zp, group, kernel=getattr(binding, "KERNEL_" + kernel), split=split).astype(np.float64)
-            assert np.array_equal(Y[:, ::2], np.full((M, N // 2), 64 * 2.0 ** -24)), (M, split, Y)
-            assert np.array_equal(Y[:, 1::2], np.full((M, N // 2), -64 * 2.0 ** -24)), (M, split, Y)
+            assert np.array_equal(Y[:, ::2], np.full((M, N // 2), 64 * step * 2.0 ** -24)), (M, split, Y)
+            assert np.array_equal(Y[:, 1::2], np.full((M, N // 2), -64 * step * 2.0 ** -24)), (M, split, Y)
+
+
+def _known_contributions(units, group):
+    """X of 16 rows (the even ones +, the odd ones -), weights and scales such that group g of column n contributes units[g, n], a pair
+    (kind, count): kind 0 is count times 2^-24, kind 1 count times 2^13, kind 2 count times 2^25; |count| <= 7.  All of Eq. 2 is exact."""
+    kind, count = units
+    G, N = kind.shape
+    q = np.full((G * group, N), 7, np.uint8)  # z = 7
+    q[::group] = np.where(kind < 2, 7 + count, 7)
+    q[1::group] = np.where(kind == 2, 7 + count, 7)
+    s = np.choose(kind, [2.0 ** -24, 2.0 ** 13, 2.0 ** 13]).astype(np.float16)
+    X = np.zeros((16, G * group), np.float32)
+    X[:, ::group], X[:, 1::group] = 1.0, 4096.0
+    X[1::2] *= -1
+    return X, wl.pack_along_k(q), s, wl.pack_along_n(np.full((G, N), 7, np.uint8))
+
+
+def _steps_of(gpu, X, Wp, s, Zp, group, bf16, M, kernel, split):
+    """Rows 0 .. M - 1 of the multiply, in units of 2^-24 and with the rows' signs taken out."""
+    torch, binding = gpu
+    dX, dW, dS, dZ = binding.to_device(X[:M].astype(np.float16), Wp, s, Zp)
+    if bf16:
+        dX = dX.to(torch.bfloat16)
+    Y = torch.full((M, Wp.shape[1]), float("nan"), dtype=dX.dtype, device="cuda")
+    (binding.gemm_bf16 if bf16 else binding.gemm_ex)(dX, dW, dS, dZ, group, kernel=kernel, split=split, out=Y)
+    torch.cuda.synchronize()
+    return Y.float().cpu().numpy().astype(np.float64) * 2.0 ** 24 * np.where(np.arange(M) % 2, -1, 1)[:, None]
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("group", [32, 128])
+def test_large_contributions_that_cancel_leave_the_small_ones(gpu, group, bf16):
+    """Contributions of +-32768 (odd multiples of 2^39 steps) among ones of a few steps of 2^-24, in another order in every column: the
+    large ones cancel and the small ones are whole, so that every order, and every share of the units among the waves, gives their sum."""
+    torch, binding = gpu
+    G, N, rng = 64, 200, np.random.default_rng(5)
+    kind, count = np.zeros((G, N), np.int64), np.zeros((G, N), np.int64)
+    for n in range(N):
+        small = rng.integers(1, 4, 32)
+        row = [(1, 4)] * 16 + [(1, -4)] * 16 + [(0, int(v)) for v in small]
+        for g, at in enumerate(rng.permutation(G)):
+            kind[g, n], count[g, n] = row[at]
+    want = np.where(kind == 0, count, 0).sum(0).astype(np.float64)  # below 256: exact in both formats
+    args = _known_contributions((kind, count), group)
+    for kernel in ("TILE", "STRIPE"):
+        for M in (1, 2, 4) if kernel == "STRIPE" else (1, 2, 4, 8, 16):
+            for split in (1, 3):
+                say("cancelling", kernel, "group", group, "bf16", bf16, "M", M, "split", split)
+                for _ in range(3):
+                    Y = _steps_of(gpu, *args, group, bf16, M, getattr(binding, "KERNEL_" + kernel), split)
+                    assert np.array_equal(Y, np.tile(want, (M, 1))), (kernel, M, split, int((Y != want).sum()))
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("knob", ["tile_unit", "stripe_waves"])
+def test_sums_of_one_wave_beyond_the_clamp_and_back(gpu, knob, bf16):
+    """A wave whose sum passes 1.5 2^27, four times the clamp of its final sum, and comes back has lost nothing: its sum is exact up to 2^29.
+    One wave has all of it: a unit of four groups (TILE), or one wave per workgroup (STRIPE)."""
+    torch, binding = gpu
+    group, N, rng = 32, 72, np.random.default_rng(6)
+    G = 8 * 4
+    kind, count = np.zeros((G, N), np.int64), np.zeros((G, N), np.int64)
+    for n in range(N):
+        for u in range(0, G, 4):
+            a, b = (int(v) for v in rng.integers(1, 4, 2))
+            for g, (k, c) in zip(range(u, u + 4), rng.permutation([(2, 6), (2, -6), (0, a), (0, b)])):
+                kind[g, n], count[g, n] = k, c
+    want = np.where(kind == 0, count, 0).sum(0).astype(np.float64)
+    args = _known_contributions((kind, count), group)
+    kernel = binding.KERNEL_TILE if knob == "tile_unit" else binding.KERNEL_STRIPE
+    try:
+        binding.tune(knob, 4 if knob == "tile_unit" else 1)
+        for M in (1, 2, 4) if knob == "stripe_waves" else (1, 2, 4, 8, 16):
+            say("beyond the clamp and back", knob, "bf16", bf16, "M", M)
+            Y = _steps_of(gpu, *args, group, bf16, M, kernel, 1)
+            assert np.array_equal(Y, np.tile(want, (M, 1))), (M, int((Y != want).sum()))
+    finally:
+        binding.tune(knob, 0)
+
+
+@pytest.mark.parametrize("group", [32, 64, 128])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_every_form_gives_the_same_bits_on_every_run(gpu, group, bf16):
+    """Which wave takes which unit differs from run to run: the forms by rows, and the units of several groups, five times each."""
+    torch, binding = gpu
+    K, N = 40 * 128, 264
+    X, Wp, s, Zp = wl.make(16, K, N, index=7300 + group, group=group)
+    dX, dW, dS, dZ = binding.to_device(X, Wp, s, Zp)
+    if bf16:
+        dX = dX.to(torch.bfloat16)
+    run = binding.gemm_bf16 if bf16 else binding.gemm_ex
+    for kernel in (binding.KERNEL_TILE, binding.KERNEL_STRIPE):
+        for M in (1, 2, 4) if kernel == binding.KERNEL_STRIPE else (1, 2, 4, 8, 16):
+            say("same bits", "bf16" if bf16 else "fp16", "group", group, "kernel", kernel, "M", M)
+            x, first = dX[:M].contiguous(), None
+            for _ in range(5):
+                Y = torch.full((M, N), float("nan"), dtype=dX.dtype, device="cuda")
+                run(x, dW, dS, dZ, group, kernel=kernel, split=2, out=Y)
+                first = Y if first is None else first
+                assert torch.equal(Y.view(torch.int16), first.view(torch.int16)), (kernel, M)
