@@ -202,6 +202,9 @@ bool stripe_by_ticket(int M) { return M <= 4 && tuning().stripe_dyn != 2; }
 // with several row blocks, which re-read the weights from the L2, 3 % slower).
 bool tile_by_ticket(int M, int rows_x) { return rows_x == 16 && (tuning().tile_dyn == 1 || (M <= 16 && tuning().tile_dyn != 2)); }
 
+// Column tiles and row blocks are grid dimensions of the ticket form (w4a16_tile_dyn.hip).
+bool ticket_grid_fits(int M, int N) { return ((long long)N + 63) / 64 <= 65535 && ((long long)M + 15) / 16 <= 65535; }
+
 // TILE with four waves per workgroup: at 32 and 64 rows of X, FP16 with groups of 128 (w4a16_tile_wide.hip), and at 64 rows
 // BF16 and the other lengths of group (w4a16_tile_tall.hip; at 32 rows these run the eight-wave form).  Both take FP16 with
 // groups of 128 at 64 rows: M = 128, N = 8192, K = 512 / 2048 / 8192: 6.6 / 10.7 / 27.7 us (wide), 6.9 / 10.7 / 27.5 (tall).
@@ -250,6 +253,7 @@ bool tile_beats_stripe(int M, int N, int K, int group, int cus)
         return (double)gps * group;
     };
     int S;
+    if (!ticket_grid_fits(M, N)) return false;  // STRIPE has a quarter of the tiles
     const long long tiles = ((long long)N + 63) / 64, stripes = ((long long)N + 255) / 256;
     const double slice = split(tiles, &S) / 128.0;
     const long long rounds = (tiles * S + cus - 1) / cus;
@@ -526,6 +530,7 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
             rows_x = c.rows;
             S = c.S;
         }
+        if (tile_by_ticket(M, rows_x) && !ticket_grid_fits(M, N)) return W4A16_ERR_UNSUPPORTED;
         p->tile_m = rows_x;
         const int tw = tuning().tile_waves;
         if (tw >= 4 && tw <= (tile_by_ticket(M, rows_x) ? 16 : 8)) { p->waves_k = tw; p->threads = 64 * tw; }

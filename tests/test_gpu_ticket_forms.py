@@ -190,3 +190,24 @@ def test_every_form_gives_the_same_bits_on_every_run(gpu, group, bf16):
                 run(x, dW, dS, dZ, group, kernel=kernel, split=2, out=Y)
                 first = Y if first is None else first
                 assert torch.equal(Y.view(torch.int16), first.view(torch.int16)), (kernel, M)
+
+
+def test_most_columns_at_few_rows(gpu):
+    """N = 2^22, more 64-column tiles than a grid's second dimension has: the multiply runs (as STRIPE) at 3 and 4 rows.  First and last
+    columns against the oracle."""
+    torch, binding = gpu
+    K, N = 32, 1 << 22
+    X, Wp, s, Zp = wl.make(4, K, 128, index=7400, group=K)
+    dX, dW, dS, dZ = binding.to_device(X, Wp, s, Zp)
+    W = torch.zeros((K // 8, N), dtype=torch.int32, device="cuda")
+    S, Z = torch.zeros((1, N), dtype=torch.float16, device="cuda"), torch.zeros((1, N // 8), dtype=torch.int32, device="cuda")
+    for big, small, n in ((W, dW, 64), (S, dS, 64), (Z, dZ, 8)):
+        big[:, :n], big[:, -n:] = small[:, :n].view(big.dtype), small[:, -n:].view(big.dtype)
+    ref = orc.gemm(X, Wp, s, Zp, K)
+    for M in (3, 4):
+        say("most columns", M)
+        Y = binding.gemm(dX[:M].contiguous(), W, S, Z, K)
+        torch.cuda.synchronize()
+        got = torch.cat([Y[:, :64], Y[:, -64:]], 1).cpu().numpy()
+        assert err_ratio(got, ref[:M]) <= 1.0, M
+        assert bool((Y[:, 64:-64] == 0).all())

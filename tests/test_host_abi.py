@@ -149,6 +149,25 @@ def test_shapes_beyond_32_bit_offsets_are_refused(binding):
     assert binding.query_plan(15, 64, K, 128, kernel=binding.KERNEL_STRIPE)["split"] >= 1  # 15 * 2^27 bytes still fits
 
 
+def test_more_column_tiles_than_a_grid_has(binding):
+    """65536 tiles of 64 columns (N = 4194248 ... 4194304) are more than the grid of TILE's form for up to 16 rows takes: up to 4 rows the
+    scheduler keeps STRIPE there, and a plan that cannot be launched is refused when it is asked for."""
+    for N in (4194240, 4194248, 4194304):
+        fits = N == 4194240
+        for M in (1, 2, 3, 4):
+            for group, K in ((32, 32), (32, 64), (128, 128)):
+                p = binding.query_plan(M, N, K, group)
+                assert p["kernel"] == binding.KERNEL_STRIPE or fits, (M, N, K, p)
+        for M in (1, 4, 5, 16):
+            if fits:
+                assert binding.query_plan(M, N, 32, 32, kernel=binding.KERNEL_TILE)["workgroups"] == 65535
+                continue
+            with pytest.raises(binding.W4A16Error) as e:
+                binding.query_plan(M, N, 32, 32, kernel=binding.KERNEL_TILE)
+            assert e.value.status == binding.ERR_UNSUPPORTED
+        assert binding.query_plan(17, N, 32, 32, kernel=binding.KERNEL_TILE)["split"] == 1  # the other forms number their tiles along x
+
+
 def test_tuning_knobs(binding):
     """w4a16_tune changes the plans of later calls and rejects unknown names."""
     assert binding.query_plan(40, 2048, 1024, 128, kernel=binding.KERNEL_TILE)["tile_m"] == 16
