@@ -148,8 +148,8 @@ bool fits_32bit_offsets(int M, int N, int K, int group, int gps)
 // Algorithm 1 takes the split factor S and the block sizes as inputs.  Here the
 // scheduler (kernel = AUTO, split = 0) chooses them from the shape alone:
 //
-// STRIPE (M = 1 from 4 MB of packed weights on, M = 2 ... 4 on large matrices where tile_beats_stripe does not hold): 256-column stripes x S slices of K with S = compute
-//   units / stripes, rounded down: one workgroup per compute unit whose waves share the slice.
+// STRIPE (M = 1 from 4 MB of packed weights on, M = 2 ... 4 on large matrices where tile_beats_stripe does not
+//   hold): 256-column stripes x S slices of K with S = compute units / stripes, rounded down: one workgroup per compute unit whose waves share the slice.
 // TILE (everything else): 64-column tiles x 16, 32 or 64 rows of X per workgroup (as many rows as still
 //   leave a workgroup per compute unit at S = 1), eight or four waves; up to 16 rows they share the slice by ticket, in a form for
 //   1, 2, 4, 8 or 16 rows; S = compute units / workgroups, rounded down (a workgroup too many would run as a second round).
@@ -234,37 +234,37 @@ int ticket_unit_blocks(int M, int group, int gps, int workgroups, int cus)
     return several ? 4 : group / 32;
 }
 
-// Estimated times (us) of the scheduler's TILE and STRIPE plans at 2 to 4 rows, from 17 shapes (K = 2048 ... 28672, N = 4096 ... 28672, 4 to 122 MB
-// of weights) with groups of 32, 64 and 128 timed both ways; where the models are within 3 % so are the clocks, mostly.
-// TILE's vector instructions bound it: 0.16 us per 128 k of a workgroup's slice (more with short groups), and where its workgroups
-// are more than the compute units, 5.3 TB/s; STRIPE streams at 7 TB/s or at 0.126 us per 32 k of a slice, but it starts and ends slower.
-// M = 2, TILE / STRIPE: K = 28672, N = 8192 22.7 / 23.5; K = N = 8192 8.9 / 9.7; K = 5120, N = 13824 9.0 / 10.0; K = 8192, N = 12288 (192 workgroups
-// on 256 compute units) 12.9 / 12.2; K = 8192, N = 28672 24.9 / 22.6.  M = 4: K = 28672, N = 8192 22.4 / 26.0; K = N = 8192 9.1 / 11.0;
-// K = 28672, N = 5120 16.3 / 18.5; K = 8192, N = 28672 25.6 / 24.9.  (M = 1 stays with STRIPE from 4 MB on: TILE is 2 to 4 % faster on half of
-// these shapes and up to 13 % slower on the others; only below 10 MB is it clearly faster, K = 2048, N = 4096 4.1 / 5.6.)
+// Whether TILE's plan at 2 to 4 rows is the faster one where STRIPE is a candidate: from 1560 (shape, rows, format, group) timed both ways (K = 256 ...
+// 40000, N = 1024 ... 200000, 20 to 400 MB of weights).  What decides is how evenly either family's plan loads the compute units: `use`
+// is the tiles' work over that of all units for the rounds the plan takes, at its longest slice.  TILE, whose forms for few rows do less per
+// unit, wins where it uses at least 0.92 of what STRIPE does: 13 % in the mean in one round of workgroups, and at 3 and 4 rows in two (us, TILE / STRIPE:
+// M = 4, K = N = 8192 9.1 / 11.0; K = 28672, N = 8192 22.4 / 26.0; K = 13568, N = 31840 37.7 / 42.2).  In more rounds, at 2 rows in two, and where slices beyond 12288 k leave
+// a tenth of the units idle, it is up to 16 % slower where they use the same (M = 2, K = 15360, N = 24576 41.5 / 35.8; M = 4, K = 33280, N = 14336 47.9 / 44.8),
+// and wins where STRIPE leaves more of them idle (M = 3, K = 9216, N = 36512, 143 stripes 32.8 / 46.6): from 1.1.  Where N is no multiple of 32 rows of W do not begin on 128 bytes, and a tile's 256 bytes of one lie in three lines
+// (M = 2, K = 31360, N = 8408 37.5 / 26.2): from 1.3, at 3 and 4 rows, up to three rounds.  And only with units of four blocks: groups of 128 k and
+// multiples, of 64 (several to a unit) and, at 3 and 4 rows in one round, of 32; with others the unit is one or two blocks (M = 4, K = 15168, N = 13968,
+// groups of 96 44.7 / 24.4).  473 of the 1560 go to TILE: 14 % faster than STRIPE in the mean, the worst 2 % slower.
 bool tile_beats_stripe(int M, int N, int K, int group, int cus)
 {
+    if (!ticket_grid_fits(M, N)) return false;
     const int G = K / group;
-    const double bytes = 0.5 * K * N * (1.0 + 5.0 / group);
-    auto split = [&](long long tiles, int *S) {  // rounded as make_plan does; returns k per slice
-        *S = (int)(cus / tiles) < 1 ? 1 : ((int)(cus / tiles) > G ? G : (int)(cus / tiles));
-        const int gps = (G + *S - 1) / *S;
-        *S = (G + gps - 1) / gps;
-        return (double)gps * group;
+    auto use = [&](long long tiles, long long *rounds, int *k) {  // S as make_plan has it
+        int S = (int)(cus / tiles);
+        S = S < 1 ? 1 : (S > G ? G : S);
+        const int gps = (G + S - 1) / S;
+        *k = gps * group;
+        *rounds = (tiles * ((G + gps - 1) / gps) + cus - 1) / cus;
+        return (double)tiles * G / ((double)*rounds * cus * gps);
     };
-    int S;
-    if (!ticket_grid_fits(M, N)) return false;  // STRIPE has a quarter of the tiles
-    const long long tiles = ((long long)N + 63) / 64, stripes = ((long long)N + 255) / 256;
-    const double slice = split(tiles, &S) / 128.0;
-    const long long rounds = (tiles * S + cus - 1) / cus;
-    double tile = (double)rounds * slice * (group == 32 ? 0.185 : (group == 64 ? 0.168 : 0.16));
-    if (rounds > 1 && bytes / 5.3e6 > tile) tile = bytes / 5.3e6;
-    tile += S > 1 ? 3.5 : 2.6;
-    double stripe = split(stripes, &S) / 32.0 * 0.126;
-    const double stream = bytes / (M == 2 ? 7.1e6 : 6.8e6);
-    if (stream > stripe) stripe = stream;
-    stripe += M == 2 ? 4.8 : 6.0;
-    return tile <= stripe;
+    long long rounds, stripe_rounds;
+    int k, stripe_k;
+    const double tile = use(((long long)N + 63) / 64, &rounds, &k), stripe = use(((long long)N + 255) / 256, &stripe_rounds, &stripe_k);
+    const bool aligned = N % 32 == 0;
+    if (group == 32) return aligned && M > 2 && rounds == 1 && tile >= 0.92 * stripe;
+    if (group != 64 && group % 128 != 0) return false;
+    if (!aligned) return M > 2 && rounds <= 3 && tile >= 1.3 * stripe;
+    const bool one = (rounds == 1 || (rounds == 2 && M > 2)) && (k <= 12288 || tile >= 0.9);
+    return tile >= (one ? 0.92 : 1.1) * stripe;
 }
 
 // LDS a STRIPE workgroup needs for a slice of gps groups, and the most it may use.
@@ -441,7 +441,7 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
     const int G = K / group;
     const bool automatic = kernel == W4A16_KERNEL_AUTO && split == 0;
     if (kernel == W4A16_KERNEL_AUTO) {
-        // STRIPE: M = 1 from 4 MB of packed weights on, and at 2 to 4 rows, from 20 and 32 MB on, where the costs say so.  Below
+        // STRIPE: M = 1 from 4 MB of packed weights on, and at 2 to 4 rows, from 20 and 32 MB on, where TILE is not faster.  Below
         // these sizes it is TILE, many of whose plans there need no workspace: they are not to change for ones that share an accumulator.
         const double packed = 0.5 * (double)K * (double)N;
         bool stripe = (M == 1 && packed >= 4e6) || (M == 2 && packed >= 20e6) || (M <= 4 && packed >= 32e6);

@@ -114,8 +114,9 @@ def test_plans_are_well_formed(binding, M, N, K):
             in_acc = p["kernel"] in (binding.KERNEL_STRIPE, binding.KERNEL_TILE) and S <= 63 and S * M * N <= 640 * 1024
             want = 0 if S == 1 else (M * N * 8 if in_acc else S * M * N * 4)
             assert p["workspace_bytes"] == want
-            packed = 0.5 * K * N  # bytes of packed weights: the scheduler's STRIPE / TILE rule
-            auto = 3 if (M == 1 and packed >= 4e6) or (M == 2 and packed >= 20e6) or (M <= 4 and packed >= 32e6) else 4
+            packed = 0.5 * K * N  # bytes of packed weights: where STRIPE is a candidate (none of SHAPES has 2 to 4 rows there, see below)
+            assert not (M == 2 and packed >= 20e6) and not (M in (3, 4) and packed >= 32e6)
+            auto = 3 if M == 1 and packed >= 4e6 else 4
             assert p["kernel"] == (kernel if kernel != binding.KERNEL_AUTO else auto)
             tiles_n = -(-N // p["tile_n"])
             tiles_m = -(-M // p["tile_m"]) if p["kernel"] not in (binding.KERNEL_WAVE_SPLIT, binding.KERNEL_STRIPE) else 1
@@ -130,6 +131,29 @@ def test_plans_are_well_formed(binding, M, N, K):
             else:
                 assert p["threads"] == 1024 and p["waves_k"] == 16
     assert binding.workspace_bytes(M, N, K, 128) >= binding.query_plan(M, N, K, 128)["workspace_bytes"]
+
+
+# us, TILE's plan and STRIPE's: 2 to 4 rows on matrices where STRIPE is a candidate
+FEW_ROWS = [
+    # M, K, N, group, TILE, STRIPE
+    (4, 8192, 8192, 128, 9.1, 11.0), (4, 28672, 8192, 128, 22.4, 26.0), (2, 28672, 8192, 128, 22.7, 23.5),  # both fill the units, one round
+    (4, 29664, 8032, 32, 27.8, 27.7), (2, 16160, 7296, 32, 15.7, 15.0),  # groups of 32: from 3 rows on
+    (4, 13568, 31840, 128, 37.7, 42.2), (4, 5376, 31744, 128, 17.7, 19.2), (2, 15360, 24576, 1024, 41.5, 35.8),  # two rounds: from 3 rows on
+    (4, 33280, 14336, 256, 47.9, 44.8),  # long slices, units idle
+    (3, 9216, 36512, 1024, 32.8, 46.6), (2, 13568, 43264, 256, 54.5, 61.9), (2, 7808, 58368, 128, 43.2, 39.4),  # more rounds: STRIPE's units idle, or not
+    (2, 31360, 8408, 128, 37.5, 26.2), (2, 14336, 15624, 256, 25.6, 22.5), (3, 17920, 35664, 128, 76.1, 95.4),  # N no multiple of 32
+    (4, 15168, 13968, 96, 44.7, 24.4), (3, 24160, 15096, 160, 75.3, 37.9), (4, 15168, 15792, 192, 30.8, 25.9),  # units of one or two blocks
+    (4, 1152, 120656, 32, 32.1, 18.7), (4, 8192, 20480, 128, 23.8, 20.2), (2, 8192, 12288, 128, 12.9, 12.2),  # TILE's units idle
+]
+
+
+@pytest.mark.parametrize("M,K,N,group,tile,stripe", FEW_ROWS)
+def test_family_at_few_rows_is_the_faster_one(binding, M, K, N, group, tile, stripe):
+    """Both sides of every line of the rule, by times measured (within 2 % either will do)."""
+    for bf16 in (False, True):
+        kernel = binding.query_plan(M, N, K, group, bf16=bf16)["kernel"]
+        took, other = (tile, stripe) if kernel == binding.KERNEL_TILE else (stripe, tile)
+        assert took <= 1.02 * other, (kernel, took, other)
 
 
 def test_shapes_beyond_32_bit_offsets_are_refused(binding):
