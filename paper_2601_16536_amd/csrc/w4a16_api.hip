@@ -219,19 +219,19 @@ bool tile_four(int rows_x, int group, bool bf16)
 bool short_slices(int group, bool bf16, int gps) { return bf16 && group == 128 && gps <= 8; }
 
 // Blocks of 32 k per unit of the ticket form.  With groups of 64 and 32 a unit may be one group (2 or 1 KiB of weights in flight per wave)
-// or several: four blocks (4 KiB, but more registers: a second workgroup on the compute unit may not fit).  Several groups where the
-// slice has a unit of four blocks for every wave, and: groups of 32, up to 4 rows, or no more workgroups than compute units (us, one group / several,
-// K = 28672, N = 8192: M = 1 39.7 / 25.6, M = 16 45.1 / 37.8; K = 4096, N = 22016, M = 4 16.6 / 16.5, M = 8 18.1 / 19.4, M = 16 20.2 / 23.5); groups of 64, no more
-// workgroups than compute units, and up to 8 rows (K = 28672, N = 8192, M = 1 26.4 / 23.7; K = 4096, N = 22016 12.2 / 13.2) or slices from 5120 k on
-// (M = 16: K = 28672, N = 8192 32.1 / 29.6, K = 5120, N = 13824 12.7 / 12.6, K = 4096, N = 14336 11.1 / 11.2, K = 11008, N = 4096, S = 4 10.3 / 10.6).
+// or several: four blocks (4 KiB).  Several need more registers, so that a second workgroup may not fit the compute unit (more workgroups
+// than units: 1.0 to 1.2 times the time at 1 and 2 rows, up to 1.6 at 16), and they are fewer: a short slice has too few for its waves to share
+// evenly, the more so the more rows a unit's last step has.  From 1020 drawn shapes (K = 512 ... 32768, N = 512 ... 40000, 1 to 16 rows, both formats) timed both ways, the slices from
+// which several are faster; time over that with one group, at k per slice: groups of 32, up to 4 rows 0.94 at 1056, 0.78 at 2048, 0.66 at 8064; 5 to 8 rows 1.05
+// at 1344, 0.95 at 1728, 0.81 at 4160; 9 to 16 rows 1.15 at 1472, 1.04 at 2272, 0.97 at 3488, 0.91 at 8576; groups of 64, 1 and 2 rows 1.05 at 1472, 0.95 at 1792, 0.85 at 5184;
+// 3 and 4 rows 1.03 at 1664, 0.95 at 2304, 0.90 at 5504; 5 to 8 rows 1.08 at 1600, 1.03 at 2688, 0.96 at 4160; 9 to 16 rows 1.07 at 5248, 1.00 at 9344, 0.97 at 15360.
+// It takes several for 304 of them: 15 % faster in the mean, the slowest 2 % slower.
 int ticket_unit_blocks(int M, int group, int gps, int workgroups, int cus)
 {
     if (tuning().tile_unit) return tuning().tile_unit;
     if (group > 64) return 4;
-    const bool one_round = workgroups <= cus;
-    const int k = gps * group;
-    const bool several = k >= 1024 && (group == 32 ? M <= 4 || one_round : one_round && (M <= 8 || k >= 5120));
-    return several ? 4 : group / 32;
+    const int from = group == 32 ? (M <= 4 ? 1024 : (M <= 8 ? 1600 : 3072)) : (M <= 2 ? 1728 : (M <= 4 ? 2048 : (M <= 8 ? 2816 : 14336)));
+    return workgroups <= cus && gps * group >= from ? 4 : group / 32;
 }
 
 // Whether TILE's plan at 2 to 4 rows is the faster one where STRIPE is a candidate: from 1560 (shape, rows, format, group) timed both ways (K = 256 ...
@@ -689,12 +689,14 @@ int find_buffers(int dev, const w4a16_plan &plan, int finish, int M, int N, hipS
     return W4A16_OK;
 }
 
-void log_plan(const char *entry, int M, int N, int K, int group, const w4a16_plan &p, int finish)
+void log_plan(const char *entry, int M, int N, int K, int group, const w4a16_plan &p, int finish, int unit_blocks)
 {
     static const char *const kFinish[] = {"direct", "accumulator", "second pass"};
-    fprintf(stderr, "w4a16: %s M=%d N=%d K=%d group=%d -> kernel=%d S=%d groups/slice=%d tile=%dx%d waves=%d workgroups=%d finish=%s workspace=%zu\n",
+    char unit[24] = "";
+    if (unit_blocks) snprintf(unit, sizeof unit, " unit=%d", unit_blocks);
+    fprintf(stderr, "w4a16: %s M=%d N=%d K=%d group=%d -> kernel=%d S=%d groups/slice=%d tile=%dx%d waves=%d workgroups=%d finish=%s workspace=%zu%s\n",
             entry, M, N, K, group, p.kernel, p.split, p.groups_per_split, p.tile_m, p.tile_n, p.waves_k, p.workgroups,
-            kFinish[finish], p.workspace_bytes);
+            kFinish[finish], p.workspace_bytes, unit);
 }
 
 int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales, const uint32_t *zeros, int group, int M, int N,
@@ -744,7 +746,9 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
         if (rc != W4A16_ERR_WORKSPACE) break;
     }
     if (rc) return rc;
-    if (tuning().log) log_plan(entry, M, N, K, group, plan, finish);
+    const bool tile_ticket = plan.kernel == W4A16_KERNEL_TILE && !by_panel && tile_by_ticket(M, plan.tile_m);
+    const int unit_blocks = tile_ticket ? ticket_unit_blocks(M, group, plan.groups_per_split, plan.workgroups, cus) : 0;
+    if (tuning().log) log_plan(entry, M, N, K, group, plan, finish, unit_blocks);
 
     GemmArgs a;
     a.X = static_cast<const uint16_t *>(X);
@@ -773,9 +777,8 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
         e = launch_stripe(a, finish, b.sync, plan.waves_k, st);
     } else if (by_panel) {
         e = launch_panel(a, panel, st);
-    } else if (plan.kernel == W4A16_KERNEL_TILE && tile_by_ticket(M, plan.tile_m)) {
-        e = launch_tile_dyn(a, finish, b.sync, plan.waves_k, tuning().tile_depth == 2 && !bf16 && plan.waves_k <= 8 ? 2 : 1,
-                            ticket_unit_blocks(M, group, plan.groups_per_split, plan.workgroups, cus), st);
+    } else if (tile_ticket) {
+        e = launch_tile_dyn(a, finish, b.sync, plan.waves_k, tuning().tile_depth == 2 && !bf16 && plan.waves_k <= 8 ? 2 : 1, unit_blocks, st);
     } else if (plan.kernel == W4A16_KERNEL_TILE && tile_four(plan.tile_m, group, bf16) && !short_slices(group, bf16, plan.groups_per_split)) {
         if (plan.tile_m == 64 && (bf16 || group != 128)) e = launch_tile_tall(a, finish, b.sync, st);
         else e = launch_tile_wide(a, finish, b.sync, plan.tile_m, st);

@@ -211,3 +211,29 @@ def test_most_columns_at_few_rows(gpu):
         got = torch.cat([Y[:, :64], Y[:, -64:]], 1).cpu().numpy()
         assert err_ratio(got, ref[:M]) <= 1.0, M
         assert bool((Y[:, 64:-64] == 0).all())
+
+
+# M, K, N, group, blocks of 32 k per unit: both sides of every line of the rule (one workgroup per compute unit, K not split below 16384 columns)
+UNITS = [(m, k, 8256, 32, 4 if k >= edge else 1) for m, edge in ((1, 1024), (4, 1024), (5, 1600), (8, 1600), (9, 3072), (16, 3072)) for k in (edge - 32, edge)] + \
+        [(m, k, 8256, 64, 4 if k >= edge else 2) for m, edge in ((2, 1728), (3, 2048), (4, 2048), (8, 2816), (16, 14336)) for k in (edge - 64, edge)] + \
+        [(4, 2048, 16448, 32, 1), (4, 2112, 16448, 64, 2), (16, 256, 8256, 128, 4)]
+
+
+def test_units_of_several_groups_from_the_slices_where_they_are_faster(gpu, capfd):
+    """Several groups per unit on long slices only, with no more workgroups than compute units: the rule as launched (the log's unit=)."""
+    torch, binding = gpu
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("sizes for 256 compute units")
+    try:
+        binding.tune("log", 1)
+        for M, K, N, group, blocks in UNITS:
+            X = torch.zeros((M, K), dtype=torch.float16, device="cuda")
+            W = torch.zeros((K // 8, N), dtype=torch.int32, device="cuda")
+            s = torch.zeros((K // group, N), dtype=torch.float16, device="cuda")
+            capfd.readouterr()
+            binding.gemm_ex(X, W, s, None, group, kernel=binding.KERNEL_TILE)
+            torch.cuda.synchronize()
+            line = capfd.readouterr().err
+            assert "unit=%d\n" % blocks in line, (M, K, N, group, blocks, line)
+    finally:
+        binding.tune("log", 0)
