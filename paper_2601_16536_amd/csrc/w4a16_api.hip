@@ -476,12 +476,14 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
         S = (G + gps - 1) / gps;
         if (stripe_lds(M, group, gps, wmin) > stripe_lds_max(M)) return W4A16_ERR_UNSUPPORTED;
         if (S > 65535) return W4A16_ERR_UNSUPPORTED;  // a grid dimension of the many-row form
-        // Waves: the many-row form's should get at least four blocks of 16 k each, eight at most.  The ticket form (M <= 4) has eight
-        // however short its slice: they stage it together and their sums meet cheaply (M = 1, us, two or four waves for a slice of one or two groups
-        // / eight: K = 2048, N = 4096 5.5 / 4.4; K = N = 4096 5.3 / 4.9; K = 6144, N = 1536 5.1 / 4.6; ten or twelve: within 3 % where the slice is long,
-        // slower where it is short).
-        const long long nblocks = (long long)gps * (group / 16);
-        int waves = stripe_by_ticket(M) ? 8 : (int)(nblocks / 4);
+        // Waves: at least four blocks of 16 k each, eight at most.  The ticket form (M <= 4) has eight however short its slice, where its workgroups
+        // are alone on their compute units: they stage the slice together and their sums meet cheaply (M = 1, us, two or four waves for a slice of
+        // one or two groups / eight: K = 2048, N = 4096 5.5 / 4.4; K = N = 4096 5.3 / 4.9; K = 6144, N = 1536 5.1 / 4.6; ten or twelve: within 3 % where the
+        // slice is long, slower where it is short).  Several workgroups of few waves share a unit better (K = 128, N = 199992, two / eight 5.9 / 7.1;
+        // M = 4, K = 256, N = 164072, four / eight 9.3 / 10.4), but for two of one or two waves each (M = 4, K = 128, N = 90888 7.7 / 6.2).
+        const long long nblocks = (long long)gps * (group / 16), wgs = tiles * S;
+        const bool eight = stripe_by_ticket(M) && (wgs <= cus || (wgs <= 2 * cus && nblocks <= 8));
+        int waves = eight ? 8 : (int)(nblocks / 4);
         const int wbest = stripe_by_ticket(M) ? 8 : (wmax > 12 ? 12 : wmax);
         waves = waves < wmin ? wmin : (waves > wbest ? wbest : waves);
         if (tuning().stripe_waves >= wmin && tuning().stripe_waves <= wmax) waves = tuning().stripe_waves;

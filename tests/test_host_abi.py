@@ -156,6 +156,15 @@ def test_family_at_few_rows_is_the_faster_one(binding, M, K, N, group, tile, str
         assert took <= 1.02 * other, (kernel, took, other)
 
 
+@pytest.mark.parametrize("M,K,N,group,waves", [
+    (1, 2048, 4096, 128, 8), (1, 4096, 4096, 128, 8), (1, 256, 65536, 256, 8), (4, 896, 9648, 128, 8),  # a compute unit for each
+    (1, 256, 65688, 128, 4), (1, 320, 67208, 64, 5), (4, 256, 164072, 256, 4), (1, 512, 65688, 128, 8),  # four blocks of 16 k per wave
+    (1, 128, 131072, 128, 8), (4, 128, 90888, 128, 8), (1, 128, 131328, 128, 2), (2, 64, 238880, 64, 1), (1, 160, 65688, 32, 2)])
+def test_waves_of_a_short_stripe(binding, M, K, N, group, waves):
+    """STRIPE by ticket: eight waves where every workgroup has a compute unit, or two of 128 k share one; else by the length of the slice."""
+    assert binding.query_plan(M, N, K, group, kernel=binding.KERNEL_STRIPE)["waves_k"] == waves
+
+
 def test_shapes_beyond_32_bit_offsets_are_refused(binding):
     """The kernels address X with 32-bit byte offsets: M K 2 >= 2^31 - 2^24 bytes answers W4A16_ERR_UNSUPPORTED
     from every family, before anything touches a GPU."""
