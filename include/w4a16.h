@@ -132,7 +132,9 @@ int w4a16_gemm(const void *X, const uint32_t *Wpacked, const void *scales, const
  * w4a16_kernel (its block sizes; AUTO = choose), `split` the split factor S
  * (0 = choose; otherwise 1 <= S <= K/group; the library lowers it so that no
  * slice is empty, and raises it where a slice would not fit a workgroup's LDS
- * or a 31-bit buffer: w4a16_query_plan tells).  For sweeps and tests.
+ * or a 31-bit buffer: w4a16_query_plan tells).  AUTO with the split of the
+ * scheduler's own plan is that plan; with another one, 2 to 4 rows on matrices
+ * where STRIPE is a candidate run as STRIPE.  For sweeps and tests.
  */
 int w4a16_gemm_ex(const void *X, const uint32_t *Wpacked, const void *scales, const uint32_t *zeros,
                   int group, int M, int N, int K, void *Y, void *stream, int kernel, int split);

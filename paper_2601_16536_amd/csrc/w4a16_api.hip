@@ -445,7 +445,11 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
         // these sizes it is TILE, many of whose plans there need no workspace: they are not to change for ones that share an accumulator.
         const double packed = 0.5 * (double)K * (double)N;
         bool stripe = (M == 1 && packed >= 4e6) || (M == 2 && packed >= 20e6) || (M <= 4 && packed >= 32e6);
-        if (stripe && automatic && M >= 2 && tile_beats_stripe(M, N, K, group, cus)) stripe = false;
+        if (stripe && M >= 2 && tile_beats_stripe(M, N, K, group, cus)) {
+            // The scheduler's own plan, or one asked for again by its S.  With another S it is STRIPE, whose workgroups TILE has four of.
+            w4a16_plan own;
+            stripe = split != 0 && !(make_plan(M, N, K, group, W4A16_KERNEL_TILE, 0, cus, &own, nullptr, bf16) == W4A16_OK && own.split == split);
+        }
         kernel = stripe ? W4A16_KERNEL_STRIPE : W4A16_KERNEL_TILE;
     }
     if (kernel != W4A16_KERNEL_WAVE_SPLIT && kernel != W4A16_KERNEL_STRIPE && kernel != W4A16_KERNEL_TILE)

@@ -156,6 +156,17 @@ def test_family_at_few_rows_is_the_faster_one(binding, M, K, N, group, tile, str
         assert took <= 1.02 * other, (kernel, took, other)
 
 
+@pytest.mark.parametrize("M,K,N,group", [f[:4] for f in FEW_ROWS] + [(M, K, N, 128) for N, K in ((4096, 14336), (8192, 28672), (1024, 4096))
+                                                                     for M in (1, 2, 4, 8, 16)])
+def test_the_schedulers_split_asks_for_its_own_plan(binding, M, K, N, group):
+    """kernel = AUTO with the split that AUTO's plan reports is that plan; another split of a shape at 2 to 4 rows is STRIPE's."""
+    for bf16 in (False, True):
+        p = binding.query_plan(M, N, K, group, bf16=bf16)
+        assert binding.query_plan(M, N, K, group, split=p["split"], bf16=bf16) == p
+        if M in (2, 3, 4) and 0.5 * K * N >= 32e6 and p["kernel"] == binding.KERNEL_TILE and p["split"] < K // group:
+            assert binding.query_plan(M, N, K, group, split=p["split"] + 1, bf16=bf16)["kernel"] == binding.KERNEL_STRIPE
+
+
 @pytest.mark.parametrize("M,K,N,group,waves", [
     (1, 2048, 4096, 128, 8), (1, 4096, 4096, 128, 8), (1, 256, 65536, 256, 8), (4, 896, 9648, 128, 8),  # a compute unit for each
     (1, 256, 65688, 128, 4), (1, 320, 67208, 64, 5), (4, 256, 164072, 256, 4), (1, 512, 65688, 128, 8),  # four blocks of 16 k per wave
