@@ -97,9 +97,9 @@ __device__ __forceinline__ float apply_scale_zero(float tot, float s, float z, f
 // final sum may have 2^49; an infinity or a NaN stays one.
 // One FP64 FMA into a sum that starts at 1.5 2^52 would multiply, round and add in three vector instructions per output instead of
 // five, but it sends a contribution halfway between two whole numbers to the even SUM (a factor on the scale only moves these
-// halves elsewhere: 1 + 2^-40 to the odd multiples of 2^39, values of 32768) and is whole up to 2^51 only.  It was no faster: us for a step of
-// several layers, FMA / as here: M = 1, K = 28672, N = 8192 47.6 / 47.7; M = 4, K = 4096, N = 11008, BF16 71.9 / 71.5; M = 8, K = 28672, N = 8192
-// 50.1 / 50.2; M = 16, K = 14336, N = 4096 80.0 / 80.0.
+// halves elsewhere: 1 + 2^-40 to the odd multiples of 2^39, values of 32768) and is whole up to 2^51 only.  us, with it / as here: steps of several
+// layers, M = 1, K = 28672, N = 8192 47.6 / 47.7; M = 4, K = 4096, N = 11008, BF16 71.9 / 71.5; M = 8, K = 28672, N = 8192 50.1 / 50.2; M = 16, K = 14336,
+// N = 4096 80.0 / 80.0; where workgroups of 16 rows run in several rounds it saves 4 to 8 % (K = 5120, N = 20864, BF16 18.9 / 20.0).
 constexpr float kFixScale = 16777216.0f;  // 2^24
 struct UnitScales {
     float sp, sz;  // 2^24 kCodeScale s (FP16: 2^48 s, P carries 2^-24) and -2^24 s (z + kCodeOffset), exact both
