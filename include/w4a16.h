@@ -50,7 +50,8 @@
  * used by every call on that device, so two calls that overlap in time on one
  * device (on different streams) race on them unless each passes its own
  * workspace through w4a16_gemm_ws.  Results are bitwise reproducible for a fixed
- * shape and plan.
+ * shape and plan (up to 16 rows: while the partial sums of a workgroup's waves,
+ * whose shares of K differ from run to run, stay within +-2^25).
  */
 #ifndef W4A16_H
 #define W4A16_H
