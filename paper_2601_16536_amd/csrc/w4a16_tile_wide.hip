@@ -9,19 +9,21 @@
 // just before their MFMAs, 95 vector instructions and 20 MFMAs per block, one kind after the other, and the waves
 // wait a quarter of their time.  With four waves a wave has 512 registers, enough to
 //   - keep the arithmetic exact and still drop the sum of x: the B operand is q - z as an exact FP16 integer
-//     (twelve vector instructions per word instead of five, but no fifth MFMA per four, no 2^-4 scaling of X,
+//     (ten vector instructions per word instead of five, but no fifth MFMA per four, no 2^-4 scaling of X,
 //     and Eq. 2's step is one FMA per output element and group, s (sum_k x_k (q_k - z)), instead of two);
 //   - put the step of one group between the first MFMAs of the next (tile by tile: step, then the MFMA that restarts
 //     the tile's sums);
 //   - unpack the next block's operands and fetch its X operands from LDS between the MFMAs of the current block;
 //   - keep two groups of weights in flight, and X three chunks ahead, loaded straight into LDS (loads return to a
 //     wave in the order it asked, so X must be asked for as far ahead as the weights that were asked for just before).
+// Cold, K = N = 8192: M = 128 25.2 us, M = 64 (32 rows) 18.0; with an unpack in twelve instructions (a byte copied into both halves
+// of a register, masked under an exponent, minus 1024 + z and 64 + z) 27.5 and 18.9; M = 40, K = 4096, N = 11008: 13.9 and 14.7.
 // Arithmetic: products x (q - z) are exact in FP32, sums over a group in FP32 inside the MFMA, times s in FP32: the
 // same values as the eight-wave form up to the order of the FP32 sums.
 #include "w4a16_device.h"
 #include "w4a16_finish.h"
 #include "w4a16_internal.h"
-#include <type_traits>
+#include "w4a16_wide_ops.h"
 
 namespace w4a16 {
 namespace {
@@ -56,7 +58,7 @@ struct Wide {
     // at the start, for the first chunk: the first group's scales, zero points and weights (6), three chunks of X, the
     // second group's (6), and the first refill (3) were asked for after it
     static constexpr int kWaitFirst = 15 + 3 * kLoadsPerChunk;
-    // vector instructions the schedule puts ahead of every MFMA: 48 per block for the next block's operands, and in a
+    // vector instructions the schedule puts ahead of every MFMA: 40 per block for the next block's operands, and in a
     // group's first block 16 RT more for the step of the group before
     static constexpr int kValuFirst = RT == 4 ? 7 : 11, kValu = RT == 4 ? 3 : 6;
 };
@@ -78,34 +80,27 @@ __device__ __forceinline__ void group_scales(GroupConst &g, uint2_t sc)
     g.s[3] = (float)s23.h[1];
 }
 
-// FP16.  Byte e of a column's word holds the codes of k = 2e (bits 0-3) and 2e + 1 (bits 4-7); copied into both
-// halves of a register and left where they are, under the exponent of 1024 (unit in the last place 1) and of 64 (unit
-// 2^-4, i.e. bits 4-7 count ones), they read 1024 + q and 64 + q; minus 1024 + z and 64 + z.  k ascending.
+// FP16: (q - z) 2^-9, unpacked in ten instructions (ExactF16, w4a16_wide_ops.h); the 2^9 goes into the scale.
 struct CodesF16 {
     typedef ActF16 Act;
-    static constexpr uint32_t kMask = 0x00F0000Fu, kMagic = 0x54006400u;
+    typedef ExactF16::Consts Consts;
     static __device__ __forceinline__ GroupConst group_const(uint2_t sc, uint32_t z)
     {
         GroupConst g;
         group_scales(g, sc);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) g.negz[c] = (((z >> (4 * c)) & 15u) * 0x00100001u) | 0xD400E400u;  // sign | 64 or 1024 | z in the bits that count ones
+        for (int c = 0; c < 4; ++c) {
+            g.negz[c] = ExactF16::zero(z >> (4 * c));
+            g.s[c] *= 512.0f;
+        }
         return g;
     }
-    static __device__ __forceinline__ ActF16::operand_t unpack(uint32_t w, uint32_t negz, uint32_t mask, uint32_t magic)
+    static __device__ __forceinline__ ActF16::operand_t unpack(uint32_t w, uint32_t negz, const Consts &k)
     {
-        H2 zv;
-        zv.u = negz;
+        ExactF16::Tmp t;
         H8 r;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            // byte selectors of v_perm_b32: 0-3 pick from the second operand, 0x0c gives zero: byte e into both halves
-            const uint32_t u = __builtin_amdgcn_perm(w, w, 0x0C000C00u + 0x00010001u * (uint32_t)e);
-            H2 t;
-            t.u = (u & mask) | magic;
-            t.h = t.h + zv.h;
-            r.u[e] = t.u;
-        }
+        for (int p = 0; p < ExactF16::kParts; ++p) ExactF16::unpack(p, w, negz, k, t, r.u);
         return r.h;
     }
 };
@@ -240,8 +235,7 @@ __global__ __launch_bounds__(64 * kWaves) void tile_wide_kernel(const GemmArgs a
                 x_fetch(3, 3);
             }
         }
-        uint32_t mask = Codes::kMask, magic = Codes::kMagic;
-        asm volatile("" : "+v"(mask), "+v"(magic));  // kept in vector registers: v_and_or_b32 has no room for two constants
+        const typename Codes::Consts consts = ExactF16::consts();
         const float4_t zero4 = {0.f, 0.f, 0.f, 0.f};
 
         // operands of the block in use and of the next one; the sums of the group in use
@@ -252,7 +246,7 @@ __global__ __launch_bounds__(64 * kWaves) void tile_wide_kernel(const GemmArgs a
         GroupConst gc = Codes::group_const(scq[0], (zwq[0] | zfill) >> zsh);
         float s_prev[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int c = 0; c < 4; ++c) bop[0][c] = Codes::unpack(wq[0][c], gc.negz[c], mask, magic);
+        for (int c = 0; c < 4; ++c) bop[0][c] = Codes::unpack(wq[0][c], gc.negz[c], consts);
         load_sz(0);     // the same place, and its first block, kRing groups on (past the run: zeros, no traffic)
         load_w(wq[0]);
 #pragma unroll
@@ -280,14 +274,14 @@ __global__ __launch_bounds__(64 * kWaves) void tile_wide_kernel(const GemmArgs a
                 // the next block's operands, independent of the MFMAs below
                 if (p + 1 < kBpg) {
 #pragma unroll
-                    for (int cc = 0; cc < 4; ++cc) bop[(p + 1) & 1][cc] = Codes::unpack(wq[R * kBpg + p + 1][cc], gc.negz[cc], mask, magic);
+                    for (int cc = 0; cc < 4; ++cc) bop[(p + 1) & 1][cc] = Codes::unpack(wq[R * kBpg + p + 1][cc], gc.negz[cc], consts);
                     load_w(wq[R * kBpg + p + 1]);  // the same block kRing groups on
                 } else {
 #pragma unroll
                     for (int cc = 0; cc < 4; ++cc) s_next[cc] = gc.s[cc];
                     gc = Codes::group_const(scq[RN], (zwq[RN] | zfill) >> zsh);  // the next group's first block
 #pragma unroll
-                    for (int cc = 0; cc < 4; ++cc) bop[0][cc] = Codes::unpack(wq[RN * kBpg][cc], gc.negz[cc], mask, magic);
+                    for (int cc = 0; cc < 4; ++cc) bop[0][cc] = Codes::unpack(wq[RN * kBpg][cc], gc.negz[cc], consts);
                     load_sz(RN);
                     load_w(wq[RN * kBpg]);
                 }
