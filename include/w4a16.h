@@ -101,7 +101,8 @@ typedef struct {
     int tile_n;            /* output columns per workgroup                                    */
     int tile_m;            /* output rows per workgroup                                       */
     int waves_k;           /* K slices inside a workgroup (waves whose results meet in LDS)   */
-    int workgroups;        /* workgroups of the multiply launch                               */
+    int workgroups;        /* workgroups of the multiply launch (tiles of 128 x 256 cut into pieces of
+                              their rows, "panel_pieces", counted as one)                     */
     int threads;           /* threads per workgroup                                           */
     size_t workspace_bytes;/* 64-bit sums [M, N] or FP32 partials [S, M, N]; 0 when S == 1.  tile_n = 256: FP32
                               partials of the split tiles, at most one tile (128 KiB) per compute unit            */
@@ -270,6 +271,8 @@ int w4a16_quantize(const void *W16, int group, int N, int K, uint32_t *Wpacked, 
  *   "panel"          M > 16, the scheduler's own plans: 1 = tiles of 128 rows x 256 columns wherever they can run, 2 = never
  *   "panel_split"    slices of those of these tiles that go past the last whole round of compute units (1 = none; where K
  *                    has as many)
+ *   "panel_pieces"   pieces of 128, 64 or 32 rows (1, 2, 4) that those tiles are cut into (where the last row block's tiles, if
+ *                    it is shorter, have as many rows)
  *   "log"            1: every w4a16_gemm* call prints its plan on stderr (the one case in which the library prints)
  * Returns W4A16_ERR_UNSUPPORTED for an unknown knob.
  */

@@ -67,6 +67,7 @@ struct Tuning {
     int tile_wide = 0;      // TILE at 32 or 64 rows of X per workgroup: 2 = the eight-wave form instead of the four-wave one
     int panel = 0;          // M > 16: 1 = always the four-wave 256-column form, 2 = never
     int panel_split = 0;    // its split of the tiles past the last whole round of compute units (1 = none)
+    int panel_pieces = 0;   // and the pieces of rows that it cuts them into (1, 2, 4)
     int log = 0;            // 1: every call prints its plan on stderr
 };
 
@@ -79,7 +80,7 @@ const Knob kKnobs[] = {
     {"stripe_unit", &Tuning::stripe_unit},     {"stripe_depth", &Tuning::stripe_depth}, {"stripe_dot2", &Tuning::stripe_dot2},
     {"tile_rows", &Tuning::tile_rows},         {"tile_dyn", &Tuning::tile_dyn},         {"tile_depth", &Tuning::tile_depth},
     {"tile_waves", &Tuning::tile_waves},       {"tile_wide", &Tuning::tile_wide},         {"tile_unit", &Tuning::tile_unit},
-    {"panel", &Tuning::panel},                 {"panel_split", &Tuning::panel_split},
+    {"panel", &Tuning::panel},                 {"panel_split", &Tuning::panel_split},     {"panel_pieces", &Tuning::panel_pieces},
     {"log", &Tuning::log},
 };
 
@@ -343,14 +344,19 @@ TileChoice choose_tiles(int M, int N, int K, int group, int split, int cus, bool
 
 // PANEL form (w4a16_panel.hip), for the scheduler's own plans beyond 16 rows: tiles of 128 x 256, the last row block of
 // 32, 64, 96 or 128 rows, one tile per compute unit at a time.  The tiles past the last whole round of compute units may be
-// cut into S slices of K that fill the units once more; their FP32 partials (at most one tile per unit, 32 MB) are summed
-// by a second launch.  Costs (us), fitted to 26 (shape, format, group) measured with and without the split (M = 129 ... 2048,
+// cut to fill the units once more: those of 128 rows into pieces of 64 or 32 rows, and all of them into S slices of K, whose FP32
+// partials (at most one tile per unit, 32 MB) are summed by a second launch.  Pieces of rows need no partials, or with slices
+// half or a quarter of them, but a word is unpacked once for each.  Costs (us), fitted to 26 (shape, format, group) measured with and without the split (M = 129 ... 2048,
 // K = 2048 ... 28672, N = 1024 ... 28672): a stage of 128 k 1.3 at 128 rows, 0.8, 0.6, 0.47 of that at 96, 64, 32 rows
 // (the unpack is the same work at any number of rows), a quarter and a half more with groups of 64 and 32 (more of Eq. 2's
-// steps), a tenth more for BF16; 3 per tile for its first loads and its stores; the second launch 5 and the partials at 3.5 TB/s.
+// steps), a tenth more for BF16; 3 per tile for its first loads and its stores; the second launch 5 and the partials at 3.5 TB/s.  A piece of 64 or 32 rows
+// takes 0.73 and 0.66 (BF16 0.77 and 0.7) of a stage: fitted to 12 shapes with every cut forced (M = 384, K = N = 5120: 60 tiles in 4 slices 33.9 us, 120 pieces
+// in 2 slices 33.6, 240 pieces of 32 rows 39.8; M = 1000, K = N = 4096, groups of 64: 47.3 in 2 slices, 43.1 in 256 pieces).  Pieces have to be 4 %
+// cheaper than slices alone.  Of 70 drawn shapes (M = 100 ... 2048) whose plan they change, against the plan before: 0.895 of its time
+// in the geometric mean (M = 567, K = 8192, N = 6720 86.7 -> 70.3; M = 777, K = 4096, N = 11008, BF16 83.5 -> 77.5; the best 0.56, the worst 1.04).
 double panel_cost(int M, int N, int K, int group, bool bf16, int cus, bool may_split, PanelPlan *p)
 {
-    static const double kRel[5] = {0.0, 0.47, 0.6, 0.8, 1.0};
+    static const double kRel[5] = {0.0, 0.47, 0.6, 0.8, 1.0}, kPieceRel[2][3] = {{0.0, 0.66, 0.73}, {0.0, 0.7, 0.77}};
     const double stage = 1.3 * (group == 32 ? 1.5 : (group == 64 ? 1.25 : 1.0)) * (bf16 ? 1.1 : 1.0);
     const double kStageUs[5] = {0.0, stage * kRel[1], stage * kRel[2], stage * kRel[3], stage};
     const double fixed = 3.0;
@@ -358,6 +364,7 @@ double panel_cost(int M, int N, int K, int group, bool bf16, int cus, bool may_s
     p->tiles_n = (N + kPanelCols - 1) / kPanelCols;
     p->last_rows = (M - (p->tiles_m - 1) * kPanelRows + 31) / 32 * 32;
     p->split_tiles = 0;
+    p->pieces = 1;
     p->split = 1;
     p->slice_k = K;
     const int unit = group < 128 ? 128 : group;  // slices begin at a group and at a whole stage
@@ -379,19 +386,30 @@ double panel_cost(int M, int N, int K, int group, bool bf16, int cus, bool may_s
     };
     double best = whole(tiles, K);
     const long long rest = tiles % cus, done = tiles - rest;
-    if (may_split && rest && units > 1 && tuning().panel_split != 1) {
+    if (rest) {
         const double before = whole(done, K);
-        const int smax = (int)(cus / rest) < units ? (int)(cus / rest) : units;
-        for (int s = 2; s <= smax && s <= 16; ++s) {
-            const int k = (units + s - 1) / s * unit;
-            if ((long long)k * (s - 1) >= K) continue;  // an empty slice
-            const double c = before + (double)((k + 127) / 128) * kStageUs[rest > small ? 4 : last_rt] + fixed + 5.0 +
-                             (double)rest * s * kPanelPartial * 4.0 / 3.5e6 * (rest > small ? 1.0 : last_rt / 4.0);
-            if (c < best || s == tuning().panel_split) {
-                best = s == tuning().panel_split ? 0.0 : c;
-                p->split_tiles = (int)rest;
-                p->split = s;
-                p->slice_k = k;
+        const int small_rest = (int)(rest < small ? rest : small), large_rest = (int)rest - small_rest;
+        const int want_split = tuning().panel_split, want_pieces = tuning().panel_pieces;
+        bool found = want_split <= 1 && want_pieces == 0;  // (a cut that was asked for is taken whatever it costs)
+        for (int pieces = 1; pieces <= 4; pieces *= 2) {
+            if (pieces > 1 && (large_rest == 0 || (small && p->last_rows != kPanelRows / pieces))) continue;
+            if (want_pieces && pieces != want_pieces) continue;
+            const int cut = large_rest * pieces + small_rest, rt = large_rest ? 4 / pieces : last_rt;
+            const int smax = (int)(cus / cut) < units ? (int)(cus / cut) : units;
+            for (int s = pieces > 1 ? 1 : 2; s <= smax && s <= 16; ++s) {
+                if ((s > 1 && (!may_split || want_split == 1)) || (want_split > 1 && s != want_split)) continue;
+                const int k = (units + s - 1) / s * unit;
+                if ((long long)k * (s - 1) >= K) continue;  // an empty slice
+                const double c = before + (double)((k + 127) / 128) * (pieces > 1 ? stage * kPieceRel[bf16][rt] : kStageUs[rt]) + fixed +
+                                 (s > 1 ? 5.0 + (double)cut * s * kPanelPartial * 4.0 / 3.5e6 * (rt / 4.0) : 0.0);
+                if (c < (pieces > 1 && p->pieces == 1 && found ? 0.96 : 1.0) * best || !found) {
+                    found = true;
+                    best = c;
+                    p->split_tiles = (int)rest;
+                    p->pieces = pieces;
+                    p->split = s;
+                    p->slice_k = s > 1 ? k : K;
+                }
             }
         }
     }
@@ -414,7 +432,7 @@ bool use_panel(int M, int N, int K, int group, bool bf16, int cus, bool may_spli
     // there it has to be 7 % cheaper, as the two models are together good for about that: of 160 FP16 shapes (M = 17, 32, 48, 64,
     // K = 4096 ... 28672, N = 1024 ... 8184, groups of 128) it is taken for 31 and faster on
     // every one, as on 150 drawn ones of 17 to 64 rows and below 8192 columns (22 % in the mean).
-    const double cost = panel_cost(M, N, K, group, bf16, cus, may_split, p), factor = M > 128 ? 1.0 : 0.93;
+    const double cost = panel_cost(M, N, K, group, bf16, cus, may_split, p), factor = M <= 128 ? 0.93 : (p->pieces > 1 ? 0.93 : 1.0);
     const int G = K / group;
     for (int r = 64; r >= 16; r /= 2) {
         const long long wgs = (long long)((N + 63) / 64) * ((M + r - 1) / r);
@@ -509,7 +527,7 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
         p->threads = 256;
         p->split = pp.split;
         p->groups_per_split = pp.slice_k / group;
-        p->workgroups = pp.tiles_m * pp.tiles_n + pp.split_tiles * (pp.split - 1);
+        p->workgroups = pp.tiles_m * pp.tiles_n + pp.split_tiles * (pp.split - 1);  // (the pieces of a tile's rows counted as one)
         p->workspace_bytes = (size_t)pp.split_tiles * (pp.split > 1 ? pp.split : 0) * kPanelPartial * sizeof(float);
         if (panel) *panel = pp;
         return W4A16_OK;

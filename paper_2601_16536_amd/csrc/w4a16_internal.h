@@ -71,8 +71,12 @@ constexpr size_t kPanelPartial = (size_t)kPanelRows * kPanelCols;  // floats of 
 struct PanelPlan {
     int tiles_m, tiles_n;
     int last_rows;    // rows of the last row block's tiles: 32, 64, 96 or 128
-    int split_tiles;  // the last so many tiles are cut into `split` slices of slice_k each, summed by a second launch
+    int split_tiles;  // the last so many tiles are cut: those of 128 rows into `pieces` of 128 / pieces rows each, and every
+    int pieces;       // piece into `split` slices of slice_k each, summed by a second launch (split > 1)
     int split, slice_k;
+    int small() const { return last_rows < kPanelRows ? tiles_n : 0; }                                   // tiles of the last row block, if it is shorter
+    int split_small() const { return split_tiles < small() ? split_tiles : small(); }                    // of the cut tiles
+    int cut() const { return (split_tiles - split_small()) * pieces + split_small(); }                   // pieces there are
 };
 // The lengths of group the PANEL form and the tall TILE form take: whole stages of 128 k, or a stage's whole parts.
 inline bool panel_takes(int group) { return group % 128 == 0 || group == 64 || group == 32; }

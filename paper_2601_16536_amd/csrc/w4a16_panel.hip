@@ -17,7 +17,7 @@
 //   - the order of instructions is written down slot by slot, one MFMA each.  Left to the compiler's scheduler the same
 //     loop took 243 us where this one takes 224 (M = 2048, K = N = 8192).
 // M = 2048, K = N = 8192: 224-232 us = 1.2 PFLOP/s (FP16; BF16 229-243), 656 us before; ten launches one after another under
-// the trace, where the power limit sets in: 231 rising to 266 (BF16 271 to 278, the first two 334 and 319).  The vendor's FP16 GEMM on dense weights takes 235-265.  M = 777, K = 4096, N = 11008: 80 us (BF16), 162 before.
+// the trace, where the power limit sets in: 231 rising to 266 (BF16 271 to 278, the first two 334 and 319).  The vendor's FP16 GEMM on dense weights takes 235-265.  M = 777, K = 4096, N = 11008: 77.5 us (BF16).
 // Arithmetic: products x (q - z) are exact in FP32, sums over a group in FP32 in the MFMA, times s in FP32: as in
 // w4a16_tile_wide.hip.
 #include "w4a16_device.h"
@@ -270,10 +270,18 @@ __device__ __forceinline__ void panel(const GemmArgs &a, unsigned char *const sm
 // Tiles are numbered blocks of 128 rows first, then the last block of 32 LAST rows (the shorter ones fill the compute
 // units that are left over); within the blocks of 128 rows, kRowGroup row blocks x all column tiles after one another,
 // row blocks fastest, so that neighbours share their weights and a few of them X.  The first `direct` tiles are done
-// whole, the others in a.split slices of K of `slice_k` each, which the second launch adds up.
+// whole.  The others are cut: those of 128 rows into `pieces` of 32 LAST rows (1: not), and each piece into a.split slices of K
+// of `slice_k` (1: none), which the second launch adds up.  Pieces of rows cost more unpack, slices their partials and the
+// launch: M = 1000, K = N = 4096, groups of 64 (128 tiles): 47.3 us in 2 slices, 43.1 in 256 pieces; M = 777, K = 4096, N = 11008, BF16 (2 tiles
+// of 128 rows and 43 of 32 past the first round): 84 in 5 slices, 77.5 in 51 pieces of 32 rows and 5 slices.
 struct TileOf {
     int m0, col0;
     bool last;
+};
+struct Cut {
+    int direct, large;  // whole tiles; tiles of 128 rows among the cut ones
+    int count;          // pieces
+    int pieces;         // of a tile of 128 rows
 };
 __device__ __forceinline__ TileOf tile_of(int id, int main_blocks, int ntiles)
 {
@@ -286,32 +294,44 @@ __device__ __forceinline__ TileOf tile_of(int id, int main_blocks, int ntiles)
     return {(band * kRowGroup + in_band - tile * band_rows) * 32 * kMainRt, tile * kCols, false};
 }
 
+__device__ __forceinline__ TileOf piece_of(const Cut &c, int id, int main_blocks, int ntiles)
+{
+    const int whole = c.large * c.pieces;
+    if (id >= whole) return tile_of(c.direct + c.large + id - whole, main_blocks, ntiles);
+    const int tile = id / c.pieces;
+    TileOf t = tile_of(c.direct + tile, main_blocks, ntiles);
+    t.m0 += (id - tile * c.pieces) * (kPanelRows / c.pieces);
+    t.last = c.pieces > 1;
+    return t;
+}
+
 template <typename Op, int LAST, int SEG>
-__global__ __launch_bounds__(64 * kWaves) void panel_kernel(const GemmArgs a, const int main_blocks, const int direct, const int split_tiles, const int slice_k)
+__global__ __launch_bounds__(64 * kWaves) void panel_kernel(const GemmArgs a, const int main_blocks, const Cut c, const int slice_k)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int ntiles = (a.N + kCols - 1) / kCols;
-    // Workgroup b runs on XCD b mod 8: an XCD takes a contiguous range of the whole tiles, then of the (tile, slice) pairs.
-    const int direct_per_xcd = (direct + kXcds - 1) / kXcds;
+    // Workgroup b runs on XCD b mod 8: an XCD takes a contiguous range of the whole tiles, then of the (piece, slice) pairs.
+    const int direct_per_xcd = (c.direct + kXcds - 1) / kXcds;
     const int xcd = (int)(blockIdx.x % kXcds);
-    int local = (int)(blockIdx.x / kXcds), id, kbeg = 0, kend = a.K;
+    int local = (int)(blockIdx.x / kXcds), kbeg = 0, kend = a.K;
     float *partial = nullptr;
+    TileOf t;
     if (local < direct_per_xcd) {
-        id = xcd * direct_per_xcd + local;
-        if (id >= direct) return;
+        const int id = xcd * direct_per_xcd + local;
+        if (id >= c.direct) return;
+        t = tile_of(id, main_blocks, ntiles);
     } else {
         local -= direct_per_xcd;
-        const int pairs = split_tiles * a.split, per_xcd = (pairs + kXcds - 1) / kXcds;
+        const int pairs = c.count * a.split, per_xcd = (pairs + kXcds - 1) / kXcds;
         const int pair = xcd * per_xcd + local;
         if (local >= per_xcd || pair >= pairs) return;
-        const int slice = pair / split_tiles;
-        id = pair - slice * split_tiles;
+        const int slice = pair / c.count, id = pair - slice * c.count;
+        t = piece_of(c, id, main_blocks, ntiles);
+        if (t.m0 >= a.M) return;  // a piece past the last row
         kbeg = slice * slice_k;
         kend = a.K - kbeg < slice_k ? a.K : kbeg + slice_k;
-        partial = a.partials + ((size_t)id * a.split + slice) * kPanelPartial;
-        id += direct;
+        if (a.split > 1) partial = a.partials + ((size_t)id * a.split + slice) * (kPanelPartial / c.pieces);
     }
-    const TileOf t = tile_of(id, main_blocks, ntiles);
     if constexpr (LAST != kMainRt) {
         if (t.last) {
             panel<Op, LAST, SEG>(a, smem, t.m0, t.col0, kbeg, kend, partial);
@@ -321,25 +341,26 @@ __global__ __launch_bounds__(64 * kWaves) void panel_kernel(const GemmArgs a, co
     panel<Op, kMainRt, SEG>(a, smem, t.m0, t.col0, kbeg, kend, partial);
 }
 
-// The second launch: Y of the split tiles, slices added in ascending order.  A workgroup takes four rows of a tile.
+// The second launch: Y of the cut tiles, slices added in ascending order.  A workgroup takes four rows of a piece.
 template <typename Act>
-__global__ __launch_bounds__(256) void panel_reduce_kernel(const GemmArgs a, const int main_blocks, const int direct)
+__global__ __launch_bounds__(256) void panel_reduce_kernel(const GemmArgs a, const int main_blocks, const Cut cut)
 {
-    const int ntiles = (a.N + kCols - 1) / kCols, idx = (int)(blockIdx.x / 32u);
-    const TileOf t = tile_of(direct + idx, main_blocks, ntiles);
-    const int r = (int)(blockIdx.x % 32u) * 4 + (int)(threadIdx.x >> 6), c = (int)(threadIdx.x & 63u) * 4;
+    const int ntiles = (a.N + kCols - 1) / kCols, parts = kPanelRows / 4 / cut.pieces, idx = (int)blockIdx.x / parts;
+    const TileOf t = piece_of(cut, idx, main_blocks, ntiles);
+    const int r = ((int)blockIdx.x - idx * parts) * 4 + (int)(threadIdx.x >> 6), c = (int)(threadIdx.x & 63u) * 4;
     if (t.m0 + r >= a.M || t.col0 + c >= a.N) return;
-    const float *p = a.partials + (size_t)idx * a.split * kPanelPartial + r * kCols + c;
+    const size_t stride = kPanelPartial / cut.pieces;
+    const float *p = a.partials + (size_t)idx * a.split * stride + r * kCols + c;
     float4_t acc = *reinterpret_cast<const float4_t *>(p);
     int s = 1;
     for (; s + 4 <= a.split; s += 4) {  // four loads in flight, added in slice order
         float4_t v[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = *reinterpret_cast<const float4_t *>(p + (size_t)(s + e) * kPanelPartial);
+        for (int e = 0; e < 4; ++e) v[e] = *reinterpret_cast<const float4_t *>(p + (size_t)(s + e) * stride);
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc += v[e];
     }
-    for (; s < a.split; ++s) acc += *reinterpret_cast<const float4_t *>(p + (size_t)s * kPanelPartial);
+    for (; s < a.split; ++s) acc += *reinterpret_cast<const float4_t *>(p + (size_t)s * stride);
     *reinterpret_cast<uint2_t *>(a.Y + (size_t)(t.m0 + r) * a.N + t.col0 + c) = (uint2_t){Act::pack2(acc[0], acc[1]), Act::pack2(acc[2], acc[3])};
 }
 
@@ -347,14 +368,14 @@ template <typename Op, int LAST, int SEG>
 hipError_t launch(const GemmArgs &a, const PanelPlan &p, hipStream_t stream)
 {
     const int main_blocks = p.tiles_m - (p.last_rows < kPanelRows ? 1 : 0);
-    const int direct = p.tiles_m * p.tiles_n - p.split_tiles;
-    const long long grid = (((long long)direct + kXcds - 1) / kXcds + ((long long)p.split_tiles * p.split + kXcds - 1) / kXcds) * kXcds;
+    const Cut cut = {p.tiles_m * p.tiles_n - p.split_tiles, p.split_tiles - p.split_small(), p.cut(), p.pieces};
+    const long long grid = (((long long)cut.direct + kXcds - 1) / kXcds + ((long long)cut.count * p.split + kXcds - 1) / kXcds) * kXcds;
     const int lds = main_blocks ? Panel<kMainRt, SEG>::kLds : Panel<LAST, SEG>::kLds;
     const void *const kernel = reinterpret_cast<const void *>(&panel_kernel<Op, LAST, SEG>);
     hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, Panel<kMainRt, SEG>::kLds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((panel_kernel<Op, LAST, SEG>), dim3((unsigned)grid), dim3(64 * kWaves), lds, stream, a, main_blocks, direct, p.split_tiles, p.slice_k);
-    if (p.split_tiles) hipLaunchKernelGGL((panel_reduce_kernel<typename Op::Act>), dim3((unsigned)p.split_tiles * 32u), dim3(256), 0, stream, a, main_blocks, direct);
+    hipLaunchKernelGGL((panel_kernel<Op, LAST, SEG>), dim3((unsigned)grid), dim3(64 * kWaves), lds, stream, a, main_blocks, cut, p.slice_k);
+    if (p.split > 1) hipLaunchKernelGGL((panel_reduce_kernel<typename Op::Act>), dim3((unsigned)(cut.count * (kPanelRows / 4 / p.pieces))), dim3(256), 0, stream, a, main_blocks, cut);
     return hipGetLastError();
 }
 
@@ -368,7 +389,7 @@ hipError_t launch_seg(const GemmArgs &a, const PanelPlan &p, hipStream_t stream)
 template <typename Op>
 hipError_t launch_op(const GemmArgs &a, const PanelPlan &p, hipStream_t stream)
 {
-    switch (p.last_rows) {
+    switch (p.pieces > 1 ? kPanelRows / p.pieces : p.last_rows) {
     case 32: return launch_seg<Op, 1>(a, p, stream);
     case 64: return launch_seg<Op, 2>(a, p, stream);
     case 96: return launch_seg<Op, 3>(a, p, stream);
@@ -383,9 +404,11 @@ hipError_t launch_panel(const GemmArgs &a, const PanelPlan &p, hipStream_t strea
     if (!panel_takes(a.group) || p.tiles_m != (a.M + kPanelRows - 1) / kPanelRows || p.tiles_n != (a.N + kPanelCols - 1) / kPanelCols) return hipErrorInvalidValue;
     if (p.last_rows % 32 || p.last_rows < a.M - (p.tiles_m - 1) * kPanelRows || p.last_rows > kPanelRows) return hipErrorInvalidValue;
     if (p.split_tiles < 0 || p.split_tiles > p.tiles_m * p.tiles_n || a.split != p.split) return hipErrorInvalidValue;
+    // pieces of the rows that the last row block's tiles have, if there are any
+    if ((p.pieces != 1 && p.pieces != 2 && p.pieces != 4) || (p.pieces > 1 && p.last_rows < kPanelRows && p.last_rows != kPanelRows / p.pieces)) return hipErrorInvalidValue;
     // slices cover K, none is empty, each begins at a group and at a whole stage of scales
-    if (p.split_tiles && (!a.partials || p.split < 2 || p.slice_k % a.group || (a.group < kStage && p.slice_k % kStage) ||
-                          (long long)p.slice_k * (p.split - 1) >= a.K || (long long)p.slice_k * p.split < a.K)) return hipErrorInvalidValue;
+    if (p.split < 1 || (p.split > 1 && (!a.partials || !p.split_tiles || p.slice_k % a.group || (a.group < kStage && p.slice_k % kStage))) ||
+        (long long)p.slice_k * (p.split - 1) >= a.K || (long long)p.slice_k * p.split < a.K) return hipErrorInvalidValue;
     if (a.K / 8 * (unsigned long long)a.N * 4ull >= 0x7F000000ull || (unsigned long long)a.M * a.K * 2ull >= 0x7F000000ull) return hipErrorInvalidValue;  // 32-bit buffer offsets
     return a.bf16 ? launch_op<ExactBF16>(a, p, stream) : launch_op<ExactF16>(a, p, stream);
 }

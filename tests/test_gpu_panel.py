@@ -92,6 +92,37 @@ def test_panel_against_the_oracle(gpu, M, K, N, group):
         binding.tune("panel_split", 0)
 
 
+# Tiles of 128 rows cut into pieces of 64 and 32: a last row block of as many rows, none, and pieces that begin at or end past the last row
+PIECES = [(2, 192, 1024, 264, 64), (2, 256, 640, 520, 128), (2, 225, 832, 248, 64), (4, 160, 1056, 512, 32), (4, 128, 1280, 264, 256),
+          (4, 97, 384, 72, 128), (4, 481, 640, 1032, 128), (2, 320, 2048, 768, 128)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("pieces,M,K,N,group", PIECES)
+def test_panel_pieces_of_rows_against_the_oracle(gpu, pieces, M, K, N, group):
+    torch, binding = gpu
+    X, Wp, s, Zp = wl.make(M, K, N, index=9700 + M + K, group=group, outliers=True)
+    Xb = wl.make_x_bf16(M, K, index=9700 + M + K)
+    _, dW, dS, dZ = binding.to_device(X, Wp, s, Zp)
+    cases = [(torch.from_numpy(X).cuda(), orc.gemm(X, Wp, s, Zp, group)),
+             (torch.from_numpy(Xb.view(np.int16)).cuda().view(torch.bfloat16), orc.gemm_bf16(Xb, Wp, s, Zp, group))]
+    binding.tune("panel", 1)
+    binding.tune("panel_pieces", pieces)
+    try:
+        for split in (1, 2, 3):
+            binding.tune("panel_split", split)
+            for x, ref in cases:
+                say("panel pieces", pieces, (M, K, N, group), "split", split, x.dtype)
+                assert binding.query_plan(M, N, K, group, bf16=x.dtype == torch.bfloat16)["split"] == split
+                Y = torch.full((M + 1, N), 7.0, dtype=x.dtype, device="cuda")  # a row beyond: not written
+                (binding.gemm_bf16 if x.dtype == torch.bfloat16 else binding.gemm)(x, dW, dS, dZ, group, out=Y[:M])
+                torch.cuda.synchronize()
+                assert err_ratio(Y[:M].double().cpu().numpy(), ref) <= 1.0 and (Y[M] == 7.0).all()
+    finally:
+        for knob in ("panel", "panel_pieces", "panel_split"):
+            binding.tune(knob, 0)
+
+
 @pytest.mark.gpu
 def test_panel_whole_numbers_and_rows_that_are_not_finite(gpu):
     """Scales that are powers of two and small whole X: every output is exact.  A row of NaN or infinities stays in its own
