@@ -51,7 +51,7 @@ struct Panel {
     static constexpr int kPerStage = kXLoads + kWLoads + kSLoads + 1;
     static constexpr int kStageBytes = kXBytes + kWaves * (kWBytes + kSBytes + kZBytes);
     static constexpr int kLds = kBuffers * kStageBytes;
-    static_assert(kLds <= 160 * 1024 && 2 * kPerStage < 64, "LDS of a compute unit, and the wait counter's range");
+    static_assert(kLds <= 160 * 1024 && 2 * kPerStage < 64 && (kBuffers + 1) * kStage / 8 <= 64, "LDS of a compute unit, and the wait counter's range");
 };
 
 // One workgroup's part: rows m0 .. m0 + 32 RT - 1, 256 columns from tile_col0 on, k from kbeg to kend.  The result goes to
@@ -76,7 +76,7 @@ __device__ __forceinline__ void panel(const GemmArgs &a, unsigned char *const sm
     const uint32_t row_x = (uint32_t)a.K * 2u, row_w = (uint32_t)a.N * 4u, row_s = (uint32_t)a.N * 2u, row_z = (uint32_t)(a.N >> 3) * 4u;
     const int grp0 = kbeg / a.group;
     const uint32_t ngroups = (uint32_t)(klen / a.group);
-    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.X) + (size_t)m0 * a.K + kbeg, 0, (uint32_t)rows_here * row_x - (uint32_t)kbeg * 2u, kRawBuffer);
+    __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.X) + (size_t)m0 * a.K + kbeg, 0, (uint32_t)rows_here * row_x - (uint32_t)kbeg * 2u, kRawBuffer);
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(a.Wp) + (size_t)(kbeg >> 3) * a.N, 0, (uint32_t)(klen >> 3) * row_w, kRawBuffer);
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.scales) + (size_t)grp0 * a.N, 0, ngroups * row_s, kRawBuffer);
     const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(a.Zp) + (size_t)grp0 * (a.N >> 3), 0, zero_point_bytes(a.Zp, ngroups * row_z), kRawBuffer);
@@ -117,7 +117,9 @@ __device__ __forceinline__ void panel(const GemmArgs &a, unsigned char *const sm
                 const int left = klen - fetched * kStage;  // k from this stage's start to the slice's end
                 o0 = xg[0] + (uint32_t)fetched * 256u;
                 o1 = xg[1] + (uint32_t)fetched * 256u;
-                if (left < kStage) {  // the slice ends inside this stage: X beyond it must read as zero, also where it is another row's
+                if constexpr (SEG == kStage) {  // slices are whole stages: past the last one nothing is to be fetched
+                    if (left <= 0) rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.X), 0, 0u, kRawBuffer);
+                } else if (left < kStage) {  // the slice ends inside this stage: X beyond it must read as zero, also where it is another row's
                     if ((int)xp[0] * 8 >= left) o0 = kOutOfRange;
                     if ((int)xp[1] * 8 >= left) o1 = kOutOfRange;
                 }
@@ -126,7 +128,7 @@ __device__ __forceinline__ void panel(const GemmArgs &a, unsigned char *const sm
         } else if (i < Sh::kXLoads + Sh::kWLoads) {
             const int q = i - Sh::kXLoads;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_ptr_t)(lds_w + buf * Sh::kWBytes + q * 1024), 16, vw + (uint32_t)q * 4u * row_w, 0, 0, 0);
-            if (q == Sh::kWLoads - 1 && vw != kOutOfRange) vw += 16u * row_w;
+            if (q == Sh::kWLoads - 1) vw += 16u * row_w;  // (columns past N stay out of range: panel_offsets_fit)
         } else if (i < Sh::kPerStage - 1) {
             const int q = i - Sh::kXLoads - Sh::kWLoads;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(lds_s + buf * (Sh::kSBytes + Sh::kZBytes) + q * 256), 4, vs + (uint32_t)q * 2u * row_s, 0, 0, 0);
@@ -138,8 +140,8 @@ __device__ __forceinline__ void panel(const GemmArgs &a, unsigned char *const sm
                 if (srem < a.group) ds = dz = 0u;
                 else srem = 0;
             }
-            if (vs != kOutOfRange) vs += ds;
-            if (vz != kOutOfRange) vz += dz;
+            vs += ds;
+            vz += dz;
             ++fetched;
         }
     };
@@ -409,7 +411,7 @@ hipError_t launch_panel(const GemmArgs &a, const PanelPlan &p, hipStream_t strea
     // slices cover K, none is empty, each begins at a group and at a whole stage of scales
     if (p.split < 1 || (p.split > 1 && (!a.partials || !p.split_tiles || p.slice_k % a.group || (a.group < kStage && p.slice_k % kStage))) ||
         (long long)p.slice_k * (p.split - 1) >= a.K || (long long)p.slice_k * p.split < a.K) return hipErrorInvalidValue;
-    if (a.K / 8 * (unsigned long long)a.N * 4ull >= 0x7F000000ull || (unsigned long long)a.M * a.K * 2ull >= 0x7F000000ull) return hipErrorInvalidValue;  // 32-bit buffer offsets
+    if (!panel_offsets_fit(a.K, a.N) || (unsigned long long)a.M * a.K * 2ull >= 0x7F000000ull) return hipErrorInvalidValue;  // 32-bit buffer offsets
     return a.bf16 ? launch_op<ExactBF16>(a, p, stream) : launch_op<ExactF16>(a, p, stream);
 }
 
