@@ -107,6 +107,8 @@ __device__ __forceinline__ void reduce_and_finish(const GemmArgs &a, const int f
             }
         }
     }
+    const int rows_here = a.M - row0 < ROWS ? a.M - row0 : ROWS;  // (64 rows of 2^22 columns stay below 2^31 bytes)
+    const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(finish == kFinishSecondPass ? a.partials + ((size_t)slice * a.M + row0) * a.N : nullptr, 0, (uint32_t)rows_here * (uint32_t)a.N * 4u, kRawBuffer);
 #pragma unroll
     for (int k = 0; k < kOwn; ++k) {
         const int o = tid + k * nthreads;
@@ -117,7 +119,7 @@ __device__ __forceinline__ void reduce_and_finish(const GemmArgs &a, const int f
             if (finish == kFinishDirect)
                 *reinterpret_cast<uint2_t *>(a.Y + out) = (uint2_t){Act::pack2(v[k][0], v[k][1]), Act::pack2(v[k][2], v[k][3])};
             else
-                *reinterpret_cast<float4_t *>(a.partials + (size_t)slice * a.M * a.N + out) = v[k];
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4_t, v[k]), rp, ((uint32_t)(m - row0) * (uint32_t)a.N + (uint32_t)col) * 4u, 0, kWriteThrough);
         } else {
             const float sum = v[k][0];
             const bool nan = sum != sum;

@@ -263,7 +263,7 @@ __device__ __forceinline__ void panel(const GemmArgs &a, unsigned char *const sm
             if (m >= a.M) continue;
             const float v0 = tot[rt][i], v1 = tot[RT + rt][i];
             if (partial)
-                *reinterpret_cast<float2 *>(partial + (m - m0) * kCols + (col - tile_col0)) = make_float2(v0, v1);
+                store_partial(partial + (m - m0) * kCols + (col - tile_col0), v0, v1);
             else
                 *reinterpret_cast<uint32_t *>(a.Y + (size_t)m * a.N + col) = Act::pack2(v0, v1);
         }

@@ -312,7 +312,7 @@ __global__ __launch_bounds__(64 * kWaves) void tile_tall_kernel(const GemmArgs a
         if (finish == kFinishDirect)
             *reinterpret_cast<uint32_t *>(a.Y + out) = Act::pack2(v[0], v[1]);
         else
-            *reinterpret_cast<float2_v *>(a.partials + (size_t)slice * a.M * a.N + out) = v;
+            store_partial(a.partials + (size_t)slice * a.M * a.N + out, v[0], v[1]);
     }
 }
 

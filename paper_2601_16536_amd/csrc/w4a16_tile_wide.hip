@@ -368,6 +368,8 @@ __global__ __launch_bounds__(64 * kWaves) void tile_wide_kernel(const GemmArgs a
     for (int u = 0; u < 4 * kRT; ++u)
         if (u / kRT != wave) own_space[u * 64 + lane] = mine4[u >> 2][u & 3];
     __syncthreads();
+    const int rows_here = a.M - m0 < kRowsX ? a.M - m0 : kRowsX;  // (64 rows of 2^22 columns stay below 2^31 bytes)
+    const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(finish == kFinishDirect ? nullptr : a.partials + ((size_t)slice * a.M + m0) * a.N, 0, (uint32_t)rows_here * (uint32_t)a.N * 4u, kRawBuffer);
 #pragma unroll
     for (int u = 0; u < 4 * kRT; ++u) {
         if (u / kRT != wave) continue;  // uniform
@@ -384,7 +386,7 @@ __global__ __launch_bounds__(64 * kWaves) void tile_wide_kernel(const GemmArgs a
         if (finish == kFinishDirect)
             *reinterpret_cast<uint2_t *>(a.Y + out) = (uint2_t){Act::pack2(v[0], v[1]), Act::pack2(v[2], v[3])};
         else
-            *reinterpret_cast<float4_t *>(a.partials + (size_t)slice * a.M * a.N + out) = v;
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4_t, v), rp, ((uint32_t)(m - m0) * (uint32_t)a.N + (uint32_t)col) * 4u, 0, kWriteThrough);
     }
 }
 
