@@ -38,7 +38,6 @@ namespace {
 
 constexpr int kTileCols = 64;
 constexpr int kBlockRows = 4;   // packed rows per block: one MFMA step of 32 k
-constexpr int kXcds = 8;
 
 template <int RT>
 struct Shape {
@@ -70,13 +69,8 @@ __global__ __launch_bounds__(512) void tile_kernel(const GemmArgs a, const int f
     const int units = ntiles * a.split;
     // (integer divisions cost dozens of dependent scalar instructions each, all ahead of the first load:
     // the common cases take none)
-    int rb = 0, unit = (int)blockIdx.x;
-    if (row_blocks > 1) {
-        const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
-        rb = local % row_blocks;
-        unit = (local / row_blocks) * kXcds + xcd;
-    }
-    if (unit >= units) return;  // the grid is rounded up to whole XCD rounds
+    int unit, rb;
+    if (!place_of(units, row_blocks, &unit, &rb)) return;
     int tile = unit, slice = 0;
     if (a.split > 1) {
         slice = unit / ntiles;
@@ -305,13 +299,8 @@ __global__ __launch_bounds__(512) void tile_group_kernel(const GemmArgs a, const
     const int units = ntiles * a.split;
     // (integer divisions cost dozens of dependent scalar instructions each, all ahead of the first load:
     // the common cases take none)
-    int rb = 0, unit = (int)blockIdx.x;
-    if (row_blocks > 1) {
-        const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
-        rb = local % row_blocks;
-        unit = (local / row_blocks) * kXcds + xcd;
-    }
-    if (unit >= units) return;  // the grid is rounded up to whole XCD rounds
+    int unit, rb;
+    if (!place_of(units, row_blocks, &unit, &rb)) return;
     int tile = unit, slice = 0;
     if (a.split > 1) {
         slice = unit / ntiles;
@@ -534,7 +523,7 @@ bool prepare(const GemmArgs &a, int rows_x, int waves, int loop, Launch *l)
     const int ntiles = (a.N + kTileCols - 1) / kTileCols;
     l->row_blocks = (a.M + rows_x - 1) / rows_x;
     const long long units = (long long)ntiles * a.split;
-    const long long grid = (units + kXcds - 1) / kXcds * kXcds * l->row_blocks;
+    const long long grid = place_grid(units, l->row_blocks);
     if (grid > 0x7FFFFFFF) return false;
     l->grid = (int)grid;
     return true;

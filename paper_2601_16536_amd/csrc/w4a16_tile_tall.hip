@@ -25,7 +25,6 @@ namespace w4a16 {
 namespace {
 
 constexpr int kTileCols = 64;
-constexpr int kXcds = 8;
 constexpr int kWaves = 4;
 
 // Sizes for RT blocks of 32 rows and SEG k per step of scales.
@@ -58,17 +57,11 @@ __global__ __launch_bounds__(64 * kWaves) void tile_tall_kernel(const GemmArgs a
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, half = lane >> 5;
 
-    // workgroup -> (column tile, K slice, row block): the row blocks of one (tile, slice) are neighbours on one XCD
-    // (workgroup b runs on XCD b mod 8) and start together: the second reader finds the weights in that XCD's L2
+    // workgroup -> (column tile, K slice, row block)
     const int ntiles = (a.N + kTileCols - 1) / kTileCols;
     const int units = ntiles * a.split;
-    int rb = 0, unit = (int)blockIdx.x;
-    if (row_blocks > 1) {
-        const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
-        rb = local % row_blocks;
-        unit = (local / row_blocks) * kXcds + xcd;
-    }
-    if (unit >= units) return;  // the grid is rounded up to whole XCD rounds
+    int unit, rb;
+    if (!place_of(units, row_blocks, &unit, &rb)) return;
     int tile = unit, slice = 0;
     if (a.split > 1) {
         slice = unit / ntiles;
@@ -322,7 +315,7 @@ hipError_t launch(const GemmArgs &a, int finish, unsigned long long *sync, hipSt
     typedef Tall<RT, SEG> Sh;
     const int ntiles = (a.N + kTileCols - 1) / kTileCols;
     const int row_blocks = (a.M + Sh::kRows - 1) / Sh::kRows;
-    const long long grid = ((long long)ntiles * a.split + kXcds - 1) / kXcds * kXcds * row_blocks;
+    const long long grid = place_grid((long long)ntiles * a.split, row_blocks);
     if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&tile_tall_kernel<Op, RT, SEG>), hipFuncAttributeMaxDynamicSharedMemorySize, Sh::kLds);  // beyond the default dynamic-LDS allowance
     if (e != hipSuccess) return e;

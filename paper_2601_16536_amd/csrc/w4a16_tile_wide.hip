@@ -31,7 +31,6 @@ namespace {
 constexpr int kTileCols = 64;
 constexpr int kBlockRows = 4;   // packed rows per block: one MFMA step of 32 k
 constexpr int kBpg = 4;         // blocks per group (group = 128)
-constexpr int kXcds = 8;
 constexpr int kWaves = 4;
 constexpr int kRing = 2;        // groups of weights in flight per wave (registers): eight blocks, about 3 us, ahead
 constexpr int kChunkBlocks = 2; // blocks per staged chunk of X: whole 128-byte lines of a row
@@ -127,17 +126,11 @@ __global__ __launch_bounds__(64 * kWaves) void tile_wide_kernel(const GemmArgs a
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g4 = lane >> 4, j = lane & 15;
 
-    // workgroup -> (column tile, K slice, row block): the row blocks of one (tile, slice) are neighbours on one XCD
-    // (workgroup b runs on XCD b mod 8) and start together: the second reader finds the weights in that XCD's L2
+    // workgroup -> (column tile, K slice, row block)
     const int ntiles = (a.N + kTileCols - 1) / kTileCols;
     const int units = ntiles * a.split;
-    int rb = 0, unit = (int)blockIdx.x;
-    if (row_blocks > 1) {
-        const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
-        rb = local % row_blocks;
-        unit = (local / row_blocks) * kXcds + xcd;
-    }
-    if (unit >= units) return;  // the grid is rounded up to whole XCD rounds
+    int unit, rb;
+    if (!place_of(units, row_blocks, &unit, &rb)) return;
     int tile = unit, slice = 0;
     if (a.split > 1) {
         slice = unit / ntiles;
@@ -400,7 +393,7 @@ hipError_t launch_rt(const GemmArgs &a, int finish, unsigned long long *sync, hi
     const size_t lds = stage > red ? stage : red;
     const int ntiles = (a.N + kTileCols - 1) / kTileCols;
     const int row_blocks = (a.M + Sh::kRowsX - 1) / Sh::kRowsX;
-    const long long grid = ((long long)ntiles * a.split + kXcds - 1) / kXcds * kXcds * row_blocks;
+    const long long grid = place_grid((long long)ntiles * a.split, row_blocks);
     if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&tile_wide_kernel<CodesF16, RT>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);  // beyond the default dynamic-LDS allowance
     if (e != hipSuccess) return e;
