@@ -268,11 +268,15 @@ int w4a16_quantize(const void *W16, int group, int N, int K, uint32_t *Wpacked, 
  *   "tile_waves"     waves per TILE workgroup (4..8)
  *   "tile_wide"      2: TILE at 32 or 64 rows of X per workgroup: the eight-wave form instead of
  *                    the four-wave one
- *   "panel"          M > 16, the scheduler's own plans: 1 = tiles of 128 rows x 256 columns wherever they can run, 2 = never
+ *   "panel"          M > 16, the scheduler's own plans: 1 = tiles of 128 rows x 256 columns wherever they can run, 2 = never (nor
+ *                    those of 128 columns, if "pair" does not ask for them)
  *   "panel_split"    slices of those of these tiles that go past the last whole round of compute units (1 = none; where K
  *                    has as many)
  *   "panel_pieces"   pieces of 128, 64 or 32 rows (1, 2, 4) that those tiles are cut into (where the last row block's tiles, if
  *                    it is shorter, have as many rows)
+ *   "pair"           M > 16, the scheduler's own plans: 1 = tiles of 32 or 64 rows ("tile_rows") x 128 columns wherever they can
+ *                    run, 2 = never
+ *   "pair_split"     their slices of K
  *   "log"            1: every w4a16_gemm* call prints its plan on stderr (the one case in which the library prints)
  * Returns W4A16_ERR_UNSUPPORTED for an unknown knob.
  */

@@ -29,7 +29,7 @@ FLAGS = [
 # Per-file additions.  The four-wave tile kernel reads its MFMA results back with vector instructions (Eq. 2's step per
 # group): with the results in accumulation registers, the compiler's default under register pressure, every read costs
 # a v_accvgpr_read first.
-FILE_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for f in ("w4a16_tile_wide.hip", "w4a16_tile_tall.hip", "w4a16_panel.hip")}
+FILE_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for f in ("w4a16_tile_wide.hip", "w4a16_tile_tall.hip", "w4a16_panel.hip", "w4a16_pair.hip")}
 
 
 def sources():

@@ -68,6 +68,8 @@ struct Tuning {
     int panel = 0;          // M > 16: 1 = always the four-wave 256-column form, 2 = never
     int panel_split = 0;    // its split of the tiles past the last whole round of compute units (1 = none)
     int panel_pieces = 0;   // and the pieces of rows that it cuts them into (1, 2, 4)
+    int pair = 0;           // M > 16: 1 = always the eight-wave 128-column form, 2 = never
+    int pair_split = 0;     // its split of K
     int log = 0;            // 1: every call prints its plan on stderr
 };
 
@@ -81,6 +83,7 @@ const Knob kKnobs[] = {
     {"tile_rows", &Tuning::tile_rows},         {"tile_dyn", &Tuning::tile_dyn},         {"tile_depth", &Tuning::tile_depth},
     {"tile_waves", &Tuning::tile_waves},       {"tile_wide", &Tuning::tile_wide},         {"tile_unit", &Tuning::tile_unit},
     {"panel", &Tuning::panel},                 {"panel_split", &Tuning::panel_split},     {"panel_pieces", &Tuning::panel_pieces},
+    {"pair", &Tuning::pair},                   {"pair_split", &Tuning::pair_split},
     {"log", &Tuning::log},
 };
 
@@ -416,12 +419,12 @@ double panel_cost(int M, int N, int K, int group, bool bf16, int cus, bool may_s
     return 3.0 + best;
 }
 
-bool use_panel(int M, int N, int K, int group, bool bf16, int cus, bool may_split, PanelPlan *p)
+bool use_panel(int M, int N, int K, int group, bool bf16, int cus, bool may_split, PanelPlan *p, double *p_cost)
 {
     if (tuning().panel == 2 || !panel_takes(group) || !fits_32bit_offsets(M, N, K, group, K / group) || !panel_offsets_fit(K, N)) return false;
     if ((long long)((M + kPanelRows - 1) / kPanelRows) * ((N + kPanelCols - 1) / kPanelCols) > (1 << 24)) return false;  // a launch's blocks
     if (tuning().panel == 1 && M > 16) {
-        (void)panel_cost(M, N, K, group, bf16, cus, may_split, p);
+        *p_cost = panel_cost(M, N, K, group, bf16, cus, may_split, p);
         return true;
     }
     if (M <= 16) return false;
@@ -432,7 +435,7 @@ bool use_panel(int M, int N, int K, int group, bool bf16, int cus, bool may_spli
     // there it has to be 7 % cheaper, as the two models are together good for about that: of 160 FP16 shapes (M = 17, 32, 48, 64,
     // K = 4096 ... 28672, N = 1024 ... 8184, groups of 128) it is taken for 31 and faster on
     // every one, as on 150 drawn ones of 17 to 64 rows and below 8192 columns (22 % in the mean).
-    const double cost = panel_cost(M, N, K, group, bf16, cus, may_split, p), factor = M <= 128 ? 0.93 : (p->pieces > 1 ? 0.93 : 1.0);
+    const double cost = *p_cost = panel_cost(M, N, K, group, bf16, cus, may_split, p), factor = M <= 128 ? 0.93 : (p->pieces > 1 ? 0.93 : 1.0);
     const int G = K / group;
     for (int r = 64; r >= 16; r /= 2) {
         const long long wgs = (long long)((N + 63) / 64) * ((M + r - 1) / r);
@@ -446,7 +449,60 @@ bool use_panel(int M, int N, int K, int group, bool bf16, int cus, bool may_spli
     return true;
 }
 
-// How much workspace a plan may ask for.  kBest: whatever pays.  kUnsplit: a plan of the PANEL form splits no tiles.
+// PAIR form (w4a16_pair.hip), for the scheduler's own plans beyond 16 rows: tiles of 32 or 64 rows x 128 columns, K in S slices, at
+// most as many workgroups as compute units where there are several.  Costs (us), fitted to 230 timings of 110 drawn shapes (M = 17 ... 700,
+// K = 2048 ... 28672, N = 1024 ... 28672), 6 % off in the mean: a round 5.8 (launch, first loads, the sums) and 1.3 to 2.7 per stage of 128 k of
+// a quarter of the slice; slices 1.4 and the partials at 1.9 TB/s.
+double pair_cost(int M, int N, int K, int group, bool bf16, int cus, int rows, int S)
+{
+    static const double kStageUs[2][2][3] = {{{1.3, 1.45, 1.77}, {1.6, 1.5, 2.03}}, {{1.75, 2.06, 2.42}, {1.99, 2.22, 2.7}}};  // rows, format, group
+    const int G = K / group, gps = (G + S - 1) / S;
+    S = (G + gps - 1) / gps;
+    const long long wgs = (long long)((N + kPairCols - 1) / kPairCols) * ((M + rows - 1) / rows) * S, rounds = (wgs + cus - 1) / cus;
+    const long long stages = ((long long)gps * group + 511) / 512;
+    return 0.3 + (double)rounds * (5.8 + (double)stages * kStageUs[rows == 64][bf16][group == 32 ? 2 : (group == 64 ? 1 : 0)]) +
+           (S > 1 ? 1.4 + (double)S * M * N * 4.0 / 1.9e6 : 0.0);
+}
+
+// Whether the PAIR form's cheapest plan is cheaper than PANEL's, where that is the plan so far (of cost `cost`), or the 64-column tiles':
+// by 4 % (PANEL's by 7, up to 128 rows by 13), as the models are good for about that; groups of 32 and 64 at up to 32 rows are dearer in 64-column tiles than
+// their model has it; and FP16 with groups of 128, whose 64-column tiles are the fast ones, gives up a plan that needs no memory for
+// one that does for a clear gain only.  Of 306 drawn shapes (17 to 700 rows, every format and group) 75 go to PAIR: 0.850 of their time before in the
+// geometric mean, 0.56 (M = 387, K = 2304, N = 2704, groups of 32) to 1.06 (M = 117, K = 16128, N = 1864, groups of 32).
+bool use_pair(int M, int N, int K, int group, bool bf16, int cus, bool by_panel, double cost, TileChoice *c)
+{
+    const int G = K / group, want = tuning().pair, want_rows = tuning().tile_rows, want_split = tuning().pair_split;
+    if (want == 2 || !panel_takes(group)) return false;
+    const Tuning &t = tuning();
+    if (want != 1 && (want_rows || t.tile_wide || t.panel || t.panel_split || t.panel_pieces)) return false;  // 64-column tiles, or PANEL, are asked for
+    c->cost = 1e30;
+    for (int rows = 32; rows <= 64; rows += 32) {
+        if ((rows == 64 && M <= 32) || (want == 1 && want_rows && rows != want_rows)) continue;
+        const long long w1 = (long long)((N + kPairCols - 1) / kPairCols) * ((M + rows - 1) / rows);
+        if (w1 > (1 << 24)) continue;
+        int smax = (int)(cus / w1);
+        smax = smax < 1 ? 1 : (smax > G ? G : smax);
+        for (int s = 1; s <= smax; s = next_split(G, s)) {
+            const int S = want_split ? (want_split < G ? want_split : G) : s, gps = (G + S - 1) / S;
+            if (!fits_32bit_offsets(M, N, K, group, gps)) continue;
+            const double t = pair_cost(M, N, K, group, bf16, cus, rows, S);
+            if (t < c->cost) *c = {rows, (G + gps - 1) / gps, t};
+        }
+    }
+    if (c->cost >= 1e30) return false;
+    if (want == 1) return true;
+    double factor = by_panel ? (M > 128 ? 0.93 : 0.87) : 0.96;
+    if (!by_panel) {
+        const TileChoice t = choose_tiles(M, N, K, group, 0, cus, bf16, false);
+        const long long wgs = (long long)((N + 63) / 64) * ((M + t.rows - 1) / t.rows) * t.S;
+        cost = t.cost + (M > 128 ? 3.5 * (double)((wgs - 1) / cus) : 0.0);
+        if (group < 128 && t.rows <= 32) factor = 1.05;
+        if (!bf16 && group == 128 && t.S == 1 && c->S > 1) factor = 0.84;
+    }
+    return c->cost < factor * cost;
+}
+
+// How much workspace a plan may ask for.  kBest: whatever pays.  kUnsplit: a plan of the PANEL form splits no tiles, and none is of the PAIR form.
 // kFrugal: 64-column tiles only, split so that the slices of up to 640 K adds meet in the accumulator: many of these plans
 // need nothing, the others 8 bytes per output where kBest may take the FP32 partials of all slices.  kBare: 64-column tiles
 // and S = 1, no workspace at all.  The last three differ from kBest for the scheduler's own plans beyond 16 rows only.
@@ -519,7 +575,22 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
         return fits_32bit_offsets(M, N, K, group, gps) ? W4A16_OK : W4A16_ERR_UNSUPPORTED;
     }
     PanelPlan pp;
-    if (automatic && thrift < kFrugal && use_panel(M, N, K, group, bf16, cus, thrift == kBest, &pp)) {
+    double cost = 0.0;
+    const bool by_panel = automatic && thrift < kFrugal && use_panel(M, N, K, group, bf16, cus, thrift == kBest, &pp, &cost);
+    TileChoice pair;
+    if (automatic && thrift == kBest && M > 16 && use_pair(M, N, K, group, bf16, cus, by_panel, cost, &pair)) {
+        p->kernel = W4A16_KERNEL_TILE;
+        p->tile_n = kPairCols;
+        p->tile_m = pair.rows;
+        p->waves_k = 4;
+        p->threads = 512;
+        p->split = pair.S;
+        p->groups_per_split = (G + pair.S - 1) / pair.S;
+        p->workgroups = (N + kPairCols - 1) / kPairCols * ((M + pair.rows - 1) / pair.rows) * pair.S;
+        p->workspace_bytes = pair.S > 1 ? (size_t)pair.S * M * N * sizeof(float) : 0;
+        return W4A16_OK;
+    }
+    if (by_panel) {
         p->kernel = W4A16_KERNEL_TILE;
         p->tile_n = kPanelCols;
         p->tile_m = kPanelRows;
@@ -739,7 +810,7 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
     const int cus = compute_units(dev);
     w4a16_plan plan;
     PanelPlan panel;
-    bool by_panel = false;
+    bool by_panel = false, by_pair = false;
     int finish = kFinishDirect;
     Buffers b;
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -763,14 +834,15 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
         if (rc) return rc;
         if (only_free && plan.workspace_bytes != 0) continue;  // (never kFrugal's)
         by_panel = plan.kernel == W4A16_KERNEL_TILE && plan.tile_n == kPanelCols;
-        finish = by_panel ? (plan.split > 1 ? kFinishSecondPass : kFinishDirect)
+        by_pair = plan.kernel == W4A16_KERNEL_TILE && plan.tile_n == kPairCols;
+        finish = by_panel || by_pair ? (plan.split > 1 ? kFinishSecondPass : kFinishDirect)
                           : finish_of(plan.kernel, M, N, plan.split, burst_rows(plan.tile_m, group, bf16, thrift == kFrugal));
         t_hip_error[0] = 0;
         rc = find_buffers(dev, plan, finish, M, N, st, src, call_ws, call_ws_bytes, &b);
         if (rc != W4A16_ERR_WORKSPACE) break;
     }
     if (rc) return rc;
-    const bool tile_ticket = plan.kernel == W4A16_KERNEL_TILE && !by_panel && tile_by_ticket(M, plan.tile_m);
+    const bool tile_ticket = plan.kernel == W4A16_KERNEL_TILE && !by_panel && !by_pair && tile_by_ticket(M, plan.tile_m);
     const int unit_blocks = tile_ticket ? ticket_unit_blocks(M, group, plan.groups_per_split, plan.workgroups, cus) : 0;
     if (tuning().log) log_plan(entry, M, N, K, group, plan, finish, unit_blocks);
 
@@ -801,6 +873,8 @@ int run(const char *entry, const void *X, const uint32_t *Wp, const void *scales
         e = launch_stripe(a, finish, b.sync, plan.waves_k, st);
     } else if (by_panel) {
         e = launch_panel(a, panel, st);
+    } else if (by_pair) {
+        e = launch_pair(a, finish, plan.tile_m, st);
     } else if (tile_ticket) {
         e = launch_tile_dyn(a, finish, b.sync, plan.waves_k, tuning().tile_depth == 2 && !bf16 && plan.waves_k <= 8 ? 2 : 1, unit_blocks, st);
     } else if (plan.kernel == W4A16_KERNEL_TILE && tile_four(plan.tile_m, group, bf16) && !short_slices(group, bf16, plan.groups_per_split)) {
@@ -867,7 +941,7 @@ size_t w4a16_scratch_bytes(int M, int N, int K, int group, int bf16)
         if (g_dev[dev].user_ws) return 0;
     }
     if (make_plan(M, N, K, group, W4A16_KERNEL_AUTO, 0, compute_units(dev), &p, nullptr, bf16 != 0)) return 0;
-    const bool by_panel = p.kernel == W4A16_KERNEL_TILE && p.tile_n == kPanelCols;
+    const bool by_panel = p.kernel == W4A16_KERNEL_TILE && (p.tile_n == kPanelCols || p.tile_n == kPairCols);
     if (!by_panel && finish_of(p.kernel, M, N, p.split, burst_rows(p.tile_m, group, bf16 != 0, false)) != kFinishSecondPass) return 0;
     return p.workspace_bytes;
 }

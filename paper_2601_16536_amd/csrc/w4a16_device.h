@@ -240,7 +240,7 @@ constexpr int kWriteThrough = 16;  // the same as a buffer store's cache policy
 // Workgroup -> (unit, row block): a unit is a column tile and K slice, whose row blocks read the same weights.  Workgroup b runs on
 // XCD b mod 8; every XCD takes an eighth of the (unit, row block) pairs, in order, the row blocks of a unit next to each other: they are on
 // one XCD (but for those at an eighth's ends) and start together, and the second reader finds the weights in that XCD's L2.  (Whole
-// units per XCD leave some of them more workgroups than compute units: M = 263, K = 2560, N = 6320, 50 units of 5 row blocks of 64, are 250 workgroups,
+// units per XCD leave some of them more workgroups than compute units: 50 column tiles of 5 row blocks are 250 workgroups,
 // but 35 on two of the XCDs, a second round.)  One row block: units in launch order.  False: nothing to do (the grid is
 // rounded up to whole rounds of XCDs).  M = 300, K = 4096, N = 3200, BF16: 29.3 -> 16.6 us; M = 190, K = 8192, N = 5376 48.8 -> 25.9; M = 48,
 // K = 4096, N = 5376 (16 rows) 14.0 -> 9.8; K = N = 8192 (whole eighths either way) the same.

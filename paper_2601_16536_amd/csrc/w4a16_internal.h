@@ -84,6 +84,9 @@ inline bool panel_takes(int group) { return group % 128 == 0 || group == 64 || g
 // rows), and those of columns past N begin at 2^31.
 inline bool panel_offsets_fit(int K, int N) { return (K / 8 + 64ull) * N * 4ull < 0x7F000000ull; }
 hipError_t launch_panel(const GemmArgs &a, const PanelPlan &p, hipStream_t stream);
+// PAIR form of the TILE family (17 rows and more): tiles of 32 or 64 rows x 128 columns (w4a16_pair.hip); `finish`: no accumulator.
+constexpr int kPairCols = 128;
+hipError_t launch_pair(const GemmArgs &a, int finish, int rows_x, hipStream_t stream);
 // TILE family at 64 rows of X per workgroup, BF16 and groups other than 128: four waves per workgroup, each alone on its SIMD
 // (w4a16_tile_tall.hip).
 hipError_t launch_tile_tall(const GemmArgs &a, int finish, unsigned long long *sync, hipStream_t stream);
