@@ -96,7 +96,7 @@ __global__ __launch_bounds__(64 * kWaves) void tile_tall_kernel(const GemmArgs a
         const uint32_t row_x = (uint32_t)a.K * 2u, row_w = (uint32_t)a.N * 4u, row_s = (uint32_t)a.N * 2u, row_z = (uint32_t)(a.N >> 3) * 4u;
         const int grp0 = kbeg / a.group;
         const uint32_t ngroups = (uint32_t)(klen / a.group);
-        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.X) + (size_t)m0 * a.K + kbeg, 0, (uint32_t)rows_here * row_x - (uint32_t)kbeg * 2u, kRawBuffer);
+        __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.X) + (size_t)m0 * a.K + kbeg, 0, (uint32_t)rows_here * row_x - (uint32_t)kbeg * 2u, kRawBuffer);
         const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(a.Wp) + (size_t)(kbeg >> 3) * a.N, 0, (uint32_t)(klen >> 3) * row_w, kRawBuffer);
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.scales) + (size_t)grp0 * a.N, 0, ngroups * row_s, kRawBuffer);
         const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(a.Zp) + (size_t)grp0 * (a.N >> 3), 0, zero_point_bytes(a.Zp, ngroups * row_z), kRawBuffer);
@@ -118,7 +118,9 @@ __global__ __launch_bounds__(64 * kWaves) void tile_tall_kernel(const GemmArgs a
             if (i == 0) {
                 o0 = xg[0] + (uint32_t)xk * 2u;
                 o1 = xg[1] + (uint32_t)xk * 2u;
-                if (klen - xk < kStage) {  // the run ends inside this stage or before it
+                if constexpr (SEG == kStage) {  // runs are whole stages: past the last one nothing is to be fetched
+                    if (xk >= klen) rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.X), 0, 0u, kRawBuffer);
+                } else if (klen - xk < kStage) {  // the run ends inside this stage or before it
                     if (xk + (int)xp[0] * 8 >= klen) o0 = kOutOfRange;
                     if (xk + (int)xp[1] * 8 >= klen) o1 = kOutOfRange;
                 }
@@ -153,15 +155,13 @@ __global__ __launch_bounds__(64 * kWaves) void tile_tall_kernel(const GemmArgs a
                         if (srem < a.group) ds = dz = 0u;
                         else srem = 0;
                     }
-                    if (vs != kOutOfRange) {
-                        vs += ds;
-                        vz += dz;
-                    }
+                    vs += ds;  // (columns past N stay out of range: a run is a quarter of 2 GiB at most)
+                    vz += dz;
                 }
             } else {
                 const int ks = i - 2 * kSegs;
                 wq[place][ks] = __builtin_amdgcn_raw_buffer_load_b64(rw, vw + (uint32_t)ks * 2u * row_w, 0, 2);  // nontemporal
-                if (ks == kSteps - 1 && vw != kOutOfRange) vw += 16u * row_w;
+                if (ks == kSteps - 1) vw += 16u * row_w;
             }
         };
 
