@@ -2,8 +2,8 @@
 // has w4a16_tile_wide.hip, BF16 with groups of 128 and slices of up to 1024 k the eight-wave w4a16_tile.hip): one workgroup of four waves per (64-column tile, 64 rows of X, K slice), every wave alone on its
 // SIMD with a quarter of the slice's K and the whole 64 x 64 result.
 //
-// What bounds it: a stage (128 k) is 64 MFMAs 32x32x16, 160 vector instructions of unpack (FP16; 272 BF16), 64 of Eq. 2's step
-// and about 60 of addressing per wave, 0.77 us measured without the loads; the loads into LDS of X, which every wave
+// What bounds it: a stage (128 k) is 32 MFMAs 32x32x16, 160 vector instructions of unpack (FP16; 272 BF16), 64 of Eq. 2's step
+// and about 45 of addressing per wave, 0.77 us measured without the loads; the loads into LDS of X, which every wave
 // fetches for itself (64 KiB per workgroup and stage from the L2), and those of the weights bring that to 1.1 and 1.3 us.  So:
 //   - the operand is q - z, exact, in the order of k (w4a16_wide_ops.h: 10 vector instructions per word for FP16, 17 for
 //     BF16, which the eight-wave form unpacks to 128 + q and pays a fifth MFMA and a second FMA to correct): X needs no
