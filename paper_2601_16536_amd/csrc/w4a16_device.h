@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "w4a16_place.h"
 
 namespace w4a16 {
 
@@ -236,26 +237,5 @@ __device__ __forceinline__ void store_partial(float *p, float v0, float v1)
     __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), __builtin_bit_cast(unsigned long long, (pair_t){v0, v1}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 constexpr int kWriteThrough = 16;  // the same as a buffer store's cache policy
-
-// Workgroup -> (unit, row block): a unit is a column tile and K slice, whose row blocks read the same weights.  Workgroup b runs on
-// XCD b mod 8; every XCD takes an eighth of the (unit, row block) pairs, in order, the row blocks of a unit next to each other: they are on
-// one XCD (but for those at an eighth's ends) and start together, and the second reader finds the weights in that XCD's L2.  (Whole
-// units per XCD leave some of them more workgroups than compute units: 50 column tiles of 5 row blocks are 250 workgroups,
-// but 35 on two of the XCDs, a second round.)  One row block: units in launch order.  False: nothing to do (the grid is
-// rounded up to whole rounds of XCDs).  M = 300, K = 4096, N = 3200, BF16: 29.3 -> 16.6 us; M = 190, K = 8192, N = 5376 48.8 -> 25.9; M = 48,
-// K = 4096, N = 5376 (16 rows) 14.0 -> 9.8; K = N = 8192 (whole eighths either way) the same.
-constexpr int kPlaceXcds = 8;
-inline long long place_grid(long long units, int row_blocks) { return (units * row_blocks + kPlaceXcds - 1) / kPlaceXcds * kPlaceXcds; }
-__device__ __forceinline__ bool place_of(int units, int row_blocks, int *unit, int *rb)
-{
-    *unit = (int)blockIdx.x;
-    *rb = 0;
-    if (row_blocks > 1) {
-        const int per = (int)(gridDim.x / kPlaceXcds), id = (int)(blockIdx.x % kPlaceXcds) * per + (int)(blockIdx.x / kPlaceXcds);
-        *unit = id / row_blocks;
-        *rb = id - *unit * row_blocks;
-    }
-    return *unit < units;
-}
 
 }  // namespace w4a16

@@ -64,7 +64,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void pair_kernel(const GemmArgs a, 
     const int ntiles = (a.N + kPairCols - 1) / kPairCols;
     const int units = ntiles * a.split;
     int unit, rb;
-    if (!place_of(units, row_blocks, &unit, &rb)) return;
+    if (!place_in_eighths(blockIdx.x, gridDim.x, units, row_blocks, &unit, &rb)) return;
     const int slice = unit / ntiles, tile = unit - slice * ntiles;
     const int m0 = rb * Sh::kRows, col = tile * kPairCols + cw * kWaveCols + 2 * l32;
 
@@ -326,7 +326,7 @@ hipError_t launch(const GemmArgs &a, int finish, hipStream_t stream)
     typedef Pair<RT, SEG> Sh;
     const int ntiles = (a.N + kPairCols - 1) / kPairCols;
     const int row_blocks = (a.M + Sh::kRows - 1) / Sh::kRows;
-    const long long grid = place_grid((long long)ntiles * a.split, row_blocks);
+    const long long grid = eighths_grid((long long)ntiles * a.split, row_blocks);
     if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&pair_kernel<Op, RT, SEG>), hipFuncAttributeMaxDynamicSharedMemorySize, Sh::kLds);  // beyond the default dynamic-LDS allowance
     if (e != hipSuccess) return e;

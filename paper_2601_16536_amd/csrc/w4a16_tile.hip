@@ -53,7 +53,7 @@ struct Shape {
 };
 
 template <typename Act, int RT>
-__global__ __launch_bounds__(512) void tile_kernel(const GemmArgs a, const int finish, unsigned long long *__restrict__ sync, const int row_blocks, const int red_waves)
+__global__ __launch_bounds__(512) void tile_kernel(const GemmArgs a, const int finish, unsigned long long *__restrict__ sync, const Place where, const int red_waves)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     typedef Shape<RT> Sh;
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(512) void tile_kernel(const GemmArgs a, const int f
     // (integer divisions cost dozens of dependent scalar instructions each, all ahead of the first load:
     // the common cases take none)
     int unit, rb;
-    if (!place_of(units, row_blocks, &unit, &rb)) return;
+    if (!place_of(where, blockIdx.x, units, &unit, &rb)) return;
     int tile = unit, slice = 0;
     if (a.split > 1) {
         slice = unit / ntiles;
@@ -283,7 +283,7 @@ struct GroupShape {
 };
 
 template <typename Act, int RT>
-__global__ __launch_bounds__(512) void tile_group_kernel(const GemmArgs a, const int finish, unsigned long long *__restrict__ sync, const int row_blocks, const int red_waves)
+__global__ __launch_bounds__(512) void tile_group_kernel(const GemmArgs a, const int finish, unsigned long long *__restrict__ sync, const Place where, const int red_waves)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     typedef GroupShape<RT> Sh;
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(512) void tile_group_kernel(const GemmArgs a, const
     // (integer divisions cost dozens of dependent scalar instructions each, all ahead of the first load:
     // the common cases take none)
     int unit, rb;
-    if (!place_of(units, row_blocks, &unit, &rb)) return;
+    if (!place_of(where, blockIdx.x, units, &unit, &rb)) return;
     int tile = unit, slice = 0;
     if (a.split > 1) {
         slice = unit / ntiles;
@@ -506,7 +506,8 @@ size_t lds_bytes(int rows_x, int waves, int loop)
 }
 
 struct Launch {
-    int grid, row_blocks, red_waves;
+    int grid, red_waves;
+    Place where;
     size_t lds;
 };
 
@@ -521,9 +522,8 @@ bool prepare(const GemmArgs &a, int rows_x, int waves, int loop, Launch *l)
     if (rows * a.N * 4ull >= 0x7F000000ull) return false;  // slice-relative 32-bit buffer offsets
     if ((unsigned long long)a.M * a.K * 2ull >= 0x7F000000ull) return false;
     const int ntiles = (a.N + kTileCols - 1) / kTileCols;
-    l->row_blocks = (a.M + rows_x - 1) / rows_x;
-    const long long units = (long long)ntiles * a.split;
-    const long long grid = place_grid(units, l->row_blocks);
+    long long grid;
+    l->where = place((long long)ntiles * a.split, (a.M + rows_x - 1) / rows_x, &grid);
     if (grid > 0x7FFFFFFF) return false;
     l->grid = (int)grid;
     return true;
@@ -536,7 +536,7 @@ hipError_t launch_kernel(Kernel kernel, const Launch &l, const GemmArgs &a, int 
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)l.lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kernel, dim3((unsigned)l.grid), dim3(waves * 64), l.lds, stream, a, finish, sync, l.row_blocks, l.red_waves);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)l.grid), dim3(waves * 64), l.lds, stream, a, finish, sync, l.where, l.red_waves);
     return hipGetLastError();
 }
 

@@ -46,7 +46,7 @@ struct Tall {
 };
 
 template <typename Op, int RT, int SEG>
-__global__ __launch_bounds__(64 * kWaves) void tile_tall_kernel(const GemmArgs a, const int finish, unsigned long long *__restrict__ sync, const int row_blocks)
+__global__ __launch_bounds__(64 * kWaves) void tile_tall_kernel(const GemmArgs a, const int finish, unsigned long long *__restrict__ sync, const Place where)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     typedef Tall<RT, SEG> Sh;
@@ -61,7 +61,7 @@ __global__ __launch_bounds__(64 * kWaves) void tile_tall_kernel(const GemmArgs a
     const int ntiles = (a.N + kTileCols - 1) / kTileCols;
     const int units = ntiles * a.split;
     int unit, rb;
-    if (!place_of(units, row_blocks, &unit, &rb)) return;
+    if (!place_of(where, blockIdx.x, units, &unit, &rb)) return;
     int tile = unit, slice = 0;
     if (a.split > 1) {
         slice = unit / ntiles;
@@ -315,11 +315,12 @@ hipError_t launch(const GemmArgs &a, int finish, unsigned long long *sync, hipSt
     typedef Tall<RT, SEG> Sh;
     const int ntiles = (a.N + kTileCols - 1) / kTileCols;
     const int row_blocks = (a.M + Sh::kRows - 1) / Sh::kRows;
-    const long long grid = place_grid((long long)ntiles * a.split, row_blocks);
+    long long grid;
+    const Place where = place((long long)ntiles * a.split, row_blocks, &grid);
     if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&tile_tall_kernel<Op, RT, SEG>), hipFuncAttributeMaxDynamicSharedMemorySize, Sh::kLds);  // beyond the default dynamic-LDS allowance
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((tile_tall_kernel<Op, RT, SEG>), dim3((unsigned)grid), dim3(64 * kWaves), Sh::kLds, stream, a, finish, sync, row_blocks);
+    hipLaunchKernelGGL((tile_tall_kernel<Op, RT, SEG>), dim3((unsigned)grid), dim3(64 * kWaves), Sh::kLds, stream, a, finish, sync, where);
     return hipGetLastError();
 }
 

@@ -116,7 +116,7 @@ __device__ __forceinline__ void fetch_chunk(__amdgpu_buffer_rsrc_t rx, unsigned 
 }
 
 template <typename Codes, int RT>
-__global__ __launch_bounds__(64 * kWaves) void tile_wide_kernel(const GemmArgs a, const int finish, unsigned long long *__restrict__ sync, const int row_blocks, const int red_waves)
+__global__ __launch_bounds__(64 * kWaves) void tile_wide_kernel(const GemmArgs a, const int finish, unsigned long long *__restrict__ sync, const Place where, const int red_waves)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     typedef Wide<RT> Sh;
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(64 * kWaves) void tile_wide_kernel(const GemmArgs a
     const int ntiles = (a.N + kTileCols - 1) / kTileCols;
     const int units = ntiles * a.split;
     int unit, rb;
-    if (!place_of(units, row_blocks, &unit, &rb)) return;
+    if (!place_of(where, blockIdx.x, units, &unit, &rb)) return;
     int tile = unit, slice = 0;
     if (a.split > 1) {
         slice = unit / ntiles;
@@ -393,11 +393,12 @@ hipError_t launch_rt(const GemmArgs &a, int finish, unsigned long long *sync, hi
     const size_t lds = stage > red ? stage : red;
     const int ntiles = (a.N + kTileCols - 1) / kTileCols;
     const int row_blocks = (a.M + Sh::kRowsX - 1) / Sh::kRowsX;
-    const long long grid = place_grid((long long)ntiles * a.split, row_blocks);
+    long long grid;
+    const Place where = place((long long)ntiles * a.split, row_blocks, &grid);
     if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&tile_wide_kernel<CodesF16, RT>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);  // beyond the default dynamic-LDS allowance
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((tile_wide_kernel<CodesF16, RT>), dim3((unsigned)grid), dim3(64 * kWaves), lds, stream, a, finish, sync, row_blocks, kWaves);
+    hipLaunchKernelGGL((tile_wide_kernel<CodesF16, RT>), dim3((unsigned)grid), dim3(64 * kWaves), lds, stream, a, finish, sync, where, kWaves);
     return hipGetLastError();
 }
 
