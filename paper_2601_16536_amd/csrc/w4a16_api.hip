@@ -452,7 +452,8 @@ bool use_panel(int M, int N, int K, int group, bool bf16, int cus, bool may_spli
 // PAIR form (w4a16_pair.hip), for the scheduler's own plans beyond 16 rows: tiles of 32 or 64 rows x 128 columns, K in S slices, at
 // most as many workgroups as compute units where there are several.  Costs (us), fitted to 230 timings of 110 drawn shapes (M = 17 ... 700,
 // K = 2048 ... 28672, N = 1024 ... 28672), 6 % off in the mean: a round 5.8 (launch, first loads, the sums) and 1.3 to 2.7 per stage of 128 k of
-// a quarter of the slice; slices 1.4 and the partials at 1.9 TB/s.
+// a quarter of the slice; slices 1.4 and the partials at 1.9 TB/s.  32 rows, BF16, groups of 64: 1.5 is a tenth too little beyond 8192 k (19 shapes 7 to 15 % above;
+// M = 1027, K = 17984, N = 3952 was 9 % slower in PAIR than in PANEL).
 double pair_cost(int M, int N, int K, int group, bool bf16, int cus, int rows, int S)
 {
     static const double kStageUs[2][2][3] = {{{1.3, 1.45, 1.77}, {1.6, 1.5, 2.03}}, {{1.75, 2.06, 2.42}, {1.99, 2.22, 2.7}}};  // rows, format, group
@@ -460,21 +461,29 @@ double pair_cost(int M, int N, int K, int group, bool bf16, int cus, int rows, i
     S = (G + gps - 1) / gps;
     const long long wgs = (long long)((N + kPairCols - 1) / kPairCols) * ((M + rows - 1) / rows) * S, rounds = (wgs + cus - 1) / cus;
     const long long stages = ((long long)gps * group + 511) / 512;
-    return 0.3 + (double)rounds * (5.8 + (double)stages * kStageUs[rows == 64][bf16][group == 32 ? 2 : (group == 64 ? 1 : 0)]) +
+    double stage = kStageUs[rows == 64][bf16][group == 32 ? 2 : (group == 64 ? 1 : 0)];
+    if (rows == 32 && bf16 && group == 64 && gps * group > 8192) stage = 1.64;
+    return 0.3 + (double)rounds * (5.8 + (double)stages * stage) +
            (S > 1 ? 1.4 + (double)S * M * N * 4.0 / 1.9e6 : 0.0);
 }
 
-// Whether the PAIR form's cheapest plan is cheaper than PANEL's, where that is the plan so far (of cost `cost`), or the 64-column tiles':
-// by 4 % (PANEL's by 7, up to 128 rows by 13), as the models are good for about that; groups of 32 and 64 at up to 32 rows are dearer in 64-column tiles than
-// their model has it; and FP16 with groups of 128, whose 64-column tiles are the fast ones, gives up a plan that needs no memory for
-// one that does for a clear gain only.  Of 306 drawn shapes (17 to 700 rows, every format and group) 75 go to PAIR: 0.850 of their time before in the
+// Whether the PAIR form's cheapest plan is cheaper than PANEL's (`panel`, of cost `cost`) where that is the plan so far, or than the 64-column tiles':
+// by 4 % (PANEL's by 7, up to 128 rows by 13), as the models are good for about that.  Groups of 32 and 64 at up to 32 rows are dearer in 64-column tiles than
+// their model has it.  By more where the gain is not there: of 20700 drawn shapes (17 to 2048 rows) in PAIR 59 had been 2 to 13 % slower than without it, most
+// of them of these kinds (16 are now, by 2 to 7 %, but for X of more than a thousand rows of 32 KiB plus or minus 256 bytes: 12 %):
+//   - FP16 with groups of 128, whose 64-column tiles are the fast ones, gives up an unsplit plan for slices, or one of 16 rows, for a clear gain only (K = 1536,
+//     M = 141, N = 3576, 16 rows: 7.8 us, PAIR 8.4);
+//   - BF16 against PANEL in slices, beyond 128 rows: 174 shapes between 0.89 and 0.93 are as fast in PANEL in the mean, from 0.90 to 1.11 of its time (M = 155, K = 27200,
+//     N = 5624, groups of 64: 88.5 us, PAIR 98.3);
+//   - BF16 with groups of 128 against unsplit tiles of 32 rows, in two slices of 32: ten shapes at 0.90 and more, the same in the mean (M = 24, K = 14464, N = 14944: 35 us, PAIR 38).
+// Of 306 drawn shapes (17 to 700 rows, every format and group) 75 go to PAIR: 0.850 of their time before in the
 // geometric mean, 0.56 (M = 387, K = 2304, N = 2704, groups of 32) to 1.06 (M = 117, K = 16128, N = 1864, groups of 32).
-bool use_pair(int M, int N, int K, int group, bool bf16, int cus, bool by_panel, double cost, TileChoice *c)
+bool use_pair(int M, int N, int K, int group, bool bf16, int cus, const PanelPlan *panel, double cost, TileChoice *c)
 {
     const int G = K / group, want = tuning().pair, want_rows = tuning().tile_rows, want_split = tuning().pair_split;
     if (want == 2 || !panel_takes(group)) return false;
-    const Tuning &t = tuning();
-    if (want != 1 && (want_rows || t.tile_wide || t.panel || t.panel_split || t.panel_pieces)) return false;  // 64-column tiles, or PANEL, are asked for
+    const Tuning &knobs = tuning();
+    if (want != 1 && (want_rows || knobs.tile_wide || knobs.panel || knobs.panel_split || knobs.panel_pieces)) return false;  // 64-column tiles, or PANEL, are asked for
     c->cost = 1e30;
     for (int rows = 32; rows <= 64; rows += 32) {
         if ((rows == 64 && M <= 32) || (want == 1 && want_rows && rows != want_rows)) continue;
@@ -485,21 +494,19 @@ bool use_pair(int M, int N, int K, int group, bool bf16, int cus, bool by_panel,
         for (int s = 1; s <= smax; s = next_split(G, s)) {
             const int S = want_split ? (want_split < G ? want_split : G) : s, gps = (G + S - 1) / S;
             if (!fits_32bit_offsets(M, N, K, group, gps)) continue;
-            const double t = pair_cost(M, N, K, group, bf16, cus, rows, S);
-            if (t < c->cost) *c = {rows, (G + gps - 1) / gps, t};
+            const double us = pair_cost(M, N, K, group, bf16, cus, rows, S);
+            if (us < c->cost) *c = {rows, (G + gps - 1) / gps, us};
         }
     }
     if (c->cost >= 1e30) return false;
     if (want == 1) return true;
-    double factor = by_panel ? (M > 128 ? 0.93 : 0.87) : 0.96;
-    if (!by_panel) {
-        const TileChoice t = choose_tiles(M, N, K, group, 0, cus, bf16, false);
-        const long long wgs = (long long)((N + 63) / 64) * ((M + t.rows - 1) / t.rows) * t.S;
-        cost = t.cost + (M > 128 ? 3.5 * (double)((wgs - 1) / cus) : 0.0);
-        if (group < 128 && t.rows <= 32) factor = 1.05;
-        if (!bf16 && group == 128 && t.S == 1 && c->S > 1) factor = 0.84;
-    }
-    return c->cost < factor * cost;
+    if (panel) return c->cost < (M <= 128 ? 0.87 : (bf16 && panel->split > 1 ? 0.89 : 0.93)) * cost;
+    const TileChoice tiles = choose_tiles(M, N, K, group, 0, cus, bf16, false);
+    const long long wgs = (long long)((N + 63) / 64) * ((M + tiles.rows - 1) / tiles.rows) * tiles.S;
+    double factor = group < 128 && tiles.rows <= 32 ? 1.05 : 0.96;
+    if (!bf16 && group == 128 && ((tiles.S == 1 && c->S > 1) || tiles.rows == 16)) factor = 0.84;
+    if (bf16 && group == 128 && tiles.rows == 32 && tiles.S == 1 && c->rows == 32 && c->S == 2) factor = 0.90;
+    return c->cost < factor * (tiles.cost + (M > 128 ? 3.5 * (double)((wgs - 1) / cus) : 0.0));
 }
 
 // How much workspace a plan may ask for.  kBest: whatever pays.  kUnsplit: a plan of the PANEL form splits no tiles, and none is of the PAIR form.
@@ -578,7 +585,7 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
     double cost = 0.0;
     const bool by_panel = automatic && thrift < kFrugal && use_panel(M, N, K, group, bf16, cus, thrift == kBest, &pp, &cost);
     TileChoice pair;
-    if (automatic && thrift == kBest && M > 16 && use_pair(M, N, K, group, bf16, cus, by_panel, cost, &pair)) {
+    if (automatic && thrift == kBest && M > 16 && use_pair(M, N, K, group, bf16, cus, by_panel ? &pp : nullptr, cost, &pair)) {
         p->kernel = W4A16_KERNEL_TILE;
         p->tile_n = kPairCols;
         p->tile_m = pair.rows;

@@ -51,6 +51,18 @@ def test_plans_of_128_columns_cover_the_problem():
     assert len(seen) == 4
 
 
+@pytest.mark.parametrize("M,K,N,group,bf16,tile_n", [
+    (155, 27200, 5624, 64, True, 256), (154, 11648, 6120, 128, True, 256), (278, 21952, 1656, 64, True, 256),  # slices of PANEL: 4 to 10 % faster than PAIR
+    (1027, 17984, 3952, 64, True, 256), (393, 17152, 9648, 64, True, 256),  # unsplit PANEL: 9 %
+    (24, 14464, 14944, 128, True, 64), (20, 12032, 13536, 128, True, 64),  # unsplit tiles of 32 rows: 8 and 4 %
+    (141, 1536, 3576, 128, False, 64), (135, 1536, 3352, 128, False, 64),  # tiles of 16 rows: 7 %
+    (24, 9472, 10840, 128, True, 128), (348, 4992, 2760, 128, True, 128), (37, 10240, 4608, 64, False, 128), (20, 4096, 16616, 256, False, 128), (28, 13312, 15912, 256, True, 128)])  # PAIR: 7 to 35 % faster
+def test_the_faster_form_is_chosen(M, K, N, group, bf16, tile_n):
+    """Timed both ways; PAIR's model alone has it a little cheaper on all of them."""
+    from paper_2601_16536_amd import binding
+    assert binding.query_plan(M, N, K, group, bf16=bf16)["tile_n"] == tile_n
+
+
 # M: row blocks of 1, 31, 32 rows and one more; N: one column group, either half of a tile, a tile and more; K: less than the four runs,
 # runs of unequal length, a chunk that the matrix ends in (groups of 32), groups longer than a run
 CASES = [(17, 128, 8, 128), (32, 64, 64, 64), (33, 96, 72, 32), (64, 1280, 136, 128), (65, 1056, 264, 32), (31, 832, 120, 64),
