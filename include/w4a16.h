@@ -101,11 +101,11 @@ typedef struct {
     int tile_n;            /* output columns per workgroup                                    */
     int tile_m;            /* output rows per workgroup                                       */
     int waves_k;           /* K slices inside a workgroup (waves whose results meet in LDS)   */
-    int workgroups;        /* workgroups of the multiply launch (tiles of 128 x 256 cut into pieces of
-                              their rows, "panel_pieces", counted as one)                     */
+    int workgroups;        /* workgroups of the multiply launch                               */
     int threads;           /* threads per workgroup                                           */
     size_t workspace_bytes;/* 64-bit sums [M, N] or FP32 partials [S, M, N]; 0 when S == 1.  tile_n = 256: FP32
-                              partials of the split tiles, at most one tile (128 KiB) per compute unit            */
+                              partials of the tiles cut into slices, at most one tile (128 KiB) per compute unit
+                              (of those cut into pieces of rows too, a piece's share of 128 KiB for each piece)   */
 } w4a16_plan;
 
 /*

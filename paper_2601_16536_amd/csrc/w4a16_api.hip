@@ -605,8 +605,8 @@ int make_plan(int M, int N, int K, int group, int kernel, int split, int cus, w4
         p->threads = 256;
         p->split = pp.split;
         p->groups_per_split = pp.slice_k / group;
-        p->workgroups = pp.tiles_m * pp.tiles_n + pp.split_tiles * (pp.split - 1);  // (the pieces of a tile's rows counted as one)
-        p->workspace_bytes = (size_t)pp.split_tiles * (pp.split > 1 ? pp.split : 0) * kPanelPartial * sizeof(float);
+        p->workgroups = pp.tiles_m * pp.tiles_n - pp.split_tiles + pp.cut() * pp.split;
+        p->workspace_bytes = pp.split > 1 ? (size_t)pp.cut() * pp.split * (kPanelPartial / pp.pieces) * sizeof(float) : 0;
         if (panel) *panel = pp;
         return W4A16_OK;
     }
