@@ -421,7 +421,7 @@ double panel_cost(int M, int N, int K, int group, bool bf16, int cus, bool may_s
 
 bool use_panel(int M, int N, int K, int group, bool bf16, int cus, bool may_split, PanelPlan *p, double *p_cost)
 {
-    if (tuning().panel == 2 || !panel_takes(group) || !fits_32bit_offsets(M, N, K, group, K / group) || !panel_offsets_fit(K, N)) return false;
+    if (tuning().panel == 2 || !panel_takes(group) || !fits_32bit_offsets(M, N, K, group, K / group)) return false;
     if ((long long)((M + kPanelRows - 1) / kPanelRows) * ((N + kPanelCols - 1) / kPanelCols) > (1 << 24)) return false;  // a launch's blocks
     if (tuning().panel == 1 && M > 16) {
         *p_cost = panel_cost(M, N, K, group, bf16, cus, may_split, p);

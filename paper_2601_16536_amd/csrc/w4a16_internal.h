@@ -80,9 +80,6 @@ struct PanelPlan {
 };
 // The lengths of group the PANEL form and the tall TILE form take: whole stages of 128 k, or a stage's whole parts.
 inline bool panel_takes(int group) { return group % 128 == 0 || group == 64 || group == 32; }
-// Its 32-bit offsets into the weights run on past the end of the matrix, by the stages it asks for ahead (at most four of 16 packed
-// rows), and those of columns past N begin at 2^31.
-inline bool panel_offsets_fit(int K, int N) { return (K / 8 + 64ull) * N * 4ull < 0x7F000000ull; }
 hipError_t launch_panel(const GemmArgs &a, const PanelPlan &p, hipStream_t stream);
 // PAIR form of the TILE family (17 rows and more): tiles of 32 or 64 rows x 128 columns (w4a16_pair.hip); `finish`: no accumulator.
 constexpr int kPairCols = 128;

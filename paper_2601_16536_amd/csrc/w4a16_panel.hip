@@ -51,7 +51,7 @@ struct Panel {
     static constexpr int kPerStage = kXLoads + kWLoads + kSLoads + 1;
     static constexpr int kStageBytes = kXBytes + kWaves * (kWBytes + kSBytes + kZBytes);
     static constexpr int kLds = kBuffers * kStageBytes;
-    static_assert(kLds <= 160 * 1024 && 2 * kPerStage < 64 && (kBuffers + 1) * kStage / 8 <= 64, "LDS of a compute unit, and the wait counter's range");
+    static_assert(kLds <= 160 * 1024 && 2 * kPerStage < 64 && (kBuffers + 1) * kStage / 8 <= 64, "LDS of a compute unit, the wait counter's range, and rows of weights asked for ahead");
 };
 
 // One workgroup's part: rows m0 .. m0 + 32 RT - 1, 256 columns from tile_col0 on, k from kbeg to kend.  The result goes to
@@ -95,7 +95,10 @@ __device__ __forceinline__ void panel(const GemmArgs &a, unsigned char *const sm
         xg[p] = (xrow + 4u * (uint32_t)p) * row_x + xp[p] * 16u;
     }
     const uint32_t wcol = (uint32_t)col0 + 4u * lp;
-    uint32_t vw = wcol < (uint32_t)a.N ? lr * row_w + wcol * 4u : kOutOfRange;  // four packed rows per load
+    // Four packed rows per load.  The offsets run on past the slice's end, for the stages asked for ahead: those of columns that exist stay below 2^32 (64 rows of
+    // 2^22 columns are 1 GiB) and return zeros.  Those of columns past N begin at 2^31; with 2 GiB of weights they pass 2^32 and come back as offsets into the
+    // matrix: the descriptor bounds them, and what they read belongs to columns that are not stored.
+    uint32_t vw = wcol < (uint32_t)a.N ? lr * row_w + wcol * 4u : kOutOfRange;
     const uint32_t scol = (uint32_t)col0 + 2u * (uint32_t)l32;
     const uint32_t zcol = (uint32_t)col0 + 8u * ((uint32_t)lane & 7u), zseg = (uint32_t)lane >> 3;
     uint32_t vs = scol < (uint32_t)a.N ? scol * 2u + (uint32_t)half * row_s : kOutOfRange;
@@ -128,7 +131,7 @@ __device__ __forceinline__ void panel(const GemmArgs &a, unsigned char *const sm
         } else if (i < Sh::kXLoads + Sh::kWLoads) {
             const int q = i - Sh::kXLoads;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_ptr_t)(lds_w + buf * Sh::kWBytes + q * 1024), 16, vw + (uint32_t)q * 4u * row_w, 0, 0, 0);
-            if (q == Sh::kWLoads - 1) vw += 16u * row_w;  // (columns past N stay out of range: panel_offsets_fit)
+            if (q == Sh::kWLoads - 1) vw += 16u * row_w;
         } else if (i < Sh::kPerStage - 1) {
             const int q = i - Sh::kXLoads - Sh::kWLoads;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(lds_s + buf * (Sh::kSBytes + Sh::kZBytes) + q * 256), 4, vs + (uint32_t)q * 2u * row_s, 0, 0, 0);
@@ -411,7 +414,7 @@ hipError_t launch_panel(const GemmArgs &a, const PanelPlan &p, hipStream_t strea
     // slices cover K, none is empty, each begins at a group and at a whole stage of scales
     if (p.split < 1 || (p.split > 1 && (!a.partials || !p.split_tiles || p.slice_k % a.group || (a.group < kStage && p.slice_k % kStage))) ||
         (long long)p.slice_k * (p.split - 1) >= a.K || (long long)p.slice_k * p.split < a.K) return hipErrorInvalidValue;
-    if (!panel_offsets_fit(a.K, a.N) || (unsigned long long)a.M * a.K * 2ull >= 0x7F000000ull) return hipErrorInvalidValue;  // 32-bit buffer offsets
+    if (a.K / 8 * (unsigned long long)a.N * 4ull >= 0x7F000000ull || (unsigned long long)a.M * a.K * 2ull >= 0x7F000000ull) return hipErrorInvalidValue;  // 32-bit buffer offsets
     return a.bf16 ? launch_op<ExactBF16>(a, p, stream) : launch_op<ExactF16>(a, p, stream);
 }
 

@@ -136,6 +136,8 @@ __global__ __launch_bounds__(64 * kWaves) void tile_tall_kernel(const GemmArgs a
 
         // ---- weights, scales, zero points: registers, kRing stages; the lane's columns are 2 l32 and 2 l32 + 1 of the tile ----
         const int col = col0 + 2 * l32;
+        // (The offsets of columns past N begin at 2^31.  A slice of few long groups may be one wave's run, up to 2 GiB of weights: then they pass 2^32 and
+        // come back as offsets into the run.  The descriptor bounds them, and what they read belongs to columns that are not stored.)
         uint32_t vw = col < a.N ? (uint32_t)half * row_w + (uint32_t)col * 4u : kOutOfRange;
         uint32_t vs = col < a.N ? (uint32_t)col * 2u : kOutOfRange;
         uint32_t vz = col < a.N ? (uint32_t)(col >> 3) * 4u : kOutOfRange;
@@ -155,7 +157,7 @@ __global__ __launch_bounds__(64 * kWaves) void tile_tall_kernel(const GemmArgs a
                         if (srem < a.group) ds = dz = 0u;
                         else srem = 0;
                     }
-                    vs += ds;  // (columns past N stay out of range: a run is a quarter of 2 GiB at most)
+                    vs += ds;
                     vz += dz;
                 }
             } else {
