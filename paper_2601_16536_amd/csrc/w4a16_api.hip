@@ -486,7 +486,8 @@ bool use_pair(int M, int N, int K, int group, bool bf16, int cus, const PanelPla
     if (want != 1 && (want_rows || knobs.tile_wide || knobs.panel || knobs.panel_split || knobs.panel_pieces)) return false;  // 64-column tiles, or PANEL, are asked for
     c->cost = 1e30;
     for (int rows = 32; rows <= 64; rows += 32) {
-        if ((rows == 64 && M <= 32) || (want == 1 && want_rows && rows != want_rows)) continue;
+        if (want == 1 && want_rows && rows != want_rows) continue;
+        if (rows == 64 && M <= 32 && !(want == 1 && want_rows == 64 && 128ll * K < 0x7F000000)) continue;  // (asked for: X's offsets of all 64 rows)
         const long long w1 = (long long)((N + kPairCols - 1) / kPairCols) * ((M + rows - 1) / rows);
         if (w1 > (1 << 24)) continue;
         int smax = (int)(cus / w1);

@@ -63,7 +63,13 @@ def test_the_faster_form_is_chosen(M, K, N, group, bf16, tile_n):
     assert binding.query_plan(M, N, K, group, bf16=bf16)["tile_n"] == tile_n
 
 
-# M: row blocks of 1, 31, 32 rows and one more; N: one column group, either half of a tile, a tile and more; K: less than the four runs,
+def is_pair(plan, K, group, rows, split):
+    """Whether a plan is tiles of `rows` x 128 in `split` slices, or as many as K has groups for."""
+    gps = -(-(K // group) // min(split, K // group))
+    return (plan["tile_n"], plan["tile_m"], plan["threads"], plan["split"]) == (128, rows, 512, -(-(K // group) // gps))
+
+
+# M: row blocks of 1, 31, 32 rows and one more (with 64 rows to a tile: up to half of it); N: one column group, either half of a tile, a tile and more; K: less than the four runs,
 # runs of unequal length, a chunk that the matrix ends in (groups of 32), groups longer than a run
 CASES = [(17, 128, 8, 128), (32, 64, 64, 64), (33, 96, 72, 32), (64, 1280, 136, 128), (65, 1056, 264, 32), (31, 832, 120, 64),
          (100, 2176, 520, 128), (130, 2304, 392, 384), (50, 3072, 256, 256), (97, 640, 1032, 64)]
@@ -88,6 +94,7 @@ def test_pair_against_the_oracle(gpu, M, K, N, group):
             binding.tune("pair_split", split)
             for (bf16, symmetric), ref in refs.items():
                 say("pair", (M, K, N, group), "rows", rows, "split", split, "bf16" if bf16 else "fp16", "symmetric" if symmetric else "")
+                assert is_pair(binding.query_plan(M, N, K, group, bf16=bf16), K, group, rows, split)
                 Y = torch.full((M + 1, N), 7.0, dtype=torch.bfloat16 if bf16 else torch.float16, device="cuda")  # a row beyond: not written
                 gemm = binding.gemm_bf16 if bf16 else binding.gemm
                 gemm(dXb if bf16 else dX, dW, dS, None if symmetric else dZ, group, out=Y[:M])
@@ -121,6 +128,7 @@ def test_pair_whole_numbers_and_rows_that_are_not_finite(gpu):
                 say("pair whole numbers", rows, split, dtype)
                 binding.tune("tile_rows", rows)
                 binding.tune("pair_split", split)
+                assert is_pair(binding.query_plan(M, N, K, group, bf16=dtype == torch.bfloat16), K, group, rows, split)
                 Y = torch.full((M, N), 7.0, dtype=dtype, device="cuda")
                 (binding.gemm if dtype == torch.float16 else binding.gemm_bf16)(torch.from_numpy(X).cuda().to(dtype), dW, dS, dZ, group, out=Y)
                 out = Y.float().cpu().numpy()
@@ -143,6 +151,8 @@ def test_row_blocks_of_column_tiles_that_are_no_multiple_of_eight(gpu, rows, M, 
                    (torch.from_numpy(Xb.view(np.int16)).cuda().view(torch.bfloat16), orc.gemm_bf16(Xb, Wp, s, Zp, group))):
         for split in (1, 2):
             say("row blocks", rows, (M, K, N, group), split, x.dtype)
+            plan = binding.query_plan(M, N, K, group, binding.KERNEL_TILE, split, bf16=x.dtype == torch.bfloat16)
+            assert (plan["tile_n"], plan["tile_m"], plan["split"]) == (64, rows, split)
             Y = torch.full((M + 1, N), 7.0, dtype=x.dtype, device="cuda")
             f = binding.gemm_bf16 if x.dtype == torch.bfloat16 else binding.gemm_ex
             f(x, dW, dS, dZ, group, kernel=binding.KERNEL_TILE, split=split, out=Y[:M])
