@@ -55,7 +55,7 @@ struct Panel {
 };
 
 // One workgroup's part: rows m0 .. m0 + 32 RT - 1, 256 columns from tile_col0 on, k from kbeg to kend.  The result goes to
-// Y, or as FP32 to `partial` ([128][256]).
+// Y, or as FP32 to `partial` ([rows of the tile or piece][256]).
 template <typename Op, int RT, int SEG>
 __device__ __forceinline__ void panel(const GemmArgs &a, unsigned char *const smem, const int m0, const int tile_col0, const int kbeg, const int kend, float *const partial)
 {
@@ -332,7 +332,6 @@ __global__ __launch_bounds__(64 * kWaves) void panel_kernel(const GemmArgs a, co
         if (local >= per_xcd || pair >= pairs) return;
         const int slice = pair / c.count, id = pair - slice * c.count;
         t = piece_of(c, id, main_blocks, ntiles);
-        if (t.m0 >= a.M) return;  // a piece past the last row
         kbeg = slice * slice_k;
         kend = a.K - kbeg < slice_k ? a.K : kbeg + slice_k;
         if (a.split > 1) partial = a.partials + ((size_t)id * a.split + slice) * (kPanelPartial / c.pieces);
@@ -407,7 +406,7 @@ hipError_t launch_op(const GemmArgs &a, const PanelPlan &p, hipStream_t stream)
 hipError_t launch_panel(const GemmArgs &a, const PanelPlan &p, hipStream_t stream)
 {
     if (!panel_takes(a.group) || p.tiles_m != (a.M + kPanelRows - 1) / kPanelRows || p.tiles_n != (a.N + kPanelCols - 1) / kPanelCols) return hipErrorInvalidValue;
-    if (p.last_rows % 32 || p.last_rows < a.M - (p.tiles_m - 1) * kPanelRows || p.last_rows > kPanelRows) return hipErrorInvalidValue;
+    if (p.last_rows != (a.M - (p.tiles_m - 1) * kPanelRows + 31) / 32 * 32) return hipErrorInvalidValue;  // (so every piece of 32 rows begins inside the matrix)
     if (p.split_tiles < 0 || p.split_tiles > p.tiles_m * p.tiles_n || a.split != p.split) return hipErrorInvalidValue;
     // pieces of the rows that the last row block's tiles have, if there are any
     if ((p.pieces != 1 && p.pieces != 2 && p.pieces != 4) || (p.pieces > 1 && p.last_rows < kPanelRows && p.last_rows != kPanelRows / p.pieces)) return hipErrorInvalidValue;

@@ -107,7 +107,7 @@ def test_panel_against_the_oracle(gpu, M, K, N, group):
         binding.tune("panel_split", 0)
 
 
-# Tiles of 128 rows cut into pieces of 64 and 32: a last row block of as many rows, none, and pieces that begin at or end past the last row
+# Tiles of 128 rows cut into pieces of 64 and 32: a last row block of as many rows, none, and pieces that end at or past the last row
 PIECES = [(2, 192, 1024, 264, 64), (2, 256, 640, 520, 128), (2, 225, 832, 248, 64), (4, 160, 1056, 512, 32), (4, 128, 1280, 264, 256),
           (4, 97, 384, 72, 128), (4, 481, 640, 1032, 128), (2, 320, 2048, 768, 128)]
 
@@ -128,11 +128,55 @@ def test_panel_pieces_of_rows_against_the_oracle(gpu, pieces, M, K, N, group):
             binding.tune("panel_split", split)
             for x, ref in cases:
                 say("panel pieces", pieces, (M, K, N, group), "split", split, x.dtype)
-                assert binding.query_plan(M, N, K, group, bf16=x.dtype == torch.bfloat16)["split"] == split
+                plan = binding.query_plan(M, N, K, group, bf16=x.dtype == torch.bfloat16)
+                assert plan["split"] == split and pieces_of(plan, M, N) == pieces
                 Y = torch.full((M + 1, N), 7.0, dtype=x.dtype, device="cuda")  # a row beyond: not written
                 (binding.gemm_bf16 if x.dtype == torch.bfloat16 else binding.gemm)(x, dW, dS, dZ, group, out=Y[:M])
                 torch.cuda.synchronize()
                 assert err_ratio(Y[:M].double().cpu().numpy(), ref) <= 1.0 and (Y[M] == 7.0).all()
+    finally:
+        for knob in ("panel", "panel_pieces", "panel_split"):
+            binding.tune(knob, 0)
+
+
+# Whole tiles before the cut ones (43 column tiles, six or seven row blocks, 256 whole): two tiles of 128 rows and a shorter row block, or 45 of 128 rows
+MIXED = [(4, 777, (1, 2, 5)), (2, 832, (1, 2, 3)), (2, 896, (1, 2)), (4, 896, (1,)), (1, 777, (2, 3)), (1, 896, (5,))]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("pieces,M,splits", MIXED)
+def test_panel_whole_tiles_and_pieces_of_others(gpu, pieces, M, splits):
+    """Every output against 64-bit sums; with a workspace of just the plan's size, beyond which nothing is written."""
+    torch, binding = gpu
+    K, N, group = 640, 11008, 64
+    gen = torch.Generator(device="cuda").manual_seed(M + pieces)
+    words = lambda *shape: torch.randint(-(1 << 31), 1 << 31, shape, dtype=torch.int32, device="cuda", generator=gen)
+    X, Wp, Zp = torch.randn((M, K), device="cuda", generator=gen), words(K // 8, N), words(K // group, N // 8)
+    s = torch.rand((K // group, N), device="cuda", generator=gen).to(torch.float16) * 0.019 + 0.001
+    shift = torch.arange(0, 32, 4, device="cuda", dtype=torch.int32)
+    q = ((Wp.unsqueeze(1) >> shift.view(1, 8, 1)) & 15).reshape(K, N).double()
+    z = ((Zp.unsqueeze(2) >> shift.view(1, 1, 8)) & 15).reshape(K // group, N).double()
+    W = (q - z.repeat_interleave(group, 0)) * s.double().repeat_interleave(group, 0)
+    binding.tune("panel", 1)
+    binding.tune("panel_pieces", pieces)
+    try:
+        for split in splits:
+            binding.tune("panel_split", split)
+            for dtype in (torch.float16, torch.bfloat16):
+                say("whole tiles and pieces", pieces, M, "split", split, dtype)
+                bf16, x = dtype == torch.bfloat16, X.to(dtype)
+                plan = binding.query_plan(M, N, K, group, bf16=bf16)
+                assert plan["split"] == split and pieces_of(plan, M, N) == pieces and plan["workgroups"] > 256
+                size = plan["workspace_bytes"]
+                ws = torch.full((size + 4096,), 0x55, dtype=torch.uint8, device="cuda")
+                Y = torch.full((M + 1, N), 7.0, dtype=dtype, device="cuda")
+                rc = binding.lib().w4a16_gemm_scratch(x.data_ptr(), Wp.data_ptr(), s.data_ptr(), Zp.data_ptr(), group, M, N, K, Y.data_ptr(),
+                                                      torch.cuda.current_stream().cuda_stream, int(bf16), ws.data_ptr(), size)
+                assert rc == binding.OK
+                torch.cuda.synchronize()
+                ref = x.double() @ W
+                assert float(((Y[:M].double() - ref).abs() / (TOL * (1.0 + ref.abs()))).max()) <= 1.0 and bool((Y[M] == 7.0).all())
+                assert bool((ws[size:] == 0x55).all()) and (split == 1 or bool((ws[:size] != 0x55).any()))
     finally:
         for knob in ("panel", "panel_pieces", "panel_split"):
             binding.tune(knob, 0)
