@@ -40,7 +40,7 @@ struct Place {
 inline Place place(long long units, int row_blocks, long long *grid)
 {
     const long long whole = (units + kPlaceXcds - 1) / kPlaceXcds * row_blocks, eighth = eighths_grid(units, row_blocks) / kPlaceXcds;
-    const bool by_units = (whole + kPlaceUnits - 1) / kPlaceUnits == (eighth + kPlaceUnits - 1) / kPlaceUnits;
+    const bool by_units = units % kPlaceXcds != 0 && (whole + kPlaceUnits - 1) / kPlaceUnits == (eighth + kPlaceUnits - 1) / kPlaceUnits;  // (units by eights: eighths are whole units, without the last step below)
     *grid = (by_units ? whole : eighth) * kPlaceXcds;
     return {(unsigned)row_blocks, by_units ? 0u : (unsigned)eighth};
 }

@@ -65,8 +65,9 @@ def test_units_are_divided_among_xcds_only_where_that_saves_a_round(placed, unit
     even = -(-units * row_blocks // 8)
     assert -(-per_xcd.max() // 32) == -(-even // 32)
     whole = -(-units // 8) * row_blocks
-    assert bool(rows[0, 3]) == (-(-whole // 32) > -(-even // 32))
-    if not rows[0, 3]:
+    divided = -(-whole // 32) > -(-even // 32)
+    assert bool(rows[0, 3]) == (divided or units % 8 == 0)  # (units by eights: eighths are whole units)
+    if not divided:
         for unit in range(units):
             blocks = np.sort(rows[rows[:, 5] == unit, 4])
             assert (np.diff(blocks) == 8).all()
