@@ -89,7 +89,9 @@ typedef enum {
                                     reduction), plain MFMA operand layout; slices of different workgroups meet as
                                     in STRIPE.  The scheduler's own plans beyond 16 rows may have tiles of 128 rows
                                     x 256 columns instead (tile_n = 256): four waves side by side, the tiles past the
-                                    last whole round of compute units in S slices of K summed by a second launch      */
+                                    last whole round of compute units cut into pieces of rows, or in S slices of K
+                                    summed by a second launch, or both; or of 32 or 64 rows x 128 columns (tile_n = 128):
+                                    eight waves, four runs of K by two halves of the columns, S > 1 summed by a second launch */
 } w4a16_kernel;
 
 /* What the scheduler decided for a shape (Algorithm 1 takes S and the block

@@ -160,6 +160,7 @@ bool fits_32bit_offsets(int M, int N, int K, int group, int gps)
 //
 // PANEL (a form of TILE, M > 16): tiles of 128 rows x 256 columns for prompts, and for batches whose 64-column tiles would
 //   run in several rounds or over a long K (use_panel).
+// PAIR (a form of TILE, M > 16): tiles of 32 or 64 rows x 128 columns, where its model has it clearly cheaper than these two (use_pair).
 //
 // WAVE_SPLIT (M <= 4) is kept as a forced plan (w4a16_gemm_ex), the data-parallel form for comparisons:
 //   one workgroup of sixteen waves per column tile of 32 or 64 columns; the sixteen waves are sixteen K
@@ -211,7 +212,7 @@ bool ticket_grid_fits(int M, int N) { return ((long long)N + 63) / 64 <= 65535 &
 
 // TILE with four waves per workgroup: at 32 and 64 rows of X, FP16 with groups of 128 (w4a16_tile_wide.hip), and at 64 rows
 // BF16 and the other lengths of group (w4a16_tile_tall.hip; at 32 rows these run the eight-wave form).  Both take FP16 with
-// groups of 128 at 64 rows: M = 128, N = 8192, K = 512 / 2048 / 8192: 6.6 / 10.7 / 27.7 us (wide), 6.9 / 10.7 / 27.5 (tall).
+// groups of 128 at 64 rows: M = 128, N = 8192, K = 512 / 2048 / 8192: 6.3 / 9.7 / 25.5 us (wide), 7.0 / 10.3 / 26.5 (tall).
 bool tile_four(int rows_x, int group, bool bf16)
 {
     return ((rows_x == 64 && panel_takes(group)) || (rows_x == 32 && group == 128 && !bf16)) && tuning().tile_wide != 2;
@@ -283,6 +284,8 @@ size_t stripe_lds_max(int M) { return (size_t)(stripe_by_ticket(M) ? stripe_dyn_
 // there as the clock does): a fixed 3 us; rounds of workgroups x blocks of 32 k per wave x the time of a block
 // (four-wave form: 0.24 us at 32 rows, 0.37 at 64; eight-wave form: 0.37, 0.56, 0.94 at 16, 32, 64 rows); and how the
 // slices meet (accumulator: 1 us, and beyond 200 K adds 1 us per 60 K; second pass: 3.3 us and the partials at 3 TB/s).
+// (The four-wave form's blocks, 5 to 9 % shorter since its unpack in ten instructions, and the second pass, since partials are written through, have the older
+// costs here and in panel_cost; only pair_cost is fitted to the kernels as they are.)
 // `frugal`: the costs by which kFrugal's plans are chosen, the same for both formats.
 double tile_plan_cost(int M, int N, int K, int group, int rows, int S, int cus, bool bf16, bool frugal)
 {
@@ -356,7 +359,7 @@ TileChoice choose_tiles(int M, int N, int K, int group, int split, int cus, bool
 // takes 0.73 and 0.66 (BF16 0.77 and 0.7) of a stage: fitted to 12 shapes with every cut forced (M = 384, K = N = 5120: 60 tiles in 4 slices 33.9 us, 120 pieces
 // in 2 slices 33.6, 240 pieces of 32 rows 39.8; M = 1000, K = N = 4096, groups of 64: 47.3 in 2 slices, 43.1 in 256 pieces).  Pieces have to be 4 %
 // cheaper than slices alone.  Of 70 drawn shapes (M = 100 ... 2048) whose plan they change, against the plan before: 0.895 of its time
-// in the geometric mean (M = 567, K = 8192, N = 6720 86.7 -> 70.3; M = 777, K = 4096, N = 11008, BF16 83.5 -> 77.5; the best 0.56, the worst 1.04).
+// in the geometric mean (M = 567, K = 8192, N = 6720 88 -> 68; M = 777, K = 4096, N = 11008, BF16 84 -> 76; the best 0.56, the worst 1.04).
 double panel_cost(int M, int N, int K, int group, bool bf16, int cus, bool may_split, PanelPlan *p)
 {
     static const double kRel[5] = {0.0, 0.47, 0.6, 0.8, 1.0}, kPieceRel[2][3] = {{0.0, 0.66, 0.73}, {0.0, 0.7, 0.77}};
@@ -949,8 +952,8 @@ size_t w4a16_scratch_bytes(int M, int N, int K, int group, int bf16)
         if (g_dev[dev].user_ws) return 0;
     }
     if (make_plan(M, N, K, group, W4A16_KERNEL_AUTO, 0, compute_units(dev), &p, nullptr, bf16 != 0)) return 0;
-    const bool by_panel = p.kernel == W4A16_KERNEL_TILE && (p.tile_n == kPanelCols || p.tile_n == kPairCols);
-    if (!by_panel && finish_of(p.kernel, M, N, p.split, burst_rows(p.tile_m, group, bf16 != 0, false)) != kFinishSecondPass) return 0;
+    const bool partials_only = p.kernel == W4A16_KERNEL_TILE && (p.tile_n == kPanelCols || p.tile_n == kPairCols);  // whatever is split there takes the second pass
+    if (!partials_only && finish_of(p.kernel, M, N, p.split, burst_rows(p.tile_m, group, bf16 != 0, false)) != kFinishSecondPass) return 0;
     return p.workspace_bytes;
 }
 

@@ -17,7 +17,7 @@
 //   - the order of instructions is written down slot by slot, one MFMA each.  Left to the compiler's scheduler the same
 //     loop took 243 us where this one takes 224 (M = 2048, K = N = 8192).
 // M = 2048, K = N = 8192: 224-232 us = 1.2 PFLOP/s (FP16; BF16 229-243), 656 us before; ten launches one after another under
-// the trace, where the power limit sets in: 231 rising to 266 (BF16 271 to 278, the first two 334 and 319).  The vendor's FP16 GEMM on dense weights takes 235-265.  M = 777, K = 4096, N = 11008: 77.5 us (BF16).
+// the trace, where the power limit sets in: 231 rising to 266 (BF16 271 to 278, the first two 334 and 319).  The vendor's FP16 GEMM on dense weights takes 235-265.  M = 777, K = 4096, N = 11008: 76 us (BF16, cold weights).
 // Arithmetic: products x (q - z) are exact in FP32, sums over a group in FP32 in the MFMA, times s in FP32: as in
 // w4a16_tile_wide.hip.
 #include "w4a16_device.h"
@@ -278,7 +278,7 @@ __device__ __forceinline__ void panel(const GemmArgs &a, unsigned char *const sm
 // whole.  The others are cut: those of 128 rows into `pieces` of 32 LAST rows (1: not), and each piece into a.split slices of K
 // of `slice_k` (1: none), which the second launch adds up.  Pieces of rows cost more unpack, slices their partials and the
 // launch: M = 1000, K = N = 4096, groups of 64 (128 tiles): 47.3 us in 2 slices, 43.1 in 256 pieces; M = 777, K = 4096, N = 11008, BF16 (2 tiles
-// of 128 rows and 43 of 32 past the first round): 84 in 5 slices, 77.5 in 51 pieces of 32 rows and 5 slices.
+// of 128 rows and 43 of 32 past the first round): 84 in 5 slices, 76 in 51 pieces of 32 rows and 5 slices.
 struct TileOf {
     int m0, col0;
     bool last;

@@ -57,8 +57,9 @@ struct Wide {
     // at the start, for the first chunk: the first group's scales, zero points and weights (6), three chunks of X, the
     // second group's (6), and the first refill (3) were asked for after it
     static constexpr int kWaitFirst = 15 + 3 * kLoadsPerChunk;
-    // vector instructions the schedule puts ahead of every MFMA: 40 per block for the next block's operands, and in a
-    // group's first block 16 RT more for the step of the group before
+    // vector instructions the schedule asks for ahead of every MFMA.  There are 40 per block for the next block's operands, and in a group's first block 16 RT more
+    // for the step of the group before, and loads' addresses beside them: the counts are a little above their share (at 32 rows 9 and 5 would be: the
+    // same within 0.5 %; at 64 rows 6 and 2 are 1 to 2 % slower)
     static constexpr int kValuFirst = RT == 4 ? 7 : 11, kValu = RT == 4 ? 3 : 6;
 };
 

@@ -1,5 +1,5 @@
-// Pieces of the kernels that give a wave 64 or more rows of X (w4a16_panel.hip, w4a16_tile_tall.hip): the exact operand
-// q - z in the order of k, compile-time loops, and what the stages (128 k) of both kernels have in common.
+// Pieces of the kernels whose B operand is q - z itself: the exact operand in the order of k (w4a16_panel.hip, w4a16_tile_tall.hip, w4a16_pair.hip,
+// and FP16's in w4a16_tile_wide.hip), the compile-time loops of the first three, and what the stages (128 k) of PANEL and the tall form have in common.
 #pragma once
 #include "w4a16_device.h"
 #include <type_traits>
