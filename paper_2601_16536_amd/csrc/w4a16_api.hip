@@ -472,14 +472,13 @@ double pair_cost(int M, int N, int K, int group, bool bf16, int cus, int rows, i
 
 // Whether the PAIR form's cheapest plan is cheaper than PANEL's (`panel`, of cost `cost`) where that is the plan so far, or than the 64-column tiles':
 // by 4 % (PANEL's by 7, up to 128 rows by 13), as the models are good for about that.  Groups of 32 and 64 at up to 32 rows are dearer in 64-column tiles than
-// their model has it.  By more where the gain is not there: of 20700 drawn shapes (17 to 2048 rows) in PAIR 59 had been 2 to 13 % slower than without it, most
-// of them of these kinds (16 are now, by 2 to 7 %, but for X of more than a thousand rows of 32 KiB plus or minus 256 bytes: 12 %):
-//   - FP16 with groups of 128, whose 64-column tiles are the fast ones, gives up an unsplit plan for slices, or one of 16 rows, for a clear gain only (K = 1536,
-//     M = 141, N = 3576, 16 rows: 7.8 us, PAIR 8.4);
-//   - BF16 against PANEL in slices, beyond 128 rows: 174 shapes between 0.89 and 0.93 are as fast in PANEL in the mean, from 0.90 to 1.11 of its time (M = 155, K = 27200,
-//     N = 5624, groups of 64: 88.5 us, PAIR 98.3);
-//   - BF16 with groups of 128 against unsplit tiles of 32 rows, in two slices of 32: ten shapes at 0.90 and more, the same in the mean (M = 24, K = 14464, N = 14944: 35 us, PAIR 38).
-// Of 306 drawn shapes (17 to 700 rows, every format and group) 75 go to PAIR: 0.850 of their time before in the
+// their model has it.  By more where the gain is not there:
+//   - FP16 with groups of 128, whose 64-column tiles are the fast ones, gives up an unsplit plan for slices, or one of 16 rows, for a clear gain only (11 shapes with 16
+//     rows at 0.90 to 0.96: 3 to 9 % faster than PAIR; K = 1536, M = 141, N = 3576: 7.8 us, PAIR 8.4);
+//   - BF16 unsplit against PANEL in slices, beyond 128 rows and 6144 k: 205 shapes at 0.89 to 0.93 are 2.4 % faster in PANEL in the mean, by up to 12 % (M = 155,
+//     K = 27200, N = 5624, groups of 64: 88.5 us, PAIR 98.3).  Not so shorter K (61: PAIR 1 % faster), PAIR in slices (236: the same) and groups of 32 (47: PAIR 8 % faster).
+// Of 5707 shapes drawn afterwards (17 to 2048 rows) that the models' error alone would send to PAIR, 57 change by these two and pair_cost's long slices, to 0.96 of their
+// time; beyond 1.02 of the time before PAIR were 17, and are 4.  Of 306 drawn shapes (17 to 700 rows, every format and group) 75 go to PAIR: 0.850 of their time before in the
 // geometric mean, 0.56 (M = 387, K = 2304, N = 2704, groups of 32) to 1.06 (M = 117, K = 16128, N = 1864, groups of 32).
 bool use_pair(int M, int N, int K, int group, bool bf16, int cus, const PanelPlan *panel, double cost, TileChoice *c)
 {
@@ -504,12 +503,14 @@ bool use_pair(int M, int N, int K, int group, bool bf16, int cus, const PanelPla
     }
     if (c->cost >= 1e30) return false;
     if (want == 1) return true;
-    if (panel) return c->cost < (M <= 128 ? 0.87 : (bf16 && panel->split > 1 ? 0.89 : 0.93)) * cost;
+    if (panel) {
+        const bool dear = bf16 && panel->split > 1 && group >= 64 && c->S == 1 && K > 6144;
+        return c->cost < (M <= 128 ? 0.87 : (dear ? 0.89 : 0.93)) * cost;
+    }
     const TileChoice tiles = choose_tiles(M, N, K, group, 0, cus, bf16, false);
     const long long wgs = (long long)((N + 63) / 64) * ((M + tiles.rows - 1) / tiles.rows) * tiles.S;
     double factor = group < 128 && tiles.rows <= 32 ? 1.05 : 0.96;
-    if (!bf16 && group == 128 && ((tiles.S == 1 && c->S > 1) || tiles.rows == 16)) factor = 0.84;
-    if (bf16 && group == 128 && tiles.rows == 32 && tiles.S == 1 && c->rows == 32 && c->S == 2) factor = 0.90;
+    if (!bf16 && group == 128 && tiles.S == 1 && (c->S > 1 || tiles.rows == 16)) factor = 0.84;
     return c->cost < factor * (tiles.cost + (M > 128 ? 3.5 * (double)((wgs - 1) / cus) : 0.0));
 }
 

@@ -181,7 +181,7 @@ def test_scratch_of_a_graph_that_torch_records(gpu):
 
 @pytest.mark.gpu
 def test_a_capture_after_calls_that_brought_their_scratch(gpu):
-    """M = 64, K = 16384, N = 4096: four slices, every plan of two or more needs a buffer.  A call through the binding brings its
+    """M = 64, K = 16384, N = 4096: slices, and every plan that has some needs a buffer.  A call through the binding brings its
     own and leaves the library without; the same shape under a capture, which may not allocate, and with an explicit stream,
     which brings none, then runs unsplit."""
     torch, binding, _, _, _ = gpu
@@ -243,7 +243,7 @@ def test_calls_take_no_memory_beside_a_registered_workspace(gpu, m, k, n, writte
 @pytest.mark.gpu
 def test_a_workspace_of_the_shapes_size_is_enough_for_both_formats(gpu):
     """w4a16_workspace_bytes does not ask for the format.  M = 101, K = 12544, N = 3216: FP16's plan needs nothing, BF16's
-    best one the partials of two slices; with a registered workspace of that size the BF16 call runs a plan that fits."""
+    best one the partials of its slices; with a registered workspace of that size the BF16 call runs a plan that fits."""
     torch, binding, _, _, _ = gpu
     m, k, n = 101, 12544, 3216
     size = binding.workspace_bytes(m, n, k, 128)
