@@ -3,7 +3,7 @@
 // SIMD with a quarter of the slice's K and the whole 64 x 64 result.
 //
 // What bounds it: a stage (128 k) is 32 MFMAs 32x32x16, 160 vector instructions of unpack (FP16; 272 BF16), 64 of Eq. 2's step
-// and about 45 of addressing per wave, 0.77 us measured without the loads; the loads into LDS of X, which every wave
+// and about 48 of addressing per wave, 0.77 us measured without the loads; the loads into LDS of X, which every wave
 // fetches for itself (64 KiB per workgroup and stage from the L2), and those of the weights bring that to 1.1 and 1.3 us.  So:
 //   - the operand is q - z, exact, in the order of k (w4a16_wide_ops.h: 10 vector instructions per word for FP16, 17 for
 //     BF16, which the eight-wave form unpacks to 128 + q and pays a fifth MFMA and a second FMA to correct): X needs no
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(64 * kWaves) void tile_tall_kernel(const GemmArgs a
         const uint32_t row_x = (uint32_t)a.K * 2u, row_w = (uint32_t)a.N * 4u, row_s = (uint32_t)a.N * 2u, row_z = (uint32_t)(a.N >> 3) * 4u;
         const int grp0 = kbeg / a.group;
         const uint32_t ngroups = (uint32_t)(klen / a.group);
-        __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.X) + (size_t)m0 * a.K + kbeg, 0, (uint32_t)rows_here * row_x - (uint32_t)kbeg * 2u, kRawBuffer);
+        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.X) + (size_t)m0 * a.K + kbeg, 0, (uint32_t)rows_here * row_x - (uint32_t)kbeg * 2u, kRawBuffer);
         const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(a.Wp) + (size_t)(kbeg >> 3) * a.N, 0, (uint32_t)(klen >> 3) * row_w, kRawBuffer);
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.scales) + (size_t)grp0 * a.N, 0, ngroups * row_s, kRawBuffer);
         const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(a.Zp) + (size_t)grp0 * (a.N >> 3), 0, zero_point_bytes(a.Zp, ngroups * row_z), kRawBuffer);
@@ -118,9 +118,10 @@ __global__ __launch_bounds__(64 * kWaves) void tile_tall_kernel(const GemmArgs a
             if (i == 0) {
                 o0 = xg[0] + (uint32_t)xk * 2u;
                 o1 = xg[1] + (uint32_t)xk * 2u;
-                if constexpr (SEG == kStage) {  // runs are whole stages: past the last one nothing is to be fetched
-                    if (xk >= klen) rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.X), 0, 0u, kRawBuffer);
-                } else if (klen - xk < kStage) {  // the run ends inside this stage or before it
+                // The run ends inside this stage or before it: by every lane's own offset.  (Where runs are whole stages, a descriptor of no bytes from there on saves
+                // three vector instructions a stage and loses: K = 512, N = 115728, M = 46, BF16, groups of 256, 46.6 us so and 50.1 with it, K = N = 8192, M = 128 27.9
+                // and 28.1; in w4a16_panel.hip it gains 0.7 %.)
+                if (klen - xk < kStage) {
                     if (xk + (int)xp[0] * 8 >= klen) o0 = kOutOfRange;
                     if (xk + (int)xp[1] * 8 >= klen) o1 = kOutOfRange;
                 }
