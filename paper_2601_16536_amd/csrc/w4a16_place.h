@@ -48,14 +48,13 @@ __host__ __device__ inline bool place_of(const Place &p, unsigned block, int uni
 {
     *unit = (int)block;
     *rb = 0;
-    if (p.row_blocks > 1) {
+    if (__builtin_expect((int)p.row_blocks > 1, 1)) {  // (with other branches the prologue of a launch of many short workgroups shows: up to 2 %)
         const unsigned xcd = block % kPlaceXcds, id = block / kPlaceXcds + xcd * p.eighth;
         unsigned u = id / p.row_blocks;
         *rb = (int)(id - u * p.row_blocks);
         if (p.eighth == 0) {
             const unsigned each = (unsigned)units / kPlaceXcds, more = (unsigned)units % kPlaceXcds;  // the first `more` XCDs have a unit more
-            if (u >= each + (xcd < more ? 1 : 0)) return false;
-            u += xcd * each + (xcd < more ? xcd : more);
+            u = u < each + (xcd < more ? 1 : 0) ? u + xcd * each + (xcd < more ? xcd : more) : (unsigned)units;  // (past the XCD's last unit: past them all)
         }
         *unit = (int)u;
     }

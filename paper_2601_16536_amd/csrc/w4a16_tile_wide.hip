@@ -117,9 +117,10 @@ __device__ __forceinline__ void fetch_chunk(__amdgpu_buffer_rsrc_t rx, unsigned 
 }
 
 template <typename Codes, int RT>
-__global__ __launch_bounds__(64 * kWaves) void tile_wide_kernel(const GemmArgs a, const int finish, unsigned long long *__restrict__ sync, const Place where, const int red_waves)
+__global__ __launch_bounds__(64 * kWaves) void tile_wide_kernel(const GemmArgs a, const int finish, unsigned long long *__restrict__ sync, const Place where, int red_waves)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    asm volatile("" : "+s"(red_waves));  // asked for with the other arguments: at the end, where it is used, the wait for it is 0.3 us per workgroup
     typedef Wide<RT> Sh;
     constexpr int kRT = RT, kRowsX = Sh::kRowsX, kLoadsPerChunk = Sh::kLoadsPerChunk, kBufBytes = Sh::kBufBytes, kWaveBytes = Sh::kWaveBytes;
     const int tid = threadIdx.x;
